@@ -38,14 +38,14 @@ __device__ __forceinline__ int phase_tid() {
   return t;
 }
 
-// 1/x from the hardware reciprocal estimate refined by two Newton steps
-// (relative error near one ulp); used where correct rounding is not required.
+// 1/x from the hardware reciprocal estimate r (relative error e near 2^-24)
+// and one third-order step, r (1 + e + e^2): the remaining error e^3 is below
+// the rounding (relative error near one ulp).  One operation less than two
+// Newton steps.  Used where correct rounding is not required.
 __device__ __forceinline__ double rcp_nr(double x) {
-  double r = __builtin_amdgcn_rcp(x);
-  double e = fma(-x, r, 1.0);
-  r = fma(r, e, r);
-  e = fma(-x, r, 1.0);
-  return fma(r, e, r);
+  const double r = __builtin_amdgcn_rcp(x);
+  const double e = fma(-x, r, 1.0);
+  return fma(r, fma(e, e, e), r);
 }
 
 // sqrt(x) for x > 0 from the hardware reciprocal square-root estimate
@@ -139,6 +139,45 @@ __device__ __forceinline__ void weno5_pair(double v0, double v1, double v2, doub
   R = nr * (dl * inv);
 }
 
+// WENO5-JS point values of a node's two edges from the five nodes a..e around
+// it (c the node): L, the left-biased value at the edge towards d, and R, the
+// right-biased value at the edge towards b.  Both use the same three windows
+// (a,b,c), (b,c,d), (c,d,e) with the same smoothness indicators; only the
+// linear weights are mirrored.  A window's parabola about the node is c +
+// (s/2) x + (k/2) x^2 with k its second difference and s its slope form at the
+// node (a - 4b + 3c, d - b, -3c + 4d - e), so its candidates times 8 are 8 c
+// + k + 2 s (at x = 1/2) and 8 c + k - 2 s (at x = -1/2), and the indicators
+// times 4 are (13/3) k^2 + s^2.  The weights are cross products (1/t_w times
+// t0 t1 t2, t = (eps + indicator)^2), shared by the two values; one reciprocal
+// of den_L den_R serves both (eps is at least 1e-20, so the product stays a
+// normal number).  The values are formed as c plus a weighted correction: a
+// constant stencil gives c exactly.  58 operations and the estimate per node,
+// against 76 per edge for weno5_pair, which forms every indicator twice (once
+// per edge of its node).
+__device__ __forceinline__ void weno5_node(double a, double b, double c, double d, double e,
+                                           double eps4, double& L, double& R) {
+  const double d0 = b - a, d1 = c - b, d2 = d - c, d3 = e - d;
+  const double k0 = d1 - d0, k1 = d2 - d1, k2 = d3 - d2;
+  const double s0 = fma(2.0, d1, k0), s1 = d1 + d2, s2 = fma(2.0, d2, -k2);
+  constexpr double c4 = 4.0 * (13.0 / 12.0);
+  const double e0 = fma(s0, s0, fma(c4 * k0, k0, eps4));
+  const double e1 = fma(s1, s1, fma(c4 * k1, k1, eps4));
+  const double e2 = fma(s2, s2, fma(c4 * k2, k2, eps4));
+  const double t0 = e0 * e0, t1 = e1 * e1, t2 = e2 * e2;
+  // weights times 16 t0 t1 t2: (t1 t2, 10 t0 t2, 5 t0 t1) for L and the
+  // mirrored (5 t1 t2, 10 t0 t2, t0 t1) for R
+  const double w12 = t1 * t2, w02 = 10.0 * (t0 * t2), w01 = t0 * t1;
+  const double v01 = 5.0 * w01, v12 = 5.0 * w12;
+  const double dl = (w12 + w02) + v01;
+  const double dr = (w01 + w02) + v12;
+  const double nl = fma(w12, fma(2.0, s0, k0), fma(w02, fma(2.0, s1, k1), v01 * fma(2.0, s2, k2)));
+  const double nr =
+      fma(w01, fma(-2.0, s2, k2), fma(w02, fma(-2.0, s1, k1), v12 * fma(-2.0, s0, k0)));
+  const double inv = rcp_nr(dl * dr) * 0.125;
+  L = fma(nl, dr * inv, c);
+  R = fma(nr, dl * inv, c);
+}
+
 __device__ __forceinline__ double central4(double b, double c, double d, double e) {
   return fma(9.0, c + d, -(b + e)) * 0.0625;
 }
@@ -198,17 +237,40 @@ struct TileShape {
   // read in runs of whole rows and keep their width.
   static constexpr int UPITCH = D == 1 ? T0 + 8 : ((T0 + 8) | 1);
   static constexpr int NUNION = UPITCH * (D >= 2 ? T1 + 8 : 1);
+  // smallest pitch >= p with the residue r modulo 16 (the doubles of one LDS
+  // pass): planes of r-wide rows then start in successive banks
+  static constexpr int pad16(int p, int r) { return p % 16 == r % 16 ? p : pad16(p + 1, r); }
+  // 3D tile extended by 4 nodes on both sides along j: row and plane pitch.
+  // The lanes of a wave take the cross-section of j (see edges_dir): across x
+  // they read one node of successive rows, across y one row of successive
+  // planes, so those pitches are odd and padded; across z they read whole
+  // planes.
   static constexpr int xpitch(int j) { return j == 0 ? ((T0 + 8) | 1) : T0; }
-  static constexpr int ext(int j) {
-    return xpitch(j) * (T1 + (j == 1 ? 8 : 0)) * (T2 + (j == 2 ? 8 : 0));
+  static constexpr int xplane(int j) {
+    return j == 1 ? pad16(T0 * (T1 + 8), T0) : xpitch(j) * T1;
   }
-  static constexpr int edges(int j) {
-    return (T0 + (j == 0 ? 3 : 0)) * (T1 + (j == 1 ? 3 : 0)) * (T2 + (j == 2 ? 3 : 0));
+  static constexpr int ext(int j) { return xplane(j) * (T2 + (j == 2 ? 8 : 0)); }
+  // layout index of tile node (t0, t1, t2) in the box extended along j
+  template <int J>
+  static __device__ __forceinline__ int node(int t0, int t1, int t2) {
+    return (t0 + (J == 0 ? 4 : 0)) + xpitch(J) * (t1 + (J == 1 ? 4 : 0)) +
+           xplane(J) * (t2 + (J == 2 ? 4 : 0));
   }
+  // Flux array of direction j: slot a (0 .. T_j + 3) of a line belongs to node
+  // a - 2 and holds its right-biased values, then the flux of the edge on its
+  // low side (a >= 1); pitches as for the nodes.
+  static constexpr int fpitch(int j) { return j == 0 ? ((T0 + 4) | 1) : T0; }
+  static constexpr int fplane(int j) {
+    return j == 1 ? pad16(T0 * (T1 + 4), T0) : fpitch(j) * T1;
+  }
+  static constexpr int slots(int j) {
+    return D < 3 ? fpitch(j) * (T1 + (j == 1 ? 4 : 0)) : fplane(j) * (T2 + (j == 2 ? 4 : 0));
+  }
+  static constexpr int fstep(int j) { return j == 0 ? 1 : (j == 1 ? fpitch(1) : fplane(2)); }
   static constexpr int cmax(int a, int b) { return a > b ? a : b; }
   static constexpr int EXTMAX = cmax(ext(0), cmax(D >= 2 ? ext(1) : 0, D >= 3 ? ext(2) : 0));
-  static constexpr int EDMAX =
-      cmax(edges(0), cmax(D >= 2 ? edges(1) : 0, D >= 3 ? edges(2) : 0));
+  static constexpr int FXMAX =
+      cmax(slots(0), cmax(D >= 2 ? slots(1) : 0, D >= 3 ? slots(2) : 0));
 };
 
 // Primitives (p, T, u_j) of one node from its conserved values.
@@ -377,50 +439,12 @@ __device__ __forceinline__ void load_union(const DevMesh& m, const double* __res
   }
 }
 
-// Riemann flux of direction J at one edge whose window (nodes i-2 .. i+3)
-// starts at layout index `base` of the primitives in LDS (NEXT nodes per
-// primitive, STEP between neighbours along J); stored doubled at sF[v NED + e].
-template <int D, int J, int NEXT, int STEP, int NED, bool CENTRAL>
-__device__ __forceinline__ void edge_at_scheme(const DevMesh& m, const double* sP, int base,
-                                               double* sF, int e) {
+// Rusanov flux (Eq. (11)-(12)) of direction J from the two edge states,
+// stored doubled at sF[v NED + e], one variable at a time.
+template <int D, int J, int NED>
+__device__ __forceinline__ void edge_rusanov(const DevMesh& m, const EdgeState<D>& wl,
+                                             const EdgeState<D>& wr, double* sF, int e) {
   constexpr int NV = D + 2;
-  const double eps4 = 4.0 * m.eps;
-  // interpolated left/right values of primitive q (p, T, u_j) at this edge,
-  // and the two nodes the edge lies between (a and b)
-  auto interp = [&](int q, double& l, double& r, double& a, double& b) {
-    const double* col = sP + q * NEXT + base;
-    const double v0 = col[0], v1 = col[STEP], v2 = col[2 * STEP];
-    const double v3 = col[3 * STEP], v4 = col[4 * STEP], v5 = col[5 * STEP];
-    if constexpr (CENTRAL) {
-      l = central4(v1, v2, v3, v4);
-      r = l;
-    } else {
-      weno5_pair(v0, v1, v2, v3, v4, v5, eps4, l, r);
-    }
-    a = v2;
-    b = v3;
-  };
-  // p and T first: their signs decide the first-order fallback, which is
-  // then applied to each velocity component as soon as it is interpolated
-  // (fewer values live at once).  The fallback takes the node values already
-  // in registers (selects, no branch: a branch keeps both sets live)
-  EdgeState<D> wl, wr;
-  double lp, rp, lT, rT, pa, pb, Ta, Tb;
-  interp(0, lp, rp, pa, pb);
-  interp(1, lT, rT, Ta, Tb);
-  const bool ok = (lp > 0.0) && (lT > 0.0) && (rp > 0.0) && (rT > 0.0);
-  wl.p = ok ? lp : pa;
-  wr.p = ok ? rp : pb;
-  wl.T = ok ? lT : Ta;
-  wr.T = ok ? rT : Tb;
-#pragma unroll
-  for (int i = 0; i < D; ++i) {
-    double lu, ru, ua, ub;
-    interp(2 + i, lu, ru, ua, ub);
-    wl.u[i] = ok ? lu : ua;
-    wr.u[i] = ok ? ru : ub;
-  }
-  // Rusanov flux (Eq. (11)-(12)), stored doubled, one variable at a time
   double rl, El, sl, rr, Er, sr;
   edge_thermo<D, J>(m, wl, rl, El, sl);
   edge_thermo<D, J>(m, wr, rr, Er, sr);
@@ -432,6 +456,77 @@ __device__ __forceinline__ void edge_at_scheme(const DevMesh& m, const double* s
     edge_uf<D, J>(wr, rr, Er, v, UR, FR);
     sF[v * NED + e] = fma(-S, UR - UL, FR + FL);
   }
+}
+
+// Primitives of one node in LDS (NEXT nodes per primitive).
+template <int D, int NEXT>
+__device__ __forceinline__ void node_state(const double* sP, int idx, EdgeState<D>& w) {
+  w.p = sP[idx];
+  w.T = sP[NEXT + idx];
+#pragma unroll
+  for (int i = 0; i < D; ++i) w.u[i] = sP[(2 + i) * NEXT + idx];
+}
+
+// Both WENO5-JS values of every primitive at one node (layout index idx, STEP
+// between neighbours along the direction): the left-biased ones stay in
+// registers for the edge above the node, the right-biased ones go to the
+// node's slot e of sF for the thread of the node below.
+template <int D, int NEXT, int STEP, int NED>
+__device__ __forceinline__ void node_values(const DevMesh& m, const double* sP, int idx,
+                                            double* left, double* sF, int e) {
+  const double eps4 = 4.0 * m.eps;
+#pragma unroll
+  for (int q = 0; q < D + 2; ++q) {
+    const double* col = sP + q * NEXT + idx;
+    double r;
+    weno5_node(col[-2 * STEP], col[-STEP], col[0], col[STEP], col[2 * STEP], eps4, left[q], r);
+    sF[q * NED + e] = r;
+  }
+}
+
+// Flux of the edge between the node idx (whose left-biased values are `left`)
+// and the next one, from the next node's right-biased values in its slot e of
+// sF, which the flux then replaces (no other thread reads the slot).  Where p
+// or T is not positive on a side the edge takes the states of its two nodes.
+template <int D, int J, int NEXT, int STEP, int NED>
+__device__ __forceinline__ void node_edge(const DevMesh& m, const double* sP, int idx,
+                                          const double* left, double* sF, int e) {
+  EdgeState<D> wl, wr;
+  wl.p = left[0];
+  wl.T = left[1];
+#pragma unroll
+  for (int i = 0; i < D; ++i) wl.u[i] = left[2 + i];
+  node_state<D, NED>(sF, e, wr);
+  if (!((wl.p > 0.0) && (wl.T > 0.0) && (wr.p > 0.0) && (wr.T > 0.0))) {
+    node_state<D, NEXT>(sP, idx, wl);
+    node_state<D, NEXT>(sP, idx + STEP, wr);
+  }
+  edge_rusanov<D, J, NED>(m, wl, wr, sF, e);
+}
+
+// Riemann flux of direction J at one edge with the central interpolation of
+// Eq. (8); the edge's nodes are idx and idx + STEP.
+template <int D, int J, int NEXT, int STEP, int NED>
+__device__ __forceinline__ void edge_central(const DevMesh& m, const double* sP, int idx,
+                                             double* sF, int e) {
+  double w[D + 2];
+#pragma unroll
+  for (int q = 0; q < D + 2; ++q) {
+    const double* col = sP + q * NEXT + idx;
+    w[q] = central4(col[-STEP], col[0], col[STEP], col[2 * STEP]);
+  }
+  EdgeState<D> wl, wr;
+  if ((w[0] > 0.0) && (w[1] > 0.0)) {
+    wl.p = w[0];
+    wl.T = w[1];
+#pragma unroll
+    for (int i = 0; i < D; ++i) wl.u[i] = w[2 + i];
+    wr = wl;
+  } else {
+    node_state<D, NEXT>(sP, idx, wl);
+    node_state<D, NEXT>(sP, idx + STEP, wr);
+  }
+  edge_rusanov<D, J, NED>(m, wl, wr, sF, e);
 }
 
 // Physical flux of direction J (Eq. (1)-(3)) of one conserved edge state
@@ -572,21 +667,6 @@ __device__ __forceinline__ void edge_char(const DevMesh& m, const double* sP, in
   for (int v = 0; v < NV; ++v) sF[v * NED + e] = fma(-S, UX[1][v] - UX[0][v], FR[v] + FL[v]);
 }
 
-// The scheme branch taken once per edge, so that each path is straight-line
-// code the compiler can schedule across the primitives.  The characteristic
-// scheme is a separate kernel instantiation (its LDS holds conserved states).
-template <int D, int J, int NEXT, int STEP, int NED, bool CHAR>
-__device__ __forceinline__ void edge_at(const DevMesh& m, const double* sP, int base, double* sF,
-                                        int e) {
-  if constexpr (CHAR)
-    edge_char<D, J, NEXT, STEP, NED>(m, sP, base, sF, e);
-  else if (m.scheme == AMR_SCHEME_CENTRAL)
-    edge_at_scheme<D, J, NEXT, STEP, NED, true>(m, sP, base, sF, e);
-  else
-    edge_at_scheme<D, J, NEXT, STEP, NED, false>(m, sP, base, sF, e);
-}
-
-
 // Face fluxes G of direction J (flux form of Eq. (9)) from the edge fluxes
 // in sF, their divergence into acc, and the patch-boundary faces into the
 // flux registers.
@@ -596,10 +676,7 @@ __device__ __forceinline__ void cells_at(const double* sF, double* __restrict__ 
                                          int wmask) {
   using S = TileShape<D, TX, TY, TZ>;
   constexpr int NV = D + 2;
-  constexpr int G0 = S::T0 + (J == 0 ? 3 : 0);
-  constexpr int G1 = S::T1 + (J == 1 ? 3 : 0);
-  constexpr int G2 = S::T2 + (J == 2 ? 3 : 0);
-  constexpr int NED = G0 * G1 * G2;
+  constexpr int NED = S::slots(J);
   constexpr int CPT = (S::NCELL + NT - 1) / NT;
   const int tid = threadIdx.x;
   const int nface = (D == 1) ? 1 : (D == 2 ? n : n * n);
@@ -615,13 +692,9 @@ __device__ __forceinline__ void cells_at(const double* sF, double* __restrict__ 
     const int t1 = (cell / S::T0) % S::T1;
     const int t2 = cell / (S::T0 * S::T1);
     const int tj = J == 0 ? t0 : (J == 1 ? t1 : t2);
-    // edge-array index of edge (t_J - 2 + k) + 1/2 in the edge box
-    int eb;
-    constexpr int ESTEP = J == 0 ? 1 : (J == 1 ? G0 : G0 * G1);
-    if constexpr (J == 0) eb = G0 * (t1 + G1 * t2);
-    else if constexpr (J == 1) eb = t0 + G0 * G1 * t2;
-    else eb = t0 + G0 * t1;
-    eb += tj * ESTEP;
+    // slot of edge (t_J - 2) + 1/2, the first of the cell's four
+    constexpr int ESTEP = S::fstep(J);
+    const int eb = t0 + S::fpitch(J) * t1 + S::fplane(J) * t2 + ESTEP;
     const int i = o[J] + tj;
     int tang = 0;
     if constexpr (D == 2) tang = (J == 0) ? (o[1] + t1) : (o[0] + t0);
@@ -648,38 +721,90 @@ __device__ __forceinline__ void cells_at(const double* sF, double* __restrict__ 
   }
 }
 
+// Where thread item t of a direction-J phase works: node a - 2 along J
+// (a = 0 .. T_J + 3) of line c of the tile's cross-section.  The cross-section
+// varies fastest, so that in 3D a wave holds one node position of 64 lines:
+// its LDS accesses meet the padded pitches without bank conflicts, and the
+// edge phase, which has one item less per line, leaves whole waves idle.
+template <int D, int TX, int TY, int TZ, int J, bool UNION>
+struct Line {
+  using S = TileShape<D, TX, TY, TZ>;
+  static constexpr int TJ = J == 0 ? S::T0 : (J == 1 ? S::T1 : S::T2);
+  static constexpr int NCROSS = S::NCELL / TJ;
+  static constexpr int NNODE = NCROSS * (TJ + 4);     // items of the node phase
+  static constexpr int NEXT = UNION ? S::NUNION : S::ext(J);
+  static constexpr int STEP =
+      J == 0 ? 1 : (UNION ? S::UPITCH : (J == 1 ? S::xpitch(1) : S::xplane(2)));
+  static constexpr int NED = S::slots(J);
+  int idx, slot;  // layout index of the node and of its slot
+  __device__ __forceinline__ explicit Line(int t) {
+    const int a = t / NCROSS, c = t % NCROSS;
+    if constexpr (J == 0) {
+      const int c1 = c % S::T1, c2 = c / S::T1;
+      idx = UNION ? (D >= 2 ? (c1 + 4) * S::UPITCH : 0) + a + 2
+                  : a + 2 + S::xpitch(0) * c1 + S::xplane(0) * c2;
+      slot = a + S::fpitch(0) * c1 + S::fplane(0) * c2;
+    } else if constexpr (J == 1) {
+      const int c0 = c % S::T0, c2 = c / S::T0;
+      idx = UNION ? (a + 2) * S::UPITCH + c0 + 4
+                  : c0 + S::xpitch(1) * (a + 2) + S::xplane(1) * c2;
+      slot = c0 + S::fpitch(1) * a + S::fplane(1) * c2;
+    } else {
+      const int c0 = c % S::T0, c1 = c / S::T0;
+      idx = c0 + S::xpitch(2) * c1 + S::xplane(2) * (a + 2);
+      slot = c0 + S::fpitch(2) * c1 + S::fplane(2) * a;
+    }
+  }
+};
+
 // Riemann flux at every edge i+1/2, i = o_J-2 .. o_J+T_J, of direction J
 // from the node values in sP (the union layout in 1D/2D, the tile extended
-// along J in 3D), into sF.
+// along J in 3D), into sF.  WENO5 of the primitives: a node phase (one thread
+// per node forms both of its edge values) and, after a block barrier, an edge
+// phase (one thread per edge).  The 8x8x8 tile has 768 nodes per direction, a
+// thread each, and 704 edges.  With one phase of 704 edges, each forming the
+// indicators of both its nodes, a stage launch took 2225 us against 1959 us
+// (3D, 20.4 M leaf cells, mostly 8^3 patches; 44.2 against 37.6 wave
+// instructions per cell, the FP64 VALU busy 72 % of the clocks), 180 against
+// 163 us (2D, 2.75 M cells in 32^2 patches) and 24.2 against 21.4 us (2D, 0.28 M
+// cells).
 template <int D, int TX, int TY, int TZ, int NT, int J, bool UNION, bool CHAR>
 __device__ __forceinline__ void edges_dir(const DevMesh& m, const double* sP, double* sF) {
-  using S = TileShape<D, TX, TY, TZ>;
-  // E0 is the row pitch of the node array
-  constexpr int E0 = UNION ? S::UPITCH : S::xpitch(J);
-  constexpr int E1 = UNION ? (D >= 2 ? S::T1 + 8 : 1) : S::T1 + (J == 1 ? 8 : 0);
-  constexpr int E2 = UNION ? 1 : S::T2 + (J == 2 ? 8 : 0);
-  constexpr int NEXT = E0 * E1 * E2;
-  constexpr int G0 = S::T0 + (J == 0 ? 3 : 0);
-  constexpr int G1 = S::T1 + (J == 1 ? 3 : 0);
-  constexpr int G2 = S::T2 + (J == 2 ? 3 : 0);
-  constexpr int NED = G0 * G1 * G2;
-  constexpr int STEP = J == 0 ? 1 : (J == 1 ? E0 : E0 * E1);
-  for (int t = threadIdx.x; t < NED; t += NT) {
-    // 3D x edges go to the lanes cross-section first: the 16 lanes of an LDS
-    // pass then read rows r..r+15 of the odd-pitched node box and write
-    // edges a0 + 11 r (distinct banks); row by row, 11 edges to a row, they
-    // would collide
-    constexpr bool XCROSS = !UNION && J == 0;
-    const int a0 = XCROSS ? t / (G1 * G2) : t % G0;
-    const int a1 = XCROSS ? t % G1 : (t / G0) % G1;
-    const int a2 = XCROSS ? (t / G1) % G2 : t / (G0 * G1);
-    const int e = XCROSS ? a0 + G0 * (a1 + G1 * a2) : t;
-    // layout index of node i-2 of this edge's window
-    int base;
-    if constexpr (!UNION) base = a0 + E0 * (a1 + E1 * a2);
-    else if constexpr (J == 0) base = (D >= 2 ? (a1 + 4) * E0 : 0) + a0;
-    else base = a1 * E0 + (a0 + 4);
-    edge_at<D, J, NEXT, STEP, NED, CHAR>(m, sP, base, sF, e);
+  using G = Line<D, TX, TY, TZ, J, UNION>;
+  constexpr int NEDGE = G::NNODE - G::NCROSS;
+  if constexpr (CHAR) {
+    for (int t = threadIdx.x; t < NEDGE; t += NT) {
+      const G g(t);
+      edge_char<D, J, G::NEXT, G::STEP, G::NED>(m, sP, g.idx - 2 * G::STEP, sF,
+                                                g.slot + TileShape<D, TX, TY, TZ>::fstep(J));
+    }
+  } else if (m.scheme == AMR_SCHEME_CENTRAL) {
+    for (int t = threadIdx.x; t < NEDGE; t += NT) {
+      const G g(t);
+      edge_central<D, J, G::NEXT, G::STEP, G::NED>(m, sP, g.idx, sF,
+                                                   g.slot + TileShape<D, TX, TY, TZ>::fstep(J));
+    }
+  } else {
+    constexpr int ITER = (G::NNODE + NT - 1) / NT;
+    double left[ITER][D + 2];
+#pragma unroll
+    for (int k = 0; k < ITER; ++k) {
+      const int t = threadIdx.x + k * NT;
+      if (t < G::NNODE) {
+        const G g(t);
+        node_values<D, G::NEXT, G::STEP, G::NED>(m, sP, g.idx, left[k], sF, g.slot);
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < ITER; ++k) {
+      const int t = threadIdx.x + k * NT;
+      if (t < NEDGE) {
+        const G g(t);
+        node_edge<D, J, G::NEXT, G::STEP, G::NED>(m, sP, g.idx, left[k], sF,
+                                                  g.slot + TileShape<D, TX, TY, TZ>::fstep(J));
+      }
+    }
   }
 }
 
@@ -696,10 +821,7 @@ __device__ __forceinline__ void load_dir(const DevMesh& m, const double* __restr
                                          const long long* sN, double* sP) {
   using S = TileShape<D, TX, TY, TZ>;
   constexpr int NV = D + 2;
-  constexpr int E0 = S::xpitch(J);             // row pitch
-  constexpr int E1 = S::T1 + (J == 1 ? 8 : 0);
-  constexpr int E2 = S::T2 + (J == 2 ? 8 : 0);
-  constexpr int NEXT = E0 * E1 * E2;
+  constexpr int NEXT = S::ext(J);
   constexpr int NC = S::NCELL;
   constexpr int TJ = J == 0 ? S::T0 : (J == 1 ? S::T1 : S::T2);
   constexpr int HL = NC / TJ;                  // nodes of one layer across J
@@ -728,8 +850,7 @@ __device__ __forceinline__ void load_dir(const DevMesh& m, const double* __restr
       t[J == 2 ? 1 : 2] = b;
     }
     const int c[3] = {o[0] + t[0], o[1] + t[1], o[2] + t[2]};
-    lidx[k] = (t[0] + (J == 0 ? 4 : 0)) + E0 * ((t[1] + (J == 1 ? 4 : 0)) +
-                                                E1 * (t[2] + (J == 2 ? 4 : 0)));
+    lidx[k] = S::template node<J>(t[0], t[1], t[2]);
     node_conserved_dir<D, J, FUSE>(m, Uin, Pin, n, full, c, pc, l, sN, u[k]);
   }
 #pragma unroll
@@ -781,8 +902,6 @@ __device__ __forceinline__ void halo_issue(const DevMesh& m, const double* __res
                                            DirHalo<D, TX, TY, TZ, NT, J>& h) {
   using S = TileShape<D, TX, TY, TZ>;
   using H = DirHalo<D, TX, TY, TZ, NT, J>;
-  constexpr int E0 = S::xpitch(J);
-  constexpr int E1 = S::T1 + (J == 1 ? 8 : 0);
   constexpr int CA = J == 0 ? S::T1 : S::T0;   // extent of the lower cross direction
   const int tid = phase_tid();
 #pragma unroll
@@ -798,9 +917,7 @@ __device__ __forceinline__ void halo_issue(const DevMesh& m, const double* __res
     t[J == 0 ? 1 : 0] = r % CA;
     t[J == 2 ? 1 : 2] = r / CA;
     const int c[3] = {o[0] + t[0], o[1] + t[1], o[2] + t[2]};
-    h.lidx[k] = h0 < H::NH ? (t[0] + (J == 0 ? 4 : 0)) +
-                                 E0 * ((t[1] + (J == 1 ? 4 : 0)) + E1 * (t[2] + (J == 2 ? 4 : 0)))
-                           : -1;
+    h.lidx[k] = h0 < H::NH ? S::template node<J>(t[0], t[1], t[2]) : -1;
     node_conserved_dir<D, J, FUSE>(m, Uin, Pin, n, full, c, pc, l, sN, h.u[k]);
   }
 }
@@ -810,15 +927,11 @@ __device__ __forceinline__ void halo_store(const DevMesh& m, const DirHalo<D, TX
                                            const double* keep, double* sP) {
   using S = TileShape<D, TX, TY, TZ>;
   using H = DirHalo<D, TX, TY, TZ, NT, J>;
-  constexpr int E0 = S::xpitch(J);
-  constexpr int E1 = S::T1 + (J == 1 ? 8 : 0);
   constexpr int NEXT = S::ext(J);
   const int tid = phase_tid();
   if (tid < S::NCELL) {
     const int t0 = tid % S::T0, t1 = (tid / S::T0) % S::T1, t2 = tid / (S::T0 * S::T1);
-    node_store<D, false>(m, keep, sP, NEXT,
-                         (t0 + (J == 0 ? 4 : 0)) +
-                             E0 * ((t1 + (J == 1 ? 4 : 0)) + E1 * (t2 + (J == 2 ? 4 : 0))));
+    node_store<D, false>(m, keep, sP, NEXT, S::template node<J>(t0, t1, t2));
   }
 #pragma unroll
   for (int k = 0; k < H::ITER; ++k)
@@ -837,9 +950,9 @@ __device__ __forceinline__ void stage_direction(const DevMesh& m, double* __rest
   __syncthreads();
 }
 
-// 2D union layout, both directions at once: the x and y edges form one work
-// range (x first), then every cell takes its x and then its y divergence,
-// the order of the direction-by-direction path.
+// 2D union layout, both directions at once: the x and y nodes (and then
+// edges) form one work range, x first, then every cell takes its x and then
+// its y divergence, the order of the direction-by-direction path.
 template <int D, int TX, int TY, int NT, bool CHAR>
 __device__ __forceinline__ void stage_both(const DevMesh& m, double* __restrict__ frp, int n,
                                            const int o[3], const double* sP, double* sFx,
@@ -847,18 +960,66 @@ __device__ __forceinline__ void stage_both(const DevMesh& m, double* __restrict_
                                            int wmask) {
   static_assert(D == 2, "combined sweep is 2D");
   using S = TileShape<D, TX, TY, 1>;
-  constexpr int E0 = S::UPITCH;                // row pitch of the union box
-  constexpr int NEXT = S::NUNION;
-  constexpr int GX0 = S::T0 + 3, NEDX = GX0 * S::T1;
-  constexpr int GY0 = S::T0, NEDY = S::T0 * (S::T1 + 3);
-  for (int e = threadIdx.x; e < NEDX + NEDY; e += NT) {
-    if (e < NEDX) {
-      const int a0 = e % GX0, a1 = e / GX0;
-      edge_at<D, 0, NEXT, 1, NEDX, CHAR>(m, sP, (a1 + 4) * E0 + a0, sFx, e);
-    } else {
-      const int f = e - NEDX;
-      const int a0 = f % GY0, a1 = f / GY0;
-      edge_at<D, 1, NEXT, E0, NEDY, CHAR>(m, sP, a1 * E0 + (a0 + 4), sFy, f);
+  using GX = Line<D, TX, TY, 1, 0, true>;
+  using GY = Line<D, TX, TY, 1, 1, true>;
+  constexpr int NX = GX::NNODE, EX = NX - GX::NCROSS, EY = GY::NNODE - GY::NCROSS;
+  auto both = [&](int t, int nx, auto fx, auto fy) {
+    if (t < nx) fx(GX(t));
+    else fy(GY(t - nx));
+  };
+  if constexpr (CHAR) {
+    for (int t = threadIdx.x; t < EX + EY; t += NT)
+      both(t, EX,
+           [&](const GX& g) {
+             edge_char<D, 0, GX::NEXT, GX::STEP, GX::NED>(m, sP, g.idx - 2 * GX::STEP, sFx,
+                                                          g.slot + S::fstep(0));
+           },
+           [&](const GY& g) {
+             edge_char<D, 1, GY::NEXT, GY::STEP, GY::NED>(m, sP, g.idx - 2 * GY::STEP, sFy,
+                                                          g.slot + S::fstep(1));
+           });
+  } else if (m.scheme == AMR_SCHEME_CENTRAL) {
+    for (int t = threadIdx.x; t < EX + EY; t += NT)
+      both(t, EX,
+           [&](const GX& g) {
+             edge_central<D, 0, GX::NEXT, GX::STEP, GX::NED>(m, sP, g.idx, sFx,
+                                                             g.slot + S::fstep(0));
+           },
+           [&](const GY& g) {
+             edge_central<D, 1, GY::NEXT, GY::STEP, GY::NED>(m, sP, g.idx, sFy,
+                                                             g.slot + S::fstep(1));
+           });
+  } else {
+    // the nodes of both phases keep their items: node item t has edge item t
+    // wherever its line has an edge above it
+    constexpr int ITER = (NX + GY::NNODE + NT - 1) / NT;
+    double left[ITER][D + 2];
+#pragma unroll
+    for (int k = 0; k < ITER; ++k) {
+      const int t = threadIdx.x + k * NT;
+      if (t < NX + GY::NNODE)
+        both(t, NX,
+             [&](const GX& g) {
+               node_values<D, GX::NEXT, GX::STEP, GX::NED>(m, sP, g.idx, left[k], sFx, g.slot);
+             },
+             [&](const GY& g) {
+               node_values<D, GY::NEXT, GY::STEP, GY::NED>(m, sP, g.idx, left[k], sFy, g.slot);
+             });
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < ITER; ++k) {
+      const int t = threadIdx.x + k * NT;
+      if (t < EX || (t >= NX && t < NX + EY))
+        both(t, NX,
+             [&](const GX& g) {
+               node_edge<D, 0, GX::NEXT, GX::STEP, GX::NED>(m, sP, g.idx, left[k], sFx,
+                                                            g.slot + S::fstep(0));
+             },
+             [&](const GY& g) {
+               node_edge<D, 1, GY::NEXT, GY::STEP, GY::NED>(m, sP, g.idx, left[k], sFy,
+                                                            g.slot + S::fstep(1));
+             });
     }
   }
   __syncthreads();
@@ -969,7 +1130,7 @@ __device__ __forceinline__ void stage_item(const DevMesh& m, int mode,
     __syncthreads();
     if constexpr (BOTH && D == 2) {
       stage_both<D, TX, TY, NT, CHAR>(m, frp, n, o, sP, sF,
-                                      sF + (D + 2) * ((S::T0 + 3) * S::T1), acc, L.inv_h, wmask);
+                                      sF + (D + 2) * S::slots(0), acc, L.inv_h, wmask);
     } else {
       stage_direction<D, TX, TY, TZ, NT, 0, CHAR>(m, frp, n, o, sP, sF, acc, L.inv_h, wmask);
       if constexpr (D >= 2)
@@ -1059,7 +1220,7 @@ __device__ __forceinline__ void stage_item(const DevMesh& m, int mode,
   // values it writes (staged in sF, free once every thread has read its
   // edge fluxes)
   const bool restrict_here = mode != kModeRHS && l == m.nlev - 1 && l >= 1;
-  static_assert(S::NCELL <= S::EDMAX, "the staged cell values fit sF");
+  static_assert(S::NCELL <= S::FXMAX, "the staged cell values fit sF");
   double* sR = sF;
   if (restrict_here) __syncthreads();
 #pragma unroll
@@ -1135,9 +1296,9 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(CHAR ? 4 : 6
   constexpr bool UNION = D <= 2;
   constexpr int NU = S::NUNION;
   // edge fluxes: one direction at a time, or x and y together (BOTH)
-  constexpr int NEDXY = (S::T0 + 3) * S::T1 + S::T0 * (S::T1 + 3);
+  constexpr int NEDXY = S::slots(0) + S::slots(1);
   __shared__ double sP[(D + 2) * (UNION ? NU : S::EXTMAX)];
-  __shared__ double sF[(D + 2) * (BOTH ? NEDXY : S::EDMAX)];
+  __shared__ double sF[(D + 2) * (BOTH ? NEDXY : S::FXMAX)];
   __shared__ long long sN[27];
   const int* list = dir ? tiles + dir[0] : tiles;
   const int item = xcd_item(dir ? dir[1] : count);
@@ -1151,11 +1312,10 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(CHAR ? 4 : 6
 
 }  // namespace
 
-// Tile variants: thread counts cover the edges of one direction of the
-// tile in one pass (multiples of 64); the 8x8x8 tile's 704 edges take 768
-// threads, 12 waves, which spread evenly over a CU's 4 SIMDs (with 11 waves
-// one SIMD holds a wave less of every block: 13.1 against 14.6 ms per RHS
-// launch over 156 M cells of a four-level 3D hierarchy).
+// Tile variants: thread counts cover the nodes (T_J + 4 per line) of one
+// direction of the tile in one pass, in whole waves (the 8x8x4 tile's z
+// direction takes two); the 8x8x8 tile's 768 nodes are 12 waves, which also
+// spread evenly over a CU's 4 SIMDs.
 static const Kernels::TileVariant kVariants[] = {
     {1, 16, 1, 1, 64}, {1, 8, 1, 1, 64},                                   // 1D
     {2, 16, 16, 1, 320}, {2, 16, 8, 1, 192}, {2, 8, 8, 1, 128},           // 2D
