@@ -1658,16 +1658,11 @@ struct amr_cnn {
   float* params = nullptr;   // FP32 master
   float* m = nullptr;
   float* v = nullptr;
-  float* grads = nullptr;
   unsigned short* wb = nullptr;  // BF16 copy
   unsigned short* X = nullptr;   // max_batch input tiles
-  unsigned short* A1 = nullptr;
-  unsigned short* A2 = nullptr;
   float* Z = nullptr;
-  float* G = nullptr;
-  float* partials = nullptr;
-  float* loss_part = nullptr;
-  int loss_blocks = 0;
+  float* partials = nullptr;     // per tile of a training batch: parameter gradient
+  float* loss_part = nullptr;    // and loss
   int* d_pids = nullptr;   // 2D: pids; 3D: tile items
   long long items_cap = 0;
   uint8_t* d_pred = nullptr;
@@ -1682,12 +1677,11 @@ struct amr_cnn {
     else
       amr::Cnn3::gather(h->dm, h->U[buf], items, count, norm, x, h->stream);
   }
-  void forward(const unsigned short* x, int count, unsigned short* a1, unsigned short* a2,
-               float* z) const {
+  void forward(const unsigned short* x, int count, float* z) const {
     if (dim == 2)
-      amr::Cnn::forward(count, n, x, wb, params, a1, a2, z, h->stream);
+      amr::Cnn::forward(count, n, x, wb, params, z, h->stream);
     else
-      amr::Cnn3::forward(count, x, wb, params, a1, a2, z, h->stream);
+      amr::Cnn3::forward(count, x, wb, params, z, h->stream);
   }
 };
 
@@ -1719,19 +1713,14 @@ amr_status amr_cnn_create(amr_hierarchy* h, const amr_cnn_config* cfg, amr_cnn**
     }
     const int n = c->n;
     const long long N = c->max_batch;
-    long long a1e, a2e;
     if (dim == 2) {
       c->np = amr::CNN_NPARAM;
       c->in_elems = 4LL * (n + 6) * (n + 6);
-      a1e = 16LL * (n + 4) * (n + 4);
-      a2e = 16LL * (n + 2) * (n + 2);
       c->out_cells = (long long)n * n;
       c->items_cap = h->forest.max_patches;
     } else {
       c->np = amr::CNN3_NPARAM;
       c->in_elems = (long long)amr::CNN3_CH * amr::CNN3_P0;
-      a1e = (long long)amr::CNN3_CH * amr::CNN3_P1;
-      a2e = (long long)amr::CNN3_CH * amr::CNN3_P2;
       c->out_cells = amr::CNN3_P3;
       int tiles = 1;
       for (int l = 0; l < h->forest.nlev; ++l) {
@@ -1745,16 +1734,11 @@ amr_status amr_cnn_create(amr_hierarchy* h, const amr_cnn_config* cfg, amr_cnn**
       c->params = (float*)c->alloc(np * sizeof(float));
       c->m = (float*)c->alloc(np * sizeof(float));
       c->v = (float*)c->alloc(np * sizeof(float));
-      c->grads = (float*)c->alloc(np * sizeof(float));
       c->wb = (unsigned short*)c->alloc(np * sizeof(unsigned short));
       c->X = (unsigned short*)c->alloc(N * c->in_elems * sizeof(unsigned short));
-      c->A1 = (unsigned short*)c->alloc(N * a1e * sizeof(unsigned short));
-      c->A2 = (unsigned short*)c->alloc(N * a2e * sizeof(unsigned short));
       c->Z = (float*)c->alloc(N * c->out_cells * sizeof(float));
-      c->G = (float*)c->alloc(N * c->out_cells * sizeof(float));
       c->partials = (float*)c->alloc(N * np * sizeof(float));
-      c->loss_blocks = 256;
-      c->loss_part = (float*)c->alloc((c->loss_blocks + 1) * sizeof(float));
+      c->loss_part = (float*)c->alloc(N * sizeof(float));
       c->d_pids = (int*)c->alloc((size_t)c->items_cap * sizeof(int));
       c->d_pred = (uint8_t*)c->alloc(h->forest.max_patches);
       HIP_OK(hipMemsetAsync(c->params, 0, np * sizeof(float), h->stream));
@@ -1842,7 +1826,7 @@ amr_status amr_cnn_gather(amr_cnn* c, int buf, const int* pids_host, int npatch,
 amr_status amr_cnn_forward(amr_cnn* c, const uint16_t* x_dev, int npatch, float* logits_dev) {
   if (!c || !x_dev || !logits_dev || npatch < 0 || npatch > c->max_batch) return AMR_E_ARG;
   return guarded(c->h, [&]() -> amr_status {
-    c->forward((const unsigned short*)x_dev, npatch, nullptr, nullptr, logits_dev);
+    c->forward((const unsigned short*)x_dev, npatch, logits_dev);
     c->h->check_launch();
     return AMR_OK;
   });
@@ -1855,20 +1839,15 @@ amr_status amr_cnn_train_step(amr_cnn* c, const uint16_t* x_dev, const uint8_t* 
   return guarded(c->h, [&]() -> amr_status {
     hipStream_t s = c->h->stream;
     const unsigned short* X = (const unsigned short*)x_dev;
-    c->forward(X, npatch, c->A1, c->A2, c->Z);
-    const long long total = (long long)npatch * c->out_cells;
-    amr::Cnn::loss(total, c->Z, labels_dev, c->cfg.pos_weight, c->G, c->loss_part,
-                   c->loss_blocks, loss_dev, s);
     if (c->dim == 2)
-      amr::Cnn::backward(npatch, c->n, X, c->A1, c->A2, c->G, c->wb, c->partials, c->grads, s);
+      amr::Cnn::train(npatch, c->n, X, labels_dev, c->wb, c->params, c->cfg.pos_weight, c->partials,
+                      c->loss_part, s);
     else
-      amr::Cnn3::backward(npatch, X, c->A1, c->A2, c->G, c->wb, c->partials, c->grads, s);
-    if (grads_dev)
-      HIP_OK(hipMemcpyAsync(grads_dev, c->grads, c->np * sizeof(float), hipMemcpyDeviceToDevice, s));
-    if (lr > 0.f) {
-      c->t += 1;
-      amr::Cnn::adam(c->params, c->grads, c->m, c->v, lr, c->t, c->np, c->wb, s);
-    }
+      amr::Cnn3::train(npatch, X, labels_dev, c->wb, c->params, c->cfg.pos_weight, c->partials,
+                       c->loss_part, s);
+    if (lr > 0.f) c->t += 1;
+    amr::Cnn::update(c->partials, c->loss_part, npatch, c->np, grads_dev, loss_dev, c->params, c->m,
+                     c->v, lr, c->t, c->wb, s);
     c->h->check_launch();
     return AMR_OK;
   });
@@ -1904,7 +1883,7 @@ amr_status amr_cnn_predict(amr_cnn* c, int buf, float tau, uint8_t* refine_req_d
     for (size_t b0 = 0; b0 < items.size(); b0 += (size_t)c->max_batch) {
       const int cnt = (int)std::min<size_t>(c->max_batch, items.size() - b0);
       c->gather(buf, c->d_pids + b0, cnt, c->X);
-      c->forward(c->X, cnt, nullptr, nullptr, c->Z);
+      c->forward(c->X, cnt, c->Z);
       if (c->dim == 2)
         amr::Cnn::requests(cnt, c->n, c->Z, c->d_pids + b0, zt, c->d_pred, s);
       else

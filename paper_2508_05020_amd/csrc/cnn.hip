@@ -68,17 +68,23 @@ __global__ __launch_bounds__(256) void k_cnn_gather(DevMesh m, const double* __r
 // ---------------------------------------------------------------------------
 constexpr int FWD_THREADS = 256;
 
-// layer-1 B operand (weights) for k-chunk kc: k = (tap, channel), tap = 4 kc + kq
+// p / w for the pixel indices of a plane of edge w <= 38 (p < w^2) by one
+// product: m = ceil(2^16 / w) exceeds 2^16 / w by less than 1, so the product
+// exceeds 2^16 p / w by less than p < 1444, below the 2^16 / w >= 1724 that
+// would change the quotient.  p m fits 32 bits.
+struct PixelDiv {
+  unsigned m;
+  __device__ __forceinline__ explicit PixelDiv(int w) : m(65535u / (unsigned)w + 1u) {}
+  __device__ __forceinline__ int operator()(int p) const { return (int)(((unsigned)p * m) >> 16); }
+};
+
+// layer-1 B operand (weights) for k-chunk kc: k = (tap, channel), tap = 4 kc +
+// kq; read in any case (no branch around the loads), zero past the last tap
 __device__ __forceinline__ s4 w1_operand(const unsigned short* __restrict__ W, int j, int kq, int kc) {
   const int tap = 4 * kc + kq;
-  if (tap >= 9) return zero4();
-  s4 r;
-  // W1 layout [o][c][tap] (o = j)
-  r.x = (short)W[(j * 4 + 0) * 9 + tap];
-  r.y = (short)W[(j * 4 + 1) * 9 + tap];
-  r.z = (short)W[(j * 4 + 2) * 9 + tap];
-  r.w = (short)W[(j * 4 + 3) * 9 + tap];
-  return r;
+  const unsigned short* w = W + j * 36 + (tap < 9 ? tap : 8);  // W1 layout [o][c][tap], o = j
+  const s4 r = pack4((short)w[0], (short)w[9], (short)w[18], (short)w[27]);
+  return tap < 9 ? r : zero4();
 }
 
 // layer-2 B operand for tap: B[k = in-channel][j = out-channel] = W2[j][k][tap]
@@ -92,13 +98,15 @@ __device__ __forceinline__ s4 w2_operand(const unsigned short* __restrict__ W, i
 }
 
 // conv 3x3 valid, 16 output channels, from an HWC LDS input of width wi and
-// CI channels (4 or 16) to an HWC output of width wo = wi - 2 (bias, ReLU,
+// CI channels (4 or 16) to an HWC LDS output of width wo = wi - 2 (bias, ReLU,
 // BF16); rows of 16 output pixels per MFMA tile.
 template <int CI>
-__device__ void conv16(const unsigned short* __restrict__ in, int wi, unsigned short* __restrict__ out,
-                       unsigned short* __restrict__ gout, const unsigned short* __restrict__ Wb,
-                       const float* __restrict__ bias) {
+__device__ __forceinline__ void conv16(const unsigned short* __restrict__ in, int wi,
+                                       unsigned short* __restrict__ out,
+                                       const unsigned short* __restrict__ Wb,
+                                       const float* __restrict__ bias) {
   const int wo = wi - 2;
+  const PixelDiv dv(wo);
   const int P = wo * wo;
   const int lane = threadIdx.x & 63;
   const int wave = threadIdx.x >> 6;
@@ -114,19 +122,15 @@ __device__ void conv16(const unsigned short* __restrict__ in, int wi, unsigned s
     // A rows: output pixel p = 16 blk + i (clamped for the tail)
     int p = 16 * blk + i;
     const int pc = p < P ? p : P - 1;
-    const int py = pc / wo, px = pc - py * wo;
+    const int py = dv(pc), px = pc - py * wo;
     f4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int kc = 0; kc < KC; ++kc) {
       s4 a;
       if (CI == 4) {
-        const int tap = 4 * kc + kq;
-        if (tap < 9) {
-          const int ty = tap / 3, tx = tap - 3 * (tap / 3);
-          a = load4(in + ((py + ty) * wi + (px + tx)) * 4);
-        } else {
-          a = zero4();
-        }
+        const int tap = 4 * kc + kq, t = tap < 9 ? tap : 8;
+        a = load4(in + ((py + t / 3) * wi + px + t % 3) * 4);
+        if (tap >= 9) a = zero4();
       } else {
         const int tap = kc;
         const int ty = tap / 3, tx = tap - 3 * (tap / 3);
@@ -141,9 +145,7 @@ __device__ void conv16(const unsigned short* __restrict__ in, int wi, unsigned s
       if (q < P) {
         float v = acc[e] + bcol;
         v = v > 0.f ? v : 0.f;
-        const unsigned short h = f2bf(v);
-        out[q * 16 + i] = h;
-        if (gout) gout[q * 16 + i] = h;
+        out[q * 16 + i] = f2bf_hw(v);
       }
     }
   }
@@ -153,8 +155,6 @@ __global__ __launch_bounds__(FWD_THREADS) void k_cnn_fwd(int count, int n,
                                                          const unsigned short* __restrict__ X,
                                                          const unsigned short* __restrict__ Wb,
                                                          const float* __restrict__ params,
-                                                         unsigned short* __restrict__ A1,
-                                                         unsigned short* __restrict__ A2,
                                                          float* __restrict__ Z) {
   extern __shared__ unsigned short smem[];
   const int b = blockIdx.x;
@@ -168,9 +168,9 @@ __global__ __launch_bounds__(FWD_THREADS) void k_cnn_fwd(int count, int n,
   for (int t = threadIdx.x; t < P0; t += blockDim.x)
     *reinterpret_cast<uint2*>(sx + 4 * t) = *reinterpret_cast<const uint2*>(xg + 4 * t);
   __syncthreads();
-  conv16<4>(sx, w0, s1, A1 ? A1 + (long long)b * P1 * 16 : nullptr, Wb + CNN_W1, params + CNN_B1);
+  conv16<4>(sx, w0, s1, Wb + CNN_W1, params + CNN_B1);
   __syncthreads();
-  conv16<16>(s1, w1, s2, A2 ? A2 + (long long)b * P2 * 16 : nullptr, Wb + CNN_W2, params + CNN_B2);
+  conv16<16>(s1, w1, s2, Wb + CNN_W2, params + CNN_B2);
   __syncthreads();
   // layer 3 (16 -> 1) on the VALU
   const int P3 = n * n;
@@ -189,255 +189,323 @@ __global__ __launch_bounds__(FWD_THREADS) void k_cnn_fwd(int count, int n,
 }
 
 // ---------------------------------------------------------------------------
-// loss: weighted BCE with logits, per-cell gradient, per-block partial sums
+// training: forward, loss and backward of one patch per block, the per-patch
+// parameter gradients and loss to global memory
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void k_cnn_loss(long long total, const float* __restrict__ Z,
-                                                  const uint8_t* __restrict__ Y, float pos_weight,
-                                                  float* __restrict__ G, float* __restrict__ partial) {
-  __shared__ float red[4];
-  float acc = 0.f;
-  const float inv = 1.0f / (float)total;
-  for (long long t = blockIdx.x * (long long)blockDim.x + threadIdx.x; t < total;
-       t += (long long)gridDim.x * blockDim.x) {
-    const float z = Z[t];
-    const float y = Y[t] ? 1.f : 0.f;
-    const float sp_pos = fmaxf(-z, 0.f) + log1pf(expf(-fabsf(z)));  // softplus(-z)
-    const float sp_neg = fmaxf(z, 0.f) + log1pf(expf(-fabsf(z)));   // softplus(z)
-    acc += pos_weight * y * sp_pos + (1.f - y) * sp_neg;
-    const float s = 1.f / (1.f + expf(-z));
-    G[t] = (pos_weight * y * (s - 1.f) + (1.f - y) * s) * inv;
+// A batch is tens of patches, so a launch is one patch's latency: 16 waves per
+// patch, every activation and gradient of it in LDS from the input to the
+// gradients (no activation goes through memory), the reductions spread over
+// the waves as MFMA chains.  It replaces a forward, a loss and a backward
+// launch (with 8 waves and serial per-parameter loops): 11.5 + 4.5 + 68.9 us
+// for 64 patches of edge 16, 20.4 us now.
+constexpr int TRAIN_THREADS = 1024;
+constexpr int TRAIN_WAVES = TRAIN_THREADS / 64;
+
+// LDS of the training kernel (bytes).  dz1 (whole blocks of 16 pixels) takes
+// the place of the second activation, the logit gradients and the FP32 copy of
+// W3, which are read before it is written; dz2 is stored with a border of two
+// zero pixels, so that the data gradient reads it without bounds checks.
+struct TrainLds {
+  int x, a1, a2, g, w3, dz1, dz2, red, wb, total;
+  __host__ __device__ explicit TrainLds(int n) {
+    const int P0 = (n + 6) * (n + 6), P1 = (n + 4) * (n + 4), P2 = (n + 2) * (n + 2), P3 = n * n;
+    x = 0;
+    a1 = x + P0 * 4 * 2;
+    a2 = dz1 = a1 + P1 * 16 * 2;
+    g = a2 + P2 * 16 * 2;
+    w3 = g + P3 * 4;
+    const int after_a = w3 + 144 * 4, after_b = dz1 + (P1 + 15) / 16 * 16 * 32;
+    dz2 = after_a > after_b ? after_a : after_b;
+    red = dz2 + P1Z(n) * 16 * 2;
+    wb = red + 12 * 256 * 4;
+    total = wb + ((CNN_NPARAM * 2 + 15) / 16) * 16;
   }
-  for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off);
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = acc;
-  __syncthreads();
-  if (threadIdx.x == 0) partial[blockIdx.x] = ((red[0] + red[1]) + (red[2] + red[3])) * inv;
-}
+  static __host__ __device__ int P1Z(int n) { return (n + 6) * (n + 6); }  // dz2 with its border
+};
 
-__global__ void k_cnn_loss_final(const float* __restrict__ partial, int nblocks, float* __restrict__ loss) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) {
-    float s = 0.f;
-    for (int i = 0; i < nblocks; ++i) s += partial[i];
-    loss[0] = s;
-  }
-}
+__device__ __forceinline__ float softplus_tail(float z) { return log1pf(expf(-fabsf(z))); }
 
-// ---------------------------------------------------------------------------
-// backward of one patch per block: per-patch parameter-gradient partials
-// ---------------------------------------------------------------------------
-constexpr int BWD_THREADS = 512;  // the loops stride over the block's waves
-
-__device__ __forceinline__ s4 pick4(const unsigned short* base, int stride) {
-  s4 r;
-  r.x = (short)base[0];
-  r.y = (short)base[stride];
-  r.z = (short)base[2 * stride];
-  r.w = (short)base[3 * stride];
-  return r;
-}
-
-__global__ __launch_bounds__(BWD_THREADS) void k_cnn_bwd(int count, int n,
-                                                         const unsigned short* __restrict__ X,
-                                                         const unsigned short* __restrict__ A1,
-                                                         const unsigned short* __restrict__ A2,
-                                                         const float* __restrict__ G,
-                                                         const unsigned short* __restrict__ Wb,
-                                                         float* __restrict__ partials,
-                                                         int stage_a1) {
-  extern __shared__ unsigned short smem[];
+__global__ __launch_bounds__(TRAIN_THREADS) void k_cnn_train(
+    int count, int n, const unsigned short* __restrict__ X, const uint8_t* __restrict__ Y,
+    const unsigned short* __restrict__ Wg, const float* __restrict__ params, float pos_weight,
+    float inv_total, float* __restrict__ partials, float* __restrict__ loss_part) {
+  extern __shared__ __align__(16) unsigned char train_smem[];
   const int b = blockIdx.x;
   if (b >= count) return;
-  const int w0 = n + 6, w1 = n + 4, w2 = n + 2;
+  const TrainLds S(n);
+  unsigned short* x = (unsigned short*)(train_smem + S.x);      // P0 x 4
+  unsigned short* a1 = (unsigned short*)(train_smem + S.a1);    // P1 x 16
+  unsigned short* a2 = (unsigned short*)(train_smem + S.a2);    // P2 x 16
+  float* g = (float*)(train_smem + S.g);                        // P3
+  float* w3 = (float*)(train_smem + S.w3);                      // 9 taps x 16
+  unsigned short* dz1 = (unsigned short*)(train_smem + S.dz1);  // P1 x 16
+  unsigned short* dz2 = (unsigned short*)(train_smem + S.dz2);  // (w2 + 4)^2 x 16
+  float* red = (float*)(train_smem + S.red);
+  unsigned short* Wb = (unsigned short*)(train_smem + S.wb);
+  const int w0 = n + 6, w1 = n + 4, w2 = n + 2, wz = n + 6;
   const int P0 = w0 * w0, P1 = w1 * w1, P2 = w2 * w2, P3 = n * n;
-  // the patch's input, second activation and logit gradients (and the first
-  // activation when LDS allows) are copied to LDS first, so that the
-  // reduction loops below read LDS
-  unsigned short* dz2 = smem;            // P2 x 16
-  unsigned short* dz1 = dz2 + P2 * 16;   // P1 x 16
-  unsigned short* sa2 = dz1 + P1 * 16;   // P2 x 16
-  unsigned short* sx = sa2 + P2 * 16;    // P0 x 4
-  float* sgr = reinterpret_cast<float*>(sx + P0 * 4);            // P3
-  unsigned short* sa1 = reinterpret_cast<unsigned short*>(sgr + P3);  // P1 x 16 (stage_a1)
-  const unsigned short* a1g = A1 + (long long)b * P1 * 16;
-  {
-    const uint4* g2 = reinterpret_cast<const uint4*>(A2 + (long long)b * P2 * 16);
-    const uint2* g0 = reinterpret_cast<const uint2*>(X + (long long)b * P0 * 4);
-    for (int t = threadIdx.x; t < P2 * 2; t += blockDim.x) reinterpret_cast<uint4*>(sa2)[t] = g2[t];
-    for (int t = threadIdx.x; t < P0; t += blockDim.x) reinterpret_cast<uint2*>(sx)[t] = g0[t];
-    for (int t = threadIdx.x; t < P3; t += blockDim.x) sgr[t] = G[(long long)b * P3 + t];
-    if (stage_a1) {
-      const uint4* g1 = reinterpret_cast<const uint4*>(a1g);
-      for (int t = threadIdx.x; t < P1 * 2; t += blockDim.x) reinterpret_cast<uint4*>(sa1)[t] = g1[t];
-    }
-  }
-  __syncthreads();
-  const unsigned short* x = sx;
-  const unsigned short* a1 = stage_a1 ? sa1 : a1g;
-  const unsigned short* a2 = sa2;
-  const float* g = sgr;
-  float* part = partials + (long long)b * CNN_NPARAM;
-  const int tid = threadIdx.x;
-  const int lane = tid & 63, wave = tid >> 6, nw = blockDim.x >> 6;
+  const PixelDiv div1(w1), div2(w2), div3(n);
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int i16 = lane & 15, kq = lane >> 4;
+  float* part = partials + (long long)b * CNN_NPARAM;
 
-  // --- layer 3: dZ2 = relu'(z2) * (W3 (x) G) on the P2 grid; dW3, db3
-  for (int q = tid; q < P2; q += blockDim.x) {
-    const int qy = q / w2, qx = q - qy * w2;
-    float acc[16];
-    for (int c = 0; c < 16; ++c) acc[c] = 0.f;
-    for (int tap = 0; tap < 9; ++tap) {
-      const int py = qy - tap / 3, px = qx - tap % 3;
-      if (py < 0 || px < 0 || py >= n || px >= n) continue;
-      const float gv = g[py * n + px];
-      for (int c = 0; c < 16; ++c) acc[c] += bf2f(Wb[CNN_W3 + c * 9 + tap]) * gv;
-    }
-    for (int c = 0; c < 16; ++c) {
-      const bool on = a2[q * 16 + c] != 0;  // a2 = relu(z2) stored in BF16: > 0 iff z2 > 0
-      dz2[q * 16 + c] = f2bf(on ? acc[c] : 0.f);
-    }
+  {
+    const uint2* gx = reinterpret_cast<const uint2*>(X + (long long)b * P0 * 4);
+    for (int t = tid; t < P0; t += TRAIN_THREADS) reinterpret_cast<uint2*>(x)[t] = gx[t];
+    for (int t = tid; t < CNN_NPARAM; t += TRAIN_THREADS) Wb[t] = Wg[t];
+    const uint4 z = {0u, 0u, 0u, 0u};
+    for (int t = tid; t < wz * wz * 2; t += TRAIN_THREADS) reinterpret_cast<uint4*>(dz2)[t] = z;
+    if (tid < 144) w3[(tid % 9) * 16 + tid / 9] = bf2f(Wg[CNN_W3 + tid]);
   }
-  // dW3[c][tap] = sum_p a2[p + tap][c] g[p]; db3 = sum_p g[p]  (one thread per (c, tap))
-  for (int k = tid; k < 16 * 9 + 1; k += blockDim.x) {
-    float s = 0.f;
-    if (k < 144) {
-      const int c = k / 9, tap = k % 9, ty = tap / 3, tx = tap % 3;
-      for (int p = 0; p < P3; ++p) {
-        const int py = p / n, px = p - py * n;
-        s += bf2f(a2[((py + ty) * w2 + px + tx) * 16 + c]) * g[p];
+  __syncthreads();
+  conv16<4>(x, w0, a1, Wb + CNN_W1, params + CNN_B1);
+  __syncthreads();
+  conv16<16>(a1, w1, a2, Wb + CNN_W2, params + CNN_B2);
+  __syncthreads();
+
+  // --- layer 3 and the loss: 4 lanes per pixel, 4 channels each; the logit
+  // gradient of the mean over all cells
+  {
+    const float b3 = params[CNN_B3];
+    const uint8_t* y = Y + (long long)b * P3;
+    const int cq = 4 * (lane & 3);
+    float loss = 0.f;
+    for (int t = tid; t < 4 * P3; t += TRAIN_THREADS) {
+      const int p = t >> 2, py = div3(p), px = p - py * n;
+      float acc = 0.f;
+#pragma unroll
+      for (int tap = 0; tap < 9; ++tap) {
+        const s4 a = load4(a2 + ((py + tap / 3) * w2 + px + tap % 3) * 16 + cq);
+        const float4 w = *reinterpret_cast<const float4*>(w3 + tap * 16 + cq);
+        acc += bf2f((unsigned short)a.x) * w.x;
+        acc += bf2f((unsigned short)a.y) * w.y;
+        acc += bf2f((unsigned short)a.z) * w.z;
+        acc += bf2f((unsigned short)a.w) * w.w;
       }
-      part[CNN_W3 + k] = s;
-    } else {
-      for (int p = 0; p < P3; ++p) s += g[p];
-      part[CNN_B3] = s;
+      acc += __shfl_xor(acc, 1);
+      acc += __shfl_xor(acc, 2);
+      if ((lane & 3) == 0) {
+        const float z = acc + b3;
+        const float yv = y[p] ? 1.f : 0.f;
+        const float tail = softplus_tail(z);
+        loss += pos_weight * yv * (fmaxf(-z, 0.f) + tail) + (1.f - yv) * (fmaxf(z, 0.f) + tail);
+        const float s = 1.f / (1.f + expf(-z));
+        g[p] = (pos_weight * yv * (s - 1.f) + (1.f - yv) * s) * inv_total;
+      }
     }
+    for (int off = 32; off > 0; off >>= 1) loss += __shfl_xor(loss, off);
+    if (lane == 0) red[wave] = loss;
+  }
+  __syncthreads();
+  if (tid == 0) {
+    float s = 0.f;
+    for (int k = 0; k < TRAIN_WAVES; ++k) s += red[k];
+    loss_part[b] = s * inv_total;
   }
   __syncthreads();
 
-  // --- layer 2 weight gradient: dW2[o][c][tap] = sum_p dz2[p][o] a1[p+tap][c]
-  // D[i = o][j = c], K = pixels; wave w owns taps w, w + nw, ...
-  for (int tap = wave; tap < 9; tap += nw) {
-    const int ty = tap / 3, tx = tap % 3;
-    f4 acc = {0.f, 0.f, 0.f, 0.f};
-    for (int p0 = 0; p0 < P2; p0 += 16) {
-      // A[o = i16][k = 4 kq + e] = dz2[p0 + 4kq + e][o]; B[k][c = i16] = a1[p + tap][c]
-      s4 a, bb;
-      short av[4], bv[4];
-      for (int e = 0; e < 4; ++e) {
-        const int p = p0 + 4 * kq + e;
-        if (p < P2) {
-          const int py = p / w2, px = p - py * w2;
-          av[e] = (short)dz2[p * 16 + i16];
-          bv[e] = (short)a1[((py + ty) * w1 + px + tx) * 16 + i16];
-        } else {
-          av[e] = 0;
-          bv[e] = 0;
-        }
-      }
-      a.x = av[0]; a.y = av[1]; a.z = av[2]; a.w = av[3];
-      bb.x = bv[0]; bb.y = bv[1]; bb.z = bv[2]; bb.w = bv[3];
-      acc = mfma(a, bb, acc);
+  // --- dW3[c][tap] = sum_p a2[p + tap][c] g[p], db3 = sum_p g[p]: a wave takes
+  // every 16th pixel, a lane one tap and 4 channels (36 lanes; lane 36 sums
+  // g); partial sums per wave into red
+  if (lane <= 36) {
+    const int tap = lane >> 2, cq = 4 * (lane & 3);
+    const int shift = lane < 36 ? ((tap / 3) * w2 + tap % 3) * 16 + cq : 0;
+    float acc[4] = {0.f, 0.f, 0.f, 0.f}, gs = 0.f;
+#pragma unroll 4
+    for (int p = wave; p < P3; p += TRAIN_WAVES) {
+      const int py = div3(p), px = p - py * n;
+      const float gv = g[p];
+      const s4 a = load4(a2 + (py * w2 + px) * 16 + shift);
+      gs += gv;
+      acc[0] += bf2f((unsigned short)a.x) * gv;
+      acc[1] += bf2f((unsigned short)a.y) * gv;
+      acc[2] += bf2f((unsigned short)a.z) * gv;
+      acc[3] += bf2f((unsigned short)a.w) * gv;
     }
-    for (int e = 0; e < 4; ++e) {
-      const int o = 4 * kq + e, c = i16;
-      part[CNN_W2 + (o * 16 + c) * 9 + tap] = acc[e];
+    if (lane < 36) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) red[wave * 145 + (cq + e) * 9 + tap] = acc[e];
+    } else {
+      red[wave * 145 + 144] = gs;
     }
   }
-  for (int o = tid; o < 16; o += blockDim.x) {
-    float s = 0.f;
-    for (int p = 0; p < P2; ++p) s += bf2f(dz2[p * 16 + o]);
-    part[CNN_B2 + o] = s;
+  // --- dz2 = relu'(z2) * (W3 (x) g) on the P2 grid, 4 channels per item
+  for (int t = tid; t < 4 * P2; t += TRAIN_THREADS) {
+    const int q = t >> 2, cq = 4 * (t & 3);
+    const int qy = div2(q), qx = q - qy * w2;
+    float acc[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int tap = 0; tap < 9; ++tap) {
+      // read in any case (no branch around the loads), zero outside
+      const int py = qy - tap / 3, px = qx - tap % 3;
+      const bool in = (unsigned)py < (unsigned)n && (unsigned)px < (unsigned)n;
+      const float gr = g[in ? py * n + px : 0];
+      const float gv = in ? gr : 0.f;
+      const float4 w = *reinterpret_cast<const float4*>(w3 + tap * 16 + cq);
+      acc[0] += w.x * gv;
+      acc[1] += w.y * gv;
+      acc[2] += w.z * gv;
+      acc[3] += w.w * gv;
+    }
+    const s4 on = load4(a2 + q * 16 + cq);  // a2 = relu(z2) in BF16: nonzero iff z2 > 0
+    uint2 o;
+    o.x = f2bf_hw(on.x ? acc[0] : 0.f) | ((unsigned)f2bf_hw(on.y ? acc[1] : 0.f) << 16);
+    o.y = f2bf_hw(on.z ? acc[2] : 0.f) | ((unsigned)f2bf_hw(on.w ? acc[3] : 0.f) << 16);
+    *reinterpret_cast<uint2*>(dz2 + ((qy + 2) * wz + qx + 2) * 16 + cq) = o;
   }
+  __syncthreads();
 
-  // --- layer 2 data gradient: dZ1[q][c] = relu'(z1) sum_tap sum_o W2[o][c][tap] dz2[q - tap][o]
-  // D[i = pixel][j = c]; A[pixel][k = o] from dz2 at q - tap; B[k = o][j = c] = W2[o][c][tap]
+  if (tid < 145) {
+    float s = 0.f;
+    for (int k = 0; k < TRAIN_WAVES; ++k) s += red[k * 145 + tid];
+    part[CNN_W3 + tid] = s;  // db3 follows W3
+  }
+  // --- dW2[o][c][tap] = sum_p dz2[p][o] a1[p + tap][c]: D[i = o][j = c], K =
+  // pixels, a tap per wave; db2 by the wave after them
+  static_assert(CNN_B3 == CNN_W3 + 144 && TRAIN_WAVES >= 10, "a wave per tap and one for db2");
+  // this lane's row (of the 4 of its K group) and 4 columns in transposed reads
+  const int row = 4 * kq + (i16 >> 2), col = 4 * (i16 & 3);
+  if (wave < 9) {
+    const int shift = ((wave / 3) * w1 + wave % 3) * 16 + col;
+    auto step = [&](int p0, f4 acc) {
+      const int p = p0 + row;
+      // past the last pixel: a border pixel of dz2 (zero)
+      const bool in = p < P2;
+      const int py = div2(in ? p : 0), px = (in ? p : 0) - py * w2;
+      const s4 a = load4_tr(dz2 + (in ? ((py + 2) * wz + px + 2) * 16 : 0) + col);
+      const s4 bb = load4_tr(a1 + (py * w1 + px) * 16 + shift);
+      return mfma(a, bb, acc);
+    };
+    f4 acc0 = {0.f, 0.f, 0.f, 0.f}, acc1 = acc0;
+    for (int p0 = 0; p0 < P2; p0 += 32) {
+      acc0 = step(p0, acc0);
+      acc1 = step(p0 + 16, acc1);
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      part[CNN_W2 + ((4 * kq + e) * 16 + i16) * 9 + wave] = acc0[e] + acc1[e];
+  } else if (wave == 9) {
+    float s = 0.f;
+#pragma unroll 4
+    for (int p = kq; p < P2; p += 4) {
+      const int py = div2(p), px = p - py * w2;
+      s += bf2f(dz2[((py + 2) * wz + px + 2) * 16 + i16]);
+    }
+    s += __shfl_xor(s, 16);
+    s += __shfl_xor(s, 32);
+    if (kq == 0) part[CNN_B2 + i16] = s;
+  }
+  // --- dz1[q][c] = relu'(z1) sum_tap sum_o W2[o][c][tap] dz2[q - tap][o]:
+  // D[i = pixel][j = c], stored like the activations in whole blocks of 16 pixels
   {
     s4 bop[9];
+#pragma unroll
     for (int tap = 0; tap < 9; ++tap) {
-      s4 r;
-      r.x = (short)Wb[CNN_W2 + ((4 * kq + 0) * 16 + i16) * 9 + tap];
-      r.y = (short)Wb[CNN_W2 + ((4 * kq + 1) * 16 + i16) * 9 + tap];
-      r.z = (short)Wb[CNN_W2 + ((4 * kq + 2) * 16 + i16) * 9 + tap];
-      r.w = (short)Wb[CNN_W2 + ((4 * kq + 3) * 16 + i16) * 9 + tap];
-      bop[tap] = r;
+      const unsigned short* w = Wb + CNN_W2 + (4 * kq * 16 + i16) * 9 + tap;
+      bop[tap] = pack4((short)w[0], (short)w[16 * 9], (short)w[32 * 9], (short)w[48 * 9]);
     }
     const int nblk = (P1 + 15) / 16;
-    for (int blk = wave; blk < nblk; blk += nw) {
+    // the waves without a tap above take their blocks first
+    for (int blk = TRAIN_WAVES - 1 - wave; blk < nblk; blk += TRAIN_WAVES) {
       const int p = 16 * blk + i16;
       const int pc = p < P1 ? p : P1 - 1;
-      const int qy = pc / w1, qx = pc - qy * w1;
+      const int qy = div1(pc), qx = pc - qy * w1;
+      const unsigned short* base = dz2 + ((qy + 2) * wz + qx + 2) * 16 + 4 * kq;
       f4 acc = {0.f, 0.f, 0.f, 0.f};
-      for (int tap = 0; tap < 9; ++tap) {
-        const int sy = qy - tap / 3, sx = qx - tap % 3;
-        s4 a = zero4();
-        if (sy >= 0 && sx >= 0 && sy < w2 && sx < w2) a = load4(dz2 + (sy * w2 + sx) * 16 + 4 * kq);
-        acc = mfma(a, bop[tap], acc);
-      }
+#pragma unroll
+      for (int tap = 0; tap < 9; ++tap)
+        acc = mfma(load4(base - ((tap / 3) * wz + tap % 3) * 16), bop[tap], acc);
+      // the rows past the last pixel of the last block are zero
+#pragma unroll
       for (int e = 0; e < 4; ++e) {
         const int q = 16 * blk + 4 * kq + e;
-        if (q < P1) {
-          const bool on = a1[q * 16 + i16] != 0;
-          dz1[q * 16 + i16] = f2bf(on ? acc[e] : 0.f);
-        }
+        const bool on = q < P1 && a1[q * 16 + i16] != 0;
+        dz1[q * 16 + i16] = f2bf_hw(on ? acc[e] : 0.f);
       }
     }
   }
   __syncthreads();
 
-  // --- layer 1 weight gradient: dW1[o][c][tap] = sum_p dz1[p][o] x[p + tap][c]
-  // D[i = o][j = k'] with k' = 4 tap' + c over 3 chunks of 16 (taps 4 kc .. 4 kc + 3)
-  for (int kc = wave; kc < 3; kc += nw) {
+  // --- dW1[o][c][tap] = sum_p dz1[p][o] x[p + tap][c]: D[i = o][j = k'] with
+  // k' = 4 tap' + c over 3 chunks (taps 4 kc .. 4 kc + 3), the pixels in 4
+  // parts (12 waves); db1 by the wave after them
+  if (wave < 12) {
+    const int kc = wave % 3, quarter = wave / 3;
+    const int tap = 4 * kc + (i16 & 3);  // taps 9 .. 11 do not exist: columns not used
+    const int shift = tap < 9 ? ((tap / 3) * w0 + tap % 3) * 4 : 0;
     f4 acc = {0.f, 0.f, 0.f, 0.f};
-    const int kp = 16 * kc + i16;     // column k' of this lane
-    const int tap = kp >> 2, c = kp & 3;
-    const int ty = tap / 3, tx = tap % 3;
-    for (int p0 = 0; p0 < P1; p0 += 16) {
-      short av[4], bv[4];
-      for (int e = 0; e < 4; ++e) {
-        const int p = p0 + 4 * kq + e;
-        if (p < P1) {
-          const int py = p / w1, px = p - py * w1;
-          av[e] = (short)dz1[p * 16 + i16];
-          bv[e] = tap < 9 ? (short)x[((py + ty) * w0 + px + tx) * 4 + c] : (short)0;
-        } else {
-          av[e] = 0;
-          bv[e] = 0;
-        }
-      }
-      s4 a, bb;
-      a.x = av[0]; a.y = av[1]; a.z = av[2]; a.w = av[3];
-      bb.x = bv[0]; bb.y = bv[1]; bb.z = bv[2]; bb.w = bv[3];
-      acc = mfma(a, bb, acc);
+#pragma unroll 2
+    for (int p0 = 16 * quarter; p0 < P1; p0 += 64) {
+      const int p = p0 + row, pc = p < P1 ? p : 0;
+      const int py = div1(pc), px = pc - py * w1;
+      acc = mfma(load4_tr(dz1 + p * 16 + col), load4_tr(x + (py * w0 + px) * 4 + shift), acc);
     }
-    if (tap < 9)
-      for (int e = 0; e < 4; ++e) {
-        const int o = 4 * kq + e;
-        part[CNN_W1 + (o * 4 + c) * 9 + tap] = acc[e];
-      }
-  }
-  for (int o = tid; o < 16; o += blockDim.x) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) red[wave * 256 + (4 * kq + e) * 16 + i16] = acc[e];
+  } else if (wave == 12) {
     float s = 0.f;
-    for (int p = 0; p < P1; ++p) s += bf2f(dz1[p * 16 + o]);
-    part[CNN_B1 + o] = s;
+#pragma unroll 4
+    for (int q = kq; q < P1; q += 4) s += bf2f(dz1[q * 16 + i16]);
+    s += __shfl_xor(s, 16);
+    s += __shfl_xor(s, 32);
+    if (kq == 0) part[CNN_B1 + i16] = s;
+  }
+  __syncthreads();
+  if (tid < 576) {
+    // parameter (o, c, tap) is element (o, 4 tap + c) of the chunk matrices
+    const int o = tid / 36, c = (tid / 9) % 4, tap = tid % 9;
+    const int kp = 4 * tap + c, at = (kp >> 4) * 256 + o * 16 + (kp & 15);
+    part[CNN_W1 + tid] = ((red[at] + red[at + 768]) + red[at + 1536]) + red[at + 2304];
   }
 }
 
-// deterministic sum of the per-patch partials (fixed order over patches)
-__global__ void k_cnn_reduce(const float* __restrict__ partials, int count, int np,
-                             float* __restrict__ grads) {
-  const int k = blockIdx.x * blockDim.x + threadIdx.x;
-  if (k >= np) return;
-  float s = 0.f;
-  for (int b = 0; b < count; ++b) s += partials[(long long)b * np + k];
-  grads[k] = s;
-}
+// ---------------------------------------------------------------------------
+// parameter update: the sum of the per-tile gradients (fixed order: a wave
+// takes every 16th tile, the 16 sums are added in wave order), then Adam on
+// the FP32 master weights and the BF16 copy (round to nearest even).  One
+// block per 64 parameters; the block after them sums the loss.
+// ---------------------------------------------------------------------------
+// With one thread per parameter walking all tiles, a loss kernel of one
+// serial thread, a gradient copy and a separate Adam launch the update took
+// 15.9 + 13.1 + 5.3 + 4.7 us for 64 tiles; one 4.7 us launch now.
+constexpr int UPDATE_THREADS = 1024;
 
-// Adam on FP32 master weights, then the BF16 copy (round to nearest even)
-__global__ void k_cnn_adam(float* __restrict__ params, const float* __restrict__ grads,
-                           float* __restrict__ m, float* __restrict__ v, float lr, float c1,
-                           float c2, int np, unsigned short* __restrict__ Wb) {
-  const int k = blockIdx.x * blockDim.x + threadIdx.x;
-  if (k >= np) return;
+__global__ __launch_bounds__(UPDATE_THREADS) void k_cnn_update(
+    const float* __restrict__ partials, const float* __restrict__ loss_part, int count, int np,
+    float* __restrict__ grads, float* __restrict__ loss, int adam, float* __restrict__ params,
+    float* __restrict__ m, float* __restrict__ v, float lr, float c1, float c2,
+    unsigned short* __restrict__ Wb) {
+  __shared__ float red[UPDATE_THREADS];
+  constexpr int NW = UPDATE_THREADS / 64;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  if (blockIdx.x == gridDim.x - 1) {
+    float s = 0.f;
+    for (int b = tid; b < count; b += UPDATE_THREADS) s += loss_part[b];
+    for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off);
+    if (lane == 0) red[wave] = s;
+    __syncthreads();
+    if (tid == 0) {
+      float t = 0.f;
+      for (int k = 0; k < NW; ++k) t += red[k];
+      loss[0] = t;
+    }
+    return;
+  }
+  const int k = blockIdx.x * 64 + lane;
+  float s = 0.f;
+  if (k < np) {
+#pragma unroll 4
+    for (int b = wave; b < count; b += NW) s += partials[(long long)b * np + k];
+  }
+  red[tid] = s;
+  __syncthreads();
+  if (wave > 0 || k >= np) return;
+  float g = red[lane];
+#pragma unroll
+  for (int w = 1; w < NW; ++w) g += red[64 * w + lane];
+  if (grads) grads[k] = g;
+  if (!adam) return;
   const float b1 = 0.9f, b2 = 0.999f, eps = 1e-8f;
-  const float g = grads[k];
   const float mk = b1 * m[k] + (1.f - b1) * g;
   const float vk = b2 * v[k] + (1.f - b2) * g * g;
   m[k] = mk;
@@ -494,20 +562,6 @@ size_t Cnn::fwd_lds(int n) {
   return (size_t)(w0 * w0 * 4 + w1 * w1 * 16 + w2 * w2 * 16) * sizeof(unsigned short);
 }
 
-// LDS of the backward kernel: dz2, dz1, a2, the input, the logit gradients,
-// and a1 when the total stays within the 160 KB of a CU
-static size_t bwd_lds_parts(int n, bool with_a1) {
-  const size_t P0 = (size_t)(n + 6) * (n + 6), P1 = (size_t)(n + 4) * (n + 4);
-  const size_t P2 = (size_t)(n + 2) * (n + 2), P3 = (size_t)n * n;
-  size_t bytes = (P2 * 16 + P1 * 16 + P2 * 16 + P0 * 4) * sizeof(unsigned short) + P3 * sizeof(float);
-  if (with_a1) bytes += P1 * 16 * sizeof(unsigned short);
-  return bytes;
-}
-
-static bool bwd_stage_a1(int n) { return bwd_lds_parts(n, true) <= 160 * 1024; }
-
-size_t Cnn::bwd_lds(int n) { return bwd_lds_parts(n, bwd_stage_a1(n)); }
-
 void Cnn::gather(const DevMesh& m, const double* U, const int* pids, int count, int n,
                  const CnnNorm& norm, unsigned short* X, hipStream_t s) {
   if (count <= 0) return;
@@ -522,47 +576,36 @@ static void allow_large_lds() {
   done = true;
   (void)hipFuncSetAttribute((const void*)k_cnn_fwd, hipFuncAttributeMaxDynamicSharedMemorySize,
                             160 * 1024);
-  (void)hipFuncSetAttribute((const void*)k_cnn_bwd, hipFuncAttributeMaxDynamicSharedMemorySize,
+  (void)hipFuncSetAttribute((const void*)k_cnn_train, hipFuncAttributeMaxDynamicSharedMemorySize,
                             160 * 1024);
 }
 
 void Cnn::forward(int count, int n, const unsigned short* X, const unsigned short* Wb,
-                  const float* params, unsigned short* A1, unsigned short* A2, float* Z,
-                  hipStream_t s) {
+                  const float* params, float* Z, hipStream_t s) {
   if (count <= 0) return;
   allow_large_lds();
   hipLaunchKernelGGL(k_cnn_fwd, dim3(count), dim3(FWD_THREADS), fwd_lds(n), s, count, n, X, Wb,
-                     params, A1, A2, Z);
+                     params, Z);
 }
 
-void Cnn::loss(long long total, const float* Z, const uint8_t* Y, float pos_weight, float* G,
-               float* partial, int nblocks, float* loss_out, hipStream_t s) {
-  hipLaunchKernelGGL(k_cnn_loss, dim3(nblocks), dim3(256), 0, s, total, Z, Y, pos_weight, G,
-                     partial);
-  hipLaunchKernelGGL(k_cnn_loss_final, dim3(1), dim3(64), 0, s, partial, nblocks, loss_out);
-}
-
-void Cnn::backward(int count, int n, const unsigned short* X, const unsigned short* A1,
-                   const unsigned short* A2, const float* G, const unsigned short* Wb,
-                   float* partials, float* grads, hipStream_t s) {
+void Cnn::train(int count, int n, const unsigned short* X, const uint8_t* Y,
+                const unsigned short* Wb, const float* params, float pos_weight, float* partials,
+                float* loss_part, hipStream_t s) {
   if (count <= 0) return;
   allow_large_lds();
-  hipLaunchKernelGGL(k_cnn_bwd, dim3(count), dim3(BWD_THREADS), bwd_lds(n), s, count, n, X, A1, A2,
-                     G, Wb, partials, bwd_stage_a1(n) ? 1 : 0);
-  reduce(partials, count, CNN_NPARAM, grads, s);
+  const float inv_total = 1.0f / (float)((long long)count * n * n);
+  hipLaunchKernelGGL(k_cnn_train, dim3(count), dim3(TRAIN_THREADS), TrainLds(n).total, s, count, n,
+                     X, Y, Wb, params, pos_weight, inv_total, partials, loss_part);
 }
 
-void Cnn::reduce(const float* partials, int count, int np, float* grads, hipStream_t s) {
-  hipLaunchKernelGGL(k_cnn_reduce, dim3((np + 255) / 256), dim3(256), 0, s, partials, count, np,
-                     grads);
-}
-
-void Cnn::adam(float* params, const float* grads, float* m, float* v, float lr, int t, int np,
-               unsigned short* Wb, hipStream_t s) {
-  const float c1 = 1.f - powf(0.9f, (float)t);
-  const float c2 = 1.f - powf(0.999f, (float)t);
-  hipLaunchKernelGGL(k_cnn_adam, dim3((np + 255) / 256), dim3(256), 0, s, params, grads, m, v, lr,
-                     c1, c2, np, Wb);
+void Cnn::update(const float* partials, const float* loss_part, int count, int np, float* grads,
+                 float* loss, float* params, float* m, float* v, float lr, int t,
+                 unsigned short* Wb, hipStream_t s) {
+  const int adam = lr > 0.f ? 1 : 0;
+  const float c1 = adam ? 1.f - powf(0.9f, (float)t) : 1.f;
+  const float c2 = adam ? 1.f - powf(0.999f, (float)t) : 1.f;
+  hipLaunchKernelGGL(k_cnn_update, dim3((np + 63) / 64 + 1), dim3(UPDATE_THREADS), 0, s, partials,
+                     loss_part, count, np, grads, loss, adam, params, m, v, lr, c1, c2, Wb);
 }
 
 void Cnn::to_bf16(const float* params, int np, unsigned short* Wb, hipStream_t s) {

@@ -36,16 +36,11 @@ constexpr int KCH = 14;  // K chunks: taps (2 kc, 2 kc + 1), 8 channels each
 // threads per block: the loops stride over the block's waves, so more waves
 // shorten a tile's latency (a training batch is only tens of tiles)
 constexpr int FWD_THREADS = 512;
-constexpr int BWD_THREADS = 1024;
+constexpr int TRAIN_THREADS = 1024;
+constexpr int TRAIN_WAVES = TRAIN_THREADS / 64;
 
 static_assert(CH == 8, "two taps of 8 channels per MFMA K chunk");
 static_assert(P1 % 16 == 0, "layer-1 voxels in whole MFMA row blocks");
-
-__device__ __forceinline__ void tap_xyz(int tap, int& tz, int& ty, int& tx) {
-  tz = tap / 9;
-  ty = (tap / 3) % 3;
-  tx = tap % 3;
-}
 
 // ---------------------------------------------------------------------------
 // gather: normalised BF16 input tiles from the FP64 state (ghosts filled)
@@ -100,60 +95,82 @@ __global__ __launch_bounds__(256) void k_cnn3_gather(DevMesh m, const double* __
 // forward of one tile per block (4 waves); activations in LDS
 // ---------------------------------------------------------------------------
 
+// Reads of the K chunks of a 3x3x3 convolution from a box of edge WI with 8
+// channels per voxel: chunk kc holds taps 2 kc (lanes of half 0) and 2 kc + 1
+// (half 1), FLIP reading tap t at the mirrored place.  The second tap lies at
+// one of three distances from the first, so three lane bases and immediate
+// offsets address every chunk.
+template <int WI, bool FLIP>
+struct TapReads {
+  static constexpr int at(int tap) {
+    const int z = tap / 9, y = (tap / 3) % 3, x = tap % 3;
+    return (FLIP ? ((2 - z) * WI + 2 - y) * WI + 2 - x : (z * WI + y) * WI + x) * CH;
+  }
+  static constexpr int kind(int kc) { return (2 * kc) % 9 == 8 ? 2 : ((2 * kc) % 3 == 2 ? 1 : 0); }
+  const unsigned short* base[3];
+  int half;
+  __device__ __forceinline__ TapReads(const unsigned short* p, int half_, int cg) : half(half_) {
+    base[0] = p + cg + half * (at(1) - at(0));
+    base[1] = p + cg + half * (at(3) - at(2));
+    base[2] = p + cg + half * (at(9) - at(8));
+  }
+  // kc: a constant after unrolling; tap 27 does not exist (read as tap 26, zero)
+  __device__ __forceinline__ s4 operator()(int kc) const {
+    if (kc < KCH - 1) return load4(base[kind(kc)] + at(2 * kc));
+    const s4 a = load4(base[0] + at(26) - half * (at(1) - at(0)));
+    return half == 0 ? a : zero4();
+  }
+};
+
+// B operand of chunk kc: weights w[c0 + e][...][tap], at wt + e * stride + tap
+// for this lane's 4 input channels; read in any case (no branch around the
+// loads), zero where the column, tap or channel does not exist.
+__device__ __forceinline__ s4 tap_weights(const unsigned short* wt, int stride, int nch, bool column,
+                                          int tap) {
+  const int t = tap < 27 ? tap : 26;
+  short w[4];
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const short v = (short)wt[(e < nch ? e : 0) * stride + t];
+    w[e] = column && tap < 27 && e < nch ? v : (short)0;
+  }
+  return pack4(w[0], w[1], w[2], w[3]);
+}
+
 // valid 3x3x3 convolution, 8 output channels, from a voxel-major LDS input of
 // edge WI with 8 stored channels (CI of them weighted) to edge WI - 2 (bias,
 // ReLU, BF16); W layout [8][CI][27].
 template <int WI, int CI>
-__device__ void conv3(const unsigned short* __restrict__ in, unsigned short* __restrict__ out,
-                      unsigned short* __restrict__ gout, const unsigned short* __restrict__ W,
-                      const float* __restrict__ bias) {
+__device__ __forceinline__ void conv3(const unsigned short* __restrict__ in,
+                                      unsigned short* __restrict__ out,
+                                      const unsigned short* __restrict__ W,
+                                      const float* __restrict__ bias) {
   constexpr int WO = WI - 2;
   constexpr int P = WO * WO * WO;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
   const int i = lane & 15, kq = lane >> 4;
   const int half = kq >> 1, cg = 4 * (kq & 1);
   s4 bop[KCH];
-  int toff[KCH];
 #pragma unroll
-  for (int kc = 0; kc < KCH; ++kc) {
-    const int tap = 2 * kc + half;
-    int tz, ty, tx;
-    tap_xyz(tap, tz, ty, tx);
-    toff[kc] = ((tz * WI + ty) * WI + tx) * CH + cg;
-    short w[4];
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const int c = cg + e;
-      w[e] = (i < 8 && tap < 27 && c < CI) ? (short)W[(i * CI + c) * 27 + tap] : (short)0;
-    }
-    bop[kc] = pack4(w[0], w[1], w[2], w[3]);
-  }
-  const float bcol = i < 8 ? bias[i] : 0.f;
+  for (int kc = 0; kc < KCH; ++kc)
+    bop[kc] = tap_weights(W + ((i & 7) * CI + cg) * 27, 27, CI - cg, i < 8, 2 * kc + half);
+  const float bcol = bias[i & 7];
   constexpr int nblk = (P + 15) / 16;
   for (int blk = wave; blk < nblk; blk += nw) {
     const int p = 16 * blk + i;
     const int pc = p < P ? p : P - 1;
     const int pz = pc / (WO * WO), r = pc - pz * WO * WO;
     const int py = r / WO, px = r - py * WO;
-    const unsigned short* base = in + ((pz * WI + py) * WI + px) * CH;
+    const TapReads<WI, false> a(in + ((pz * WI + py) * WI + px) * CH, half, cg);
     f4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int kc = 0; kc < KCH; ++kc) {
-      const bool ok = kc < KCH - 1 || half == 0;  // tap 27 does not exist
-      const s4 a = ok ? load4(base + toff[kc]) : zero4();
-      acc = mfma(a, bop[kc], acc);
-    }
+    for (int kc = 0; kc < KCH; ++kc) acc = mfma(a(kc), bop[kc], acc);
     if (i < 8) {
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         const int q = 16 * blk + 4 * kq + e;
-        if (q < P) {
-          float v = acc[e] + bcol;
-          v = v > 0.f ? v : 0.f;
-          const unsigned short hb = f2bf(v);
-          out[q * CH + i] = hb;
-          if (gout) gout[q * CH + i] = hb;
-        }
+        const float v = acc[e] + bcol;
+        if (q < P) out[q * CH + i] = f2bf_hw(v > 0.f ? v : 0.f);
       }
     }
   }
@@ -162,8 +179,6 @@ __device__ void conv3(const unsigned short* __restrict__ in, unsigned short* __r
 __global__ __launch_bounds__(FWD_THREADS) void k_cnn3_fwd(int count, const unsigned short* __restrict__ X,
                                                       const unsigned short* __restrict__ Wb,
                                                       const float* __restrict__ params,
-                                                      unsigned short* __restrict__ A1,
-                                                      unsigned short* __restrict__ A2,
                                                       float* __restrict__ Z) {
   extern __shared__ unsigned short smem[];
   const int b = blockIdx.x;
@@ -174,9 +189,9 @@ __global__ __launch_bounds__(FWD_THREADS) void k_cnn3_fwd(int count, const unsig
   const uint4* xg = reinterpret_cast<const uint4*>(X) + (long long)b * P0;
   for (int t = threadIdx.x; t < P0; t += blockDim.x) reinterpret_cast<uint4*>(sx)[t] = xg[t];
   __syncthreads();
-  conv3<W0, 5>(sx, s1, A1 ? A1 + (long long)b * P1 * CH : nullptr, Wb + CNN3_W1, params + CNN3_B1);
+  conv3<W0, 5>(sx, s1, Wb + CNN3_W1, params + CNN3_B1);
   __syncthreads();
-  conv3<W1, 8>(s1, s2, A2 ? A2 + (long long)b * P2 * CH : nullptr, Wb + CNN3_W2, params + CNN3_B2);
+  conv3<W1, 8>(s1, s2, Wb + CNN3_W2, params + CNN3_B2);
   __syncthreads();
   // layer 3 (8 -> 1) on the VALU
   const float b3 = params[CNN3_B3];
@@ -184,8 +199,7 @@ __global__ __launch_bounds__(FWD_THREADS) void k_cnn3_fwd(int count, const unsig
     const int pz = p / (T * T), py = (p / T) % T, px = p % T;
     float acc = 0.f;
     for (int tap = 0; tap < 27; ++tap) {
-      int tz, ty, tx;
-      tap_xyz(tap, tz, ty, tx);
+      const int tz = tap / 9, ty = (tap / 3) % 3, tx = tap % 3;
       const uint4 a = *reinterpret_cast<const uint4*>(
           s2 + (((pz + tz) * W2 + (py + ty)) * W2 + (px + tx)) * CH);
       const unsigned int u[4] = {a.x, a.y, a.z, a.w};
@@ -200,196 +214,281 @@ __global__ __launch_bounds__(FWD_THREADS) void k_cnn3_fwd(int count, const unsig
 }
 
 // ---------------------------------------------------------------------------
-// backward of one tile per block: per-tile parameter-gradient partials
+// training: forward, loss and backward of one tile per block, the per-tile
+// parameter gradients and loss to global memory (the 3D form of k_cnn_train)
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(BWD_THREADS) void k_cnn3_bwd(int count, const unsigned short* __restrict__ X,
-                                                      const unsigned short* __restrict__ A1,
-                                                      const unsigned short* __restrict__ A2,
-                                                      const float* __restrict__ G,
-                                                      const unsigned short* __restrict__ Wb,
-                                                      float* __restrict__ partials) {
-  extern __shared__ unsigned short smem[];
+// One tile's latency per launch: the forward (29 us for 64 tiles), the loss
+// (4.6 us) and the backward (124 us) were launches of their own, with
+// activations through memory, bounds checks per tap and serial sums per
+// parameter; one 45.6 us launch now.
+//
+// LDS (bytes): dz1 takes the place of the second activation,
+// the logit gradients and the FP32 copy of W3; dz2 has a border of two zero
+// voxels.
+constexpr int TL_X = 0;
+constexpr int TL_A1 = TL_X + P0 * CH * 2;
+constexpr int TL_A2 = TL_A1 + (P1 + 2) * CH * 2;  // two zero voxels behind a1 (see dW2)
+constexpr int TL_G = TL_A2 + P2 * CH * 2;
+constexpr int TL_W3 = TL_G + P3 * 4;
+constexpr int TL_DZ1 = TL_A2;
+constexpr int TL_DZ2 = TL_DZ1 + P1 * CH * 2;
+constexpr int TL_RED = TL_DZ2 + P0 * CH * 2;      // dz2 with its border is as large as the input
+constexpr int RED_N = 8 * 27 + 1;                 // dW3 and db3 of one wave
+constexpr int TL_WB = TL_RED + ((TRAIN_WAVES * RED_N * 4 + 15) / 16) * 16;
+constexpr int TL_TOTAL = TL_WB + ((CNN3_NPARAM * 2 + 15) / 16) * 16;
+static_assert(TL_W3 + 27 * 8 * 4 <= TL_DZ2, "a2, g and W3 fit under dz1");
+static_assert(TL_TOTAL <= 160 * 1024, "one block per CU");
+static_assert(W2 + 4 == W0, "dz2 with its border has the input's shape");
+
+__global__ __launch_bounds__(TRAIN_THREADS) void k_cnn3_train(
+    int count, const unsigned short* __restrict__ X, const uint8_t* __restrict__ Y,
+    const unsigned short* __restrict__ Wg, const float* __restrict__ params, float pos_weight,
+    float inv_total, float* __restrict__ partials, float* __restrict__ loss_part) {
+  extern __shared__ __align__(16) unsigned char train_smem[];
   const int b = blockIdx.x;
   if (b >= count) return;
-  // the tile's input and saved activations are copied to LDS first (one
-  // round of 16-byte loads), so that the reduction loops below read LDS
-  unsigned short* dz2 = smem;              // P2 x 8
-  unsigned short* dz1 = dz2 + P2 * CH;     // P1 x 8
-  unsigned short* a2 = dz1 + P1 * CH;      // P2 x 8
-  unsigned short* a1 = a2 + P2 * CH;       // P1 x 8
-  unsigned short* x = a1 + P1 * CH;        // P0 x 8
-  float* sg = reinterpret_cast<float*>(x + P0 * CH);  // P3 logit gradients
+  unsigned short* x = (unsigned short*)(train_smem + TL_X);
+  unsigned short* a1 = (unsigned short*)(train_smem + TL_A1);
+  unsigned short* a2 = (unsigned short*)(train_smem + TL_A2);
+  float* g = (float*)(train_smem + TL_G);
+  float* w3 = (float*)(train_smem + TL_W3);                       // [27][8]
+  unsigned short* dz1 = (unsigned short*)(train_smem + TL_DZ1);   // [P1][8]
+  unsigned short* dz2 = (unsigned short*)(train_smem + TL_DZ2);   // [W0^3][8]
+  float* red = (float*)(train_smem + TL_RED);
+  unsigned short* Wb = (unsigned short*)(train_smem + TL_WB);
   float* part = partials + (long long)b * CNN3_NPARAM;
   const int tid = threadIdx.x;
-  const int lane = tid & 63, wave = tid >> 6, nw = blockDim.x >> 6;
+  const int lane = tid & 63, wave = tid >> 6;
   const int i = lane & 15, kq = lane >> 4;
   const int half = kq >> 1, cg = 4 * (kq & 1);
 
   {
-    const uint4* g2 = reinterpret_cast<const uint4*>(A2) + (long long)b * P2;
-    const uint4* g1 = reinterpret_cast<const uint4*>(A1) + (long long)b * P1;
-    const uint4* g0 = reinterpret_cast<const uint4*>(X) + (long long)b * P0;
-    for (int t = tid; t < P2; t += blockDim.x) reinterpret_cast<uint4*>(a2)[t] = g2[t];
-    for (int t = tid; t < P1; t += blockDim.x) reinterpret_cast<uint4*>(a1)[t] = g1[t];
-    for (int t = tid; t < P0; t += blockDim.x) reinterpret_cast<uint4*>(x)[t] = g0[t];
+    const uint4* gx = reinterpret_cast<const uint4*>(X) + (long long)b * P0;
+    const uint4 z = {0u, 0u, 0u, 0u};
+    for (int t = tid; t < P0; t += TRAIN_THREADS) {
+      reinterpret_cast<uint4*>(x)[t] = gx[t];
+      reinterpret_cast<uint4*>(dz2)[t] = z;
+    }
+    for (int t = tid; t < CNN3_NPARAM; t += TRAIN_THREADS) Wb[t] = Wg[t];
+    if (tid < 2) reinterpret_cast<uint4*>(a1 + P1 * CH)[tid] = z;
+    if (tid < 27 * 8) w3[(tid % 27) * 8 + tid / 27] = bf2f(Wg[CNN3_W3 + tid]);
   }
-  for (int p = tid; p < P3; p += blockDim.x) sg[p] = G[(long long)b * P3 + p];
+  __syncthreads();
+  conv3<W0, 5>(x, a1, Wb + CNN3_W1, params + CNN3_B1);
+  __syncthreads();
+  conv3<W1, 8>(a1, a2, Wb + CNN3_W2, params + CNN3_B2);
   __syncthreads();
 
-  // --- layer 3: dz2 = relu'(z2) * (W3 (x) g) on the layer-2 grid; dW3, db3
-  for (int q = tid; q < P2; q += blockDim.x) {
-    const int qz = q / (W2 * W2), qy = (q / W2) % W2, qx = q % W2;
-    float acc[8];
+  // --- layer 3 and the loss: 2 lanes per voxel, 4 channels each
+  {
+    static_assert(2 * P3 == TRAIN_THREADS, "one layer-3 item per thread");
+    const int p = tid >> 1, c4 = 4 * (tid & 1);
+    const int pz = p / (T * T), py = (p / T) % T, px = p % T;
+    const unsigned short* base = a2 + ((pz * W2 + py) * W2 + px) * CH + c4;
+    float acc = 0.f;
 #pragma unroll
-    for (int c = 0; c < 8; ++c) acc[c] = 0.f;
     for (int tap = 0; tap < 27; ++tap) {
-      int tz, ty, tx;
-      tap_xyz(tap, tz, ty, tx);
-      const int pz = qz - tz, py = qy - ty, px = qx - tx;
-      if (pz < 0 || py < 0 || px < 0 || pz >= T || py >= T || px >= T) continue;
-      const float gv = sg[(pz * T + py) * T + px];
-#pragma unroll
-      for (int c = 0; c < 8; ++c) acc[c] += bf2f(Wb[CNN3_W3 + c * 27 + tap]) * gv;
+      const s4 a = load4(base + (((tap / 9) * W2 + (tap / 3) % 3) * W2 + tap % 3) * CH);
+      const float4 w = *reinterpret_cast<const float4*>(w3 + tap * 8 + c4);
+      acc += bf2f((unsigned short)a.x) * w.x;
+      acc += bf2f((unsigned short)a.y) * w.y;
+      acc += bf2f((unsigned short)a.z) * w.z;
+      acc += bf2f((unsigned short)a.w) * w.w;
     }
-#pragma unroll
-    for (int c = 0; c < 8; ++c) {
-      const bool on = a2[q * CH + c] != 0;  // a2 = relu(z2) in BF16: nonzero iff z2 > 0
-      dz2[q * CH + c] = f2bf(on ? acc[c] : 0.f);
+    acc += __shfl_xor(acc, 1);
+    float loss = 0.f;
+    if ((tid & 1) == 0) {
+      const float z = acc + params[CNN3_B3];
+      const float yv = Y[(long long)b * P3 + p] ? 1.f : 0.f;
+      const float tail = log1pf(expf(-fabsf(z)));
+      loss = pos_weight * yv * (fmaxf(-z, 0.f) + tail) + (1.f - yv) * (fmaxf(z, 0.f) + tail);
+      const float s = 1.f / (1.f + expf(-z));
+      g[p] = (pos_weight * yv * (s - 1.f) + (1.f - yv) * s) * inv_total;
     }
+    for (int off = 32; off > 0; off >>= 1) loss += __shfl_xor(loss, off);
+    if (lane == 0) red[wave] = loss;
   }
-  // dW3[c][tap] = sum_p a2[p + tap][c] g[p]; db3 = sum_p g[p]
-  for (int k = tid; k < 8 * 27 + 1; k += blockDim.x) {
+  __syncthreads();
+  if (tid == 0) {
     float s = 0.f;
-    if (k < 8 * 27) {
-      const int c = k / 27, tap = k % 27;
-      int tz, ty, tx;
-      tap_xyz(tap, tz, ty, tx);
-      for (int p = 0; p < P3; ++p) {
-        const int pz = p / (T * T), py = (p / T) % T, px = p % T;
-        s += bf2f(a2[(((pz + tz) * W2 + (py + ty)) * W2 + (px + tx)) * CH + c]) * sg[p];
-      }
-      part[CNN3_W3 + k] = s;
-    } else {
-      for (int p = 0; p < P3; ++p) s += sg[p];
-      part[CNN3_B3] = s;
-    }
+    for (int k = 0; k < TRAIN_WAVES; ++k) s += red[k];
+    loss_part[b] = s * inv_total;
   }
   __syncthreads();
 
-  // --- layer 2 weight gradient: dW2[o][c][tap] = sum_p dz2[p][o] a1[p + tap][c]
-  // D[i = o][j = 8 tsub + c], tap = 2 tp + tsub; K = layer-2 voxels
-  for (int tp = wave; tp < KCH; tp += nw) {
-    const int tsub = i >> 3, c = i & 7, tap = 2 * tp + tsub;
-    const bool valid = tap < 27;
-    int tz = 0, ty = 0, tx = 0;
-    if (valid) tap_xyz(tap, tz, ty, tx);
-    const int toff = ((tz * W1 + ty) * W1 + tx) * CH + c;
-    f4 acc = {0.f, 0.f, 0.f, 0.f};
-    for (int p0 = 0; p0 < P2; p0 += 16) {
-      short av[4], bv[4];
+  // --- dW3[c][tap] = sum_p a2[p + tap][c] g[p], db3 = sum_p g[p]: a wave takes
+  // x rows, a lane one tap and 4 channels (54 lanes; lane 54 sums g); partial
+  // sums per wave into red
+  if (lane <= 54) {
+    const int tap = lane < 54 ? lane >> 1 : 0, c4 = 4 * (lane & 1);
+    const unsigned short* at = a2 + (((tap / 9) * W2 + (tap / 3) % 3) * W2 + tap % 3) * CH + c4;
+    float acc[4] = {0.f, 0.f, 0.f, 0.f}, gs = 0.f;
+    for (int r = wave; r < T * T; r += TRAIN_WAVES) {
+      const unsigned short* ar = at + ((r / T) * W2 + r % T) * W2 * CH;
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int p = p0 + 4 * kq + e;
-        av[e] = 0;
-        bv[e] = 0;
-        if (p < P2) {
-          const int pz = p / (W2 * W2), py = (p / W2) % W2, px = p % W2;
-          if (i < 8) av[e] = (short)dz2[p * CH + i];
-          if (valid) bv[e] = (short)a1[((pz * W1 + py) * W1 + px) * CH + toff];
-        }
+      for (int px = 0; px < T; ++px) {
+        const float gv = g[r * T + px];
+        const s4 a = load4(ar + px * CH);
+        gs += gv;
+        acc[0] += bf2f((unsigned short)a.x) * gv;
+        acc[1] += bf2f((unsigned short)a.y) * gv;
+        acc[2] += bf2f((unsigned short)a.z) * gv;
+        acc[3] += bf2f((unsigned short)a.w) * gv;
       }
-      acc = mfma(pack4(av[0], av[1], av[2], av[3]), pack4(bv[0], bv[1], bv[2], bv[3]), acc);
     }
-    if (valid) {
+    if (lane < 54) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) red[wave * RED_N + (c4 + e) * 27 + tap] = acc[e];
+    } else {
+      red[wave * RED_N + 8 * 27] = gs;
+    }
+  }
+  // --- dz2 = relu'(z2) * (W3 (x) g) on the layer-2 grid, 4 channels per item
+  for (int t = tid; t < 2 * P2; t += TRAIN_THREADS) {
+    const int q = t >> 1, c4 = 4 * (t & 1);
+    const int qz = q / (W2 * W2), qy = (q / W2) % W2, qx = q % W2;
+    float acc[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int tap = 0; tap < 27; ++tap) {
+      const int pz = qz - tap / 9, py = qy - (tap / 3) % 3, px = qx - tap % 3;
+      // read in any case (no branch around the loads), zero outside
+      const bool in = (unsigned)pz < (unsigned)T && (unsigned)py < (unsigned)T && (unsigned)px < (unsigned)T;
+      const float gr = g[in ? (pz * T + py) * T + px : 0];
+      const float gv = in ? gr : 0.f;
+      const float4 w = *reinterpret_cast<const float4*>(w3 + tap * 8 + c4);
+      acc[0] += w.x * gv;
+      acc[1] += w.y * gv;
+      acc[2] += w.z * gv;
+      acc[3] += w.w * gv;
+    }
+    const s4 on = load4(a2 + q * CH + c4);  // a2 = relu(z2) in BF16: nonzero iff z2 > 0
+    uint2 o;
+    o.x = f2bf_hw(on.x ? acc[0] : 0.f) | ((unsigned)f2bf_hw(on.y ? acc[1] : 0.f) << 16);
+    o.y = f2bf_hw(on.z ? acc[2] : 0.f) | ((unsigned)f2bf_hw(on.w ? acc[3] : 0.f) << 16);
+    *reinterpret_cast<uint2*>(dz2 + (((qz + 2) * W0 + qy + 2) * W0 + qx + 2) * CH + c4) = o;
+  }
+  __syncthreads();
+
+  if (tid < RED_N) {
+    float s = 0.f;
+    for (int k = 0; k < TRAIN_WAVES; ++k) s += red[k * RED_N + tid];
+    part[CNN3_W3 + tid] = s;  // db3 follows W3
+  }
+  static_assert(CNN3_B3 == CNN3_W3 + 8 * 27 && KCH < TRAIN_WAVES,
+                "a wave per tap pair and one for the bias sums");
+  // column j of a weight-gradient product: (tap of the pair, input channel);
+  // in transposed reads this lane points at voxel i / 4 of its K group of 4 x
+  // neighbours and at 4 columns of it: channels c4 of tap `ltap` (the second
+  // tap of the last pair does not exist: its columns are not used)
+  const int wtap = 2 * wave + (i >> 3), wc = i & 7;
+  const int gx = i >> 2, c4 = 4 * (i & 1);
+  const int ltap = min(2 * wave + ((i >> 1) & 1), 26);
+
+  // --- dW2[o][c][tap] = sum_p dz2[p][o] a1[p + tap][c]: D[i = o][j = (tap, c)],
+  // K = layer-2 voxels, a tap pair per wave; db2 by the wave after them.  A
+  // step's 4 K groups are 4 rows y of one plane (the last two rows of two
+  // planes together), the same x in each, so that a step's reads differ from
+  // the lane's first by a wave-uniform offset; x runs to 12: dz2's border is
+  // zero there, and a1 reads at most two voxels past its end.
+  if (wave < KCH) {
+    const int tz = ltap / 9, ty = (ltap / 3) % 3, tx = ltap % 3;
+    const unsigned short* za = dz2 + ((2 * W0 + 2 + kq) * W0 + 2 + gx) * CH + c4;
+    const unsigned short* aa = a1 + ((tz * W1 + ty + kq) * W1 + tx + gx) * CH + c4;
+    // the same for rows 8 and 9 of planes z and z + 1
+    const int ky = 8 + (kq & 1), kz = kq >> 1;
+    const unsigned short* zb = dz2 + (((2 + kz) * W0 + 2 + ky) * W0 + 2 + gx) * CH + c4;
+    const unsigned short* ab = a1 + (((tz + kz) * W1 + ty + ky) * W1 + tx + gx) * CH + c4;
+    f4 acc[3] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+    static_assert(W2 == 10, "rows 0 .. 7 in blocks of four, 8 and 9 in pairs of planes");
+    for (int z = 0; z < W2; ++z) {
+#pragma unroll
+      for (int yb = 0; yb < 2; ++yb)
+#pragma unroll
+        for (int xg = 0; xg < 3; ++xg)
+          acc[xg] = mfma(load4_tr(za + ((z * W0 + 4 * yb) * W0 + 4 * xg) * CH),
+                         load4_tr(aa + ((z * W1 + 4 * yb) * W1 + 4 * xg) * CH), acc[xg]);
+      if (z & 1) continue;
+#pragma unroll
+      for (int xg = 0; xg < 3; ++xg)
+        acc[xg] = mfma(load4_tr(zb + (z * W0 * W0 + 4 * xg) * CH),
+                       load4_tr(ab + (z * W1 * W1 + 4 * xg) * CH), acc[xg]);
+    }
+    if (wtap < 27) {
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         const int o = 4 * kq + e;
-        if (o < 8) part[CNN3_W2 + (o * 8 + c) * 27 + tap] = acc[e];
+        if (o < 8) part[CNN3_W2 + (o * 8 + wc) * 27 + wtap] = (acc[0][e] + acc[1][e]) + acc[2][e];
       }
     }
-  }
-  for (int o = tid; o < 8; o += blockDim.x) {
+  } else if (wave == KCH) {
+    const int o = lane & 7;
     float s = 0.f;
-    for (int p = 0; p < P2; ++p) s += bf2f(dz2[p * CH + o]);
-    part[CNN3_B2 + o] = s;
+#pragma unroll 4
+    for (int p = lane >> 3; p < P2; p += 8) {
+      const int pz = p / (W2 * W2), py = (p / W2) % W2, px = p % W2;
+      s += bf2f(dz2[(((pz + 2) * W0 + py + 2) * W0 + px + 2) * CH + o]);
+    }
+    s += __shfl_xor(s, 8);
+    s += __shfl_xor(s, 16);
+    s += __shfl_xor(s, 32);
+    if (lane < 8) part[CNN3_B2 + o] = s;
   }
 
-  // --- layer 2 data gradient: dz1[q][c] = relu'(z1) sum_tap sum_o W2[o][c][tap] dz2[q - tap][o]
-  // D[i = voxel][j = c]; K = (tap, o), 2 taps x 8 channels per chunk
+  // --- dz1[q][c] = relu'(z1) sum_tap sum_o W2[o][c][tap] dz2[q - tap][o]:
+  // D[i = voxel][j = c], K = (tap, o), 2 taps x 8 channels per chunk
   {
     s4 bop[KCH];
 #pragma unroll
-    for (int kc = 0; kc < KCH; ++kc) {
-      const int tap = 2 * kc + half;
-      short w[4];
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int o = cg + e;
-        w[e] = (i < 8 && tap < 27) ? (short)Wb[CNN3_W2 + (o * 8 + i) * 27 + tap] : (short)0;
-      }
-      bop[kc] = pack4(w[0], w[1], w[2], w[3]);
-    }
+    for (int kc = 0; kc < KCH; ++kc)
+      bop[kc] = tap_weights(Wb + CNN3_W2 + (cg * 8 + (i & 7)) * 27, 8 * 27, 4, i < 8, 2 * kc + half);
     constexpr int nblk = P1 / 16;
-    for (int blk = wave; blk < nblk; blk += nw) {
+    for (int blk = TRAIN_WAVES - 1 - wave; blk < nblk; blk += TRAIN_WAVES) {
       const int q = 16 * blk + i;
       const int qz = q / (W1 * W1), qy = (q / W1) % W1, qx = q % W1;
+      const TapReads<W0, true> a(dz2 + ((qz * W0 + qy) * W0 + qx) * CH, half, cg);
       f4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int kc = 0; kc < KCH; ++kc) {
-        const int tap = 2 * kc + half;
-        s4 a = zero4();
-        if (tap < 27) {
-          int tz, ty, tx;
-          tap_xyz(tap, tz, ty, tx);
-          const int sz = qz - tz, sy = qy - ty, sx = qx - tx;
-          if (sz >= 0 && sy >= 0 && sx >= 0 && sz < W2 && sy < W2 && sx < W2)
-            a = load4(dz2 + ((sz * W2 + sy) * W2 + sx) * CH + cg);
-        }
-        acc = mfma(a, bop[kc], acc);
-      }
+      for (int kc = 0; kc < KCH; ++kc) acc = mfma(a(kc), bop[kc], acc);
       if (i < 8) {
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-          const int qq = 16 * blk + 4 * kq + e;
-          const bool on = a1[qq * CH + i] != 0;
-          dz1[qq * CH + i] = f2bf(on ? acc[e] : 0.f);
+          const int q = 16 * blk + 4 * kq + e;
+          dz1[q * CH + i] = f2bf_hw(a1[q * CH + i] != 0 ? acc[e] : 0.f);
         }
       }
     }
   }
   __syncthreads();
 
-  // --- layer 1 weight gradient: dW1[o][c][tap] = sum_p dz1[p][o] x[p + tap][c]
-  for (int tp = wave; tp < KCH; tp += nw) {
-    const int tsub = i >> 3, c = i & 7, tap = 2 * tp + tsub;
-    const bool valid = tap < 27 && c < 5;
-    int tz = 0, ty = 0, tx = 0;
-    if (valid) tap_xyz(tap, tz, ty, tx);
-    const int toff = ((tz * W0 + ty) * W0 + tx) * CH + c;
-    f4 acc = {0.f, 0.f, 0.f, 0.f};
-    for (int p0 = 0; p0 < P1; p0 += 16) {
-      short av[4], bv[4];
+  // --- dW1[o][c][tap] = sum_p dz1[p][o] x[p + tap][c], db1 by the wave after
+  if (wave < KCH) {
+    const unsigned short* da = dz1 + (kq * W1 + gx) * CH + c4;
+    const unsigned short* xa = x + (((ltap / 9) * W0 + (ltap / 3) % 3 + kq) * W0 + ltap % 3 + gx) * CH + c4;
+    f4 acc[3] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+    static_assert(W1 == 12, "three blocks of four rows and of four voxels in x");
+    for (int z = 0; z < W1; ++z)
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int p = p0 + 4 * kq + e;
-        const int pz = p / (W1 * W1), py = (p / W1) % W1, px = p % W1;
-        av[e] = i < 8 ? (short)dz1[p * CH + i] : (short)0;
-        bv[e] = valid ? (short)x[((pz * W0 + py) * W0 + px) * CH + toff] : (short)0;
-      }
-      acc = mfma(pack4(av[0], av[1], av[2], av[3]), pack4(bv[0], bv[1], bv[2], bv[3]), acc);
-    }
-    if (valid) {
+      for (int yb = 0; yb < 3; ++yb)
+#pragma unroll
+        for (int xg = 0; xg < 3; ++xg)
+          acc[xg] = mfma(load4_tr(da + ((z * W1 + 4 * yb) * W1 + 4 * xg) * CH),
+                         load4_tr(xa + ((z * W0 + 4 * yb) * W0 + 4 * xg) * CH), acc[xg]);
+    if (wtap < 27 && wc < 5) {
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         const int o = 4 * kq + e;
-        if (o < 8) part[CNN3_W1 + (o * 5 + c) * 27 + tap] = acc[e];
+        if (o < 8) part[CNN3_W1 + (o * 5 + wc) * 27 + wtap] = (acc[0][e] + acc[1][e]) + acc[2][e];
       }
     }
-  }
-  for (int o = tid; o < 8; o += blockDim.x) {
+  } else if (wave == KCH) {
+    const int o = lane & 7;
     float s = 0.f;
-    for (int p = 0; p < P1; ++p) s += bf2f(dz1[p * CH + o]);
-    part[CNN3_B1 + o] = s;
+#pragma unroll 4
+    for (int q = lane >> 3; q < P1; q += 8) s += bf2f(dz1[q * CH + o]);
+    s += __shfl_xor(s, 8);
+    s += __shfl_xor(s, 16);
+    s += __shfl_xor(s, 32);
+    if (lane < 8) part[CNN3_B1 + o] = s;
   }
 }
 
@@ -413,17 +512,13 @@ __global__ __launch_bounds__(256) void k_cnn3_requests(int count, const float* _
 // ---------------------------------------------------------------------------
 size_t Cnn3::fwd_lds() { return (size_t)(P0 + P1) * CH * sizeof(unsigned short); }
 
-size_t Cnn3::bwd_lds() {
-  return (size_t)(2 * P2 + 2 * P1 + P0) * CH * sizeof(unsigned short) + P3 * sizeof(float);
-}
-
 static void allow_large_lds3() {
   static bool done = false;
   if (done) return;
   done = true;
   (void)hipFuncSetAttribute((const void*)k_cnn3_fwd, hipFuncAttributeMaxDynamicSharedMemorySize,
                             160 * 1024);
-  (void)hipFuncSetAttribute((const void*)k_cnn3_bwd, hipFuncAttributeMaxDynamicSharedMemorySize,
+  (void)hipFuncSetAttribute((const void*)k_cnn3_train, hipFuncAttributeMaxDynamicSharedMemorySize,
                             160 * 1024);
 }
 
@@ -436,21 +531,21 @@ void Cnn3::gather(const DevMesh& m, const double* U, const int* items, int count
 }
 
 void Cnn3::forward(int count, const unsigned short* X, const unsigned short* Wb, const float* params,
-                   unsigned short* A1, unsigned short* A2, float* Z, hipStream_t s) {
+                   float* Z, hipStream_t s) {
   if (count <= 0) return;
   allow_large_lds3();
-  hipLaunchKernelGGL(k_cnn3_fwd, dim3(count), dim3(FWD_THREADS), fwd_lds(), s, count, X, Wb, params, A1,
-                     A2, Z);
+  hipLaunchKernelGGL(k_cnn3_fwd, dim3(count), dim3(FWD_THREADS), fwd_lds(), s, count, X, Wb, params,
+                     Z);
 }
 
-void Cnn3::backward(int count, const unsigned short* X, const unsigned short* A1,
-                    const unsigned short* A2, const float* G, const unsigned short* Wb,
-                    float* partials, float* grads, hipStream_t s) {
+void Cnn3::train(int count, const unsigned short* X, const uint8_t* Y, const unsigned short* Wb,
+                 const float* params, float pos_weight, float* partials, float* loss_part,
+                 hipStream_t s) {
   if (count <= 0) return;
   allow_large_lds3();
-  hipLaunchKernelGGL(k_cnn3_bwd, dim3(count), dim3(BWD_THREADS), bwd_lds(), s, count, X, A1, A2, G, Wb,
-                     partials);
-  Cnn::reduce(partials, count, CNN3_NPARAM, grads, s);
+  const float inv_total = 1.0f / (float)((long long)count * P3);
+  hipLaunchKernelGGL(k_cnn3_train, dim3(count), dim3(TRAIN_THREADS), TL_TOTAL, s, count, X, Y, Wb,
+                     params, pos_weight, inv_total, partials, loss_part);
 }
 
 void Cnn3::requests(int count, const float* Z, const int* items, float zt, uint8_t* flag,

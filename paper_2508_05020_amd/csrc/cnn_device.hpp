@@ -25,6 +25,13 @@ __device__ __forceinline__ unsigned short f2bf(float f) {
   return (unsigned short)(u >> 16);
 }
 
+// f2bf by the gfx950 conversion instruction (the same rounding to nearest
+// even; a NaN stays a NaN)
+__device__ __forceinline__ unsigned short f2bf_hw(float f) {
+  const __bf16 h = (__bf16)f;
+  return __builtin_bit_cast(unsigned short, h);
+}
+
 __device__ __forceinline__ float bf2f(unsigned short h) { return __uint_as_float(((unsigned)h) << 16); }
 
 __device__ __forceinline__ f4 mfma(s4 a, s4 b, f4 c) {
@@ -40,6 +47,17 @@ __device__ __forceinline__ s4 load4(const unsigned short* p) {
   r.z = (short)(v.y & 0xffff);
   r.w = (short)(v.y >> 16);
   return r;
+}
+
+// Transposed LDS read (ds_read_b64_tr_b16): the 16 lanes of a group point at
+// the 8-byte pieces of 4 rows of 16 values, lane t at piece t % 4 of row
+// t / 4, and lane t receives column t of the 4 rows.  With rows = K and
+// columns = the operand's other index that is an MFMA operand from K-major
+// storage in one read (the lane order is checked by the weight-gradient
+// tests).  p: LDS memory, 8-byte aligned.
+__device__ __forceinline__ s4 load4_tr(const unsigned short* p) {
+  typedef __attribute__((address_space(3))) s4 lds_s4;
+  return __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4*)p);
 }
 
 __device__ __forceinline__ s4 zero4() {

@@ -49,20 +49,20 @@ struct CnnNorm {
 
 struct Cnn {
   static size_t fwd_lds(int n);
-  static size_t bwd_lds(int n);
   static void gather(const DevMesh& m, const double* U, const int* pids, int count, int n,
                      const CnnNorm& norm, unsigned short* X, hipStream_t s);
   static void forward(int count, int n, const unsigned short* X, const unsigned short* Wb,
-                      const float* params, unsigned short* A1, unsigned short* A2, float* Z,
-                      hipStream_t s);
-  static void loss(long long total, const float* Z, const uint8_t* Y, float pos_weight, float* G,
-                   float* partial, int nblocks, float* loss_out, hipStream_t s);
-  static void backward(int count, int n, const unsigned short* X, const unsigned short* A1,
-                       const unsigned short* A2, const float* G, const unsigned short* Wb,
-                       float* partials, float* grads, hipStream_t s);
-  static void reduce(const float* partials, int count, int np, float* grads, hipStream_t s);
-  static void adam(float* params, const float* grads, float* m, float* v, float lr, int t, int np,
-                   unsigned short* Wb, hipStream_t s);
+                      const float* params, float* Z, hipStream_t s);
+  // forward, loss and backward: per-tile parameter gradients (partials) and
+  // losses (loss_part), `count` of each
+  static void train(int count, int n, const unsigned short* X, const uint8_t* Y,
+                    const unsigned short* Wb, const float* params, float pos_weight,
+                    float* partials, float* loss_part, hipStream_t s);
+  // sums them (gradient to `grads`, nullable; loss to `loss`) and, when
+  // lr > 0, takes Adam step t
+  static void update(const float* partials, const float* loss_part, int count, int np,
+                     float* grads, float* loss, float* params, float* m, float* v, float lr, int t,
+                     unsigned short* Wb, hipStream_t s);
   static void to_bf16(const float* params, int np, unsigned short* Wb, hipStream_t s);
   static void requests(int count, int n, const float* Z, const int* pids, float zt,
                        uint8_t* flag, hipStream_t s);
@@ -73,15 +73,13 @@ struct Cnn {
 // 3D kernels; `items` are tile items (see CNN3_MAX_TILES), one block each.
 struct Cnn3 {
   static size_t fwd_lds();
-  static size_t bwd_lds();
   static void gather(const DevMesh& m, const double* U, const int* items, int count,
                      const CnnNorm& norm, unsigned short* X, hipStream_t s);
   static void forward(int count, const unsigned short* X, const unsigned short* Wb,
-                      const float* params, unsigned short* A1, unsigned short* A2, float* Z,
-                      hipStream_t s);
-  static void backward(int count, const unsigned short* X, const unsigned short* A1,
-                       const unsigned short* A2, const float* G, const unsigned short* Wb,
-                       float* partials, float* grads, hipStream_t s);
+                      const float* params, float* Z, hipStream_t s);
+  static void train(int count, const unsigned short* X, const uint8_t* Y, const unsigned short* Wb,
+                    const float* params, float pos_weight, float* partials, float* loss_part,
+                    hipStream_t s);
   static void requests(int count, const float* Z, const int* items, float zt, uint8_t* flag,
                        hipStream_t s);
 };
