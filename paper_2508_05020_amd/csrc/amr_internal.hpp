@@ -34,6 +34,10 @@ struct LevelC {
   long long fr_stride; // doubles per patch of flux registers (2 dim nvar n^(dim-1))
   long long tag_off;   // offset (bytes) of this level's cell-tag pool
   double h, inv_h;
+  // ceil(2^32 / n) and ceil(2^32 / full) where the high half of a product with
+  // them is the exact quotient for every cell index of the level, of a patch's
+  // interior (n_mul) or of its box (full_mul); else 0 (see div_by)
+  unsigned n_mul, full_mul;
 };
 
 // Everything a kernel needs to address patch data, passed by value.
@@ -66,10 +70,10 @@ struct ListView {
 
 // Launch wrappers implemented in kernels.hip.
 struct Kernels {
-  // coarse_only: write only the ghost cells without a same-level source
-  // (the prolonged ones)
-  static void fill(const DevMesh& m, double* U, const int* list, int count, int* err,
-                   bool coarse_only, hipStream_t s);
+  // ghosts of the listed patches that have a same-level source (copies), and
+  // the prolonged ones of the listed (pid, ghost region) pairs
+  static void fill(const DevMesh& m, double* U, const int* list, int count, const int* regions,
+                   int nregions, int* err, hipStream_t s);
   // prolonged ghost cells only, over (pid, ghost region) pairs
   // dir (nullable): list directory entry; with it `list` is the list buffer
   // and the list and its live count are read at run time, and `count` only

@@ -284,6 +284,16 @@ void validate_config(const amr_config& c) {
     throw ArgError("patch edges must be multiples of 8 (1D, 2D) or 4 (3D)");
 }
 
+// m = ceil(2^32 / d) where floor(v m / 2^32) = v / d for 0 <= v <= vmax, else
+// 0: m d exceeds 2^32 by e < d, and v m / 2^32 exceeds v / d by v e / (2^32 d),
+// which must stay below the 1 / d that would reach the next quotient
+unsigned exact_mul(int d, long long vmax) {
+  const unsigned long long two32 = 1ULL << 32, m = (two32 + d - 1) / d;
+  const unsigned long long e = m * (unsigned long long)d - two32;
+  if (d < 2 || vmax >= (1LL << 31) || (unsigned long long)vmax * e >= two32) return 0;
+  return (unsigned)m;
+}
+
 void build_devmesh(amr_hierarchy* h) {
   const amr_config& c = h->cfg;
   amr::DevMesh& m = h->dm;
@@ -330,6 +340,11 @@ void build_devmesh(amr_hierarchy* h) {
     L.tag_off = tg;
     L.h = (c.hi - c.lo) / (double)L.cells;
     L.inv_h = 1.0 / L.h;
+    // largest value divided: a cell index of the level, an index into the
+    // patch's interior or faces; into its box
+    const long long inner = std::max<long long>(ipow(L.n, c.dim), 2LL * c.dim * ipow(L.n, c.dim - 1));
+    L.n_mul = exact_mul(L.n, std::max<long long>(2 * inner, L.cells));
+    L.full_mul = exact_mul(L.full, box);
     pool += L.stride * L.cap;
     frp += L.fr_stride * L.cap;
     tg += box * L.cap;
@@ -726,9 +741,20 @@ void over_list_dir(amr_hierarchy* h, const amr::ListView& lv, int stride_ints, i
   h->check_launch();
 }
 
-void do_fill(amr_hierarchy* h, int buf, const amr::ListView& lv, bool coarse_only = false) {
+// Ghosts of the patches of `lv`: same-level copies, and the prolonged regions
+// of the leaves (patches with children have every same-level neighbour).
+void do_fill(amr_hierarchy* h, int buf, const amr::ListView& lv) {
+  if (h->exec_mode == AMR_EXEC_BATCHED) {
+    Kernels::fill(h->dm, h->U[buf], lv.ptr, lv.count, h->cfregions.ptr, h->cfregions.count,
+                  h->d_flags, h->stream);
+    h->check_launch();
+    return;
+  }
   over_list(h, lv, 1, [&](const int* p, int c) {
-    Kernels::fill(h->dm, h->U[buf], p, c, h->d_flags, coarse_only, h->stream);
+    Kernels::fill(h->dm, h->U[buf], p, c, nullptr, 0, h->d_flags, h->stream);
+  });
+  over_list(h, h->cfregions, 2, [&](const int* p, int c) {
+    Kernels::fill_cf(h->dm, h->U[buf], p, c, nullptr, h->d_flags, h->stream);
   });
 }
 

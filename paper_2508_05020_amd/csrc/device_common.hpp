@@ -27,6 +27,12 @@ __device__ __forceinline__ int bc_map(int g, int N, int periodic) {
   return g < 0 ? 0 : (g >= N ? N - 1 : g);
 }
 
+// bc_map for an index at most one period outside the domain
+__device__ __forceinline__ int bc_near(int g, int N, int periodic) {
+  if (periodic) return g < 0 ? g + N : (g >= N ? g - N : g);
+  return g < 0 ? 0 : (g >= N ? N - 1 : g);
+}
+
 template <int D>
 __device__ __forceinline__ int box_off(int full, int x, int y, int z) {
   // offsets inside one patch fit 32 bits, and the factors 24 (one full-rate
@@ -56,24 +62,39 @@ __device__ __forceinline__ int map_at(const DevMesh& m, int l, const int q[3]) {
   return m.map[L.map_off + idx];
 }
 
-// Conserved values of the level-l cell at in-domain global index g.
+// v / d for 0 <= v where mul = ceil(2^32 / d) gives the exact quotient (one
+// product instead of an integer division of about 25 instructions), or by
+// division where mul is 0
+__device__ __forceinline__ int div_by(int v, int d, unsigned mul) {
+  return mul ? (int)__umulhi((unsigned)v, mul) : v / d;
+}
+
+// Same-level patches around the patch at pc, by offset code (o0+1) + 3 (o1+1)
+// + 9 (o2+1), o in {-1,0,1}^D (periodic wrap), as the offsets of their data in
+// the state buffer (-1 where no patch or outside a non-periodic domain); one
+// per thread of the first 3^D.
 template <int D>
-__device__ bool fetch_cell(const DevMesh& m, const double* __restrict__ U, int l,
-                           const int g[3], double out[D + 2]) {
-  const LevelC& L = m.lv[l];
-  int q[3] = {0, 0, 0}, c[3] = {0, 0, 0};
-  for (int j = 0; j < D; ++j) {
-    q[j] = g[j] / L.n;
-    c[j] = g[j] - q[j] * L.n;
-  }
-  const int pid = map_at<D>(m, l, q);
-  if (pid < 0) return false;
-  const double* P = U + patch_base(m, pid, l);
-  const int off = box_off<D>(L.full, c[0] + NG, c[1] + NG, c[2] + NG);
-  const int vs = var_stride<D>(L.full);
+__device__ __forceinline__ void load_neighbours(const DevMesh& m, int l, const int pc[3],
+                                                long long* sNB) {
+  constexpr int NO = D == 1 ? 3 : (D == 2 ? 9 : 27);
+  const int t = threadIdx.x;
+  if (t < NO) {
+    const int np = m.lv[l].np;
+    int q[3] = {0, 0, 0};
+    bool in = true;
 #pragma unroll
-  for (int v = 0; v < D + 2; ++v) out[v] = P[v * vs + off];
-  return true;
+    for (int j = 0; j < D; ++j) {
+      const int o = (j == 0 ? t : (j == 1 ? t / 3 : t / 9)) % 3 - 1;
+      int v = pc[j] + o;
+      if (v < 0 || v >= np) {
+        if (m.periodic[j]) v = (v + np) % np;
+        else in = false;
+      }
+      q[j] = v;
+    }
+    const int pid = in ? map_at<D>(m, l, q) : -1;
+    sNB[t] = pid >= 0 ? patch_base(m, pid, l) : -1;
+  }
 }
 
 // Pressure from conserved values in the reference operation order:
@@ -88,40 +109,59 @@ __device__ __forceinline__ double pressure_exact(const double* u, double gm1) {
   return gm1 * (u[D + 1] - ke);
 }
 
-// Conservative MC-limited linear prolongation of the level-lf cell at mapped
-// global index g from level lf-1.  Slopes are dropped when any of the 2^D
-// children of the coarse cell would have rho <= 0 or p <= 0.
+// Centre value phi and MC-limited slopes sl of the level-lc cell at in-domain
+// index gc, for its conservative linear prolongation: a child on the sides
+// sig_j = +-1 is phi + sum_j (sig_j / 4) sl_j, terms added in the order x, y,
+// z.  All slopes are zero when any of the 2^D children would have rho <= 0 or
+// p <= 0.  False when a cell of the stencil has no patch.
 template <int D>
-__device__ bool prolong_cell(const DevMesh& m, const double* __restrict__ U, int lf,
-                             const int g[3], double out[D + 2]) {
+__device__ __forceinline__ bool prolong_coarse(const DevMesh& m, const double* __restrict__ U,
+                                               int lc, const int gc[3], double phi[D + 2],
+                                               double sl[D][D + 2]) {
   constexpr int NV = D + 2;
   constexpr int NS = 2 * D + 1;  // coarse stencil: centre, then (+1, -1) per direction
-  const int lc = lf - 1;
   const LevelC& C = m.lv[lc];
-  int gc[3] = {0, 0, 0};
-  double sig[3] = {0.0, 0.0, 0.0};
-  for (int j = 0; j < D; ++j) {
-    gc[j] = g[j] >> 1;
-    sig[j] = (g[j] & 1) ? 1.0 : -1.0;
-  }
-  // all map lookups first, then all loads, so the latencies overlap
-  int pids[NS];
-  long long offs[NS];
-  const int vs = var_stride<D>(C.full);
+  // the centre's patch and cell; a stencil cell leaves the patch by one cell
+  // at most (periodic wrap of the patch position; at a transmissive boundary
+  // the clamped position is the centre itself)
+  int q[3] = {0, 0, 0}, c[3] = {0, 0, 0};
 #pragma unroll
-  for (int s = 0; s < NS; ++s) {
-    int gs[3] = {gc[0], gc[1], gc[2]};
-    if (s > 0) {
-      const int j = (s - 1) >> 1;
-      gs[j] = bc_map(gc[j] + (((s - 1) & 1) ? -1 : 1), C.cells, m.periodic[j]);
+  for (int j = 0; j < D; ++j) {
+    q[j] = div_by(gc[j], C.n, C.n_mul);
+    c[j] = gc[j] - q[j] * C.n;
+  }
+  const int vs = var_stride<D>(C.full);
+  const int step[3] = {1, C.full, __mul24(C.full, C.full)};
+  const int mstep[3] = {1, C.np, C.np * C.np};
+  int at = q[0], off0 = box_off<D>(C.full, c[0] + NG, c[1] + NG, c[2] + NG);
+  if constexpr (D >= 2) at += C.np * q[1];
+  if constexpr (D >= 3) at += C.np * C.np * q[2];
+  // all map lookups first, then all loads, so the latencies overlap
+  int pids[NS], offs[NS];
+  const int* map = m.map + C.map_off;
+  pids[0] = map[at];
+  offs[0] = off0;
+#pragma unroll
+  for (int j = 0; j < D; ++j) {
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      const int o = k == 0 ? 1 : -1, cj = c[j] + o;
+      int am = at, of = off0 + o * step[j];
+      if ((unsigned)cj >= (unsigned)C.n) {
+        int qj = q[j] + o;
+        if ((unsigned)qj >= (unsigned)C.np) {
+          if (m.periodic[j]) qj -= o * C.np;
+        }
+        if ((unsigned)qj >= (unsigned)C.np) {
+          of = off0;
+        } else {
+          am = at + (qj - q[j]) * mstep[j];
+          of = off0 - o * (C.n - 1) * step[j];
+        }
+      }
+      pids[1 + 2 * j + k] = map[am];
+      offs[1 + 2 * j + k] = of;
     }
-    int q[3] = {0, 0, 0}, c[3] = {0, 0, 0};
-    for (int j = 0; j < D; ++j) {
-      q[j] = gs[j] / C.n;
-      c[j] = gs[j] - q[j] * C.n;
-    }
-    pids[s] = map_at<D>(m, lc, q);
-    offs[s] = box_off<D>(C.full, c[0] + NG, c[1] + NG, c[2] + NG);
   }
   bool found = true;
 #pragma unroll
@@ -134,8 +174,8 @@ __device__ bool prolong_cell(const DevMesh& m, const double* __restrict__ U, int
 #pragma unroll
     for (int v = 0; v < NV; ++v) val[s][v] = P[v * vs];
   }
-  const double* phi = val[0];
-  double sl[D][NV];
+#pragma unroll
+  for (int v = 0; v < NV; ++v) phi[v] = val[0][v];
 #pragma unroll
   for (int j = 0; j < D; ++j) {
 #pragma unroll
@@ -147,25 +187,96 @@ __device__ bool prolong_cell(const DevMesh& m, const double* __restrict__ U, int
       sl[j][v] = same ? copysign(mag, a) : 0.0;
     }
   }
-  bool bad = false;
-  for (int c = 0; c < (1 << D); ++c) {
-    double ch[NV];
-#pragma unroll
-    for (int v = 0; v < NV; ++v) {
-      double x = phi[v];
-      for (int j = 0; j < D; ++j) x = x + (((c >> j) & 1) ? 0.25 : -0.25) * sl[j][v];
-      ch[v] = x;
-    }
-    const double p = pressure_exact<D>(ch, m.gm1);
-    if (!(ch[0] > 0.0 && p > 0.0)) bad = true;
-  }
+  // Every child lies within dev = sum_j |sl_j| / 4 of phi in every variable.
+  // Where the smallest density and energy within that are at least 1e-3 of the
+  // cell's own (so that their rounding stays below 1e-12 of them) and give
+  // 2 rho E > |m|^2 with the largest momenta by a margin far above it, every
+  // child passes the exact test; only the other cells (and NaN) go through the
+  // children one by one.
+  double lo[2], mm = 0.0;
 #pragma unroll
   for (int v = 0; v < NV; ++v) {
+    double dev = fabs(sl[0][v]);
+#pragma unroll
+    for (int j = 1; j < D; ++j) dev = dev + fabs(sl[j][v]);
+    if (v == 0 || v == NV - 1) {
+      lo[v == 0 ? 0 : 1] = phi[v] - 0.25 * dev;
+    } else {
+      const double hi = fabs(phi[v]) + 0.25 * dev;
+      mm = mm + hi * hi;
+    }
+  }
+  if (!(lo[0] > 1e-3 * phi[0] && lo[1] > 1e-3 * phi[NV - 1] &&
+        2.0 * lo[0] * lo[1] > mm * (1.0 + 1e-10))) {
+    bool bad = false;
+    for (int k = 0; k < (1 << D); ++k) {
+      double ch[NV];
+#pragma unroll
+      for (int v = 0; v < NV; ++v) {
+        double x = phi[v];
+#pragma unroll
+        for (int j = 0; j < D; ++j) x = x + (((k >> j) & 1) ? 0.25 : -0.25) * sl[j][v];
+        ch[v] = x;
+      }
+      const double p = pressure_exact<D>(ch, m.gm1);
+      if (!(ch[0] > 0.0 && p > 0.0)) bad = true;
+    }
+    if (bad) {
+#pragma unroll
+      for (int j = 0; j < D; ++j)
+#pragma unroll
+        for (int v = 0; v < NV; ++v) sl[j][v] = 0.0;
+    }
+  }
+  return true;
+}
+
+// The level-lf cell at mapped global index g prolonged from level lf-1.
+template <int D>
+__device__ __forceinline__ bool prolong_cell(const DevMesh& m, const double* __restrict__ U, int lf,
+                                             const int g[3], double out[D + 2]) {
+  int gc[3] = {0, 0, 0};
+#pragma unroll
+  for (int j = 0; j < D; ++j) gc[j] = g[j] >> 1;
+  double phi[D + 2], sl[D][D + 2];
+  if (!prolong_coarse<D>(m, U, lf - 1, gc, phi, sl)) return false;
+#pragma unroll
+  for (int v = 0; v < D + 2; ++v) {
     double x = phi[v];
-    for (int j = 0; j < D; ++j) x = x + (sig[j] * 0.25) * (bad ? 0.0 : sl[j][v]);
+#pragma unroll
+    for (int j = 0; j < D; ++j) x = x + ((g[j] & 1) ? 0.25 : -0.25) * sl[j][v];
     out[v] = x;
   }
   return true;
+}
+
+// The 2^D children of a coarse cell into a patch at box offset off (of the
+// lowest child): side sg[j][f] = +-1 of child f (0 low, 1 high) along j; NaN
+// when `ok` is false.  x pairs go out as one 16-byte store: every offset here
+// is even (even patch edges and box rows, ghost width 4, pools of whole
+// patches behind an even head pad) and the state buffers are 256-byte aligned.
+template <int D>
+__device__ __forceinline__ void store_children(double* P, int vs, int full, int off, bool ok,
+                                               const double phi[D + 2], const double sl[D][D + 2],
+                                               const double sg[3][2]) {
+#pragma unroll
+  for (int f = 0; f < (1 << (D - 1)); ++f) {
+    const int o = off + (f & 1 ? full : 0) + (f & 2 ? __mul24(full, full) : 0);
+#pragma unroll
+    for (int v = 0; v < D + 2; ++v) {
+      double2 x;
+      x.x = phi[v] + (sg[0][0] * 0.25) * sl[0][v];
+      x.y = phi[v] + (sg[0][1] * 0.25) * sl[0][v];
+#pragma unroll
+      for (int j = 1; j < D; ++j) {
+        const double t = (sg[j][(f >> (j - 1)) & 1] * 0.25) * sl[j][v];
+        x.x = x.x + t;
+        x.y = x.y + t;
+      }
+      if (!ok) x.x = x.y = __builtin_nan("");
+      *reinterpret_cast<double2*>(P + v * vs + o) = x;
+    }
+  }
 }
 
 // CFL rate of one cell, sum_j (|u_j| + c) / h with c = sqrt(gamma p / rho),
@@ -223,6 +334,17 @@ __device__ __forceinline__ int xcd_item(int count) {
   const int k = (int)blockIdx.x / kXcds;
   const int item = ((int)blockIdx.x % kXcds) * per + k;
   return (k < per && item < count) ? item : -1;
+}
+
+// Work item of this block where items differ in size: chunks of C consecutive
+// items go to the XCDs in turn (block b runs on XCD b mod kXcds), so that an
+// XCD's items at any time are neighbours in the list and every XCD gets a
+// share of each part of it.  The grid is whole groups of kXcds C blocks.
+template <int C>
+__device__ __forceinline__ int xcd_chunk(int count) {
+  const int b = (int)blockIdx.x, g = b / (kXcds * C) * (kXcds * C);
+  const int item = g + (b % kXcds) * C + (b / kXcds) % C;
+  return item < count ? item : -1;
 }
 
 }  // namespace

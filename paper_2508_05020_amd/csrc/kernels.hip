@@ -31,46 +31,90 @@
 namespace amr {
 namespace {
 
+// Consecutive patches whose ghosts an XCD copies at a time (xcd_chunk): they
+// read each other's cells.  3D, 4288 patches of 8^3 and 448 of 16^3: 336 us
+// with patch b on XCD b mod 8, 478 us with a contiguous eighth of the list per
+// XCD (the first holds all the large patches), 306 us with chunks of 32.
+constexpr int kCopyChunk = 32;
+
 // ---------------------------------------------------------------------------
 // ghost fill
 // ---------------------------------------------------------------------------
-template <int D>
-__global__ __launch_bounds__(256) void k_fill(DevMesh m, double* __restrict__ U,
-                                              const int* __restrict__ list, int count,
-                                              int* __restrict__ err, int coarse_only) {
+// Ghost cells of one patch that lie in a same-level patch, by the whole block:
+// copied from that patch (neighbour table sNB by offset code), x pairs as
+// 16-byte accesses (a pair lies on one side of every region boundary and, but
+// for the clamp at a transmissive wall, in one source row).  Regions without a
+// same-level patch are prolonged elsewhere.  The cells read are interior
+// cells, the cells written ghosts.  Bound by memory: 40 B written per 3D cell.
+template <int D, int NT>
+__device__ __forceinline__ void copy_ghosts(const DevMesh& m, const double* __restrict__ Uin,
+                                            double* __restrict__ U, int pid, long long* sNB) {
   constexpr int NV = D + 2;
-  if ((int)blockIdx.x >= count) return;
-  const int pid = list[blockIdx.x];
   const int l = m.level[pid];
   const LevelC& L = m.lv[l];
-  const int n = L.n, full = L.full;
-  const int vs = var_stride<D>(full);
-  double* P = U + patch_base(m, pid, l);
+  const int n = L.n, full = L.full, vs = var_stride<D>(full);
   const int pc[3] = {m.coord[3 * pid], m.coord[3 * pid + 1], m.coord[3 * pid + 2]};
-  const int total = (int)vs;
-  for (int idx = threadIdx.x; idx < total; idx += blockDim.x) {
-    int b[3] = {idx % full, 0, 0};
-    if constexpr (D >= 2) b[1] = (idx / full) % full;
-    if constexpr (D >= 3) b[2] = idx / (full * full);
-    bool ghost = false;
-    int g[3] = {0, 0, 0};
+  load_neighbours<D>(m, l, pc, sNB);
+  __syncthreads();
+  double* P = U + patch_base(m, pid, l);
+#pragma unroll 2
+  for (int pair = threadIdx.x; pair < vs / 2; pair += NT) {
+    const int idx = 2 * pair;
+    const int r = D >= 2 ? div_by(idx, full, L.full_mul) : 0;
+    const int rz = D >= 3 ? div_by(r, full, L.full_mul) : 0;
+    const int c[3] = {idx - r * full - NG, D >= 2 ? r - rz * full - NG : 0, rz - NG};
+    int code = 0, mul = 1, loc[3] = {0, 0, 0};
+    bool ghost = false, dup = false;
+#pragma unroll
     for (int j = 0; j < D; ++j) {
-      const int c = b[j] - NG;
-      ghost |= (c < 0) || (c >= n);
-      g[j] = bc_map(pc[j] * n + c, L.cells, m.periodic[j]);
+      int o = c[j] < 0 ? -1 : (c[j] >= n ? 1 : 0);
+      ghost |= o != 0;
+      loc[j] = c[j] - o * n;
+      if (o != 0 && !m.periodic[j] && (unsigned)(pc[j] + o) >= (unsigned)L.np) {
+        loc[j] = o < 0 ? 0 : n - 1;
+        if (j == 0) dup = true;
+        o = 0;
+      }
+      code += (o + 1) * mul;
+      mul *= 3;
     }
     if (!ghost) continue;
-    double val[NV];
-    bool ok = fetch_cell<D>(m, U, l, g, val);
-    if (ok && coarse_only) continue;
-    if (!ok) ok = (l > 0) && prolong_cell<D>(m, U, l, g, val);
-    if (!ok) {
-      err[0] = 1;
-      for (int v = 0; v < NV; ++v) val[v] = __builtin_nan("");
+    const long long sb = sNB[code];
+    if (sb < 0) continue;
+    const double* S = Uin + sb;
+    const int src = box_off<D>(full, loc[0] + NG, loc[1] + NG, loc[2] + NG);
+    double2 x[NV];
+    if (dup) {
+#pragma unroll
+      for (int v = 0; v < NV; ++v) x[v].x = x[v].y = S[v * vs + src];
+    } else {
+#pragma unroll
+      for (int v = 0; v < NV; ++v) x[v] = *reinterpret_cast<const double2*>(S + v * vs + src);
     }
 #pragma unroll
-    for (int v = 0; v < NV; ++v) P[v * vs + idx] = val[v];
+    for (int v = 0; v < NV; ++v) {
+      double* to = P + v * vs + idx;
+      if constexpr (D == 3) {
+        // ghosts are the larger part of a 3D box: stored past the L2, which
+        // keeps the interiors for the neighbours (312 to 291 us, and the
+        // prolongation after it 72 to 54 us)
+        typedef double d2 __attribute__((ext_vector_type(2)));
+        const d2 y = {x[v].x, x[v].y};
+        __builtin_nontemporal_store(y, reinterpret_cast<d2*>(to));
+      } else {
+        *reinterpret_cast<double2*>(to) = x[v];
+      }
+    }
   }
+}
+
+template <int D>
+__global__ __launch_bounds__(256) void k_fill_copy(DevMesh m, const double* __restrict__ Uin,
+                                                   double* __restrict__ U,
+                                                   const int* __restrict__ list, int count) {
+  __shared__ long long sNB[27];
+  const int item = xcd_chunk<kCopyChunk>(count);
+  if (item >= 0) copy_ghosts<D, 256>(m, Uin, U, list[item], sNB);
 }
 
 // Ghost cells without a same-level source: one work item per (leaf, ghost
@@ -104,7 +148,7 @@ __device__ __forceinline__ void fill_cf_region(const DevMesh& m, double* __restr
     if constexpr (D >= 2) c[1] = start[1] + (idx / ext[0]) % ext[1];
     if constexpr (D >= 3) c[2] = start[2] + idx / (ext[0] * ext[1]);
     int g[3] = {0, 0, 0};
-    for (int j = 0; j < D; ++j) g[j] = bc_map(pc[j] * n + c[j], L.cells, m.periodic[j]);
+    for (int j = 0; j < D; ++j) g[j] = bc_near(pc[j] * n + c[j], L.cells, m.periodic[j]);
     double val[NV];
     const bool ok = (l > 0) && prolong_cell<D>(m, U, l, g, val);
     if (!ok) {
@@ -144,143 +188,97 @@ __global__ __launch_bounds__(NT) void k_fill_cf(DevMesh m,
 // those of the per-fine-cell fill.  A block takes G consecutive regions and
 // spreads all their coarse cells over its lanes: a 3D region covers as few
 // as 8 coarse cells (a corner).
+template <int G>
+struct RegionGroup {
+  int pid[G], code[G], lev[G], pc[G][3], pre[G + 1];
+};
+
 template <int D, int NT, int G>
 __device__ __forceinline__ void fill_cf_coarse_group(const DevMesh& m, double* __restrict__ U,
                                                      const int* __restrict__ list, int count,
                                                      int first, int* __restrict__ err,
-                                                     int* s_pid, int* s_code, int* s_pre) {
-  constexpr int NV = D + 2, NS = 2 * D + 1, NF = 1 << D;
-  if (threadIdx.x < G) {
-    const int i = first + (int)threadIdx.x;
-    int pid = -1, code = 0, cnt = 0;
-    if (i < count) {
-      pid = list[2 * i];
-      code = list[2 * i + 1];
-      const int n = m.lv[m.level[pid]].n;
+                                                     RegionGroup<G>& s) {
+  constexpr int NV = D + 2;
+  static_assert(G <= 64 && (G & (G - 1)) == 0, "one wave scans the group's counts");
+  if (threadIdx.x < 64) {
+    const int t = threadIdx.x, i = first + t;
+    int cnt = 0;
+    if (t < G && i < count) {
+      const int pid = list[2 * i], code = list[2 * i + 1];
+      const int l = m.level[pid];
+      const int n = m.lv[l].n;
       cnt = 1;
+#pragma unroll
       for (int j = 0; j < D; ++j) {
         const int r = (j == 0 ? code : (j == 1 ? code / 3 : code / 9)) % 3 - 1;
         cnt *= (r == 0 ? n : NG) / 2;
+        s.pc[t][j] = m.coord[3 * pid + j];
       }
+      s.pid[t] = pid;
+      s.code[t] = code;
+      s.lev[t] = l;
     }
-    s_pid[threadIdx.x] = pid;
-    s_code[threadIdx.x] = code;
-    s_pre[threadIdx.x + 1] = cnt;
+    int sum = cnt;
+#pragma unroll
+    for (int d = 1; d < G; d *= 2) {
+      const int o = __shfl_up(sum, d);
+      if (t >= d) sum += o;
+    }
+    if (t < G) s.pre[t + 1] = sum;
+    if (t == 0) s.pre[0] = 0;
   }
   __syncthreads();
-  if (threadIdx.x == 0) {
-    s_pre[0] = 0;
-    for (int i = 0; i < G; ++i) s_pre[i + 1] += s_pre[i];
-  }
-  __syncthreads();
-  const int total = s_pre[G];
+  const int total = s.pre[G];
   for (int idx = threadIdx.x; idx < total; idx += NT) {
-    int it = 0;
-    while (idx >= s_pre[it + 1]) ++it;
-    const int pid = s_pid[it], code = s_code[it];
-    const int local = idx - s_pre[it];
-    const int l = m.level[pid];
-    const LevelC& L = m.lv[l];
-    const int n = L.n, full = L.full;
-    const int vs = var_stride<D>(full);
-    double* P = U + patch_base(m, pid, l);
-    int start[3] = {0, 0, 0}, half[3] = {1, 1, 1};
-    for (int j = 0; j < D; ++j) {
-      const int r = (j == 0 ? code : (j == 1 ? code / 3 : code / 9)) % 3 - 1;
-      start[j] = r < 0 ? -NG : (r == 0 ? 0 : n);
-      half[j] = (r == 0 ? n : NG) / 2;
-    }
-    const int k[3] = {local % half[0], (local / half[0]) % half[1], local / (half[0] * half[1])};
-    int c0[3] = {0, 0, 0}, gc[3] = {0, 0, 0};
-    double sg[3][2] = {{0.0, 0.0}, {0.0, 0.0}, {0.0, 0.0}};
-    for (int j = 0; j < D; ++j) {
-      const int pcj = m.coord[3 * pid + j];
-      c0[j] = start[j] + 2 * k[j];
-      const int g0 = bc_map(pcj * n + c0[j], L.cells, m.periodic[j]);
-      const int g1 = bc_map(pcj * n + c0[j] + 1, L.cells, m.periodic[j]);
-      gc[j] = g0 >> 1;
-      sg[j][0] = (g0 & 1) ? 1.0 : -1.0;
-      sg[j][1] = (g1 & 1) ? 1.0 : -1.0;
-    }
-    const int lc = l > 0 ? l - 1 : 0;
-    const LevelC& C = m.lv[lc];
-    const long long vsc = var_stride<D>(C.full);
-    int pids[NS];
-    long long offs[NS];
+    int it = 0;  // the region with pre[it] <= idx < pre[it + 1]
 #pragma unroll
-    for (int s = 0; s < NS; ++s) {
-      int gs[3] = {gc[0], gc[1], gc[2]};
-      if (s > 0) {
-        const int j = (s - 1) >> 1;
-        gs[j] = bc_map(gc[j] + (((s - 1) & 1) ? -1 : 1), C.cells, m.periodic[j]);
-      }
-      int q[3] = {0, 0, 0}, c[3] = {0, 0, 0};
+    for (int d = G / 2; d > 0; d /= 2)
+      if (idx >= s.pre[it + d]) it += d;
+    const int pid = s.pid[it], code = s.code[it], lev = s.lev[it];
+    const int local = idx - s.pre[it];
+    // one pass per level among the wave's lanes (nearly always one: the list
+    // is in level order), so that the level's constants are scalar
+    for (bool done = false; !done;) {
+      const int l = __builtin_amdgcn_readfirstlane(lev);
+      if (lev != l) continue;
+      done = true;
+      const LevelC& L = m.lv[l];
+      const int n = L.n, full = L.full;
+      double* P = U + patch_base(m, pid, l);
+      int start[3] = {0, 0, 0}, half[3] = {1, 1, 1};
+#pragma unroll
       for (int j = 0; j < D; ++j) {
-        q[j] = gs[j] / C.n;
-        c[j] = gs[j] - q[j] * C.n;
+        const int r = (j == 0 ? code : (j == 1 ? code / 3 : code / 9)) % 3 - 1;
+        start[j] = r < 0 ? -NG : (r == 0 ? 0 : n);
+        half[j] = (r == 0 ? n : NG) / 2;
       }
-      pids[s] = l > 0 ? map_at<D>(m, lc, q) : -1;
-      offs[s] = box_off<D>(C.full, c[0] + NG, c[1] + NG, c[2] + NG);
-    }
-    bool found = true;
+      // half is n / 2 or 2 in every direction
+      auto by_half = [&](int v, int h) { return h == NG / 2 ? v / (NG / 2) : div_by(2 * v, n, L.n_mul); };
+      const int r0 = D >= 2 ? by_half(local, half[0]) : 0;
+      const int r1 = D >= 3 ? by_half(r0, half[1]) : 0;
+      const int k[3] = {local - r0 * half[0], D >= 2 ? r0 - r1 * half[1] : 0, r1};
+      int c0[3] = {0, 0, 0}, gc[3] = {0, 0, 0};
+      double sg[3][2] = {{0.0, 0.0}, {0.0, 0.0}, {0.0, 0.0}};
 #pragma unroll
-    for (int s = 0; s < NS; ++s) found &= pids[s] >= 0;
-    if (!found) {
-      err[0] = 1;
-      for (int f = 0; f < NF; ++f) {
-        const int off = box_off<D>(full, c0[0] + (f & 1) + NG, c0[1] + ((f >> 1) & 1) + NG,
-                                         c0[2] + ((f >> 2) & 1) + NG);
-#pragma unroll
-        for (int v = 0; v < NV; ++v) P[v * vs + off] = __builtin_nan("");
+      for (int j = 0; j < D; ++j) {
+        c0[j] = start[j] + 2 * k[j];
+        const int g = s.pc[it][j] * n + c0[j];
+        const int g0 = bc_near(g, L.cells, m.periodic[j]);
+        const int g1 = bc_near(g + 1, L.cells, m.periodic[j]);
+        gc[j] = g0 >> 1;
+        sg[j][0] = (g0 & 1) ? 1.0 : -1.0;
+        sg[j][1] = (g1 & 1) ? 1.0 : -1.0;
       }
-      continue;
-    }
-    double val[NS][NV];
-#pragma unroll
-    for (int s = 0; s < NS; ++s) {
-      const double* Q = U + patch_base(m, pids[s], lc) + offs[s];
-#pragma unroll
-      for (int v = 0; v < NV; ++v) val[s][v] = Q[v * vsc];
-    }
-    const double* phi = val[0];
-    double sl[D][NV];
-#pragma unroll
-    for (int j = 0; j < D; ++j) {
-#pragma unroll
-      for (int v = 0; v < NV; ++v) {
-        const double a = val[1 + 2 * j][v] - phi[v];
-        const double b = phi[v] - val[2 + 2 * j][v];
-        const bool same = (a > 0.0 && b > 0.0) || (a < 0.0 && b < 0.0);
-        const double mag = fmin(fmin(2.0 * fabs(a), 2.0 * fabs(b)), 0.5 * fabs(a + b));
-        sl[j][v] = same ? copysign(mag, a) : 0.0;
-      }
-    }
-    bool bad = false;
-    for (int c = 0; c < NF; ++c) {
-      double ch[NV];
-#pragma unroll
-      for (int v = 0; v < NV; ++v) {
-        double x = phi[v];
-        for (int j = 0; j < D; ++j) x = x + (((c >> j) & 1) ? 0.25 : -0.25) * sl[j][v];
-        ch[v] = x;
-      }
-      const double p = pressure_exact<D>(ch, m.gm1);
-      if (!(ch[0] > 0.0 && p > 0.0)) bad = true;
-    }
-    for (int f = 0; f < NF; ++f) {
-      const int off = box_off<D>(full, c0[0] + (f & 1) + NG, c0[1] + ((f >> 1) & 1) + NG,
-                                       c0[2] + ((f >> 2) & 1) + NG);
-#pragma unroll
-      for (int v = 0; v < NV; ++v) {
-        double x = phi[v];
-        for (int j = 0; j < D; ++j) x = x + (sg[j][(f >> j) & 1] * 0.25) * (bad ? 0.0 : sl[j][v]);
-        P[v * vs + off] = x;
-      }
+      double phi[NV] = {}, sl[D][NV] = {};
+      const bool ok = l > 0 && prolong_coarse<D>(m, U, l - 1, gc, phi, sl);
+      if (!ok) err[0] = 1;
+      store_children<D>(P, var_stride<D>(full), full,
+                        box_off<D>(full, c0[0] + NG, c0[1] + NG, c0[2] + NG), ok, phi, sl, sg);
     }
   }
 }
 
-// Block b takes the group of G regions starting at G b.  With `dir` (batched
+// A block takes a group of G consecutive regions.  With `dir` (batched
 // launches) the list and count are read at run time.
 template <int D, int NT, int G>
 __global__ __launch_bounds__(NT) void k_fill_cf_coarse(DevMesh m,
@@ -288,14 +286,13 @@ __global__ __launch_bounds__(NT) void k_fill_cf_coarse(DevMesh m,
                                                        const int* __restrict__ list, int count,
                                                        const int* __restrict__ dir,
                                                        int* __restrict__ err) {
-  __shared__ int s_pid[G], s_code[G], s_pre[G + 1];
+  __shared__ RegionGroup<G> s;
   if (dir) {
     list += dir[0];
     count = dir[1];
   }
   const int first = (int)blockIdx.x * G;
-  if (first < count)
-    fill_cf_coarse_group<D, NT, G>(m, U, list, count, first, err, s_pid, s_code, s_pre);
+  if (first < count) fill_cf_coarse_group<D, NT, G>(m, U, list, count, first, err, s);
 }
 
 // ---------------------------------------------------------------------------
@@ -865,37 +862,41 @@ __global__ void k_requests(DevMesh m, const uint8_t* __restrict__ has_tag,
   if (coarsen) coarsen[pid] = cq;
 }
 
-// prolongation of the interiors of newly created patches of one level
-template <int D>
-__global__ __launch_bounds__(256) void k_prolong_new(DevMesh m, double* __restrict__ U,
-                                                     const int* __restrict__ list, int count,
-                                                     int* __restrict__ err) {
+// prolongation of the interiors of newly created patches of one level, by
+// coarse cell: one thread forms the limited slopes of a coarse cell and its
+// 2^D children (84.7 us for 3456 patches of 8^3 with a thread per fine cell,
+// 30.3 us now)
+template <int D, int NT>
+__global__ __launch_bounds__(NT) void k_prolong_new(DevMesh m, const double* __restrict__ Uin,
+                                                    double* __restrict__ U,
+                                                    const int* __restrict__ list, int count,
+                                                    int* __restrict__ err) {
   constexpr int NV = D + 2;
   if ((int)blockIdx.x >= count) return;
   const int pid = list[blockIdx.x];
   const int l = m.level[pid];
   const LevelC& L = m.lv[l];
-  const int n = L.n;
+  const int n = L.n, h = n / 2;
   double* P = U + patch_base(m, pid, l);
   const int vs = var_stride<D>(L.full);
-  const int pc[3] = {m.coord[3 * pid], m.coord[3 * pid + 1], m.coord[3 * pid + 2]};
-  int total = n;
-  if constexpr (D >= 2) total *= n;
-  if constexpr (D >= 3) total *= n;
-  for (int idx = threadIdx.x; idx < total; idx += blockDim.x) {
-    int c[3] = {idx % n, 0, 0};
-    if constexpr (D >= 2) c[1] = (idx / n) % n;
-    if constexpr (D >= 3) c[2] = idx / (n * n);
-    int g[3] = {0, 0, 0};
-    for (int j = 0; j < D; ++j) g[j] = pc[j] * n + c[j];
-    double val[NV];
-    if (!prolong_cell<D>(m, U, l, g, val)) {
-      err[0] = 1;
-      for (int v = 0; v < NV; ++v) val[v] = __builtin_nan("");
-    }
-    const int off = box_off<D>(L.full, c[0] + NG, c[1] + NG, c[2] + NG);
+  const double sg[3][2] = {{-1.0, 1.0}, {-1.0, 1.0}, {-1.0, 1.0}};
+  int total = h;
+  if constexpr (D >= 2) total *= h;
+  if constexpr (D >= 3) total *= h;
+  for (int idx = threadIdx.x; idx < total; idx += NT) {
+    // 2 idx / n = idx / h
+    const int r = D >= 2 ? div_by(2 * idx, n, L.n_mul) : 0;
+    const int z = D >= 3 ? div_by(2 * r, n, L.n_mul) : 0;
+    const int k[3] = {idx - r * h, D >= 2 ? r - z * h : 0, z};
+    int gc[3] = {0, 0, 0};
 #pragma unroll
-    for (int v = 0; v < NV; ++v) P[v * vs + off] = val[v];
+    for (int j = 0; j < D; ++j) gc[j] = m.coord[3 * pid + j] * h + k[j];
+    double phi[NV] = {}, sl[D][NV] = {};
+    const bool ok = prolong_coarse<D>(m, Uin, l - 1, gc, phi, sl);
+    if (!ok) err[0] = 1;
+    store_children<D>(P, vs, L.full,
+                      box_off<D>(L.full, 2 * k[0] + NG, 2 * k[1] + NG, 2 * k[2] + NG), ok, phi, sl,
+                      sg);
   }
 }
 
@@ -954,16 +955,17 @@ __global__ __launch_bounds__(256) void k_check(DevMesh m, const double* __restri
     else hipLaunchKernelGGL(KERNEL<3>, GRID, BLOCK, 0, STREAM, __VA_ARGS__);             \
   } while (0)
 
-// Regions per block of the coarse/fine fill launch for this mesh (the
-// kernel choice of fill_cf below).
+// Whether the coarse/fine fill launch of this mesh works by coarse cell, and
+// its regions per block (the kernel choice of fill_cf below).
+static bool fill_cf_by_coarse(const DevMesh& m) {
+  int nmax = 0;
+  for (int l = 1; l < m.nlev; ++l) nmax = std::max(nmax, m.lv[l].n);
+  return m.dim == 3 || (m.dim == 2 && nmax > 16);
+}
+
 static int fill_cf_per_block(const DevMesh& m) {
-  if (m.dim == 1) return 1;
-  if (m.dim == 2) {
-    int nmax = 0;
-    for (int l = 1; l < m.nlev; ++l) nmax = std::max(nmax, m.lv[l].n);
-    return nmax <= 16 ? 1 : 2;
-  }
-  return 4;
+  if (!fill_cf_by_coarse(m)) return 1;
+  return m.dim == 2 ? 2 : 4;
 }
 
 int Kernels::fill_cf_grid(const DevMesh& m, int count) {
@@ -975,46 +977,46 @@ void Kernels::fill_cf(const DevMesh& m, double* U, const int* list, int count, c
                       int* err, hipStream_t s) {
   if (count <= 0) return;
   // one block per region (group of regions)
-  auto launch = [&](auto kern, int threads, int per_block) {
-    const int nb = (count + per_block - 1) / per_block;
-    hipLaunchKernelGGL(kern, dim3(nb), dim3(threads), 0, s, m, U, list, count, dir, err);
+  auto launch = [&](auto kern, int threads) {
+    hipLaunchKernelGGL(kern, dim3(fill_cf_grid(m, count)), dim3(threads), 0, s, m, U, list, count,
+                       dir, err);
   };
   switch (m.dim) {
-    case 1: launch(k_fill_cf<1, 64>, 64, 1); break;
+    case 1: launch(k_fill_cf<1, 64>, 64); break;
     case 2: {
       // refined patches of edge 16 or less: one fine cell per thread (a side
       // region is 4 n = 64 cells); wider ones: by coarse cell, two regions
       // per wave (a side region of a 32^2 patch is 64 coarse cells).  Level 0
       // has no prolonged ghosts.  Per launch on a 3-level 2D hierarchy of
-      // base 256^2 with 32/16/16 patches: 7.2 us per fine cell, 10.1 / 8.5 /
-      // 11.1 us by coarse cell with 1 / 2 / 8 regions per block; on a
-      // 5-level one of base 512^2 with 32^2 patches: 30.3 us per fine cell
-      // (128 threads), 34.1 / 25.4 us by coarse cell with 1 / 2 regions per
-      // block.
-      int nmax = 0;
-      for (int l = 1; l < m.nlev; ++l) nmax = std::max(nmax, m.lv[l].n);
-      if (nmax <= 16)
-        launch(k_fill_cf<2, 64>, 64, 1);
+      // base 256^2 with 32/16/16 patches (484 side regions): 5.2 us per fine
+      // cell, 5.6 us by coarse cell; on a 5-level one of base 512^2 with 32^2
+      // patches (1808): 11.0 us by coarse cell with 2 regions per wave, 10.9
+      // with 4 per two waves, 12.9 with 4 per wave.
+      if (fill_cf_by_coarse(m))
+        launch(k_fill_cf_coarse<2, 64, 2>, 64);
       else
-        launch(k_fill_cf_coarse<2, 64, 2>, 64, 2);
+        launch(k_fill_cf<2, 64>, 64);
       break;
     }
     default:
-      // one thread per coarse cell, 4 regions per wave: a region of an 8^3
-      // patch covers 8, 16 or 32 coarse cells and one of a 16^3 patch 8 to
-      // 128 (per launch on a four-level 3D hierarchy of base 256^3 with
-      // 32/16/16/8 patches: 2.12 ms with 4 regions per block, 2.19 with 8,
-      // 2.27 with 16)
-      launch(k_fill_cf_coarse<3, 64, 4>, 64, 4);
+      // one thread per coarse cell, 4 regions per two waves: a side region of
+      // an 8^3 patch covers 32 coarse cells and one of a 16^3 patch 128 (side
+      // regions of four-level hierarchies of base 64^3 with 32/16/16/8 patches:
+      // 114 us with 4 regions per 128 threads, 135 with 4 per 64, 118 with 8
+      // per 256, 145 with 8 per 128; 16.3 / 23.3 / 20.9 / 24.9 us on a two-level
+      // one of 12^3 patches)
+      launch(k_fill_cf_coarse<3, 128, 4>, 128);
       break;
   }
 }
 
-void Kernels::fill(const DevMesh& m, double* U, const int* list, int count, int* err,
-                   bool coarse_only, hipStream_t s) {
-  if (count <= 0) return;
-  AMR_DISPATCH_DIM(m.dim, k_fill, dim3(count), dim3(256), s, m, U, list, count, err,
-                   coarse_only ? 1 : 0);
+void Kernels::fill(const DevMesh& m, double* U, const int* list, int count, const int* regions,
+                   int nregions, int* err, hipStream_t s) {
+  const int group = kXcds * kCopyChunk;  // blocks per group of chunks (xcd_chunk)
+  if (count > 0)
+    AMR_DISPATCH_DIM(m.dim, k_fill_copy, dim3((count + group - 1) / group * group), dim3(256), s, m, U,
+                     U, list, count);
+  fill_cf(m, U, regions, nregions, nullptr, err, s);
 }
 
 void Kernels::reflux(const DevMesh& m, int mode, double* out, const double* fr,
@@ -1131,7 +1133,12 @@ void Kernels::requests(const DevMesh& m, const uint8_t* has_tag, const uint8_t* 
 void Kernels::prolong_new(const DevMesh& m, double* U, const int* list, int count, int* err,
                           hipStream_t s) {
   if (count <= 0) return;
-  AMR_DISPATCH_DIM(m.dim, k_prolong_new, dim3(count), dim3(256), s, m, U, list, count, err);
+  // a new patch of 8^3 has 64 coarse cells, one wave's worth
+  switch (m.dim) {
+    case 1: k_prolong_new<1, 64><<<count, 64, 0, s>>>(m, U, U, list, count, err); break;
+    case 2: k_prolong_new<2, 64><<<count, 64, 0, s>>>(m, U, U, list, count, err); break;
+    default: k_prolong_new<3, 64><<<count, 64, 0, s>>>(m, U, U, list, count, err); break;
+  }
 }
 
 void Kernels::count_nonzero(const uint8_t* a, int n, int* out, hipStream_t s) {

@@ -306,34 +306,6 @@ __device__ __forceinline__ void node_store(const DevMesh& m, const double* u, do
 }
 
 
-// Same-level patches around the tile's patch, by offset code
-// (o0+1) + 3 (o1+1) + 9 (o2+1), o in {-1,0,1}^D (periodic wrap), as the
-// offsets of their data in the state buffer (-1 where no patch or outside a
-// non-periodic domain), looked up once per block.
-template <int D>
-__device__ __forceinline__ void load_neighbours(const DevMesh& m, int l, const int pc[3],
-                                                long long* sNB) {
-  constexpr int NO = D == 1 ? 3 : (D == 2 ? 9 : 27);
-  const int t = threadIdx.x;
-  if (t < NO) {
-    const int np = m.lv[l].np;
-    int q[3] = {0, 0, 0};
-    bool in = true;
-#pragma unroll
-    for (int j = 0; j < D; ++j) {
-      const int o = (j == 0 ? t : (j == 1 ? t / 3 : t / 9)) % 3 - 1;
-      int v = pc[j] + o;
-      if (v < 0 || v >= np) {
-        if (m.periodic[j]) v = (v + np) % np;
-        else in = false;
-      }
-      q[j] = v;
-    }
-    const int pid = in ? map_at<D>(m, l, q) : -1;
-    sNB[t] = pid >= 0 ? patch_base(m, pid, l) : -1;
-  }
-}
-
 // Conserved values of a node at patch-local cell c (may lie in the halo,
 // at most 4 cells outside the patch): from the patch itself, or by the
 // ghost-fill rule when outside the patch (same-level source from the
