@@ -92,8 +92,9 @@ struct Kernels {
   // ev0/ev1 (optional): events stamped at the dispatch's own start and end.
   // lam_in (stage 1 only, optional): take dt = CFL / *lam_in instead of *dt,
   // write it to *dt_out and clear *lam_next (the slot stage 3 accumulates in)
-  // In the stage modes a tile of the finest level (nlev - 1 >= 1) also
-  // restricts its new values into its parent patch.
+  // In the stage modes a tile of a leaf without coarse/fine faces (level >= 1,
+  // cfmask 0: refluxing does not change it) also restricts its new values into
+  // its parent patch.
   static void stage(const DevMesh& m, int mode, const double* Uin, const double* Un,
                     double* out, double* fr, const int* tiles, int count, const int* dir,
                     const double* dt, bool fuse, unsigned long long* lam_next,
@@ -103,17 +104,16 @@ struct Kernels {
   static void reflux(const DevMesh& m, int mode, double* out, const double* fr,
                      const int* list, int count, const double* dt, double w,
                      unsigned long long* lam_next, hipStream_t s);
-  // refluxing and the restriction of the two finest levels in one launch:
-  // reflux items, level-lup patches with children (plist), level-lup leaves
-  // without coarse/fine faces (slist); lup = finest level - 1
-  // dir (nullable): the directory entries of the three lists, in order;
-  // with it the list pointers are the list buffer, the live counts are read
-  // at run time and nref + npair + nsingle only sizes the grid.
-  // fine_done: the stage kernel has already restricted the finest level.
+  // refluxing and the restriction of level lup = finest - 1 in one launch:
+  // reflux items and level-lup patches with children (plist); the stage kernel
+  // has restricted the leaves without coarse/fine faces, the finest level
+  // among them
+  // dir (nullable): the directory entries of the two lists, in order; with it
+  // the list pointers are the list buffer, the live counts are read at run
+  // time and nref + npair only sizes the grid.
   static void post(const DevMesh& m, int mode, double* out, const double* fr, const int* rlist,
-                   int nref, const int* plist, int npair, const int* slist, int nsingle,
-                   const int* dir, int lup, bool fine_done, const double* dt, double w,
-                   unsigned long long* lam_next, hipStream_t s);
+                   int nref, const int* plist, int npair, const int* dir, int lup,
+                   const double* dt, double w, unsigned long long* lam_next, hipStream_t s);
   static void restrict_level(const DevMesh& m, double* U, const int* list, int count,
                              const int* dir, hipStream_t s);
   static void max_rate(const DevMesh& m, const double* U, const int* list, int count,

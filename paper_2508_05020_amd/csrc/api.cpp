@@ -40,8 +40,8 @@ struct StateError : std::runtime_error {
   } while (0)
 
 // entries of the device list directory
-enum { kDirCf = 0, kDirTiles = 1, kDirReflux = 2, kDirPairs = 3, kDirSingles = 4, kDirCfFace = 5,
-       kDirRestr = 6, kDirEntries = kDirRestr + amr::kMaxLev };
+enum { kDirCf = 0, kDirTiles = 1, kDirReflux = 2, kDirPairs = 3, kDirCfFace = 4, kDirRestr = 5,
+       kDirEntries = kDirRestr + amr::kMaxLev };
 
 }  // namespace
 
@@ -114,7 +114,7 @@ struct amr_hierarchy {
   long long lists_cap = 0;
   // list directory: {offset into d_lists, count} of the lists the step's
   // kernels take (entries kDirCf, kDirTiles, kDirReflux, kDirPairs,
-  // kDirSingles, kDirRestr + level), rewritten with the lists; batched
+  // kDirCfFace, kDirRestr + level), rewritten with the lists; batched
   // launches read it, so a recorded step survives a regrid
   int* d_dir = nullptr;
   int* h_dir = nullptr;  // pinned staging of the directory
@@ -131,9 +131,11 @@ struct amr_hierarchy {
   // cffaces: the face regions of cfregions (all the stage kernel reads;
   // the tagger's dilated box reads the edge and corner regions too)
   amr::ListView all{}, leaves{}, tiles{}, reflux{}, cfregions{}, cffaces{}, cands{};
-  // post-stage restriction of the two finest levels (see Kernels::post)
-  amr::ListView post_pairs{}, post_singles{};
-  amr::ListView restr[amr::kMaxLev]{}, fresh[amr::kMaxLev]{};
+  // post-stage restriction (see Kernels::post): level-(L-2) patches with
+  // children, and per level the patches that the stage kernel has not
+  // restricted itself (with children or coarse/fine faces); restr: all patches
+  amr::ListView post_pairs{};
+  amr::ListView restr[amr::kMaxLev]{}, restr_post[amr::kMaxLev]{}, fresh[amr::kMaxLev]{};
   std::vector<int> last_created;
   // scratch of sync_tables, per parent: all Moore neighbours have children;
   // bit mask (offset codes) of the Moore neighbours with children
@@ -562,20 +564,23 @@ void sync_tables(amr_hierarchy* h, bool full) {
       ++nref;
     }
   }
-  // level-(L-2) patches with children, and level-(L-2) leaves (L-2 >= 1)
-  // without coarse/fine faces
+  // level-(L-2) patches with children (L-2 >= 1)
   const int lup = f.nlev - 2;
   const int pp0 = begin_list();
   for (int pid : order)
-    if (lup >= 0 && f.level[pid] == lup && !f.is_leaf(pid)) L.push_back(pid);
-  const int ps0 = begin_list();
-  {
-    std::vector<uint8_t> has_reflux(f.max_patches, 0);
-    for (int i = r0; i < r0 + 2 * nref; i += 2) has_reflux[L[i]] = 1;
+    if (lup >= 1 && f.level[pid] == lup && !f.is_leaf(pid)) L.push_back(pid);
+  const int pp1 = begin_list();
+  // per level: patches with children or coarse/fine faces
+  std::vector<uint8_t> has_reflux(f.max_patches, 0);
+  for (int i = r0; i < r0 + 2 * nref; i += 2) has_reflux[L[i]] = 1;
+  int rp[amr::kMaxLev + 1] = {};
+  for (int l = 0; l < f.nlev; ++l) {
+    rp[l] = begin_list();
+    if (l == 0) continue;
     for (int pid : order)
-      if (lup >= 1 && f.level[pid] == lup && f.is_leaf(pid) && !has_reflux[pid]) L.push_back(pid);
+      if (f.level[pid] == l && (!f.is_leaf(pid) || has_reflux[pid])) L.push_back(pid);
   }
-  const int ps1 = begin_list();
+  rp[f.nlev] = begin_list();
   int rs[amr::kMaxLev + 1] = {};
   for (int l = 0; l < f.nlev; ++l) {
     rs[l] = begin_list();
@@ -612,10 +617,10 @@ void sync_tables(amr_hierarchy* h, bool full) {
   h->cands = {h->d_lists + k0, t0 - k0};
   h->tiles = {h->d_lists + t0, (r0 - t0) / 2, dd + 2 * kDirTiles};
   h->reflux = {h->d_lists + r0, nref, dd + 2 * kDirReflux};
-  h->post_pairs = {h->d_lists + pp0, ps0 - pp0, dd + 2 * kDirPairs};
-  h->post_singles = {h->d_lists + ps0, ps1 - ps0, dd + 2 * kDirSingles};
+  h->post_pairs = {h->d_lists + pp0, pp1 - pp0, dd + 2 * kDirPairs};
   for (int l = 0; l < f.nlev; ++l) {
-    h->restr[l] = {h->d_lists + rs[l], rs[l + 1] - rs[l], dd + 2 * (kDirRestr + l)};
+    h->restr[l] = {h->d_lists + rs[l], rs[l + 1] - rs[l]};
+    h->restr_post[l] = {h->d_lists + rp[l], rp[l + 1] - rp[l], dd + 2 * (kDirRestr + l)};
     h->fresh[l] = {h->d_lists + ns[l], ns[l + 1] - ns[l]};
   }
   {
@@ -632,8 +637,7 @@ void sync_tables(amr_hierarchy* h, bool full) {
     put(kDirTiles, h->tiles);
     put(kDirReflux, h->reflux);
     put(kDirPairs, h->post_pairs);
-    put(kDirSingles, h->post_singles);
-    for (int l = 0; l < f.nlev; ++l) put(kDirRestr + l, h->restr[l]);
+    for (int l = 0; l < f.nlev; ++l) put(kDirRestr + l, h->restr_post[l]);
     HIP_OK(hipMemcpyAsync(h->d_dir, hd, 2 * kDirEntries * sizeof(int), hipMemcpyHostToDevice,
                           h->stream));
   }
@@ -773,8 +777,8 @@ void stage_fill(amr_hierarchy* h, int buf) {
 
 void do_restrict(amr_hierarchy* h, int buf) {
   for (int l = h->forest.nlev - 1; l >= 1; --l)
-    over_list_dir(h, h->restr[l], 1, kGnRestrict, [&](const int* p, int c, const int* dir) {
-      Kernels::restrict_level(h->dm, h->U[buf], p, c, dir, h->stream);
+    over_list(h, h->restr[l], 1, [&](const int* p, int c) {
+      Kernels::restrict_level(h->dm, h->U[buf], p, c, nullptr, h->stream);
     });
 }
 
@@ -798,18 +802,17 @@ void do_stage(amr_hierarchy* h, int stage, const double* dt,
                    lam_in, dt_out);
   });
   if (h->exec_mode == AMR_EXEC_BATCHED) {
-    // refluxing and the restriction of the two finest levels share a launch;
-    // coarser levels follow, finest first (lists and counts from the list
-    // directory: the three post-stage entries are consecutive)
+    // refluxing and the restriction of level L-2 share a launch; coarser levels
+    // follow, finest first (lists and counts from the list directory: the two
+    // post-stage entries are consecutive)
     const int lup = h->forest.nlev - 2;
     Kernels::post(h->dm, stage, h->U[d], h->fr, h->d_lists, grid_count(h, h->reflux), h->d_lists,
-                  grid_count(h, h->post_pairs), h->d_lists, grid_count(h, h->post_singles),
-                  h->reflux.dir, lup, true, dt, w[stage], stage == 3 ? lam_next : nullptr,
-                  h->stream);
+                  grid_count(h, h->post_pairs), h->reflux.dir, lup, dt, w[stage],
+                  stage == 3 ? lam_next : nullptr, h->stream);
     h->check_launch();
-    note_node(h, kGnPost, kDirReflux, kDirPairs, kDirSingles);
+    note_node(h, kGnPost, kDirReflux, kDirPairs);
     for (int l = lup - 1; l >= 1; --l)
-      over_list_dir(h, h->restr[l], 1, kGnRestrict, [&](const int* p, int c, const int* dir) {
+      over_list_dir(h, h->restr_post[l], 1, kGnRestrict, [&](const int* p, int c, const int* dir) {
         Kernels::restrict_level(h->dm, h->U[d], p, c, dir, h->stream);
       });
   } else {
@@ -1020,8 +1023,8 @@ amr_status amr_create_hierarchy(const amr_config* cfg, const amr_allocator* allo
       for (int l = 0; l < f.nlev; ++l) t += (long long)f.cap[l] * Kernels::tiles_per_patch(v, f.n[l]);
       tiles = std::max(tiles, t);
     }
-    // all, leaves, coarsening candidates, reflux (2), post-stage pairs and
-    // singles, restriction, new patches: 9 per patch; ghost regions and
+    // all, leaves, coarsening candidates, reflux (2), post-stage pairs,
+    // restriction (all, post-stage), new patches: 9 per patch; ghost regions and
     // their faces: 2 per region and patch; tiles: 2 per tile
     const long long regions = ipow(3, cfg->dim) - 1;
     h->lists_cap = 2 * tiles + (9 + 2 * regions + 2 * 2 * cfg->dim) * mp + 64;

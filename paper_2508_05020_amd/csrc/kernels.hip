@@ -316,69 +316,46 @@ __device__ __forceinline__ void face_correct(const DevMesh& m, const double* __r
   const int j = f >> 1, side = f & 1;
   // fine cell column adjacent to the face (periodic wrap on the high side,
   // and on the low side of the domain)
-  int F = 2 * ((j == 0 ? pc[0] : (j == 1 ? pc[1] : pc[2])) * n + (side ? n : 0));
-  int cj;
-  if (side) {
-    F %= Nf;
-    cj = F;
-  } else {
-    if (F == 0) F = Nf;
-    cj = F - 1;
-  }
-  const int fside = side ? 0 : 1;
-  // tangential coordinates of the cell in ascending dimension order (all
-  // indexing below is by compile-time constants; j selects)
-  int tc[2] = {0, 0}, tp[2] = {0, 0};
+  const int F = 2 * ((j == 0 ? pc[0] : (j == 1 ? pc[1] : pc[2])) * n + (side ? n : 0));
+  const int cj = side ? (F == Nf ? 0 : F) : (F == 0 ? Nf : F) - 1;
+  // tangential coordinates in ascending dimension order (all indexing by
+  // compile-time constants; j selects): of the cell, and of its fine sub-faces
+  // 2 g and 2 g + 1, which one fine patch holds (even edges)
+  int t = 0, ft = 0, at = div_by(cj, nf, Fv.n_mul) * (j == 0 ? 1 : (j == 1 ? Fv.np : Fv.np * Fv.np));
 #pragma unroll
   for (int d = 0; d < D; ++d) {
     if (d == j) continue;
-    const int k = d - (d > j ? 1 : 0);
-#pragma unroll
-    for (int kk = 0; kk < 2; ++kk)
-      if (kk == k) {
-        tc[kk] = c[d];
-        tp[kk] = pc[d];
-      }
+    const bool second = d - (d > j ? 1 : 0) == 1;
+    const int g = 2 * (pc[d] * n + c[d]);
+    const int q = div_by(g, nf, Fv.n_mul);
+    t += c[d] * (second ? n : 1);
+    ft += (g - q * nf) * (second ? nf : 1);
+    at += q * (d == 0 ? 1 : (d == 1 ? Fv.np : Fv.np * Fv.np));
   }
-  const int t = (D >= 2 ? tc[0] : 0) + (D >= 3 ? n * tc[1] : 0);
-  double sub[4][NV];
-  constexpr int nsub = 1 << (D - 1);
-  bool ok = true;
-#pragma unroll
-  for (int s = 0; s < nsub; ++s) {
-    int qt[2] = {0, 0}, fl[2] = {0, 0};
-#pragma unroll
-    for (int k = 0; k < D - 1; ++k) {
-      const int gfc = 2 * (tp[k] * n + tc[k]) + ((s >> k) & 1);
-      qt[k] = gfc / nf;
-      fl[k] = gfc - qt[k] * nf;
-    }
-    // fine patch position: normal component cj / nf, tangential ones qt in
-    // ascending dimension order
-    int q[3] = {0, 0, 0};
-#pragma unroll
-    for (int d = 0; d < D; ++d) {
-      const int k = d - (d > j ? 1 : 0);
-      const int qtd = (k == 0) ? qt[0] : qt[1];
-      q[d] = (d == j) ? cj / nf : qtd;
-    }
-    const int fpid = map_at<D>(m, l + 1, q);
-    ok &= fpid >= 0;
-    const double* frf = fr + Fv.fr_off + (long long)((fpid < 0 ? Fv.pid_base : fpid) - Fv.pid_base) * Fv.fr_stride;
-    const int ft = fl[0] + nf * fl[1];
-#pragma unroll
-    for (int v = 0; v < NV; ++v) sub[s][v] = frf[((j * 2 + fside) * NV + v) * nfface + ft];
-  }
+  const int fpid = m.map[Fv.map_off + at];
+  const double* gcp = frc + (j * 2 + side) * NV * nface + t;
+  const double* frf = fr + Fv.fr_off +
+                      (long long)((fpid < 0 ? Fv.pid_base : fpid) - Fv.pid_base) * Fv.fr_stride +
+                      (j * 2 + (side ? 0 : 1)) * NV * nfface + ft;
   const double sgn = side ? 1.0 : -1.0;
 #pragma unroll
   for (int v = 0; v < NV; ++v) {
+    // sub-face pairs as 16-byte loads (every offset is even, as nf is)
+    const double* sub = frf + v * nfface;
     double avg;
-    if constexpr (D == 1) avg = sub[0][v];
-    else if constexpr (D == 2) avg = (sub[0][v] + sub[1][v]) * 0.5;
-    else avg = ((sub[0][v] + sub[1][v]) + (sub[2][v] + sub[3][v])) * 0.25;
-    if (!ok) avg = __builtin_nan("");
-    const double gc = frc[((j * 2 + side) * NV + v) * nface + t];
-    u[v] = fma(coef, sgn * (gc - avg), u[v]);
+    if constexpr (D == 1) {
+      avg = sub[0];
+    } else {
+      const double2 a = *reinterpret_cast<const double2*>(sub);
+      if constexpr (D == 2) {
+        avg = (a.x + a.y) * 0.5;
+      } else {
+        const double2 b = *reinterpret_cast<const double2*>(sub + nf);
+        avg = ((a.x + a.y) + (b.x + b.y)) * 0.25;
+      }
+    }
+    if (fpid < 0) avg = __builtin_nan("");
+    u[v] = fma(coef, sgn * (gcp[v * nface] - avg), u[v]);
   }
 }
 
@@ -412,13 +389,17 @@ __device__ __forceinline__ void reflux_item(const DevMesh& m, int mode, double* 
     return cj == ((g & 1) ? n - 1 : 0);
   };
   unsigned long long best = 0ull;
-  for (int it = threadIdx.x; it < 2 * D * nface; it += NT) {
-    const int f = it / nface, t = it - f * nface;
-    if (!(mask & (1 << f))) continue;
-    const int j = f >> 1;
-    // cell on face f: normal coordinate 0 or n-1, tangential ones from t in
-    // ascending dimension order
-    const int t0 = (D >= 2) ? t % n : 0, t1 = (D >= 3) ? t / n : 0;
+  // one item per cell of a masked face (a front crosses one to three of them)
+  const int items = __popc(mask) * nface;
+  for (int it = threadIdx.x; it < items; it += NT) {
+    const int row = D >= 2 ? div_by(it, n, L.n_mul) : it;
+    const int nth = D >= 3 ? div_by(row, n, L.n_mul) : row;
+    int left = mask;
+    for (int k = 0; k < nth; ++k) left &= left - 1;
+    const int f = __ffs(left) - 1, j = f >> 1;
+    // cell on face f: normal coordinate 0 or n-1, tangential ones in ascending
+    // dimension order
+    const int t0 = D >= 2 ? it - row * n : 0, t1 = D >= 3 ? row - nth * n : 0;
     int c[3] = {0, 0, 0};
 #pragma unroll
     for (int d = 0; d < D; ++d) {
@@ -470,9 +451,10 @@ __device__ __forceinline__ void restrict_cell(const DevMesh& m, double* __restri
   const double* Pc = U + patch_base(m, cpid, lf);
   double* Pp = U + patch_base(m, ppid, lf - 1);
   const long long vsf = var_stride<D>(F.full), vsc = var_stride<D>(C.full);
-  const int a = idx % h;
-  const int b = D >= 2 ? (idx / h) % h : 0;
-  const int c = D >= 3 ? idx / (h * h) : 0;
+  // h = F.n / 2: idx / h = 2 idx / F.n
+  const int row = D >= 2 ? div_by(2 * idx, F.n, F.n_mul) : 0;
+  const int c = D >= 3 ? div_by(2 * row, F.n, F.n_mul) : 0;
+  const int a = idx - row * h, b = D >= 2 ? row - c * h : 0;
   const long long dst = box_off<D>(C.full, o[0] + a + NG, o[1] + b + NG, o[2] + c + NG);
 #pragma unroll
   for (int v = 0; v < NV; ++v) {
@@ -515,22 +497,6 @@ __device__ __forceinline__ void restrict_patch(const DevMesh& m, double* __restr
     restrict_cell<D>(m, U, cpid, ppid, lf, h, idx);
 }
 
-// restriction of every child of ppid into it, all children's covered cells in
-// one loop over the block (children share their level and edge)
-template <int D>
-__device__ __forceinline__ void restrict_children(const DevMesh& m, double* __restrict__ U,
-                                                  int ppid) {
-  const int nc = m.nchild[ppid];
-  if (nc <= 0) return;
-  const int lf = m.level[ppid] + 1;
-  const int h = m.lv[lf].n / 2;
-  const int per = covered_cells<D>(h);
-  for (int idx = threadIdx.x; idx < nc * per; idx += blockDim.x) {
-    const int k = idx / per;
-    restrict_cell<D>(m, U, m.child[(long long)ppid * m.maxc + k], ppid, lf, h, idx - k * per);
-  }
-}
-
 template <int D>
 __global__ __launch_bounds__(256) void k_restrict(DevMesh m,
                                                   double* __restrict__ U,
@@ -543,25 +509,35 @@ __global__ __launch_bounds__(256) void k_restrict(DevMesh m,
   if ((int)blockIdx.x < count) restrict_patch<D>(m, U, list[blockIdx.x]);
 }
 
-// After a stage, in one launch: refluxing and the restriction of the two
-// finest levels, L-1 into L-2 and L-2 into L-3 (when L-2 >= 1).  Blocks:
-//  [0, nref)            reflux items (pid, mask); a level-(L-2) item then
-//                       restricts its (corrected) patch into its parent;
-//  [nref, +npair)       level-(L-2) patches with children: restrict every
-//                       child into the patch, then the patch into its parent;
-//  [.., +nsingle)       level-(L-2) leaves without coarse/fine faces:
-//                       restrict into the parent.
-// Each block's second restriction reads only what the same block wrote
+// After a stage, in one launch: refluxing, and the restriction of level L-2
+// into L-3 (when lup = L-2 >= 1) where the stage kernel, which restricts every
+// leaf without coarse/fine faces, has not done it.  Blocks:
+//  [0, nref)       reflux items (pid, mask); a level-(L-2) item then restricts
+//                  its (corrected) patch into its parent;
+//  [nref, +npair)  level-(L-2) patches with children (whose values the stage
+//                  kernel has restricted into them): restrict into the parent.
+// A block's restriction after refluxing reads only what the same block wrote
 // (block barrier between); the blocks touch disjoint cells otherwise:
-// refluxing changes leaf cells, restriction writes non-leaf cells.
+// refluxing changes leaf cells, restriction writes non-leaf cells.  With
+// `dir` (batched launches) the lists and their counts are read at run time
+// from their directory entries, in order; rlist is then the list buffer.
 template <int D, int NT>
-__device__ __forceinline__ void post_block(const DevMesh& m, int mode, double* __restrict__ out,
-                                           const double* __restrict__ fr,
-                                           const int* __restrict__ rlist, int nref,
-                                           const int* __restrict__ plist, int npair,
-                                           const int* __restrict__ slist, int nsingle, int lup,
-                                           int fine_done, const double* __restrict__ dtp, double w,
-                                           unsigned long long* __restrict__ lam_next, int b) {
+__global__ __launch_bounds__(NT) void k_post(DevMesh m, int mode,
+                                             double* __restrict__ out,
+                                             const double* __restrict__ fr,
+                                             const int* __restrict__ rlist, int nref,
+                                             const int* __restrict__ plist, int npair,
+                                             const int* __restrict__ dir, int lup,
+                                             const double* __restrict__ dtp, double w,
+                                             unsigned long long* __restrict__ lam_next) {
+  if (dir) {
+    const int* buf = rlist;
+    rlist = buf + dir[0];
+    nref = dir[1];
+    plist = buf + dir[2];
+    npair = dir[3];
+  }
+  const int b = blockIdx.x;
   if (b < nref) {
     reflux_item<D, NT>(m, mode, out, fr, rlist, b, dtp, w, lam_next);
     const int pid = rlist[2 * b];
@@ -570,45 +546,8 @@ __device__ __forceinline__ void post_block(const DevMesh& m, int mode, double* _
       restrict_patch<D>(m, out, pid);
     }
   } else if (b - nref < npair) {
-    const int pid = plist[b - nref];
-    // the stage kernel has restricted the finest level (the children) itself
-    // unless the launch says otherwise
-    if (!fine_done) {
-      restrict_children<D>(m, out, pid);
-      __syncthreads();
-    }
-    if (lup >= 1) restrict_patch<D>(m, out, pid);
-  } else if (b - nref - npair < nsingle) {
-    restrict_patch<D>(m, out, slist[b - nref - npair]);
+    restrict_patch<D>(m, out, plist[b - nref]);
   }
-}
-
-
-// One block per block index.  With `dir` (batched launches) the three lists
-// and their counts are read at run time from their directory entries.
-template <int D, int NT>
-__global__ __launch_bounds__(NT) void k_post(DevMesh m, int mode,
-                                             double* __restrict__ out,
-                                             const double* __restrict__ fr,
-                                             const int* __restrict__ rlist, int nref,
-                                             const int* __restrict__ plist, int npair,
-                                             const int* __restrict__ slist, int nsingle,
-                                             const int* __restrict__ dir,
-                                             int lup, int fine_done,
-                                             const double* __restrict__ dtp, double w,
-                                             unsigned long long* __restrict__ lam_next) {
-  if (dir) {
-    // the three lists' directory entries, in order; rlist is the list buffer
-    const int* buf = rlist;
-    rlist = buf + dir[0];
-    nref = dir[1];
-    plist = buf + dir[2];
-    npair = dir[3];
-    slist = buf + dir[4];
-    nsingle = dir[5];
-  }
-  post_block<D, NT>(m, mode, out, fr, rlist, nref, plist, npair, slist, nsingle, lup, fine_done,
-                    dtp, w, lam_next, blockIdx.x);
 }
 
 // ---------------------------------------------------------------------------
@@ -1031,15 +970,14 @@ void Kernels::reflux(const DevMesh& m, int mode, double* out, const double* fr,
 }
 
 void Kernels::post(const DevMesh& m, int mode, double* out, const double* fr,
-                   const int* rlist, int nref, const int* plist, int npair, const int* slist,
-                   int nsingle, const int* dir, int lup, bool fine_done, const double* dt,
-                   double w, unsigned long long* lam_next, hipStream_t s) {
-  const int nb = nref + npair + nsingle;
+                   const int* rlist, int nref, const int* plist, int npair, const int* dir,
+                   int lup, const double* dt, double w, unsigned long long* lam_next,
+                   hipStream_t s) {
+  const int nb = nref + npair;
   if (nb <= 0) return;
   auto launch = [&](auto kern, int threads) {
     hipLaunchKernelGGL(kern, dim3(nb), dim3(threads), 0, s, m, mode, out, fr, rlist, nref,
-                       plist, npair, slist, nsingle, dir, lup, fine_done ? 1 : 0, dt, w,
-                       lam_next);
+                       plist, npair, dir, lup, dt, w, lam_next);
   };
   switch (m.dim) {
     case 1: launch(k_post<1, 64>, 64); break;
@@ -1058,7 +996,8 @@ void Kernels::restrict_level(const DevMesh& m, double* U, const int* list, int c
   };
   switch (m.dim) {
     case 1: launch(k_restrict<1>, 64); break;
-    case 2: launch(k_restrict<2>, 64); break;
+    // 2D: a 32^2 patch covers 256 parent cells
+    case 2: launch(k_restrict<2>, 256); break;
     default: launch(k_restrict<3>, 256); break;
   }
 }

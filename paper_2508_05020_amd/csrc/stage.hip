@@ -1001,12 +1001,12 @@ __device__ __forceinline__ void stage_both(const DevMesh& m, double* __restrict_
 
 // One (pid, tile) work item: the whole RHS of the tile and its stage
 // combination; `best` collects the CFL rate bits of the item's cells.
-// Restriction of a finest-level tile into its parent patch, from the new
-// values of its cells (sR: variable v of tile cell i at sR[v NCELL + i]):
-// each parent cell is the mean of its 2^D children, summed as the
-// post-stage restriction sums them (x pairs first, then y, then z).  The
-// finest level is never the coarse side of a coarse/fine face, so its values
-// are final once the stage kernel has written them.  SERIAL: one variable
+// Restriction of a tile into its parent patch, from the new values of its
+// cells (sR: variable v of tile cell i at sR[v NCELL + i]): each parent cell
+// is the mean of its 2^D children, summed as the post-stage restriction sums
+// them (x pairs first, then y, then z).  For patches that are not the coarse
+// side of a coarse/fine face: their values are final once the stage kernel
+// has written them.  SERIAL: one variable
 // at a time (unrolled, the reads of all variables are issued at once and can
 // take more registers than the primitive schemes' kernels have).
 template <int D, int TX, int TY, int TZ, int NT, bool SERIAL>
@@ -1187,11 +1187,12 @@ __device__ __forceinline__ void stage_item(const DevMesh& m, int mode,
   // next step's CFL rate from the final leaf values; cells on coarse/fine
   // faces are left to the flux-correction kernel, which changes them
   const bool want_rate = lam_next != nullptr && mode == kModeStage3;
-  const int fmask = want_rate ? cfmask[pid] : 0;
-  // a tile of the finest level is restricted into its parent here, from the
-  // values it writes (staged in sF, free once every thread has read its
-  // edge fluxes)
-  const bool restrict_here = mode != kModeRHS && l == m.nlev - 1 && l >= 1;
+  const int fmask = cfmask[pid];
+  // a tile of a leaf without coarse/fine faces (the finest level's among them;
+  // refluxing leaves it as it is) is restricted into its parent here, from the
+  // values it writes (staged in sF, free once every thread has read its edge
+  // fluxes), instead of being read back by the post-stage launches
+  const bool restrict_here = mode != kModeRHS && l >= 1 && fmask == 0;
   static_assert(S::NCELL <= S::FXMAX, "the staged cell values fit sF");
   double* sR = sF;
   if (restrict_here) __syncthreads();
