@@ -727,14 +727,19 @@ void note_node(amr_hierarchy* h, int kind, int e0, int e1 = -1, int e2 = -1) {
   h->gnodes[h->cap_slot].push_back(g);
 }
 
-// The step's kernels: in batched mode one launch that reads the list and its
-// live count from the list directory (launch(list buffer, grid count,
-// directory entry)); per-patch mode as over_list.
+// The step's kernels: in batched mode one launch over the list; while a step
+// graph is recorded it reads the list and its live count from the list
+// directory (launch(list buffer, grid count, directory entry)), eagerly it
+// takes them as they are (launch(list, count, null)), one dependent load less
+// at the start of every block.  Per-patch mode as over_list.
 template <typename F>
 void over_list_dir(amr_hierarchy* h, const amr::ListView& lv, int stride_ints, int kind,
                    F launch) {
   if (h->exec_mode == AMR_EXEC_BATCHED) {
-    launch(h->d_lists, grid_count(h, lv), lv.dir);
+    if (h->capturing)
+      launch(h->d_lists, grid_count(h, lv), lv.dir);
+    else
+      launch(lv.ptr, lv.count, (const int*)nullptr);
     h->check_launch();
     note_node(h, kind, dir_entry(h, lv.dir));
     return;
@@ -806,8 +811,10 @@ void do_stage(amr_hierarchy* h, int stage, const double* dt,
     // follow, finest first (lists and counts from the list directory: the two
     // post-stage entries are consecutive)
     const int lup = h->forest.nlev - 2;
-    Kernels::post(h->dm, stage, h->U[d], h->fr, h->d_lists, grid_count(h, h->reflux), h->d_lists,
-                  grid_count(h, h->post_pairs), h->reflux.dir, lup, dt, w[stage],
+    const bool rec = h->capturing;
+    Kernels::post(h->dm, stage, h->U[d], h->fr, rec ? h->d_lists : h->reflux.ptr,
+                  grid_count(h, h->reflux), rec ? h->d_lists : h->post_pairs.ptr,
+                  grid_count(h, h->post_pairs), rec ? h->reflux.dir : nullptr, lup, dt, w[stage],
                   stage == 3 ? lam_next : nullptr, h->stream);
     h->check_launch();
     note_node(h, kGnPost, kDirReflux, kDirPairs);

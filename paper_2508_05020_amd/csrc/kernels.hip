@@ -965,7 +965,7 @@ void Kernels::reflux(const DevMesh& m, int mode, double* out, const double* fr,
   switch (m.dim) {
     case 1: k_reflux<1, 64><<<count, 64, 0, s>>>(m, mode, out, fr, list, count, dt, w, lam_next); break;
     case 2: k_reflux<2, 64><<<count, 64, 0, s>>>(m, mode, out, fr, list, count, dt, w, lam_next); break;
-    default: k_reflux<3, 256><<<count, 256, 0, s>>>(m, mode, out, fr, list, count, dt, w, lam_next); break;
+    default: k_reflux<3, 512><<<count, 512, 0, s>>>(m, mode, out, fr, list, count, dt, w, lam_next); break;
   }
 }
 
@@ -982,7 +982,9 @@ void Kernels::post(const DevMesh& m, int mode, double* out, const double* fr,
   switch (m.dim) {
     case 1: launch(k_post<1, 64>, 64); break;
     case 2: launch(k_post<2, 256>, 256); break;
-    default: launch(k_post<3, 256>, 256); break;
+    // 3D: the cells of two 16^3 faces (74 us against 90 with 256 threads, 73
+    // with 1024, 20 M cells; 18 / 22 / 17 us, 0.7 M)
+    default: launch(k_post<3, 512>, 512); break;
   }
 }
 
