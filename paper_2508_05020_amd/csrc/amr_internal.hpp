@@ -85,8 +85,9 @@ struct Kernels {
   static void fill_cf(const DevMesh& m, double* U, const int* list, int count, const int* dir,
                       int* err, hipStream_t s);
   // fuse = halo nodes outside the patch with a same-level source are read
-  // from that source by the kernel itself; the others (prolonged) come from
-  // ghost layers filled before by fill_cf
+  // from that source by the kernel itself; the others are prolonged by the
+  // kernel too in 1D (into Uin's ghost layers; *err set where a source is
+  // missing), in 2D and 3D they come from ghost layers filled before by fill_cf
   // lam_next (nullable, stage 3 only): accumulate the next step's CFL rate
   // over leaf cells not on coarse/fine faces (cfmask: per-pid face bits)
   // ev0/ev1 (optional): events stamped at the dispatch's own start and end.
@@ -95,7 +96,7 @@ struct Kernels {
   // In the stage modes a tile of a leaf without coarse/fine faces (level >= 1,
   // cfmask 0: refluxing does not change it) also restricts its new values into
   // its parent patch.
-  static void stage(const DevMesh& m, int mode, const double* Uin, const double* Un,
+  static void stage(const DevMesh& m, int mode, double* Uin, int* err, const double* Un,
                     double* out, double* fr, const int* tiles, int count, const int* dir,
                     const double* dt, bool fuse, unsigned long long* lam_next,
                     const uint8_t* cfmask, hipStream_t s, hipEvent_t ev0 = nullptr,

@@ -769,14 +769,15 @@ void do_fill(amr_hierarchy* h, int buf, const amr::ListView& lv) {
 
 // ghosts the stage kernel reads from memory: all of them, or with the fused
 // halo only the prolonged ones of the face regions (its stencils are
-// one-directional; edge and corner regions are read by no stencil)
+// one-directional; edge and corner regions are read by no stencil), which in
+// 1D it forms and writes itself
 void stage_fill(amr_hierarchy* h, int buf) {
-  if (h->fuse_halo) {
+  if (!h->fuse_halo) {
+    do_fill(h, buf, h->leaves);
+  } else if (h->cfg.dim > 1) {
     over_list_dir(h, h->cffaces, 2, kGnFill, [&](const int* p, int c, const int* dir) {
       Kernels::fill_cf(h->dm, h->U[buf], p, c, dir, h->d_flags, h->stream);
     });
-  } else {
-    do_fill(h, buf, h->leaves);
   }
 }
 
@@ -802,7 +803,7 @@ void do_stage(amr_hierarchy* h, int stage, const double* dt,
   over_list_dir(h, h->tiles, 2, kGnStage, [&](const int* p, int c, const int* dir) {
     hipEvent_t a = nullptr, b = nullptr;
     if (h->profiling) h->prof_pair(&a, &b, (long long)c * tcells);
-    Kernels::stage(h->dm, stage, h->U[s], h->U[0], h->U[d], h->fr, p, c, dir, dt, h->fuse_halo,
+    Kernels::stage(h->dm, stage, h->U[s], h->d_flags, h->U[0], h->U[d], h->fr, p, c, dir, dt, h->fuse_halo,
                    (stage == 3 || lam_in) ? lam_next : nullptr, h->d_cfmask, h->stream, a, b,
                    lam_in, dt_out);
   });
@@ -1284,7 +1285,7 @@ amr_status amr_rhs(amr_hierarchy* h, int buf, double* rhs_dev) {
   return guarded(h, [&]() -> amr_status {
     stage_fill(h, buf);
     over_list_dir(h, h->tiles, 2, kGnStage, [&](const int* p, int c, const int* dir) {
-      Kernels::stage(h->dm, amr::kModeRHS, h->U[buf], h->U[0], rhs_dev, h->fr, p, c, dir, h->d_dt,
+      Kernels::stage(h->dm, amr::kModeRHS, h->U[buf], h->d_flags, h->U[0], rhs_dev, h->fr, p, c, dir, h->d_dt,
                      h->fuse_halo, nullptr, h->d_cfmask, h->stream);
     });
     over_list(h, h->reflux, 2, [&](const int* p, int c) {
@@ -1510,12 +1511,12 @@ amr_status amr_autotune(amr_hierarchy* h, int reps, int* best, float* best_ms) {
       h->last_created.clear();
       sync_tables(h, false);
       // the launch the batched step makes (list and count from the directory)
-      Kernels::stage(h->dm, amr::kModeRHS, h->U[0], h->U[0], scratch, h->fr, h->d_lists,
+      Kernels::stage(h->dm, amr::kModeRHS, h->U[0], h->d_flags, h->U[0], scratch, h->fr, h->d_lists,
                      h->tiles.count, h->tiles.dir, h->d_dt, h->fuse_halo, nullptr, h->d_cfmask,
                      h->stream);
       HIP_OK(hipEventRecord(e0, h->stream));
       for (int r = 0; r < reps; ++r)
-        Kernels::stage(h->dm, amr::kModeRHS, h->U[0], h->U[0], scratch, h->fr, h->d_lists,
+        Kernels::stage(h->dm, amr::kModeRHS, h->U[0], h->d_flags, h->U[0], scratch, h->fr, h->d_lists,
                        h->tiles.count, h->tiles.dir, h->d_dt, h->fuse_halo, nullptr,
                        h->d_cfmask, h->stream);
       HIP_OK(hipEventRecord(e1, h->stream));

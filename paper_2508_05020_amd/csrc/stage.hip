@@ -306,21 +306,24 @@ __device__ __forceinline__ void node_store(const DevMesh& m, const double* u, do
 }
 
 
-// Conserved values of a node at patch-local cell c (may lie in the halo,
-// at most 4 cells outside the patch): from the patch itself, or by the
-// ghost-fill rule when outside the patch (same-level source from the
-// neighbour table, where a position beyond a transmissive boundary is the
-// nearest cell of this patch, else the patch's own ghost layer, which holds
-// the prolonged value).
+// 1D/2D: where the conserved values of the node at patch-local cell c (it may
+// lie in the halo, at most 4 cells outside the patch along one direction) are
+// read by the ghost-fill rule: in the patch itself, in the same-level source
+// of the neighbour table (a position beyond a transmissive boundary is the
+// nearest cell of this patch), or in no patch of the level (`prolonged`: the
+// value comes from the level below; src, off then name the node's place in the
+// patch's own ghost layer).
 template <int D, bool FUSE>
-__device__ __forceinline__ void node_conserved(const DevMesh& m, const double* __restrict__ Uin,
-                                               const double* __restrict__ Pin, int n, int full,
-                                               const int c[3], const int pc[3], int l,
-                                               const long long* sNB, double* u) {
-  constexpr int NV = D + 2;
+__device__ __forceinline__ void node_source(const DevMesh& m, const double* Uin, const double* Pin,
+                                            int n, int full, const int c[3], const int pc[3], int l,
+                                            const long long* sNB, const double*& src, int& off,
+                                            bool& prolonged) {
   bool inside = true;
+#pragma unroll
   for (int j = 0; j < D; ++j) inside &= (c[j] >= 0 && c[j] < n);
-  const int vs = var_stride<D>(full);
+  src = Pin;
+  off = box_off<D>(full, c[0] + NG, c[1] + NG, c[2] + NG);
+  prolonged = false;
   if (FUSE && !inside) {
     const int np = m.lv[l].np;
     int code = 0, loc[3] = {0, 0, 0}, mul = 1;
@@ -338,22 +341,16 @@ __device__ __forceinline__ void node_conserved(const DevMesh& m, const double* _
     }
     const long long sb = sNB[code];
     if (sb >= 0) {
-      const double* S = Uin + sb;
-      const int off = box_off<D>(full, loc[0] + NG, loc[1] + NG, loc[2] + NG);
-#pragma unroll
-      for (int v = 0; v < NV; ++v) u[v] = S[v * vs + off];
-      return;
+      src = Uin + sb;
+      off = box_off<D>(full, loc[0] + NG, loc[1] + NG, loc[2] + NG);
+    } else {
+      prolonged = true;
     }
-    // no same-level source: the prolonged ghost value was written into the
-    // patch's own ghost layer by the coarse-ghost fill pass
   }
-  const int off = box_off<D>(full, c[0] + NG, c[1] + NG, c[2] + NG);
-#pragma unroll
-  for (int v = 0; v < NV; ++v) u[v] = Pin[v * vs + off];
 }
 
-// node_conserved for a node of a 3D tile's halo along J (or of the tile
-// itself): only its J component can lie outside the patch, so the neighbour
+// Conserved values of a node of a 3D tile's halo along J (or of the tile
+// itself), by the ghost-fill rule: only its J component can lie outside the patch, so the neighbour
 // code and the wrap or clamp are formed for that component alone.
 template <int D, int J, bool FUSE>
 __device__ __forceinline__ void node_conserved_dir(const DevMesh& m,
@@ -388,26 +385,74 @@ __device__ __forceinline__ void node_conserved_dir(const DevMesh& m,
   for (int v = 0; v < NV; ++v) u[v] = src[v * vs + off];
 }
 
-// 1D/2D: primitives of the tile plus 4-node halos in every direction
-// (corner nodes, used by no stencil, are skipped), loaded once per launch.
+// 1D/2D: primitives of the tile plus 4-node halos in every direction (corner
+// nodes are used by no stencil), loaded once per launch.  The nodes are the
+// tile's rows with their x halos, then the y halo rows; a thread issues the
+// loads of all its nodes before it converts any.  Nodes without a same-level
+// source (fused halo): in 1D they are prolonged here, each by the one thread
+// that loads it, and also written to the patch's ghost layer (Pg in the source
+// buffer; no kernel reads that layer in this mode), which saves the fill
+// launch before the stage: 20 tiles, 3.6 + 6.3 us per stage in two launches,
+// 7.4 in one.  In 2D they come from the ghost layer that the fill launch has
+// written: prolonged here they cost the kernel 80 VGPRs and a spill, 27.8 us
+// against 5.1 + 21.6 (0.28 M cells) and 204 against 11 + 164 (2.75 M).
 template <int D, int TX, int TY, int NT, bool FUSE, bool CHAR>
 __device__ __forceinline__ void load_union(const DevMesh& m, const double* __restrict__ Uin,
-                                           const double* __restrict__ Pin, int n, int full,
-                                           const int o[3], const int pc[3], int l,
+                                           const double* __restrict__ Pin, double* Pg, int* err,
+                                           int n, int full, const int o[3], const int pc[3], int l,
                                            const long long* sN, double* sP) {
   using S = TileShape<D, TX, TY, 1>;
+  constexpr int NV = D + 2;
   constexpr int T0 = TX, T1 = D >= 2 ? TY : 1;
-  constexpr int U0 = T0 + 8, U1 = D >= 2 ? T1 + 8 : 1;
-  constexpr int NU = U0 * U1;
-  for (int idx = threadIdx.x; idx < NU; idx += NT) {
-    const int e0 = idx % U0, e1 = idx / U0;
-    const bool hx = e0 < 4 || e0 >= T0 + 4;
-    const bool hy = D >= 2 && (e1 < 4 || e1 >= T1 + 4);
-    if (hx && hy) continue;
-    const int c[3] = {o[0] + e0 - 4, D >= 2 ? o[1] + e1 - 4 : 0, 0};
-    double u[D + 2];
-    node_conserved<D, FUSE>(m, Uin, Pin, n, full, c, pc, l, sN, u);
-    node_store<D, CHAR>(m, u, sP, S::NUNION, e0 + S::UPITCH * e1);
+  constexpr int U0 = T0 + 8;
+  constexpr int NROWS = U0 * T1;                        // nodes of the tile's rows
+  constexpr int NU = NROWS + (D >= 2 ? 8 * T0 : 0);
+  constexpr int ITER = (NU + NT - 1) / NT;
+  constexpr bool PROLONG = FUSE && D == 1;
+  const int vs = var_stride<D>(full);
+  double u[ITER][NV];
+  int e0[ITER], e1[ITER];
+  bool pro[ITER];
+#pragma unroll
+  for (int k = 0; k < ITER; ++k) {
+    const int idx = threadIdx.x + k * NT;
+    pro[k] = false;
+    e0[k] = -1;
+    if (idx >= NU) continue;
+    if (D == 1 || idx < NROWS) {
+      e0[k] = idx % U0;
+      e1[k] = D >= 2 ? 4 + idx / U0 : 0;
+    } else {
+      const int r = (idx - NROWS) / T0;
+      e0[k] = 4 + (idx - NROWS) % T0;
+      e1[k] = r < 4 ? r : T1 + r;
+    }
+    const int c[3] = {o[0] + e0[k] - 4, D >= 2 ? o[1] + e1[k] - 4 : 0, 0};
+    const double* src;
+    int off;
+    node_source<D, FUSE>(m, Uin, Pin, n, full, c, pc, l, sN, src, off, pro[k]);
+#pragma unroll
+    for (int v = 0; v < NV; ++v) u[k][v] = src[v * vs + off];
+  }
+#pragma unroll
+  for (int k = 0; k < ITER; ++k) {
+    if (e0[k] < 0) continue;
+    if (PROLONG && pro[k]) {
+      const LevelC& L = m.lv[l];
+      const int c[3] = {o[0] + e0[k] - 4, D >= 2 ? o[1] + e1[k] - 4 : 0, 0};
+      int g[3] = {0, 0, 0};
+#pragma unroll
+      for (int j = 0; j < D; ++j) g[j] = bc_near(pc[j] * n + c[j], L.cells, m.periodic[j]);
+      if (!(l > 0 && prolong_cell<D>(m, Uin, l, g, u[k]))) {
+        err[0] = 1;
+#pragma unroll
+        for (int v = 0; v < NV; ++v) u[k][v] = __builtin_nan("");
+      }
+      const int off = box_off<D>(full, c[0] + NG, c[1] + NG, c[2] + NG);
+#pragma unroll
+      for (int v = 0; v < NV; ++v) Pg[v * vs + off] = u[k][v];
+    }
+    node_store<D, CHAR>(m, u[k], sP, S::NUNION, e0[k] + S::UPITCH * e1[k]);
   }
 }
 
@@ -1054,8 +1099,8 @@ __device__ __forceinline__ void restrict_tile(const DevMesh& m, double* __restri
 
 template <int D, int TX, int TY, int TZ, int NT, bool FUSE, bool BOTH, bool CHAR>
 __device__ __forceinline__ void stage_item(const DevMesh& m, int mode,
-                                           const double* __restrict__ Uin, const double* Un,
-                                           double* out, double* __restrict__ fr,
+                                           const double* __restrict__ Uin, double* Ug, int* err,
+                                           const double* Un, double* out, double* __restrict__ fr,
                                            const int* __restrict__ tiles, int item,
                                            const double* __restrict__ dtp,
                                            unsigned long long* __restrict__ lam_next,
@@ -1098,7 +1143,7 @@ __device__ __forceinline__ void stage_item(const DevMesh& m, int mode,
     __syncthreads();
   }
   if constexpr (UNION) {
-    load_union<D, TX, TY, NT, FUSE, CHAR>(m, Uin, Pin, n, full, o, pc, l, sN, sP);
+    load_union<D, TX, TY, NT, FUSE, CHAR>(m, Uin, Pin, Ug + base, err, n, full, o, pc, l, sN, sP);
     __syncthreads();
     if constexpr (BOTH && D == 2) {
       stage_both<D, TX, TY, NT, CHAR>(m, frp, n, o, sP, sF,
@@ -1256,7 +1301,7 @@ __device__ __forceinline__ void stage_item(const DevMesh& m, int mode,
 // halos from that XCD's L2.
 template <int D, int TX, int TY, int TZ, int NT, bool FUSE, bool BOTH, bool CHAR>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(CHAR ? 4 : 6))) void k_stage(DevMesh m, int mode, const double* __restrict__ Uin,
-                                              const double* Un, double* out,
+                                              double* Ug, int* err, const double* Un, double* out,
                                               double* __restrict__ fr,
                                               const int* __restrict__ tiles, int count,
                                               const int* __restrict__ dir,
@@ -1277,7 +1322,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(CHAR ? 4 : 6
   const int item = xcd_item(dir ? dir[1] : count);
   if (item < 0) return;
   unsigned long long best = 0ull;
-  stage_item<D, TX, TY, TZ, NT, FUSE, BOTH, CHAR>(m, mode, Uin, Un, out, fr, list, item, dtp,
+  stage_item<D, TX, TY, TZ, NT, FUSE, BOTH, CHAR>(m, mode, Uin, Ug, err, Un, out, fr, list, item, dtp,
                                                   lam_next, cfmask, lam_in, dt_out, sP, sF, sN,
                                                   best);
   if (lam_next != nullptr && mode == kModeStage3) block_max_atomic(best, lam_next);
@@ -1326,7 +1371,7 @@ int Kernels::tiles_per_patch(int v, int n) {
   return r;
 }
 
-void Kernels::stage(const DevMesh& m, int mode, const double* Uin, const double* Un,
+void Kernels::stage(const DevMesh& m, int mode, double* Uin, int* err, const double* Un,
                     double* out, double* fr, const int* tiles, int count, const int* dir,
                     const double* dt, bool fuse, unsigned long long* lam_next,
                     const uint8_t* cfmask, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1,
@@ -1340,10 +1385,10 @@ void Kernels::stage(const DevMesh& m, int mode, const double* Uin, const double*
   do {                                                                                          \
     auto kern = k_stage<D, TX, TY, TZ, NT, F, B, C>;                                            \
     if (ev0)                                                                                    \
-      hipExtLaunchKernelGGL(kern, dim3(nb), dim3(NT), 0, s, ev0, ev1, 0, m, mode, Uin, Un,  \
+      hipExtLaunchKernelGGL(kern, dim3(nb), dim3(NT), 0, s, ev0, ev1, 0, m, mode, Uin, Uin, err, Un, \
                             out, fr, tiles, count, dir, dt, lam_next, cfmask, lam_in, dt_out);  \
     else                                                                                        \
-      hipLaunchKernelGGL(kern, dim3(nb), dim3(NT), 0, s, m, mode, Uin, Un, out, fr, tiles, \
+      hipLaunchKernelGGL(kern, dim3(nb), dim3(NT), 0, s, m, mode, Uin, Uin, err, Un, out, fr, tiles, \
                          count, dir, dt, lam_next, cfmask, lam_in, dt_out);                     \
   } while (0)
 #define AMR_STAGE_F(D, TX, TY, TZ, NT, F, B)          \
