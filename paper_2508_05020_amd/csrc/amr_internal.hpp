@@ -68,6 +68,11 @@ struct ListView {
   const int* dir = nullptr;
 };
 
+// Blocks of the 3D tag launch: patches and 8^3 tiles per patch of each level.
+struct TagLevels {
+  int count[kMaxLev], tiles[kMaxLev];
+};
+
 // Launch wrappers implemented in kernels.hip.
 struct Kernels {
   // ghosts of the listed patches that have a same-level source (copies), and
@@ -127,6 +132,12 @@ struct Kernels {
   // hold only the prolonged cells (filled by fill_cf beforehand)
   static void tag(const DevMesh& m, const double* U, const int* list, int count,
                   uint8_t* has_tag, uint8_t* raw, bool fuse, hipStream_t s);
+  // 3D, fused halo: tag flags of every active patch (`list` in level order,
+  // level_count patches per level; prolonged regions filled before); mask:
+  // scratch of max_patches ints
+  static void tag_flags3(const DevMesh& m, const double* U, const int* list,
+                         const int* level_count, const int* regions, int nregions, int* mask,
+                         uint8_t* has_tag, hipStream_t s);
   static void cell_tags(const DevMesh& m, const uint8_t* raw, const int* list, int count,
                         uint8_t* out, hipStream_t s);
   static void requests(const DevMesh& m, const uint8_t* has_tag, const uint8_t* active_leaf,

@@ -105,6 +105,7 @@ struct amr_hierarchy {
   uint8_t* d_active_leaf = nullptr;
   uint8_t* d_has_tag = nullptr;
   uint8_t* d_raw = nullptr;
+  int* d_tag_mask = nullptr;  // 3D: per pid, see Kernels::tag_flags3
   uint8_t* d_refine = nullptr;
   uint8_t* d_coarsen = nullptr;
   unsigned long long* d_lam = nullptr;
@@ -130,6 +131,7 @@ struct amr_hierarchy {
   std::vector<int> lists;
   // cffaces: the face regions of cfregions (all the stage kernel reads;
   // the tagger's dilated box reads the edge and corner regions too)
+  int level_count[amr::kMaxLev] = {};  // active patches per level
   amr::ListView all{}, leaves{}, tiles{}, reflux{}, cfregions{}, cffaces{}, cands{};
   // post-stage restriction (see Kernels::post): level-(L-2) patches with
   // children, and per level the patches that the stage kernel has not
@@ -419,7 +421,11 @@ void sync_tables(amr_hierarchy* h, bool full) {
   const std::vector<int> order = f.sorted_active();
   auto begin_list = [&]() { return (int)L.size(); };
   int a0 = begin_list();
-  for (int pid : order) L.push_back(pid);
+  std::fill(h->level_count, h->level_count + amr::kMaxLev, 0);
+  for (int pid : order) {
+    L.push_back(pid);
+    ++h->level_count[f.level[pid]];
+  }
   const int a1 = begin_list();
   for (int pid : order)
     if (f.is_leaf(pid)) L.push_back(pid);
@@ -877,13 +883,20 @@ void do_tag(amr_hierarchy* h, int buf, uint8_t* refine, uint8_t* coarsen, uint8_
     do_fill(h, buf, h->leaves);
     do_fill(h, buf, h->cands);
   }
-  over_list(h, h->leaves, 1, [&](const int* p, int c) {
-    Kernels::tag(h->dm, h->U[buf], p, c, h->d_has_tag, cells ? h->d_raw : nullptr, fuse,
-                 h->stream);
-  });
-  over_list(h, h->cands, 1, [&](const int* p, int c) {
-    Kernels::tag(h->dm, h->U[buf], p, c, h->d_has_tag, nullptr, fuse, h->stream);
-  });
+  if (h->cfg.dim == 3 && fuse && !cells && h->exec_mode == AMR_EXEC_BATCHED) {
+    // flags only: every cell tested once, the patches share the outcome
+    Kernels::tag_flags3(h->dm, h->U[buf], h->all.ptr, h->level_count, h->cfregions.ptr,
+                        h->cfregions.count, h->d_tag_mask, h->d_has_tag, h->stream);
+    h->check_launch();
+  } else {
+    over_list(h, h->leaves, 1, [&](const int* p, int c) {
+      Kernels::tag(h->dm, h->U[buf], p, c, h->d_has_tag, cells ? h->d_raw : nullptr, fuse,
+                   h->stream);
+    });
+    over_list(h, h->cands, 1, [&](const int* p, int c) {
+      Kernels::tag(h->dm, h->U[buf], p, c, h->d_has_tag, nullptr, fuse, h->stream);
+    });
+  }
   if (cells)
     over_list(h, h->leaves, 1, [&](const int* p, int c) {
       Kernels::cell_tags(h->dm, h->d_raw, p, c, cells, h->stream);
@@ -1021,6 +1034,7 @@ amr_status amr_create_hierarchy(const amr_config* cfg, const amr_allocator* allo
     h->d_refine = (uint8_t*)h->dev_alloc(mp);
     h->d_coarsen = (uint8_t*)h->dev_alloc(mp);
     h->d_raw = (uint8_t*)h->dev_alloc(h->tag_bytes);
+    h->d_tag_mask = (int*)h->dev_alloc(cfg->dim == 3 ? mp * sizeof(int) : 0);
     h->d_lam = (unsigned long long*)h->dev_alloc(64);
     h->d_dt = (double*)h->dev_alloc(64);
     h->d_flags = (int*)h->dev_alloc(64);

@@ -773,15 +773,319 @@ __global__ __launch_bounds__(256) void k_cell_tags(DevMesh m, const uint8_t* __r
   }
 }
 
+// ---------------------------------------------------------------------------
+// 3D tag flags in three passes (fused halo, no per-cell output).  A patch has a
+// tag when a cell within tag_buffer = b cells of its interior is tagged; a cell
+// of the dilated box that lies in a same-level patch has there the tag it has
+// here (the same cell values around it), so every cell is tested once, by its
+// own patch, and the patches share the outcome:
+//  k_tag_cells    each patch's cells, as a 27-bit mask: bit (r0+1) + 3 (r1+1) +
+//                 9 (r2+1) is set when a tagged cell lies within b cells of
+//                 the low (r = -1) or high (r = 1) side in each direction
+//                 with r != 0;
+//  k_tag_regions  the cells of ghost regions without a same-level patch
+//                 (prolonged values), b deep, of leaves without a tag of their
+//                 own;
+//  k_tag_flags    a patch's flag from its own mask, its regions' flag and the
+//                 facing bits of its neighbours' masks.
+// A position beyond a transmissive wall repeats the boundary cell along the
+// wall and adds no difference across it: its tag implies the boundary cell's.
+// One block per patch over the dilated box evaluated 5 nodes per 8^3 patch cell
+// (2744 for 512) with three divisions each, and 6 per cell without LDS for
+// larger patches: 908 us for 13.8 k leaves (11.8 M cells) and 218 us for 195
+// coarsening candidates, against 542 us for the three passes (309, 214 and 7)
+// with the clear and the requests.
+// ---------------------------------------------------------------------------
+constexpr int kTagTile = 8;   // cells per tile edge of k_tag_cells
+
+// pressure_exact with one reciprocal for the D quotients: r refined by two
+// Newton steps, q = m r and one correction fma(fma(-rho, q, m), r, q), which is
+// the correctly rounded quotient, as the division is, while no scaling is
+// needed; operands outside [2^-300, 2^300] (zero momenta excepted) take the
+// division.
+template <int D>
+__device__ __forceinline__ double pressure_fast(const double* u, double gm1) {
+  const double rho = u[0];
+  const double lo = 0x1p-300, hi = 0x1p300;
+  bool ok = fabs(rho) > lo && fabs(rho) < hi;
+#pragma unroll
+  for (int j = 0; j < D; ++j)
+    ok = ok && ((fabs(u[1 + j]) > lo && fabs(u[1 + j]) < hi) || u[1 + j] == 0.0);
+  if (!ok) return pressure_exact<D>(u, gm1);
+  double r = __builtin_amdgcn_rcp(rho);
+  r = fma(fma(-rho, r, 1.0), r, r);
+  r = fma(fma(-rho, r, 1.0), r, r);
+  double ke = 0.0;
+#pragma unroll
+  for (int j = 0; j < D; ++j) {
+    const double q = u[1 + j] * r;
+    const double v = fma(fma(-rho, q, u[1 + j]), r, q);
+    ke = j == 0 ? u[1] * v : ke + u[1 + j] * v;
+  }
+  ke = 0.5 * ke;
+  return gm1 * (u[D + 1] - ke);
+}
+
+__device__ __forceinline__ bool differs(double a, double b, double theta) {
+  return fabs(a - b) > theta * (fabs(a) + fabs(b));
+}
+
+// rho and p at patch-local cell c (at most 4 cells outside patch P of the
+// neighbour table sNB): in the same-level patch that holds it, else in P's own
+// ghost layer.
+__device__ __forceinline__ void tag_node(const DevMesh& m, const double* __restrict__ U,
+                                         const double* __restrict__ P, int n, int full, int vs,
+                                         int np, const int pc[3], const long long* sNB,
+                                         const int c[3], double& rho, double& p) {
+  int code = 0, mul = 1, loc[3];
+#pragma unroll
+  for (int j = 0; j < 3; ++j) {
+    int o = c[j] < 0 ? -1 : (c[j] >= n ? 1 : 0);
+    loc[j] = c[j] - o * n;
+    if (o != 0 && !m.periodic[j] && (unsigned)(pc[j] + o) >= (unsigned)np) {
+      loc[j] = o < 0 ? 0 : n - 1;
+      o = 0;
+    }
+    code += (o + 1) * mul;
+    mul *= 3;
+  }
+  const long long sb = sNB[code];
+  const double* src = U + sb;
+  int off = box_off<3>(full, loc[0] + NG, loc[1] + NG, loc[2] + NG);
+  if (sb < 0) {
+    src = P;
+    off = box_off<3>(full, c[0] + NG, c[1] + NG, c[2] + NG);
+  }
+  double u[5];
+#pragma unroll
+  for (int v = 0; v < 5; ++v) u[v] = src[v * vs + off];
+  rho = u[0];
+  p = pressure_fast<3>(u, m.gm1);
+}
+
+// One block per 8^3 tile of every active patch (`list` in level order; the
+// level of a block and its patch and tile follow from the blocks per level):
+// rho and p of the tile and one layer around it in LDS, then the tile's cells.
+// Bound by memory: the 64-byte rows of an 8^3 patch are fetched as 128-byte
+// lines, 9.2 of the 13.8 KB of a variable for 4 KB of cells.  Chunks of 16
+// consecutive tiles per XCD, so that x neighbours share their cells in one L2:
+// 14.6 M cells 425 us in launch order, 309 so (64 and 128 the same).
+constexpr int kTagChunk = 16;
+
+__global__ __launch_bounds__(256) void k_tag_cells(DevMesh m, const double* __restrict__ U,
+                                                   const int* __restrict__ list, TagLevels tl,
+                                                   int blocks, int* __restrict__ mask) {
+  constexpr int B = kTagTile + 2;
+  __shared__ long long sNB[27];
+  __shared__ double sr[B * B * B], sp[B * B * B];
+  __shared__ int sm;
+  int b = xcd_chunk<kTagChunk>(blocks), first = 0, l = 0;
+  if (b < 0) return;
+  for (; l < m.nlev - 1 && b >= tl.count[l] * tl.tiles[l]; ++l) {
+    b -= tl.count[l] * tl.tiles[l];
+    first += tl.count[l];
+  }
+  const int tile = b % tl.tiles[l], pid = list[first + b / tl.tiles[l]];
+  const LevelC& L = m.lv[l];
+  const int n = L.n, full = L.full, vs = var_stride<3>(full);
+  const int nt = (n + kTagTile - 1) / kTagTile;
+  const int o[3] = {tile % nt * kTagTile, tile / nt % nt * kTagTile, tile / (nt * nt) * kTagTile};
+  const int pc[3] = {m.coord[3 * pid], m.coord[3 * pid + 1], m.coord[3 * pid + 2]};
+  load_neighbours<3>(m, l, pc, sNB);
+  if (threadIdx.x == 0) sm = 0;
+  __syncthreads();
+  const double* P = U + patch_base(m, pid, l);
+  int e[3];  // cells of the tile (the last tile of an edge may be partial)
+#pragma unroll
+  for (int j = 0; j < 3; ++j) e[j] = min(kTagTile, n - o[j]);
+#pragma unroll 2
+  for (int idx = threadIdx.x; idx < B * B * B; idx += 256) {
+    const int t[3] = {idx % B - 1, idx / B % B - 1, idx / (B * B) - 1};
+    int outside = 0;
+    bool in = true;
+#pragma unroll
+    for (int j = 0; j < 3; ++j) {
+      outside += t[j] < 0 || t[j] >= e[j];
+      in = in && t[j] <= e[j];
+    }
+    if (outside > 1 || !in) continue;  // edges and corners are not tested
+    const int c[3] = {o[0] + t[0], o[1] + t[1], o[2] + t[2]};
+    tag_node(m, U, P, n, full, vs, L.np, pc, sNB, c, sr[idx], sp[idx]);
+  }
+  __syncthreads();
+  int bits = 0;
+  const int tb = m.tag_buffer;
+  for (int idx = threadIdx.x; idx < kTagTile * kTagTile * kTagTile; idx += 256) {
+    const int t[3] = {idx % kTagTile, idx / kTagTile % kTagTile, idx / (kTagTile * kTagTile)};
+    if (t[0] >= e[0] || t[1] >= e[1] || t[2] >= e[2]) continue;
+    const int node = t[0] + 1 + B * (t[1] + 1 + B * (t[2] + 1));
+    bool tag = false;
+#pragma unroll
+    for (int j = 0; j < 3; ++j) {
+      const int st = j == 0 ? 1 : (j == 1 ? B : B * B);
+      tag |= differs(sr[node + st], sr[node - st], m.theta);
+      tag |= differs(sp[node + st], sp[node - st], m.theta);
+    }
+    if (!tag) continue;
+    // sides the cell is near, per direction: bit 0 low, 1 always, 2 high
+    int side[3];
+#pragma unroll
+    for (int j = 0; j < 3; ++j) {
+      const int c = o[j] + t[j];
+      side[j] = 2 | (c < tb ? 1 : 0) | (c >= n - tb ? 4 : 0);
+    }
+    int m9 = 0, m27 = 0;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) m9 |= (side[1] >> k & 1) ? side[0] << (3 * k) : 0;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) m27 |= (side[2] >> k & 1) ? m9 << (9 * k) : 0;
+    bits |= m27;
+  }
+  if (bits) atomicOr(&sm, bits);
+  __syncthreads();
+  if (threadIdx.x == 0 && sm) atomicOr(mask + pid, sm);
+}
+
+// Ghost regions without a same-level patch, 4 per block: bit 27 of the leaf's
+// mask is set when a cell of the region within tag_buffer of the leaf is
+// tagged (values prolonged into the leaf's ghost layer by the fill).
+__global__ __launch_bounds__(128) void k_tag_regions(DevMesh m, const double* __restrict__ U,
+                                                     const int* __restrict__ list, int count,
+                                                     int* __restrict__ mask) {
+  constexpr int G = 4, CENTRE = 1 << 13;
+  __shared__ long long sNB[G][27];
+  __shared__ int s_pid[G], s_code[G], s_lev[G], s_pc[G][3], s_pre[G + 1];
+  const int b = m.tag_buffer;
+  {
+    // one neighbour table per region, by the threads [27 g, 27 g + 27)
+    const int g = (int)threadIdx.x / 27, t = (int)threadIdx.x - 27 * g;
+    const int i = (int)blockIdx.x * G + g;
+    if (g < G && i < count) {
+      const int pid = list[2 * i], l = m.level[pid], np = m.lv[l].np;
+      int q[3];
+      bool in = true;
+#pragma unroll
+      for (int j = 0; j < 3; ++j) {
+        const int o = (j == 0 ? t : (j == 1 ? t / 3 : t / 9)) % 3 - 1;
+        q[j] = m.coord[3 * pid + j] + o;
+        if (t == 13) s_pc[g][j] = q[j];
+        if ((unsigned)q[j] >= (unsigned)np) {
+          if (m.periodic[j]) q[j] -= o * np;
+          else in = false;
+        }
+      }
+      const int nb = in ? map_at<3>(m, l, q) : -1;
+      sNB[g][t] = nb >= 0 ? patch_base(m, nb, l) : -1;
+    }
+  }
+  if (threadIdx.x == 0) {
+    s_pre[0] = 0;
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+      const int i = (int)blockIdx.x * G + g;
+      int cells = 0;
+      if (i < count) {
+        const int pid = list[2 * i], code = list[2 * i + 1], l = m.level[pid];
+        s_pid[g] = pid;
+        s_code[g] = code;
+        s_lev[g] = l;
+        // a leaf with a tag of its own needs no more
+        if (!(mask[pid] & CENTRE)) {
+          cells = 1;
+#pragma unroll
+          for (int j = 0; j < 3; ++j)
+            cells *= (j == 0 ? code : (j == 1 ? code / 3 : code / 9)) % 3 == 1 ? m.lv[l].n : b;
+        }
+      }
+      s_pre[g + 1] = s_pre[g] + cells;
+    }
+  }
+  __syncthreads();
+  for (int idx = threadIdx.x; idx < s_pre[G]; idx += 128) {
+    int it = idx >= s_pre[2] ? 2 : 0;
+    if (idx >= s_pre[it + 1]) ++it;
+    const int local = idx - s_pre[it], code = s_code[it];
+    const LevelC& L = m.lv[s_lev[it]];
+    const int n = L.n, full = L.full, vs = var_stride<3>(full);
+    const double* P = U + sNB[it][13];
+    const int pc[3] = {s_pc[it][0], s_pc[it][1], s_pc[it][2]};
+    int c[3], left = local;
+#pragma unroll
+    for (int j = 0; j < 3; ++j) {
+      const int r = (j == 0 ? code : (j == 1 ? code / 3 : code / 9)) % 3 - 1;
+      const int ext = r == 0 ? n : b;
+      const int k = left % ext;
+      left /= ext;
+      c[j] = r < 0 ? k - b : (r == 0 ? k : n + k);
+    }
+    bool tag = false;
+#pragma unroll
+    for (int j = 0; j < 3; ++j) {
+      int cp[3] = {c[0], c[1], c[2]}, cm[3] = {c[0], c[1], c[2]};
+      cp[j] += 1;
+      cm[j] -= 1;
+      double rp, pp, rm, pm;
+      tag_node(m, U, P, n, full, vs, L.np, pc, sNB[it], cp, rp, pp);
+      tag_node(m, U, P, n, full, vs, L.np, pc, sNB[it], cm, rm, pm);
+      tag |= differs(rp, rm, m.theta);
+      tag |= differs(pp, pm, m.theta);
+    }
+    if (tag) atomicOr(mask + s_pid[it], 1 << 27);
+  }
+}
+
+// Tag flag of every patch of `list`: a tagged cell of its own, one of its
+// prolonged regions, or one of a neighbour within tag_buffer of it (the
+// neighbour at offset code k faces it with its side 26 - k).  8 lanes a patch.
+__global__ __launch_bounds__(256) void k_tag_flags(DevMesh m, const int* __restrict__ list,
+                                                   int count, const int* __restrict__ mask,
+                                                   uint8_t* __restrict__ has_tag) {
+  const int i = (int)(blockIdx.x * blockDim.x + threadIdx.x) >> 3, lane = threadIdx.x & 7;
+  int any = 0, pid = -1;
+  if (i < count) {
+    pid = list[i];
+    const int l = m.level[pid], np = m.lv[l].np;
+    const int pc[3] = {m.coord[3 * pid], m.coord[3 * pid + 1], m.coord[3 * pid + 2]};
+    if (lane == 0) any = mask[pid] & (1 << 13 | 1 << 27);
+#pragma unroll
+    for (int k0 = 0; k0 < 32; k0 += 8) {
+      const int k = k0 + lane;
+      int q[3];
+      bool in = k < 27 && k != 13;
+#pragma unroll
+      for (int j = 0; j < 3; ++j) {
+        const int o = (j == 0 ? k : (j == 1 ? k / 3 : k / 9)) % 3 - 1;
+        q[j] = pc[j] + o;
+        if ((unsigned)q[j] >= (unsigned)np) {
+          if (m.periodic[j]) q[j] -= o * np;
+          else in = false;
+        }
+      }
+      const int nb = in ? map_at<3>(m, l, q) : -1;
+      if (nb >= 0) any |= mask[nb] >> (26 - k) & 1;
+    }
+  }
+  for (int d = 4; d > 0; d >>= 1) any |= __shfl_xor(any, d);
+  if (lane == 0 && pid >= 0) has_tag[pid] = any ? 1 : 0;
+}
+
+__global__ void k_zero_int(int* __restrict__ p, int n) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < n) p[i] = 0;
+}
+
 // refine request: active leaf below the finest level with a tag;
-// coarsen request: patch whose children are all leaves without tags
-__global__ void k_requests(DevMesh m, const uint8_t* __restrict__ has_tag,
-                           const uint8_t* __restrict__ active_leaf, int nslots,
-                           uint8_t* __restrict__ refine, uint8_t* __restrict__ coarsen) {
-  const int pid = blockIdx.x * blockDim.x + threadIdx.x;
-  if (pid >= nslots) return;
+// coarsen request: patch whose children are all leaves without tags.  8 lanes a
+// patch: a 3D patch has up to 64 children, whose flags one lane would read in
+// a chain of 64 (20 us for 16 k slots, 6.8 us now).
+__global__ __launch_bounds__(256) void k_requests(DevMesh m, const uint8_t* __restrict__ has_tag,
+                                                  const uint8_t* __restrict__ active_leaf,
+                                                  int nslots, uint8_t* __restrict__ refine,
+                                                  uint8_t* __restrict__ coarsen) {
+  const int pid = (int)((blockIdx.x * blockDim.x + threadIdx.x) >> 3), lane = threadIdx.x & 7;
+  if (pid >= nslots) return;  // whole groups of 8 lanes
   const uint8_t al = active_leaf[pid];  // 0 inactive, 1 leaf, 2 non-leaf
-  uint8_t rq = 0, cq = 0;
+  int rq = 0, cq = 0;
   if (al == 1) {
     rq = (has_tag[pid] && m.level[pid] < m.nlev - 1) ? 1 : 0;
   } else if (al == 2) {
@@ -789,16 +1093,17 @@ __global__ void k_requests(DevMesh m, const uint8_t* __restrict__ has_tag,
     // restricted data as well; it is coarsened only if that is untagged too
     cq = has_tag[pid] ? 0 : 1;
     const int nc = m.nchild[pid];
-    for (int k = 0; k < nc; ++k) {
+#pragma unroll 4
+    for (int k = lane; k < nc; k += 8) {
       const int c = m.child[(long long)pid * m.maxc + k];
-      if (active_leaf[c] != 1 || has_tag[c]) {
-        cq = 0;
-        break;
-      }
+      cq &= (active_leaf[c] == 1 && !has_tag[c]) ? 1 : 0;
     }
   }
-  if (refine) refine[pid] = rq;
-  if (coarsen) coarsen[pid] = cq;
+  for (int d = 4; d > 0; d >>= 1) cq &= __shfl_xor(cq, d);
+  if (lane == 0) {
+    if (refine) refine[pid] = (uint8_t)rq;
+    if (coarsen) coarsen[pid] = (uint8_t)cq;
+  }
 }
 
 // prolongation of the interiors of newly created patches of one level, by
@@ -1058,6 +1363,32 @@ void Kernels::tag(const DevMesh& m, const double* U, const int* list, int count,
 #undef AMR_TAG
 }
 
+void Kernels::tag_flags3(const DevMesh& m, const double* U, const int* list, const int* level_count,
+                         const int* regions, int nregions, int* mask, uint8_t* has_tag,
+                         hipStream_t s) {
+  TagLevels tl{};
+  int blocks = 0, count = 0;
+  for (int l = 0; l < m.nlev; ++l) {
+    const int nt = (m.lv[l].n + kTagTile - 1) / kTagTile;
+    tl.count[l] = level_count[l];
+    tl.tiles[l] = nt * nt * nt;
+    blocks += tl.count[l] * tl.tiles[l];
+    count += tl.count[l];
+  }
+  if (count <= 0) return;
+  hipLaunchKernelGGL(k_zero_int, dim3((m.max_patches + 255) / 256), dim3(256), 0, s, mask,
+                     m.max_patches);
+  const int group = kXcds * kTagChunk;  // blocks per group of chunks (xcd_chunk)
+  hipLaunchKernelGGL(k_tag_cells, dim3((blocks + group - 1) / group * group), dim3(256), 0, s, m, U,
+                     list, tl, blocks, mask);
+  // without dilation no ghost cell counts
+  if (nregions > 0 && m.tag_buffer > 0)
+    hipLaunchKernelGGL(k_tag_regions, dim3((nregions + 3) / 4), dim3(128), 0, s, m, U, regions,
+                       nregions, mask);
+  hipLaunchKernelGGL(k_tag_flags, dim3((count + 31) / 32), dim3(256), 0, s, m, list, count, mask,
+                     has_tag);
+}
+
 void Kernels::cell_tags(const DevMesh& m, const uint8_t* raw, const int* list, int count,
                         uint8_t* out, hipStream_t s) {
   if (count <= 0) return;
@@ -1067,7 +1398,7 @@ void Kernels::cell_tags(const DevMesh& m, const uint8_t* raw, const int* list, i
 void Kernels::requests(const DevMesh& m, const uint8_t* has_tag, const uint8_t* active_leaf,
                        int nslots, uint8_t* refine, uint8_t* coarsen, hipStream_t s) {
   if (nslots <= 0) return;
-  hipLaunchKernelGGL(k_requests, dim3((nslots + 255) / 256), dim3(256), 0, s, m, has_tag,
+  hipLaunchKernelGGL(k_requests, dim3((nslots + 31) / 32), dim3(256), 0, s, m, has_tag,
                      active_leaf, nslots, refine, coarsen);
 }
 
