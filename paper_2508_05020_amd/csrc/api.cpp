@@ -8,7 +8,6 @@
 #include <exception>
 #include <sstream>
 #include <string>
-#include <thread>
 #include <vector>
 
 #include "amr_internal.hpp"
@@ -139,10 +138,6 @@ struct amr_hierarchy {
   amr::ListView post_pairs{};
   amr::ListView restr[amr::kMaxLev]{}, restr_post[amr::kMaxLev]{}, fresh[amr::kMaxLev]{};
   std::vector<int> last_created;
-  // scratch of sync_tables, per parent: all Moore neighbours have children;
-  // bit mask (offset codes) of the Moore neighbours with children
-  std::vector<int8_t> parent_interior;
-  std::vector<int> parent_kids;
   std::vector<uint8_t> h_active_leaf;
   long long leaf_cells = 0;
 
@@ -368,24 +363,7 @@ void sync_tables(amr_hierarchy* h, bool full) {
   ++h->mesh_version;  // recorded step graphs resize their launches before the next replay
   amr::Forest& f = h->forest;
   const int mp = f.max_patches;
-  // table deltas
-  std::vector<int> pairs;
-  auto push_pid = [&](int pid) {
-    pairs.push_back((int)(h->off_level + pid));
-    pairs.push_back(f.level[pid]);
-    pairs.push_back((int)(h->off_parent + pid));
-    pairs.push_back(f.parent[pid]);
-    pairs.push_back((int)(h->off_nchild + pid));
-    pairs.push_back(f.nchild[pid]);
-    for (int j = 0; j < 3; ++j) {
-      pairs.push_back((int)(h->off_coord + 3LL * pid + j));
-      pairs.push_back(f.coord[3 * pid + j]);
-    }
-    for (int k = 0; k < f.maxc; ++k) {
-      pairs.push_back((int)(h->off_child + (long long)pid * f.maxc + k));
-      pairs.push_back(f.child[(size_t)pid * f.maxc + k]);
-    }
-  };
+  std::vector<int> pairs;  // (index, value) of the changed table entries
   if (full) {
     std::vector<int> tab(h->tab_ints);
     std::copy(f.level.begin(), f.level.end(), tab.begin() + h->off_level);
@@ -398,17 +376,38 @@ void sync_tables(amr_hierarchy* h, bool full) {
                           h->stream));
     h->sync();
   } else {
+    // dirty bits of a pid: 1 its own row, 2 its children
     std::vector<uint8_t> dirty(mp, 0);
-    for (int mi : f.map_dirty) {
-      pairs.push_back((int)(h->off_map + mi));
-      pairs.push_back(f.map[mi]);
-    }
-    for (int q : f.touched) dirty[q] = 1;
+    for (int q : f.touched) dirty[q] |= 1;
+    for (int q : f.touched_kids) dirty[q] |= 2;
+    size_t count = f.map_dirty.size();
     for (int pid = 0; pid < mp; ++pid)
-      if (dirty[pid]) push_pid(pid);
+      count += (dirty[pid] ? 1 : 0) + (dirty[pid] & 1 ? 5 : 0) + (dirty[pid] & 2 ? f.maxc : 0);
+    pairs.resize(2 * count);
+    int* at = pairs.data();
+    auto put = [&](long long index, int value) {
+      *at++ = (int)index;
+      *at++ = value;
+    };
+    for (int mi : f.map_dirty) put(h->off_map + mi, f.map[mi]);
+    for (int pid = 0; pid < mp; ++pid) {
+      if (!dirty[pid]) continue;
+      put(h->off_nchild + pid, f.nchild[pid]);
+      if (dirty[pid] & 1) {
+        put(h->off_level + pid, f.level[pid]);
+        put(h->off_parent + pid, f.parent[pid]);
+        for (int j = 0; j < 3; ++j) put(h->off_coord + 3LL * pid + j, f.coord[3 * pid + j]);
+      }
+      if (dirty[pid] & 2)
+        for (int k = 0; k < f.maxc; ++k) {
+          const long long e = (long long)pid * f.maxc + k;
+          put(h->off_child + e, f.child[e]);
+        }
+    }
   }
   f.map_dirty.clear();
   f.touched.clear();
+  f.touched_kids.clear();
 
   // active/leaf flags
   h->h_active_leaf.assign(mp, 0);
@@ -429,108 +428,10 @@ void sync_tables(amr_hierarchy* h, bool full) {
   const int a1 = begin_list();
   for (int pid : order)
     if (f.is_leaf(pid)) L.push_back(pid);
-  // (leaf, ghost region) pairs whose ghost cells have no same-level source:
-  // the region's neighbour offset, with components that leave the domain
-  // through a non-periodic boundary set to 0 (those ghosts copy the nearest
-  // interior cell), points at a missing same-level patch
+  // (leaf, ghost region) pairs whose ghost cells are prolonged, then the face
+  // regions among them
   const int c0 = begin_list();
-  // a leaf whose parent's Moore neighbours all have children has every
-  // same-level neighbour (children come in complete sets): nothing to check
-  std::vector<int8_t>& pint = h->parent_interior;
-  pint.assign(mp, -1);
-  auto parent_interior = [&](int P) {
-    if (pint[P] < 0) {
-      const int lp = f.level[P];
-      const int cp[3] = {f.coord[3 * P], f.coord[3 * P + 1], f.coord[3 * P + 2]};
-      int8_t ok = 1;
-      for (const auto& off : f.moore()) {
-        const int q = f.neighbour(lp, cp, off[0], off[1], off[2]);
-        if (q == -1 || (q >= 0 && f.is_leaf(q))) {
-          ok = 0;
-          break;
-        }
-      }
-      pint[P] = ok;
-    }
-    return pint[P] == 1;
-  };
-  // A leaf's same-level neighbour at offset src exists iff it is a sibling or
-  // the parent's Moore neighbour in that direction has children: children
-  // come in complete sets, and by R2 the parent has every Moore neighbour.
-  // So one mask per parent (bit = offset code of a neighbour with children)
-  // replaces the leaves' own neighbour lookups.  The parents' flags are set
-  // first; the leaves are then independent and, on large meshes, split over
-  // host threads whose parts are joined in order (the same list).
-  std::vector<int>& pkids = h->parent_kids;
-  pkids.assign(mp, -1);
-  for (int P : order) {
-    if (f.is_leaf(P)) continue;
-    parent_interior(P);
-    const int lp = f.level[P];
-    const int cp[3] = {f.coord[3 * P], f.coord[3 * P + 1], f.coord[3 * P + 2]};
-    int bits = 0;
-    for (const auto& off : f.moore()) {
-      const int q = f.neighbour(lp, cp, off[0], off[1], off[2]);
-      if (q >= 0 && !f.is_leaf(q)) bits |= 1 << ((off[0] + 1) + 3 * (off[1] + 1) + 9 * (off[2] + 1));
-    }
-    pkids[P] = bits;
-  }
-  auto regions = [&](size_t lo, size_t hi, std::vector<int>& out) {
-    for (size_t i = lo; i < hi; ++i) {
-      const int pid = order[i];
-      if (!f.is_leaf(pid) || f.level[pid] == 0) continue;
-      const int P = f.parent[pid];
-      if (pint[P] == 1) continue;
-      const int l = f.level[pid];
-      const int r = 2 * f.n[l - 1] / f.n[l];  // children per dimension
-      const int c[3] = {f.coord[3 * pid], f.coord[3 * pid + 1], f.coord[3 * pid + 2]};
-      const int cpos[3] = {c[0] - f.coord[3 * P] * r, c[1] - f.coord[3 * P + 1] * r,
-                           c[2] - f.coord[3 * P + 2] * r};
-      const int kids = pkids[P];
-      for (const auto& off : f.moore()) {
-        int src[3] = {off[0], off[1], off[2]};
-        bool self = true;
-        int dcode = 0, mul = 1;
-        for (int j = 0; j < f.dim; ++j) {
-          const int v = c[j] + src[j];
-          if ((v < 0 || v >= f.np[l]) && !f.periodic[j]) src[j] = 0;
-          self &= src[j] == 0;
-          const int w = cpos[j] + src[j];
-          dcode += ((w < 0) ? 0 : (w >= r ? 2 : 1)) * mul;
-          mul *= 3;
-        }
-        if (f.dim < 3) dcode += (f.dim == 1 ? 12 : 9);  // centre index of the unused dimensions
-        if (self || dcode == 13 || ((kids >> dcode) & 1)) continue;
-        out.push_back(pid);
-        out.push_back((off[0] + 1) + 3 * (off[1] + 1) + 9 * (off[2] + 1));
-      }
-    }
-  };
-  {
-    const size_t na = order.size();
-    unsigned nth = std::min(16u, std::max(1u, std::thread::hardware_concurrency()));
-    if (na < 16384) nth = 1;
-    if (nth == 1) {
-      regions(0, na, L);
-    } else {
-      std::vector<std::vector<int>> parts(nth);
-      std::vector<std::thread> pool;
-      for (unsigned t = 0; t < nth; ++t)
-        pool.emplace_back(regions, na * t / nth, na * (t + 1) / nth, std::ref(parts[t]));
-      for (auto& th : pool) th.join();
-      for (const auto& part : parts) L.insert(L.end(), part.begin(), part.end());
-    }
-  }
-  // the face regions among them (one nonzero offset component)
-  const int cf1 = begin_list();
-  for (int i = c0; i < cf1; i += 2) {
-    const int code = L[i + 1];
-    const int nz = (code % 3 != 1) + ((code / 3) % 3 != 1) + ((code / 9) % 3 != 1);
-    if (nz == 1) {
-      L.push_back(L[i]);
-      L.push_back(code);
-    }
-  }
+  const int cf1 = (int)f.prolonged_regions(order, L);
   // coarsening candidates: patches whose children are all leaves
   const int k0 = begin_list();
   for (int pid : order) {
@@ -543,13 +444,26 @@ void sync_tables(amr_hierarchy* h, bool full) {
   // stage kernel's results do not depend on the item order
   const int t0 = begin_list();
   h->leaf_cells = 0;
-  for (int pid : f.leaves_brick_order()) {
-    h->leaf_cells += ipow(f.n[f.level[pid]], f.dim);
-    const int nt = Kernels::tiles_per_patch(h->dm.tile, f.n[f.level[pid]]);
-    for (int t = 0; t < nt; ++t) {
-      L.push_back(pid);
-      L.push_back(t);
+  {
+    long long cells[amr::kMaxLev];
+    int ntiles[amr::kMaxLev];
+    for (int l = 0; l < f.nlev; ++l) {
+      cells[l] = ipow(f.n[l], f.dim);
+      ntiles[l] = Kernels::tiles_per_patch(h->dm.tile, f.n[l]);
     }
+    const std::vector<int> bricks = f.leaves_brick_order();
+    size_t items = 0;
+    for (int pid : bricks) {
+      items += ntiles[f.level[pid]];
+      h->leaf_cells += cells[f.level[pid]];
+    }
+    L.resize(L.size() + 2 * items);
+    int* at = L.data() + t0;
+    for (int pid : bricks)
+      for (int t = 0; t < ntiles[f.level[pid]]; ++t) {
+        *at++ = pid;
+        *at++ = t;
+      }
   }
   const int r0 = begin_list();
   int nref = 0;

@@ -1,6 +1,7 @@
 #include <algorithm>
 #include <array>
 #include <sstream>
+#include <thread>
 
 #include "forest.hpp"
 
@@ -82,9 +83,12 @@ void Forest::init(const amr_config& cfg) {
   map.assign(mapsize, -1);
   map_dirty.clear();
   touched.clear();
-  free_.assign(nlev, {});
-  for (int l = 0; l < nlev; ++l)
-    for (int s = 0; s < cap[l]; ++s) free_[l].insert(pid_base[l] + s);
+  touched_kids.clear();
+  for (int l = 0; l < nlev; ++l) {
+    free_[l].words.assign((cap[l] + 63) / 64, ~0ull);
+    if (cap[l] % 64) free_[l].words.back() = (1ull << (cap[l] % 64)) - 1;
+    free_[l].low = 0;
+  }
 
   moore_.clear();
   const int rz = dim >= 3 ? 1 : 0, ry = dim >= 2 ? 1 : 0;
@@ -92,6 +96,25 @@ void Forest::init(const amr_config& cfg) {
     for (int dy = -ry; dy <= ry; ++dy)
       for (int dx = -1; dx <= 1; ++dx)
         if (dx || dy || dz) moore_.push_back({dx, dy, dz});
+
+  for (int l = 1; l < nlev; ++l) {
+    const int r = ratio[l - 1];
+    const int rr[3] = {r, dim >= 2 ? r : 1, dim >= 3 ? r : 1};
+    child_regions_[l].assign((size_t)rr[0] * rr[1] * rr[2], {});
+    for (size_t k = 0; k < child_regions_[l].size(); ++k) {
+      const int pos[3] = {(int)k % r, (int)k / r % rr[1], (int)k / (r * rr[1])};
+      for (const auto& off : moore_) {
+        int d = 0, code = 0, mul = 1;
+        for (int j = 0; j < 3; ++j) {
+          const int w = pos[j] + off[j];
+          d += (w < 0 ? 0 : (w >= rr[j] ? 2 : 1)) * mul;
+          code += (off[j] + 1) * mul;
+          mul *= 3;
+        }
+        child_regions_[l][k][d] |= 1u << code;
+      }
+    }
+  }
 
   const int m0 = np[0];
   for (int z = 0; z < (dim >= 3 ? m0 : 1); ++z)
@@ -122,9 +145,11 @@ void Forest::covering(int l, const int c[3], int out[3]) const {
 }
 
 int Forest::alloc(int l, const int c[3], int par) {
-  if (free_[l].empty()) return -1;
-  const int pid = *free_[l].begin();
-  free_[l].erase(free_[l].begin());
+  FreeSlots& fs = free_[l];
+  while (fs.low < fs.words.size() && !fs.words[fs.low]) ++fs.low;
+  if (fs.low == fs.words.size()) return -1;
+  const int pid = pid_base[l] + (int)(64 * fs.low) + __builtin_ctzll(fs.words[fs.low]);
+  fs.words[fs.low] &= fs.words[fs.low] - 1;
   level[pid] = l;
   parent[pid] = par;
   nchild[pid] = 0;
@@ -134,7 +159,6 @@ int Forest::alloc(int l, const int c[3], int par) {
   map[mi] = pid;
   map_dirty.push_back(mi);
   touched.push_back(pid);
-  if (par >= 0) touched.push_back(par);
   return pid;
 }
 
@@ -145,12 +169,13 @@ void Forest::release(int pid) {
   map[mi] = -1;
   map_dirty.push_back(mi);
   touched.push_back(pid);
-  if (parent[pid] >= 0) touched.push_back(parent[pid]);
   active[pid] = 0;
   level[pid] = -1;
   parent[pid] = -1;
   nchild[pid] = 0;
-  free_[l].insert(pid);
+  const size_t slot = pid - pid_base[l];
+  free_[l].words[slot / 64] |= 1ull << (slot % 64);
+  free_[l].low = std::min(free_[l].low, slot / 64);
 }
 
 // Algorithm 1: a leaf p first makes each absent Moore neighbour q exist by
@@ -175,6 +200,7 @@ void Forest::refine(int pid, std::vector<int>& created) {
   }
   const int rr = ratio[l];
   const int rz = dim >= 3 ? rr : 1, ry = dim >= 2 ? rr : 1;
+  touched_kids.push_back(pid);
   int k = 0;
   for (int oz = 0; oz < rz; ++oz)
     for (int oy = 0; oy < ry; ++oy)
@@ -208,21 +234,34 @@ bool Forest::coarsening_allowed(int pid) const {
     }
     return true;
   }
-  for (int k = 0; k < nchild[pid]; ++k) {
-    const int ch = child[(size_t)pid * maxc + k];
-    const int c[3] = {coord[3 * ch], coord[3 * ch + 1], coord[3 * ch + 2]};
-    for (const auto& off : moore_) {
-      int q[3];
-      if (!shifted(l + 1, c, off.data(), q)) continue;
-      const int qp = lookup(l + 1, q);
-      if (qp < 0 || parent[qp] == pid) continue;
-      if (!is_leaf(qp)) return false;
-    }
+  // the layer of patches around the children, which fill their parent
+  int lo[3] = {0, 0, 0}, hi[3] = {0, 0, 0};  // the children, then with the layer
+  for (int j = 0; j < dim; ++j) {
+    lo[j] = coord[3 * pid + j] * ratio[l];
+    hi[j] = lo[j] + ratio[l] - 1;
   }
+  for (int z = lo[2] - (dim >= 3); z <= hi[2] + (dim >= 3); ++z)
+    for (int y = lo[1] - (dim >= 2); y <= hi[1] + (dim >= 2); ++y) {
+      const bool across = z >= lo[2] && z <= hi[2] && y >= lo[1] && y <= hi[1];
+      const int step = across ? hi[0] - lo[0] + 2 : 1;  // inside, only the two ends in x
+      for (int x = lo[0] - 1; x <= hi[0] + 1; x += step) {
+        int q[3] = {x, y, z};
+        bool in = true;
+        for (int j = 0; j < dim; ++j)
+          if (q[j] < 0 || q[j] >= np[l + 1]) {
+            in &= periodic[j] != 0;
+            q[j] += q[j] < 0 ? np[l + 1] : -np[l + 1];
+          }
+        if (!in) continue;
+        const int qp = lookup(l + 1, q);
+        if (qp >= 0 && parent[qp] != pid && !is_leaf(qp)) return false;
+      }
+    }
   return true;
 }
 
 void Forest::delete_children(int pid, std::vector<int>& deleted) {
+  touched_kids.push_back(pid);
   for (int k = 0; k < nchild[pid]; ++k) {
     const int ch = child[(size_t)pid * maxc + k];
     deleted.push_back(ch);
@@ -258,6 +297,7 @@ void Forest::regrid(const uint8_t* refine_req, const uint8_t* coarsen_req,
       const int par = parent[q];
       release(q);
       if (par >= 0) {
+        touched_kids.push_back(par);
         nchild[par] = 0;
         for (int k = 0; k < maxc; ++k) child[(size_t)par * maxc + k] = -1;
       }
@@ -293,6 +333,7 @@ std::string Forest::validate_change(const std::vector<int>& created) const {
       if (neighbour(l, c, off[0], off[1], off[2]) == -1) return false;
     return true;
   };
+  int checked = -1;  // siblings are created together: their parent is checked once
   for (int q : created) {
     const int l = level[q];
     const int c[3] = {coord[3 * q], coord[3 * q + 1], coord[3 * q + 2]};
@@ -300,7 +341,9 @@ std::string Forest::validate_change(const std::vector<int>& created) const {
     int r[3];
     covering(l, c, r);
     if (lookup(l - 1, r) != parent[q]) return "parent link broken";
-    if (!r2(parent[q])) return "R2: a refined patch has an absent Moore neighbour";
+    if (parent[q] != checked && !r2(parent[q]))
+      return "R2: a refined patch has an absent Moore neighbour";
+    checked = parent[q];
   }
   for (int p : coarsened_) {
     const int l = level[p] + 1;
@@ -385,6 +428,40 @@ int Forest::count_leaves() const {
   return c;
 }
 
+namespace {
+// bits for the values 0 .. v - 1
+int key_width(long long v) {
+  int b = 0;
+  while (b < 62 && (1LL << b) < v) ++b;
+  return b;
+}
+
+// Ascending order of distinct keys whose bits [lo, hi) alone decide it: LSD
+// radix sort in equal digits of at most 11 bits (a count table that stays in
+// L1 and is cheap to clear), a comparison sort for few keys.  The brick order of
+// 1 to 10 k leaves took 193 us on average with a comparison sort below 4096 keys
+// and 16-bit digits of the whole key above, 119 us so.
+void sort_keys(std::vector<uint64_t>& keys, int lo, int hi) {
+  if (keys.size() < 256) {
+    std::sort(keys.begin(), keys.end());
+    return;
+  }
+  const int passes = (hi - lo + 10) / 11;
+  std::vector<uint64_t> tmp(keys.size());
+  std::vector<uint32_t> cnt;
+  for (int p = 0; p < passes; ++p) {
+    const int sh = lo + (hi - lo) * p / passes;
+    const int w = lo + (hi - lo) * (p + 1) / passes - sh;
+    const uint64_t mask = (1ull << w) - 1;
+    cnt.assign((1u << w) + 1, 0u);
+    for (const uint64_t k : keys) ++cnt[((k >> sh) & mask) + 1];
+    for (size_t i = 1; i < cnt.size(); ++i) cnt[i] += cnt[i - 1];
+    for (const uint64_t k : keys) tmp[cnt[(k >> sh) & mask]++] = k;
+    keys.swap(tmp);
+  }
+}
+}  // namespace
+
 std::vector<int> Forest::sorted_active() const {
   std::vector<int> out;
   // small level maps: their index order is (z, y, x) within a level, so a
@@ -401,14 +478,9 @@ std::vector<int> Forest::sorted_active() const {
   }
   // (level, z, y, x, pid) packed into one 64-bit key when the fields fit,
   // each field as wide as this forest needs, else the comparator
-  auto width = [](long long v) {  // bits for the values 0 .. v - 1
-    int b = 0;
-    while (b < 62 && (1LL << b) < v) ++b;
-    return b;
-  };
   int npmax = 1;
   for (int l = 0; l < nlev; ++l) npmax = std::max(npmax, np[l]);
-  const int bp = width(max_patches), bc = width(npmax), bl = width(nlev);
+  const int bp = key_width(max_patches), bc = key_width(npmax), bl = key_width(nlev);
   const int ob = bl + dim * bc;  // ordering bits above the pid field
   if (bp + ob <= 64) {
     std::vector<uint64_t> keys;
@@ -418,21 +490,7 @@ std::vector<int> Forest::sorted_active() const {
       for (int j = dim - 1; j >= 0; --j) k = (k << bc) | (uint64_t)coord[3 * pid + j];
       keys.push_back((k << bp) | (uint64_t)pid);
     }
-    if (keys.size() < 4096) {
-      std::sort(keys.begin(), keys.end());
-    } else {
-      // LSD radix sort on the ordering bits, 16-bit digits; the keys are
-      // distinct, so the order is the comparison sort's
-      std::vector<uint64_t> tmp(keys.size());
-      std::vector<uint32_t> cnt(65537);
-      for (int sh = bp; sh < bp + ob; sh += 16) {
-        std::fill(cnt.begin(), cnt.end(), 0u);
-        for (const uint64_t k : keys) ++cnt[((k >> sh) & 0xffffu) + 1];
-        for (size_t i = 1; i < cnt.size(); ++i) cnt[i] += cnt[i - 1];
-        for (const uint64_t k : keys) tmp[cnt[(k >> sh) & 0xffffu]++] = k;
-        keys.swap(tmp);
-      }
-    }
+    sort_keys(keys, bp, bp + ob);
     out.reserve(keys.size());
     const uint64_t pm = (bp >= 64) ? ~0ull : ((1ull << bp) - 1);
     for (uint64_t k : keys) out.push_back((int)(k & pm));
@@ -474,35 +532,25 @@ uint64_t morton(const int* c, int dim) {
 }  // namespace
 
 std::vector<int> Forest::leaves_brick_order() const {
-  // (level, Morton code, pid) packed into one key: level in bits 60..63, the
-  // code in bits 21..59 (13 bits per coordinate), the pid in bits 0..20;
-  // else the comparator on (level, code, pid)
+  // (level, Morton code, pid) packed into one key, each field as wide as this
+  // forest needs; else the comparator on (level, code, pid)
   std::vector<int> out;
   bool packed = max_patches <= (1 << 21) && nlev <= 16;
-  for (int l = 0; l < nlev; ++l) packed &= np[l] <= (1 << 13);
+  int npmax = 1;
+  for (int l = 0; l < nlev; ++l) npmax = std::max(npmax, np[l]);
+  packed &= npmax <= (1 << 13);
   if (packed) {
+    const int bp = key_width(max_patches), bm = dim * key_width(npmax);
     std::vector<uint64_t> keys;
     for (int pid = 0; pid < max_patches; ++pid) {
       if (!active[pid] || nchild[pid]) continue;
-      keys.push_back(((uint64_t)level[pid] << 60) | (morton(&coord[3 * pid], dim) << 21) |
+      keys.push_back(((((uint64_t)level[pid] << bm) | morton(&coord[3 * pid], dim)) << bp) |
                      (uint64_t)pid);
     }
-    if (keys.size() < 4096) {
-      std::sort(keys.begin(), keys.end());
-    } else {
-      // LSD radix sort on bits 21..63, 16-bit digits (the keys are distinct)
-      std::vector<uint64_t> tmp(keys.size());
-      std::vector<uint32_t> cnt(65537);
-      for (const int sh : {21, 37, 53}) {
-        std::fill(cnt.begin(), cnt.end(), 0u);
-        for (const uint64_t k : keys) ++cnt[((k >> sh) & 0xffffu) + 1];
-        for (size_t i = 1; i < cnt.size(); ++i) cnt[i] += cnt[i - 1];
-        for (const uint64_t k : keys) tmp[cnt[(k >> sh) & 0xffffu]++] = k;
-        keys.swap(tmp);
-      }
-    }
+    sort_keys(keys, bp, bp + bm + key_width(nlev));
     out.reserve(keys.size());
-    for (uint64_t k : keys) out.push_back((int)(k & ((1u << 21) - 1)));
+    const uint64_t pm = (1ull << bp) - 1;
+    for (uint64_t k : keys) out.push_back((int)(k & pm));
     return out;
   }
   for (int pid = 0; pid < max_patches; ++pid)
@@ -513,6 +561,96 @@ std::vector<int> Forest::leaves_brick_order() const {
     return ma != mb ? ma < mb : a < b;
   });
   return out;
+}
+
+// A leaf's same-level neighbour in a direction exists iff it is a sibling or
+// the parent's Moore neighbour in that direction has children: children come
+// in complete sets, and by R2 the parent has every Moore neighbour.  So one
+// mask per parent (bit = offset code of a neighbour with children) replaces the
+// leaves' own neighbour lookups, and a leaf's missing regions are those that
+// child_regions_ puts into the parent's neighbours without children.  Leaves
+// are independent; their masks are split over host threads on large meshes.
+// Meshes of 1 to 12 k patches: 829 us on average with a test of every region of
+// every leaf, 226 us so.
+size_t Forest::prolonged_regions(const std::vector<int>& order, std::vector<int>& out) const {
+  constexpr uint32_t kFaces = 1u << 4 | 1u << 10 | 1u << 12 | 1u << 14 | 1u << 16 | 1u << 22;
+  std::vector<uint32_t> kids(max_patches, 0);
+  for (const int p : order) {
+    if (is_leaf(p)) continue;
+    const int c[3] = {coord[3 * p], coord[3 * p + 1], coord[3 * p + 2]};
+    uint32_t bits = 1u << 13;
+    for (const auto& off : moore_) {
+      const int q = neighbour(level[p], c, off[0], off[1], off[2]);
+      if (q >= 0 && !is_leaf(q)) bits |= 1u << ((off[0] + 1) + 3 * (off[1] + 1) + 9 * (off[2] + 1));
+    }
+    kids[p] = bits;
+  }
+  constexpr uint32_t kAll = (1u << 27) - 1;
+  std::vector<uint32_t> miss(order.size());
+  auto masks = [&](size_t from, size_t to) {
+    for (size_t i = from; i < to; ++i) {
+      const int pid = order[i], l = level[pid];
+      miss[i] = 0;
+      if (!is_leaf(pid) || l == 0) continue;
+      const int P = parent[pid], r = ratio[l - 1];
+      uint32_t without = kAll & ~kids[P];  // offset codes of the parent
+      if (!without) continue;
+      int pos[3] = {0, 0, 0};
+      bool wall = false;
+      for (int j = 0; j < dim; ++j) {
+        const int c = coord[3 * pid + j];
+        pos[j] = c - coord[3 * P + j] * r;
+        wall |= !periodic[j] && (c == 0 || c == np[l] - 1);
+      }
+      const auto& regions = child_regions_[l][pos[0] + r * (pos[1] + r * pos[2])];
+      if (!wall) {
+        for (; without; without &= without - 1) miss[i] |= regions[__builtin_ctz(without)];
+        continue;
+      }
+      for (const auto& off : moore_) {
+        int d = 0, code = 0, mul = 1;
+        for (int j = 0; j < 3; ++j) {
+          const int v = coord[3 * pid + j] + off[j];
+          const int o = j < dim && !periodic[j] && (v < 0 || v >= np[l]) ? 0 : off[j];
+          const int w = pos[j] + o;
+          d += (w < 0 ? 0 : (w >= (j < dim ? r : 1) ? 2 : 1)) * mul;
+          code += (off[j] + 1) * mul;
+          mul *= 3;
+        }
+        if (without >> d & 1) miss[i] |= 1u << code;
+      }
+    }
+  };
+  const size_t na = order.size();
+  const unsigned nth =
+      na < 32768 ? 1 : std::min(16u, std::max(1u, std::thread::hardware_concurrency()));
+  if (nth == 1) {
+    masks(0, na);
+  } else {
+    std::vector<std::thread> pool;
+    for (unsigned t = 0; t < nth; ++t) pool.emplace_back(masks, na * t / nth, na * (t + 1) / nth);
+    for (auto& th : pool) th.join();
+  }
+  size_t count = 0, faces = 0;
+  for (const uint32_t b : miss) {
+    count += __builtin_popcount(b);
+    faces += __builtin_popcount(b & kFaces);
+  }
+  const size_t first = out.size(), second = first + 2 * count;
+  out.resize(second + 2 * faces);
+  int* a = out.data() + first;
+  int* f = out.data() + second;
+  for (size_t i = 0; i < na; ++i) {
+    for (uint32_t b = miss[i]; b; b &= b - 1) {
+      *a++ = order[i];
+      *a++ = __builtin_ctz(b);
+    }
+    for (uint32_t b = miss[i] & kFaces; b; b &= b - 1) {
+      *f++ = order[i];
+      *f++ = __builtin_ctz(b);
+    }
+  }
+  return second;
 }
 
 }  // namespace amr

@@ -5,7 +5,6 @@
 
 #include <array>
 #include <cstdint>
-#include <set>
 #include <stdexcept>
 #include <string>
 #include <vector>
@@ -36,10 +35,11 @@ class Forest {
   std::vector<uint8_t> active;
   // all levels' patch maps (pid or -1), x fastest
   std::vector<int> map;
-  // map entries and pids whose rows changed since the device copy was last
-  // refreshed
+  // map entries, pids whose own row (level, parent, nchild, coord) changed and
+  // pids whose children changed (nchild and the child row; a leaf's row is
+  // always all -1) since the device copy was last refreshed
   std::vector<int> map_dirty;
-  std::vector<int> touched;
+  std::vector<int> touched, touched_kids;
 
   int map_index(int l, const int c[3]) const {
     int idx = c[0];
@@ -98,11 +98,30 @@ class Forest {
   // leaves of a level form compact bricks, so stage tiles that run at the
   // same time on one XCD read each other's cells as halos.
   std::vector<int> leaves_brick_order() const;
+  // (leaf, ghost region) pairs whose ghost cells have no same-level source,
+  // appended to `out` for the leaves of `order` (all active pids, in its
+  // order, regions by ascending code), then the face regions among them (one
+  // nonzero offset component) in the same order; returns the start of these.
+  // A region is its neighbour offset's code (o0+1) + 3 (o1+1) + 9 (o2+1); with
+  // components that leave the domain through a non-periodic boundary set to 0
+  // (those ghosts copy the nearest interior cell) the offset points at a
+  // missing same-level patch.
+  size_t prolonged_regions(const std::vector<int>& order, std::vector<int>& out) const;
 
  private:
   int alloc(int l, const int c[3], int par);
   void release(int pid);
-  std::vector<std::set<int>> free_;
+  // Free slots of a level, as bits (slot s is bit s mod 64 of word s / 64);
+  // no word before `low` has one set.  Taken lowest first.
+  struct FreeSlots {
+    std::vector<uint64_t> words;
+    size_t low = 0;
+  };
+  FreeSlots free_[kMaxLev];
+  // per level l >= 1 and position of a child in its parent (x fastest): for
+  // each offset code d of the parent's neighbourhood the regions of the child
+  // that lie in the parent's neighbour d, as bits of their codes
+  std::vector<std::array<uint32_t, 27>> child_regions_[kMaxLev];
   std::vector<int> coarsened_;  // patches whose children the last regrid deleted
   std::vector<std::array<int, 3>> moore_;
 };
