@@ -684,9 +684,12 @@ __device__ __forceinline__ void edge_char(const DevMesh& m, const double* sP, in
   for (int v = 0; v < NV; ++v) sF[v * NED + e] = fma(-S, UX[1][v] - UX[0][v], FR[v] + FL[v]);
 }
 
-// Face fluxes G of direction J (flux form of Eq. (9)) from the edge fluxes
-// in sF, their divergence into acc, and the patch-boundary faces into the
-// flux registers.
+// Divergence of the face fluxes G = F - (F_- - 2 F + F_+) / 24 of direction J
+// (flux form of Eq. (9)) from the edge fluxes in sF into acc, as the difference
+// F_0 - F_-1 and the correction of it (five operations per variable; the two
+// face fluxes first took eight: 2D, 2.75 M cells 160.4 against 158.3 us, 0.28 M
+// 22.2 against 21.2 us; 3D the same within 0.5 %), and the face fluxes
+// themselves on patch boundaries with flux registers, by their few threads.
 template <int D, int TX, int TY, int TZ, int NT, int J>
 __device__ __forceinline__ void cells_at(const double* sF, double* __restrict__ frp, int n,
                                          const int o[3], double acc[][D + 2], double inv_h,
@@ -723,17 +726,23 @@ __device__ __forceinline__ void cells_at(const double* sF, double* __restrict__ 
     // the flux registers of this face (variable v at v nface + tang of the
     // face's block; 32-bit offsets, 24-bit products), written per variable
     const bool lo = i == 0 && lo_reg, hi = i == n - 1 && hi_reg;
-    double* fb = frp + __mul24((J * 2 + (hi ? 1 : 0)) * NV, nface) + tang;
 #pragma unroll
     for (int v = 0; v < NV; ++v) {
       // edge fluxes are stored doubled (the Rusanov 1/2 is applied here, as
       // 1/2 inv_h, and to the boundary faces; power-of-two scaling is exact)
       const double* F = sF + v * NED + eb;
       const double Fm2 = F[0], Fm1 = F[ESTEP], F0 = F[2 * ESTEP], Fp1 = F[3 * ESTEP];
-      const double Gp = fma(-c24, fma(-2.0, F0, Fm1) + Fp1, F0);
-      const double Gm = fma(-c24, fma(-2.0, Fm1, Fm2) + F0, Fm1);
-      acc[cc][v] = fma(-(Gp - Gm), half_inv_h, acc[cc][v]);
-      if (lo || hi) fb[__mul24(v, nface)] = 0.5 * (hi ? Gp : Gm);
+      const double d = F0 - Fm1;
+      const double dG = fma(c24, fma(3.0, d, Fm2 - Fp1), d);
+      acc[cc][v] = fma(-dG, half_inv_h, acc[cc][v]);
+    }
+    if (lo || hi) {
+      double* fb = frp + __mul24((J * 2 + (hi ? 1 : 0)) * NV, nface) + tang;
+#pragma unroll 1
+      for (int v = 0; v < NV; ++v) {
+        const double* F = sF + v * NED + eb + (hi ? ESTEP : 0);
+        fb[__mul24(v, nface)] = 0.5 * fma(-c24, fma(-2.0, F[ESTEP], F[0]) + F[2 * ESTEP], F[ESTEP]);
+      }
     }
   }
 }
