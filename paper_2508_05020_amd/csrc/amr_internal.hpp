@@ -68,6 +68,23 @@ struct ListView {
   const int* dir = nullptr;
 };
 
+// Work item of the stage kernel: a tile of a leaf, with what its block would
+// else gather through the tables one dependent load after the other (level and
+// position of the patch, then its neighbours, at the end the parent).  One
+// 64-byte line per item, read by the scalar unit.
+struct alignas(64) StageItem {
+  int pid, level;
+  int cf, regs;      // coarse/fine faces of the leaf; faces with flux registers
+  int o[3];          // first cell of the tile in the patch
+  int nb[6];         // same-level patch across each face (x-, x+, y-, ...): its pid,
+                     // kNbNone, or kNbWall beyond a transmissive boundary
+  int px;            // position of the patch along x (1D prolongation)
+  long long parent;  // level >= 1: offset in a state buffer of the parent cell
+                     // (first variable) that covers the tile's first cells
+};
+static_assert(sizeof(StageItem) == 64, "one line per item");
+constexpr int kNbNone = -1, kNbWall = -2;
+
 // Blocks of the 3D tag launch: patches and 8^3 tiles per patch of each level.
 struct TagLevels {
   int count[kMaxLev], tiles[kMaxLev];
@@ -93,20 +110,27 @@ struct Kernels {
   // from that source by the kernel itself; the others are prolonged by the
   // kernel too in 1D (into Uin's ghost layers; *err set where a source is
   // missing), in 2D and 3D they come from ghost layers filled before by fill_cf
+  // dir (nullable, recorded launches): list directory entry whose count is read at
+  // run time; `count` then only sizes the grid
   // lam_next (nullable, stage 3 only): accumulate the next step's CFL rate
-  // over leaf cells not on coarse/fine faces (cfmask: per-pid face bits)
+  // over leaf cells not on coarse/fine faces
   // ev0/ev1 (optional): events stamped at the dispatch's own start and end.
   // lam_in (stage 1 only, optional): take dt = CFL / *lam_in instead of *dt,
   // write it to *dt_out and clear *lam_next (the slot stage 3 accumulates in)
-  // In the stage modes a tile of a leaf without coarse/fine faces (level >= 1,
-  // cfmask 0: refluxing does not change it) also restricts its new values into
+  // In the stage modes a tile of a leaf without coarse/fine faces (level >= 1:
+  // refluxing does not change it) also restricts its new values into
   // its parent patch.
   static void stage(const DevMesh& m, int mode, double* Uin, int* err, const double* Un,
-                    double* out, double* fr, const int* tiles, int count, const int* dir,
-                    const double* dt, bool fuse, unsigned long long* lam_next,
-                    const uint8_t* cfmask, hipStream_t s, hipEvent_t ev0 = nullptr,
+                    double* out, double* fr, const StageItem* items, int count, const int* dir,
+                    const double* dt, bool fuse, unsigned long long* lam_next, hipStream_t s,
+                    hipEvent_t ev0 = nullptr,
                     hipEvent_t ev1 = nullptr, const unsigned long long* lam_in = nullptr,
                     double* dt_out = nullptr);
+  // The stage kernel's items for a list of (pid, tile of variant m.tile) pairs;
+  // cfmask: per pid the leaf's coarse/fine faces, then (from max_patches) the
+  // faces with flux registers.  Built again whenever lists or tables change.
+  static void stage_items(const DevMesh& m, const int* tiles, int count, const uint8_t* cfmask,
+                          StageItem* items, hipStream_t s);
   static void reflux(const DevMesh& m, int mode, double* out, const double* fr,
                      const int* list, int count, const double* dt, double w,
                      unsigned long long* lam_next, hipStream_t s);

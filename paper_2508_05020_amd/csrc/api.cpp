@@ -112,18 +112,21 @@ struct amr_hierarchy {
   int* d_flags = nullptr;  // [0] fill/prolong error, [1] nonphysical count
   int* d_lists = nullptr;
   long long lists_cap = 0;
+  amr::StageItem* d_items = nullptr;  // the stage kernel's items, in the order of the tile list
   // list directory: {offset into d_lists, count} of the lists the step's
   // kernels take (entries kDirCf, kDirTiles, kDirReflux, kDirPairs,
   // kDirCfFace, kDirRestr + level), rewritten with the lists; batched
   // launches read it, so a recorded step survives a regrid
   int* d_dir = nullptr;
-  int* h_dir = nullptr;  // pinned staging of the directory
-  int* d_pairs = nullptr;
+  int* h_dir = nullptr;  // the directory in h_stage
   long long pairs_cap = 0;
-  // pinned host staging for table/list uploads (reused; every regrid first
-  // drains the stream, so earlier copies from it have completed)
+  // What a regrid uploads, in one copy: the directory, d_active_leaf, d_cfmask
+  // and the lists at fixed offsets, the changed table entries after the lists.
+  // d_lists and those are places in one device buffer, laid out as the pinned
+  // host staging (reused; every regrid first drains the stream, so earlier
+  // copies from it have completed).
   char* h_stage = nullptr;
-  size_t h_stage_bytes = 0;
+  size_t lists_off = 0;  // of the lists, from the directory's start
   uint8_t* h_req = nullptr;  // pinned: refine and coarsen requests read back by amr_adapt
 
   // host mirrors of the work lists
@@ -199,8 +202,6 @@ struct amr_hierarchy {
     h_stage = nullptr;
     if (h_req) (void)hipHostFree(h_req);
     h_req = nullptr;
-    if (h_dir) (void)hipHostFree(h_dir);
-    h_dir = nullptr;
     for (hipEvent_t e : ev_pool) (void)hipEventDestroy(e);
     ev_pool.clear();
     for (void* p : owned) {
@@ -519,23 +520,20 @@ void sync_tables(amr_hierarchy* h, bool full) {
   if ((long long)L.size() > h->lists_cap) throw StateError("work-list buffer too small");
   const long long np = (long long)pairs.size() / 2;
   if (np > h->pairs_cap) throw StateError("table update buffer too small");
-  char* st = h->h_stage;
-  int* sl = (int*)st;
-  int* sp = sl + h->lists_cap;
-  uint8_t* sa = (uint8_t*)(sp + 2 * h->pairs_cap);
+  int* sl = (int*)(h->h_stage + h->lists_off);
+  uint8_t* sa = (uint8_t*)h->h_stage + (h->d_active_leaf - (uint8_t*)h->d_dir);
+  uint8_t* sm = (uint8_t*)h->h_stage + (h->d_cfmask - (uint8_t*)h->d_dir);
+  const size_t pairs_at = (L.size() + 1) / 2 * 2;  // in the list buffer
   std::copy(L.begin(), L.end(), sl);
-  std::copy(pairs.begin(), pairs.end(), sp);
+  std::copy(pairs.begin(), pairs.end(), sl + pairs_at);
   std::copy(h->h_active_leaf.begin(), h->h_active_leaf.end(), sa);
-  if (!L.empty())
-    HIP_OK(hipMemcpyAsync(h->d_lists, sl, L.size() * sizeof(int), hipMemcpyHostToDevice,
-                          h->stream));
   const int* dd = h->d_dir;
   h->all = {h->d_lists + a0, a1 - a0};
   h->leaves = {h->d_lists + a1, c0 - a1};
   h->cfregions = {h->d_lists + c0, (cf1 - c0) / 2, dd + 2 * kDirCf};
   h->cffaces = {h->d_lists + cf1, (k0 - cf1) / 2, dd + 2 * kDirCfFace};
   h->cands = {h->d_lists + k0, t0 - k0};
-  h->tiles = {h->d_lists + t0, (r0 - t0) / 2, dd + 2 * kDirTiles};
+  h->tiles = {(const int*)h->d_items, (r0 - t0) / 2, dd + 2 * kDirTiles};
   h->reflux = {h->d_lists + r0, nref, dd + 2 * kDirReflux};
   h->post_pairs = {h->d_lists + pp0, pp1 - pp0, dd + 2 * kDirPairs};
   for (int l = 0; l < f.nlev; ++l) {
@@ -544,12 +542,10 @@ void sync_tables(amr_hierarchy* h, bool full) {
     h->fresh[l] = {h->d_lists + ns[l], ns[l + 1] - ns[l]};
   }
   {
-    // the previous directory upload has completed: every regrid drains the
-    // stream before rebuilding the lists
     int* hd = h->h_dir;
     std::fill(hd, hd + 2 * kDirEntries, 0);
     auto put = [&](int e, const amr::ListView& lv) {
-      hd[2 * e] = (int)(lv.ptr - h->d_lists);
+      hd[2 * e] = e == kDirTiles ? 0 : (int)(lv.ptr - h->d_lists);
       hd[2 * e + 1] = lv.count;
     };
     put(kDirCf, h->cfregions);
@@ -558,16 +554,12 @@ void sync_tables(amr_hierarchy* h, bool full) {
     put(kDirReflux, h->reflux);
     put(kDirPairs, h->post_pairs);
     for (int l = 0; l < f.nlev; ++l) put(kDirRestr + l, h->restr_post[l]);
-    HIP_OK(hipMemcpyAsync(h->d_dir, hd, 2 * kDirEntries * sizeof(int), hipMemcpyHostToDevice,
-                          h->stream));
   }
-  HIP_OK(hipMemcpyAsync(h->d_active_leaf, sa, mp, hipMemcpyHostToDevice, h->stream));
   // coarse/fine faces of coarse-side leaves, then the faces whose flux
   // registers refluxing reads: those coarse faces, and every face of a leaf
   // across which no same-level patch lies inside the domain (a fine-side
   // face of a coarse/fine interface, by R2); the stage kernel writes only
   // these registers
-  uint8_t* sm = sa + mp;
   std::fill(sm, sm + 2 * mp, (uint8_t)0);
   for (int i = 0; i < nref; ++i) sm[L[r0 + 2 * i]] = (uint8_t)L[r0 + 2 * i + 1];
   uint8_t* sw = sm + mp;
@@ -581,14 +573,18 @@ void sync_tables(amr_hierarchy* h, bool full) {
     for (int j = 0; j < f.dim; ++j)
       if (o[j] != 0) sw[L[i]] |= (uint8_t)(1 << (2 * j + (o[j] > 0 ? 1 : 0)));
   }
-  HIP_OK(hipMemcpyAsync(h->d_cfmask, sm, 2 * mp, hipMemcpyHostToDevice, h->stream));
+  HIP_OK(hipMemcpyAsync(h->d_dir, h->h_stage,
+                        h->lists_off + (pairs_at + pairs.size()) * sizeof(int),
+                        hipMemcpyHostToDevice, h->stream));
   if (np > 0) {
-    HIP_OK(hipMemcpyAsync(h->d_pairs, sp, pairs.size() * sizeof(int), hipMemcpyHostToDevice,
-                          h->stream));
-    Kernels::scatter_int(h->d_tab, h->d_pairs, (int)np, h->stream);
+    Kernels::scatter_int(h->d_tab, h->d_lists + pairs_at, (int)np, h->stream);
     h->check_launch();
   }
+  Kernels::stage_items(h->dm, h->d_lists + t0, h->tiles.count, h->d_cfmask, h->d_items, h->stream);
+  h->check_launch();
 }
+
+constexpr int kItemInts = sizeof(amr::StageItem) / sizeof(int);
 
 // Per-patch mode launches one kernel per list entry (the unfused baseline).
 template <typename F>
@@ -720,11 +716,12 @@ void do_stage(amr_hierarchy* h, int stage, const double* dt,
   stage_fill(h, s);
   const Kernels::TileVariant tv = Kernels::variant(h->dm.tile);
   const int tcells = tv.tx * tv.ty * tv.tz;
-  over_list_dir(h, h->tiles, 2, kGnStage, [&](const int* p, int c, const int* dir) {
+  over_list_dir(h, h->tiles, kItemInts, kGnStage, [&](const int* p, int c, const int* dir) {
     hipEvent_t a = nullptr, b = nullptr;
     if (h->profiling) h->prof_pair(&a, &b, (long long)c * tcells);
-    Kernels::stage(h->dm, stage, h->U[s], h->d_flags, h->U[0], h->U[d], h->fr, p, c, dir, dt, h->fuse_halo,
-                   (stage == 3 || lam_in) ? lam_next : nullptr, h->d_cfmask, h->stream, a, b,
+    Kernels::stage(h->dm, stage, h->U[s], h->d_flags, h->U[0], h->U[d], h->fr,
+                   dir ? h->d_items : (const amr::StageItem*)p, c, dir, dt, h->fuse_halo,
+                   (stage == 3 || lam_in) ? lam_next : nullptr, h->stream, a, b,
                    lam_in, dt_out);
   });
   if (h->exec_mode == AMR_EXEC_BATCHED) {
@@ -941,9 +938,6 @@ amr_status amr_create_hierarchy(const amr_config* cfg, const amr_allocator* allo
     }
     h->fr = (double*)h->dev_alloc(h->fr_doubles * sizeof(double));
     h->d_tab = (int*)h->dev_alloc(h->tab_ints * sizeof(int));
-    h->d_active_leaf = (uint8_t*)h->dev_alloc(mp);
-    // per pid: coarse/fine face mask [0, mp), flux-register write mask [mp, 2 mp)
-    h->d_cfmask = (uint8_t*)h->dev_alloc(2 * mp);
     h->d_has_tag = (uint8_t*)h->dev_alloc(mp);
     h->d_refine = (uint8_t*)h->dev_alloc(mp);
     h->d_coarsen = (uint8_t*)h->dev_alloc(mp);
@@ -964,15 +958,23 @@ amr_status amr_create_hierarchy(const amr_config* cfg, const amr_allocator* allo
     // their faces: 2 per region and patch; tiles: 2 per tile
     const long long regions = ipow(3, cfg->dim) - 1;
     h->lists_cap = 2 * tiles + (9 + 2 * regions + 2 * 2 * cfg->dim) * mp + 64;
-    h->d_lists = (int*)h->dev_alloc(h->lists_cap * sizeof(int));
-    h->d_dir = (int*)h->dev_alloc(2 * kDirEntries * sizeof(int));
-    HIP_OK(hipHostMalloc((void**)&h->h_dir, 2 * kDirEntries * sizeof(int), hipHostMallocDefault));
+    h->d_items = (amr::StageItem*)h->dev_alloc(tiles * sizeof(amr::StageItem));
     h->pairs_cap = mp * (6 + f.maxc) + 2 * (long long)f.map.size() + 64;
     h->pairs_cap = std::min<long long>(h->pairs_cap, 64LL << 20);
-    h->d_pairs = (int*)h->dev_alloc(h->pairs_cap * 2 * sizeof(int));
-    h->h_stage_bytes = (size_t)h->lists_cap * sizeof(int) + (size_t)h->pairs_cap * 2 * sizeof(int) +
-                       3 * (size_t)mp + 256;
-    HIP_OK(hipHostMalloc((void**)&h->h_stage, h->h_stage_bytes, hipHostMallocDefault));
+    // directory, active/leaf flags, per pid coarse/fine face mask [0, mp) and
+    // flux-register write mask [mp, 2 mp), lists and table updates
+    auto lines = [](size_t bytes) { return (bytes + 255) / 256 * 256; };
+    const size_t active_off = lines(2 * kDirEntries * sizeof(int));
+    const size_t cfmask_off = active_off + lines(mp);
+    h->lists_off = cfmask_off + lines(2 * mp);
+    const size_t bytes = h->lists_off + (h->lists_cap + 1 + 2 * h->pairs_cap) * sizeof(int);
+    char* up = (char*)h->dev_alloc(bytes);
+    h->d_dir = (int*)up;
+    h->d_active_leaf = (uint8_t*)up + active_off;
+    h->d_cfmask = (uint8_t*)up + cfmask_off;
+    h->d_lists = (int*)(up + h->lists_off);
+    HIP_OK(hipHostMalloc((void**)&h->h_stage, bytes, hipHostMallocDefault));
+    h->h_dir = (int*)h->h_stage;
     HIP_OK(hipHostMalloc((void**)&h->h_req, req_flag_offset(mp) + 64, hipHostMallocDefault));
     HIP_OK(hipMemsetAsync(h->d_has_tag, 0, mp, h->stream));
     HIP_OK(hipMemsetAsync(h->fr, 0, h->fr_doubles * sizeof(double), h->stream));
@@ -1212,9 +1214,10 @@ amr_status amr_rhs(amr_hierarchy* h, int buf, double* rhs_dev) {
   if (!h || !buf_ok(buf) || !rhs_dev) return AMR_E_ARG;
   return guarded(h, [&]() -> amr_status {
     stage_fill(h, buf);
-    over_list_dir(h, h->tiles, 2, kGnStage, [&](const int* p, int c, const int* dir) {
-      Kernels::stage(h->dm, amr::kModeRHS, h->U[buf], h->d_flags, h->U[0], rhs_dev, h->fr, p, c, dir, h->d_dt,
-                     h->fuse_halo, nullptr, h->d_cfmask, h->stream);
+    over_list_dir(h, h->tiles, kItemInts, kGnStage, [&](const int* p, int c, const int* dir) {
+      Kernels::stage(h->dm, amr::kModeRHS, h->U[buf], h->d_flags, h->U[0], rhs_dev, h->fr,
+                     dir ? h->d_items : (const amr::StageItem*)p, c, dir, h->d_dt, h->fuse_halo,
+                     nullptr, h->stream);
     });
     over_list(h, h->reflux, 2, [&](const int* p, int c) {
       Kernels::reflux(h->dm, amr::kModeRHS, rhs_dev, h->fr, p, c, h->d_dt, 1.0, nullptr, h->stream);
@@ -1439,14 +1442,12 @@ amr_status amr_autotune(amr_hierarchy* h, int reps, int* best, float* best_ms) {
       h->last_created.clear();
       sync_tables(h, false);
       // the launch the batched step makes (list and count from the directory)
-      Kernels::stage(h->dm, amr::kModeRHS, h->U[0], h->d_flags, h->U[0], scratch, h->fr, h->d_lists,
-                     h->tiles.count, h->tiles.dir, h->d_dt, h->fuse_halo, nullptr, h->d_cfmask,
-                     h->stream);
+      Kernels::stage(h->dm, amr::kModeRHS, h->U[0], h->d_flags, h->U[0], scratch, h->fr, h->d_items,
+                     h->tiles.count, h->tiles.dir, h->d_dt, h->fuse_halo, nullptr, h->stream);
       HIP_OK(hipEventRecord(e0, h->stream));
       for (int r = 0; r < reps; ++r)
-        Kernels::stage(h->dm, amr::kModeRHS, h->U[0], h->d_flags, h->U[0], scratch, h->fr, h->d_lists,
-                       h->tiles.count, h->tiles.dir, h->d_dt, h->fuse_halo, nullptr,
-                       h->d_cfmask, h->stream);
+        Kernels::stage(h->dm, amr::kModeRHS, h->U[0], h->d_flags, h->U[0], scratch, h->fr, h->d_items,
+                       h->tiles.count, h->tiles.dir, h->d_dt, h->fuse_halo, nullptr, h->stream);
       HIP_OK(hipEventRecord(e1, h->stream));
       HIP_OK(hipEventSynchronize(e1));
       float ms = 0.f;
