@@ -85,6 +85,17 @@ struct alignas(64) StageItem {
 static_assert(sizeof(StageItem) == 64, "one line per item");
 constexpr int kNbNone = -1, kNbWall = -2;
 
+// Work item of the refluxing kernels, in the list buffer: a leaf with finer
+// neighbours, with its level, position and parent cells (one load instead of
+// two dependent ones before the fine patches can be looked up).
+struct alignas(32) RefluxItem {
+  int pid, mask, level;  // mask: faces 2 j + side with a finer patch across
+  int pc[3];
+  long long target;      // level >= 1: offset in a state buffer of the first
+                         // parent cell it covers
+};
+static_assert(sizeof(RefluxItem) == 32, "eight ints in the list buffer");
+
 // Blocks of the 3D tag launch: patches and 8^3 tiles per patch of each level.
 struct TagLevels {
   int count[kMaxLev], tiles[kMaxLev];
@@ -117,9 +128,8 @@ struct Kernels {
   // ev0/ev1 (optional): events stamped at the dispatch's own start and end.
   // lam_in (stage 1 only, optional): take dt = CFL / *lam_in instead of *dt,
   // write it to *dt_out and clear *lam_next (the slot stage 3 accumulates in)
-  // In the stage modes a tile of a leaf without coarse/fine faces (level >= 1:
-  // refluxing does not change it) also restricts its new values into
-  // its parent patch.
+  // In the stage modes a tile of a leaf (level >= 1) also restricts its new
+  // values into its parent patch; post corrects this where it refluxes.
   static void stage(const DevMesh& m, int mode, double* Uin, int* err, const double* Un,
                     double* out, double* fr, const StageItem* items, int count, const int* dir,
                     const double* dt, bool fuse, unsigned long long* lam_next, hipStream_t s,
@@ -132,17 +142,17 @@ struct Kernels {
   static void stage_items(const DevMesh& m, const int* tiles, int count, const uint8_t* cfmask,
                           StageItem* items, hipStream_t s);
   static void reflux(const DevMesh& m, int mode, double* out, const double* fr,
-                     const int* list, int count, const double* dt, double w,
+                     const RefluxItem* list, int count, const double* dt, double w,
                      unsigned long long* lam_next, hipStream_t s);
-  // refluxing and the restriction of level lup = finest - 1 in one launch:
-  // reflux items and level-lup patches with children (plist); the stage kernel
-  // has restricted the leaves without coarse/fine faces, the finest level
-  // among them
+  // refluxing with what it changes of the leaves' restriction, and the
+  // restriction of the patches with children of level finest - 1 (plist) in one
+  // launch; the stage kernel has restricted the leaves
   // dir (nullable): the directory entries of the two lists, in order; with it
-  // the list pointers are the list buffer, the live counts are read at run
+  // the list pointers are the list
+  // buffer (reflux: its items start at a multiple of their size), the live counts are read at run
   // time and nref + npair only sizes the grid.
-  static void post(const DevMesh& m, int mode, double* out, const double* fr, const int* rlist,
-                   int nref, const int* plist, int npair, const int* dir, int lup,
+  static void post(const DevMesh& m, int mode, double* out, const double* fr,
+                   const RefluxItem* rlist, int nref, const int* plist, int npair, const int* dir,
                    const double* dt, double w, unsigned long long* lam_next, hipStream_t s);
   static void restrict_level(const DevMesh& m, double* U, const int* list, int count,
                              const int* dir, hipStream_t s);

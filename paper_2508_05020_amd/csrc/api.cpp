@@ -136,8 +136,8 @@ struct amr_hierarchy {
   int level_count[amr::kMaxLev] = {};  // active patches per level
   amr::ListView all{}, leaves{}, tiles{}, reflux{}, cfregions{}, cffaces{}, cands{};
   // post-stage restriction (see Kernels::post): level-(L-2) patches with
-  // children, and per level the patches that the stage kernel has not
-  // restricted itself (with children or coarse/fine faces); restr: all patches
+  // children, and per level the patches with children (the stage kernel
+  // restricts the leaves); restr: all patches
   amr::ListView post_pairs{};
   amr::ListView restr[amr::kMaxLev]{}, restr_post[amr::kMaxLev]{}, fresh[amr::kMaxLev]{};
   std::vector<int> last_created;
@@ -354,6 +354,10 @@ void build_devmesh(amr_hierarchy* h) {
   h->tag_bytes = tg;
 }
 
+// ints of the items in the stage and reflux lists
+constexpr int kItemInts = sizeof(amr::StageItem) / sizeof(int);
+constexpr int kRefluxInts = sizeof(amr::RefluxItem) / sizeof(int);
+
 // Rebuild work lists on the host and upload them (plus the changed table
 // entries) to the device.
 // byte offset of the pinned flag slot in h_req (after 2 max_patches bytes of
@@ -466,6 +470,8 @@ void sync_tables(amr_hierarchy* h, bool full) {
         *at++ = t;
       }
   }
+  const int r_items = begin_list();
+  while (L.size() % kRefluxInts) L.push_back(0);  // aligned items
   const int r0 = begin_list();
   int nref = 0;
   for (int pid : order) {
@@ -480,8 +486,17 @@ void sync_tables(amr_hierarchy* h, bool full) {
         if (qp >= 0 && !f.is_leaf(qp)) mask |= 1 << (2 * j + side);
       }
     if (mask) {
-      L.push_back(pid);
-      L.push_back(mask);
+      amr::RefluxItem ri{pid, mask, l, {c[0], c[1], c[2]}, 0};
+      if (l > 0) {
+        const int P = f.parent[pid];
+        const amr::LevelC& C = h->dm.lv[l - 1];
+        long long off = 0;
+        for (int j = f.dim - 1; j >= 0; --j)
+          off = off * C.full + c[j] * (f.n[l] / 2) - f.coord[3 * P + j] * C.n + amr::kNG;
+        ri.target = C.pool_off + (long long)(P - C.pid_base) * C.stride + off;
+      }
+      L.resize(L.size() + kRefluxInts);
+      std::memcpy(&L[L.size() - kRefluxInts], &ri, sizeof ri);
       ++nref;
     }
   }
@@ -491,15 +506,13 @@ void sync_tables(amr_hierarchy* h, bool full) {
   for (int pid : order)
     if (lup >= 1 && f.level[pid] == lup && !f.is_leaf(pid)) L.push_back(pid);
   const int pp1 = begin_list();
-  // per level: patches with children or coarse/fine faces
-  std::vector<uint8_t> has_reflux(f.max_patches, 0);
-  for (int i = r0; i < r0 + 2 * nref; i += 2) has_reflux[L[i]] = 1;
+  // per level: patches with children
   int rp[amr::kMaxLev + 1] = {};
   for (int l = 0; l < f.nlev; ++l) {
     rp[l] = begin_list();
     if (l == 0) continue;
     for (int pid : order)
-      if (f.level[pid] == l && (!f.is_leaf(pid) || has_reflux[pid])) L.push_back(pid);
+      if (f.level[pid] == l && !f.is_leaf(pid)) L.push_back(pid);
   }
   rp[f.nlev] = begin_list();
   int rs[amr::kMaxLev + 1] = {};
@@ -533,7 +546,7 @@ void sync_tables(amr_hierarchy* h, bool full) {
   h->cfregions = {h->d_lists + c0, (cf1 - c0) / 2, dd + 2 * kDirCf};
   h->cffaces = {h->d_lists + cf1, (k0 - cf1) / 2, dd + 2 * kDirCfFace};
   h->cands = {h->d_lists + k0, t0 - k0};
-  h->tiles = {(const int*)h->d_items, (r0 - t0) / 2, dd + 2 * kDirTiles};
+  h->tiles = {(const int*)h->d_items, (r_items - t0) / 2, dd + 2 * kDirTiles};
   h->reflux = {h->d_lists + r0, nref, dd + 2 * kDirReflux};
   h->post_pairs = {h->d_lists + pp0, pp1 - pp0, dd + 2 * kDirPairs};
   for (int l = 0; l < f.nlev; ++l) {
@@ -561,7 +574,7 @@ void sync_tables(amr_hierarchy* h, bool full) {
   // face of a coarse/fine interface, by R2); the stage kernel writes only
   // these registers
   std::fill(sm, sm + 2 * mp, (uint8_t)0);
-  for (int i = 0; i < nref; ++i) sm[L[r0 + 2 * i]] = (uint8_t)L[r0 + 2 * i + 1];
+  for (int i = 0; i < nref; ++i) sm[L[r0 + kRefluxInts * i]] = (uint8_t)L[r0 + kRefluxInts * i + 1];
   uint8_t* sw = sm + mp;
   for (int pid : order)
     if (f.is_leaf(pid)) sw[pid] = sm[pid];
@@ -583,8 +596,6 @@ void sync_tables(amr_hierarchy* h, bool full) {
   Kernels::stage_items(h->dm, h->d_lists + t0, h->tiles.count, h->d_cfmask, h->d_items, h->stream);
   h->check_launch();
 }
-
-constexpr int kItemInts = sizeof(amr::StageItem) / sizeof(int);
 
 // Per-patch mode launches one kernel per list entry (the unfused baseline).
 template <typename F>
@@ -730,9 +741,9 @@ void do_stage(amr_hierarchy* h, int stage, const double* dt,
     // post-stage entries are consecutive)
     const int lup = h->forest.nlev - 2;
     const bool rec = h->capturing;
-    Kernels::post(h->dm, stage, h->U[d], h->fr, rec ? h->d_lists : h->reflux.ptr,
+    Kernels::post(h->dm, stage, h->U[d], h->fr, (const amr::RefluxItem*)(rec ? h->d_lists : h->reflux.ptr),
                   grid_count(h, h->reflux), rec ? h->d_lists : h->post_pairs.ptr,
-                  grid_count(h, h->post_pairs), rec ? h->reflux.dir : nullptr, lup, dt, w[stage],
+                  grid_count(h, h->post_pairs), rec ? h->reflux.dir : nullptr, dt, w[stage],
                   stage == 3 ? lam_next : nullptr, h->stream);
     h->check_launch();
     note_node(h, kGnPost, kDirReflux, kDirPairs);
@@ -741,8 +752,8 @@ void do_stage(amr_hierarchy* h, int stage, const double* dt,
         Kernels::restrict_level(h->dm, h->U[d], p, c, dir, h->stream);
       });
   } else {
-    over_list(h, h->reflux, 2, [&](const int* p, int c) {
-      Kernels::reflux(h->dm, stage, h->U[d], h->fr, p, c, dt, w[stage],
+    over_list(h, h->reflux, kRefluxInts, [&](const int* p, int c) {
+      Kernels::reflux(h->dm, stage, h->U[d], h->fr, (const amr::RefluxItem*)p, c, dt, w[stage],
                       stage == 3 ? lam_next : nullptr, h->stream);
     });
     do_restrict(h, d);
@@ -953,11 +964,11 @@ amr_status amr_create_hierarchy(const amr_config* cfg, const amr_allocator* allo
       for (int l = 0; l < f.nlev; ++l) t += (long long)f.cap[l] * Kernels::tiles_per_patch(v, f.n[l]);
       tiles = std::max(tiles, t);
     }
-    // all, leaves, coarsening candidates, reflux (2), post-stage pairs,
-    // restriction (all, post-stage), new patches: 9 per patch; ghost regions and
+    // all, leaves, coarsening candidates, reflux (8), post-stage pairs,
+    // restriction (all, post-stage), new patches: 15 per patch; ghost regions and
     // their faces: 2 per region and patch; tiles: 2 per tile
     const long long regions = ipow(3, cfg->dim) - 1;
-    h->lists_cap = 2 * tiles + (9 + 2 * regions + 2 * 2 * cfg->dim) * mp + 64;
+    h->lists_cap = 2 * tiles + (15 + 2 * regions + 2 * 2 * cfg->dim) * mp + 64;
     h->d_items = (amr::StageItem*)h->dev_alloc(tiles * sizeof(amr::StageItem));
     h->pairs_cap = mp * (6 + f.maxc) + 2 * (long long)f.map.size() + 64;
     h->pairs_cap = std::min<long long>(h->pairs_cap, 64LL << 20);
@@ -1219,8 +1230,9 @@ amr_status amr_rhs(amr_hierarchy* h, int buf, double* rhs_dev) {
                      dir ? h->d_items : (const amr::StageItem*)p, c, dir, h->d_dt, h->fuse_halo,
                      nullptr, h->stream);
     });
-    over_list(h, h->reflux, 2, [&](const int* p, int c) {
-      Kernels::reflux(h->dm, amr::kModeRHS, rhs_dev, h->fr, p, c, h->d_dt, 1.0, nullptr, h->stream);
+    over_list(h, h->reflux, kRefluxInts, [&](const int* p, int c) {
+      Kernels::reflux(h->dm, amr::kModeRHS, rhs_dev, h->fr, (const amr::RefluxItem*)p, c, h->d_dt, 1.0,
+                      nullptr, h->stream);
     });
     return AMR_OK;
   });

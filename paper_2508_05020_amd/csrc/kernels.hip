@@ -299,28 +299,27 @@ __global__ __launch_bounds__(NT) void k_fill_cf_coarse(DevMesh m,
 // coarse/fine flux correction: list of (pid, face mask); faces are processed
 // in the order x-, x+, y-, y+, z-, z+ so that corner cells see a fixed order
 // ---------------------------------------------------------------------------
-// Correction of the coarse leaf cell c (patch-local) for its c/f face f =
-// 2 j + side: coef (G_c - mean of the 2^(D-1) fine sub-face fluxes), signed
-// +1 on the high face and -1 on the low face.
+// The fine side of a coarse cell's c/f face: the same-level position of the
+// fine patch that holds the face's 2^(D-1) sub-faces in its patch map, and the
+// offsets of the face in the two patches' flux registers (variable 0).
+struct FinePart {
+  int map, coarse, fine;
+};
+
 template <int D>
-__device__ __forceinline__ void face_correct(const DevMesh& m, const double* __restrict__ fr,
-                                             const double* __restrict__ frc, int l,
-                                             const int pc[3], const int c[3], int f,
-                                             double coef, double u[D + 2]) {
+__device__ __forceinline__ FinePart fine_part(const DevMesh& m, int l, const int pc[3],
+                                              const int c[3], int j, int side) {
   constexpr int NV = D + 2;
-  const LevelC& L = m.lv[l];
   const LevelC& Fv = m.lv[l + 1];
-  const int n = L.n, nf = Fv.n, Nf = Fv.cells;
+  const int n = m.lv[l].n, nf = Fv.n, Nf = Fv.cells;
   const int nface = (D == 1) ? 1 : (D == 2 ? n : n * n);
   const int nfface = (D == 1) ? 1 : (D == 2 ? nf : nf * nf);
-  const int j = f >> 1, side = f & 1;
   // fine cell column adjacent to the face (periodic wrap on the high side,
   // and on the low side of the domain)
-  const int F = 2 * ((j == 0 ? pc[0] : (j == 1 ? pc[1] : pc[2])) * n + (side ? n : 0));
+  const int F = 2 * (pc[j] * n + (side ? n : 0));
   const int cj = side ? (F == Nf ? 0 : F) : (F == 0 ? Nf : F) - 1;
-  // tangential coordinates in ascending dimension order (all indexing by
-  // compile-time constants; j selects): of the cell, and of its fine sub-faces
-  // 2 g and 2 g + 1, which one fine patch holds (even edges)
+  // tangential coordinates in ascending dimension order: of the cell, and of
+  // its fine sub-faces 2 g and 2 g + 1, which one fine patch holds (even edges)
   int t = 0, ft = 0, at = div_by(cj, nf, Fv.n_mul) * (j == 0 ? 1 : (j == 1 ? Fv.np : Fv.np * Fv.np));
 #pragma unroll
   for (int d = 0; d < D; ++d) {
@@ -332,11 +331,27 @@ __device__ __forceinline__ void face_correct(const DevMesh& m, const double* __r
     ft += (g - q * nf) * (second ? nf : 1);
     at += q * (d == 0 ? 1 : (d == 1 ? Fv.np : Fv.np * Fv.np));
   }
-  const int fpid = m.map[Fv.map_off + at];
-  const double* gcp = frc + (j * 2 + side) * NV * nface + t;
+  return {Fv.map_off + at, (j * 2 + side) * NV * nface + t,
+          (j * 2 + (side ? 0 : 1)) * NV * nfface + ft};
+}
+
+// Correction of the coarse cell values u by one c/f face (fine patch fpid):
+// coef (G_c - mean of the 2^(D-1) fine sub-face fluxes), signed +1 on the high
+// face and -1 on the low face.
+template <int D>
+__device__ __forceinline__ void face_correct(const DevMesh& m, const double* __restrict__ fr,
+                                             const double* __restrict__ frc, int l,
+                                             const FinePart& fp, int fpid, int side, double coef,
+                                             double u[D + 2]) {
+  constexpr int NV = D + 2;
+  const LevelC& Fv = m.lv[l + 1];
+  const int n = m.lv[l].n, nf = Fv.n;
+  const int nface = (D == 1) ? 1 : (D == 2 ? n : n * n);
+  const int nfface = (D == 1) ? 1 : (D == 2 ? nf : nf * nf);
+  const double* gcp = frc + fp.coarse;
   const double* frf = fr + Fv.fr_off +
                       (long long)((fpid < 0 ? Fv.pid_base : fpid) - Fv.pid_base) * Fv.fr_stride +
-                      (j * 2 + (side ? 0 : 1)) * NV * nfface + ft;
+                      fp.fine;
   const double sgn = side ? 1.0 : -1.0;
 #pragma unroll
   for (int v = 0; v < NV; ++v) {
@@ -359,35 +374,34 @@ __device__ __forceinline__ void face_correct(const DevMesh& m, const double* __r
   }
 }
 
-// Refluxing on (leaf, c/f face mask) items.  Every cell on a masked face is
+// Refluxing on the items of leaves with c/f faces.  Every cell on a masked face is
 // owned by one thread (the first masked face containing it in the order
 // x-, x+, y-, y+, z-, z+), which applies the corrections of all masked faces
 // containing the cell in that order; at stage 3 it also feeds the corrected
-// cell's CFL rate to the next step's maximum.
+// cell's CFL rate to the next step's maximum.  Bound by its chain of dependent
+// loads: a cell is on at most one face per direction, and the fine patches of
+// all of them are looked up before any register is read (a cell on the edge of
+// two masked faces took one such chain after the other, and its wave with it);
+// the level and position come with the item.  k_post with both, and with the
+// restriction of the corrected faces alone (see there): 1D 3.6 to 2.9 us (20
+// tiles), 2D 7.2 to 6.1 (0.28 M cells) and 14.8 to 12.0 (2.75 M), 3D 18.0 to
+// 15.3 (0.7 M) and 76 to 67 (20.4 M).
 template <int D, int NT>
 __device__ __forceinline__ void reflux_item(const DevMesh& m, int mode, double* __restrict__ out,
-                                            const double* __restrict__ fr,
-                                            const int* __restrict__ list, int item,
+                                            const double* __restrict__ fr, const RefluxItem& ri,
                                             const double* __restrict__ dtp, double w,
                                             unsigned long long* __restrict__ lam_next) {
   constexpr int NV = D + 2;
-  const int pid = list[2 * item];
-  const int mask = list[2 * item + 1];
-  const int l = m.level[pid];
+  const int pid = ri.pid, mask = ri.mask, l = ri.level;
   const LevelC& L = m.lv[l];
   const int n = L.n;
   const int nface = (D == 1) ? 1 : (D == 2 ? n : n * n);
-  const int pc[3] = {m.coord[3 * pid], m.coord[3 * pid + 1], m.coord[3 * pid + 2]};
+  const int* pc = ri.pc;
   const double* frc = fr + L.fr_off + (long long)(pid - L.pid_base) * L.fr_stride;
   double* P = out + patch_base(m, pid, l);
   const int vs = var_stride<D>(L.full);
   const double coef = (mode == kModeRHS) ? L.inv_h : (w * dtp[0]) * L.inv_h;
   const bool want_rate = lam_next != nullptr && mode == kModeStage3;
-  auto on_face = [&](const int c[3], int g) {
-    const int j = g >> 1;
-    const int cj = (j == 0) ? c[0] : (j == 1 ? c[1] : c[2]);
-    return cj == ((g & 1) ? n - 1 : 0);
-  };
   unsigned long long best = 0ull;
   // one item per cell of a masked face (a front crosses one to three of them)
   const int items = __popc(mask) * nface;
@@ -396,26 +410,40 @@ __device__ __forceinline__ void reflux_item(const DevMesh& m, int mode, double* 
     const int nth = D >= 3 ? div_by(row, n, L.n_mul) : row;
     int left = mask;
     for (int k = 0; k < nth; ++k) left &= left - 1;
-    const int f = __ffs(left) - 1, j = f >> 1;
+    const int f = __ffs(left) - 1;
     // cell on face f: normal coordinate 0 or n-1, tangential ones in ascending
     // dimension order
     const int t0 = D >= 2 ? it - row * n : 0, t1 = D >= 3 ? row - nth * n : 0;
     int c[3] = {0, 0, 0};
+    // per direction, whether the cell is on a masked face and on which side
+    bool on[3] = {false, false, false};
+    int side[3];
+    bool owned = true;
 #pragma unroll
     for (int d = 0; d < D; ++d) {
-      const int k = d - (d > j ? 1 : 0);
+      const int j = f >> 1, k = d - (d > j ? 1 : 0);
       c[d] = (d == j) ? ((f & 1) ? n - 1 : 0) : (k == 0 ? t0 : t1);
+      side[d] = c[d] == 0 ? 0 : 1;
+      on[d] = (c[d] == 0 || c[d] == n - 1) && (mask >> (2 * d + side[d]) & 1);
+      if (d < j) owned &= !on[d];
     }
-    bool owned = true;
-    for (int g = 0; g < f; ++g) owned &= !((mask & (1 << g)) && on_face(c, g));
     if (!owned) continue;
     // the cell's values stay in registers through all of its corrections
     const int off = box_off<D>(L.full, c[0] + NG, c[1] + NG, c[2] + NG);
+    FinePart fp[D];
+    int fpid[D];
+#pragma unroll
+    for (int d = 0; d < D; ++d) {
+      fp[d] = fine_part<D>(m, l, pc, c, d, side[d]);
+      fpid[d] = -1;
+      if (on[d]) fpid[d] = m.map[fp[d].map];
+    }
     double u[NV];
 #pragma unroll
     for (int v = 0; v < NV; ++v) u[v] = P[v * vs + off];
-    for (int g = f; g < 2 * D; ++g)
-      if ((mask & (1 << g)) && on_face(c, g)) face_correct<D>(m, fr, frc, l, pc, c, g, coef, u);
+#pragma unroll
+    for (int d = 0; d < D; ++d)
+      if (on[d]) face_correct<D>(m, fr, frc, l, fp[d], fpid[d], side[d], coef, u);
 #pragma unroll
     for (int v = 0; v < NV; ++v) P[v * vs + off] = u[v];
     if (want_rate) {
@@ -429,33 +457,40 @@ __device__ __forceinline__ void reflux_item(const DevMesh& m, int mode, double* 
 template <int D, int NT>
 __global__ __launch_bounds__(NT) void k_reflux(DevMesh m, int mode, double* __restrict__ out,
                                                const double* __restrict__ fr,
-                                               const int* __restrict__ list, int count,
+                                               const RefluxItem* __restrict__ list, int count,
                                                const double* __restrict__ dtp, double w,
                                                unsigned long long* __restrict__ lam_next) {
   if ((int)blockIdx.x >= count) return;
-  reflux_item<D, NT>(m, mode, out, fr, list, blockIdx.x, dtp, w, lam_next);
+  reflux_item<D, NT>(m, mode, out, fr, list[blockIdx.x], dtp, w, lam_next);
+}
+
+// Where a child patch (level lf >= 1) is restricted to: the offset in a state
+// buffer of the first parent cell it covers.
+template <int D>
+__device__ __forceinline__ long long restrict_target(const DevMesh& m, int cpid, int lf) {
+  const LevelC& C = m.lv[lf - 1];
+  const int ppid = m.parent[cpid];
+  int q[3] = {0, 0, 0};
+#pragma unroll
+  for (int j = 0; j < D; ++j)
+    q[j] = m.coord[3 * cpid + j] * (m.lv[lf].n / 2) - m.coord[3 * ppid + j] * C.n + NG;
+  return patch_base(m, ppid, lf - 1) + box_off<D>(C.full, q[0], q[1], q[2]);
 }
 
 // Restriction of one child patch into the covered cells of its parent:
 // pairwise sums in x, then y, then z order, times 2^-D.
-// One covered parent cell (index idx of the h^D cells a child covers): the
+// One covered parent cell ((a, b, c) among those the child covers): the
 // pairwise sum of its 2^D child cells times 2^-D.
 template <int D>
 __device__ __forceinline__ void restrict_cell(const DevMesh& m, double* __restrict__ U, int cpid,
-                                              int ppid, int lf, int h, int idx) {
+                                              long long target, int lf, int a, int b, int c) {
   constexpr int NV = D + 2;
   const LevelC& F = m.lv[lf];
   const LevelC& C = m.lv[lf - 1];
-  int o[3] = {0, 0, 0};
-  for (int j = 0; j < D; ++j) o[j] = m.coord[3 * cpid + j] * h - m.coord[3 * ppid + j] * C.n;
   const double* Pc = U + patch_base(m, cpid, lf);
-  double* Pp = U + patch_base(m, ppid, lf - 1);
+  double* Pp = U + target;
   const long long vsf = var_stride<D>(F.full), vsc = var_stride<D>(C.full);
-  // h = F.n / 2: idx / h = 2 idx / F.n
-  const int row = D >= 2 ? div_by(2 * idx, F.n, F.n_mul) : 0;
-  const int c = D >= 3 ? div_by(2 * row, F.n, F.n_mul) : 0;
-  const int a = idx - row * h, b = D >= 2 ? row - c * h : 0;
-  const long long dst = box_off<D>(C.full, o[0] + a + NG, o[1] + b + NG, o[2] + c + NG);
+  const long long dst = box_off<D>(C.full, a, b, c);
 #pragma unroll
   for (int v = 0; v < NV; ++v) {
     const double* S = Pc + v * vsf;
@@ -477,24 +512,51 @@ __device__ __forceinline__ void restrict_cell(const DevMesh& m, double* __restri
   }
 }
 
+// idx / (n / 2) of a level
+__device__ __forceinline__ int div_half(int idx, const LevelC& L) {
+  return div_by(2 * idx, L.n, L.n_mul);
+}
+
+// restriction of patch cpid (level lf) into its parent, by the whole block
 template <int D>
-__device__ __forceinline__ int covered_cells(int h) {
+__device__ __forceinline__ void restrict_patch(const DevMesh& m, double* __restrict__ U,
+                                               int cpid, int lf, long long target) {
+  const LevelC& F = m.lv[lf];
+  const int h = F.n / 2;
   int total = h;
   if constexpr (D >= 2) total *= h;
   if constexpr (D >= 3) total *= h;
-  return total;
+  for (int idx = threadIdx.x; idx < total; idx += blockDim.x) {
+    const int row = D >= 2 ? div_half(idx, F) : 0;
+    const int c = D >= 3 ? div_half(row, F) : 0;
+    restrict_cell<D>(m, U, cpid, target, lf, idx - row * h, D >= 2 ? row - c * h : 0, c);
+  }
 }
 
-// restriction of patch cpid into its parent, by the whole block
+// the covered parent cells along the masked faces of a leaf, by the whole block
+// (cells on an edge of two faces are written from both, with the same value)
 template <int D>
-__device__ __forceinline__ void restrict_patch(const DevMesh& m, double* __restrict__ U,
-                                               int cpid) {
-  const int lf = m.level[cpid];
-  const int ppid = m.parent[cpid];
-  const int h = m.lv[lf].n / 2;
-  const int total = covered_cells<D>(h);
-  for (int idx = threadIdx.x; idx < total; idx += blockDim.x)
-    restrict_cell<D>(m, U, cpid, ppid, lf, h, idx);
+__device__ __forceinline__ void restrict_faces(const DevMesh& m, double* __restrict__ U, int cpid,
+                                               int lf, long long target, int mask) {
+  const LevelC& F = m.lv[lf];
+  const int h = F.n / 2;
+  const int face = (D == 1) ? 1 : (D == 2 ? h : h * h);
+  const int total = __popc(mask) * face;
+  for (int idx = threadIdx.x; idx < total; idx += blockDim.x) {
+    const int row = D >= 2 ? div_half(idx, F) : idx;
+    const int nth = D >= 3 ? div_half(row, F) : row;
+    int left = mask;
+    for (int k = 0; k < nth; ++k) left &= left - 1;
+    const int f = __ffs(left) - 1, j = f >> 1;
+    const int t0 = D >= 2 ? idx - row * h : 0, t1 = D >= 3 ? row - nth * h : 0;
+    int q[3] = {0, 0, 0};
+#pragma unroll
+    for (int d = 0; d < D; ++d) {
+      const int k = d - (d > j ? 1 : 0);
+      q[d] = (d == j) ? ((f & 1) ? h - 1 : 0) : (k == 0 ? t0 : t1);
+    }
+    restrict_cell<D>(m, U, cpid, target, lf, q[0], q[1], q[2]);
+  }
 }
 
 template <int D>
@@ -506,47 +568,53 @@ __global__ __launch_bounds__(256) void k_restrict(DevMesh m,
     list += dir[0];
     count = dir[1];
   }
-  if ((int)blockIdx.x < count) restrict_patch<D>(m, U, list[blockIdx.x]);
+  if ((int)blockIdx.x >= count) return;
+  const int pid = list[blockIdx.x], l = m.level[pid];
+  restrict_patch<D>(m, U, pid, l, restrict_target<D>(m, pid, l));
 }
 
-// After a stage, in one launch: refluxing, and the restriction of level L-2
-// into L-3 (when lup = L-2 >= 1) where the stage kernel, which restricts every
-// leaf without coarse/fine faces, has not done it.  Blocks:
-//  [0, nref)       reflux items (pid, mask); a level-(L-2) item then restricts
-//                  its (corrected) patch into its parent;
-//  [nref, +npair)  level-(L-2) patches with children (whose values the stage
-//                  kernel has restricted into them): restrict into the parent.
+// After a stage, in one launch: refluxing, and what it changes of the
+// restriction of the leaves (the stage kernel restricts every leaf as it writes
+// it), and the restriction of level L-2 into L-3.  Blocks:
+//  [0, nref)       reflux items; the parent cells along the
+//                  corrected faces are then formed again;
+//  [nref, +npair)  level-(L-2) patches with children: restrict into the parent
+//                  (their children, on the finest level, are never refluxed:
+//                  the stage kernel has restricted their final values).
 // A block's restriction after refluxing reads only what the same block wrote
 // (block barrier between); the blocks touch disjoint cells otherwise:
 // refluxing changes leaf cells, restriction writes non-leaf cells.  With
 // `dir` (batched launches) the lists and their counts are read at run time
 // from their directory entries, in order; rlist is then the list buffer.
+// Restricting the corrected leaves whole, here and in the coarser levels'
+// launches: 76 and 26 us (3D, 20.4 M cells), 67 and 16 so.
 template <int D, int NT>
 __global__ __launch_bounds__(NT) void k_post(DevMesh m, int mode,
                                              double* __restrict__ out,
                                              const double* __restrict__ fr,
-                                             const int* __restrict__ rlist, int nref,
+                                             const RefluxItem* __restrict__ rlist, int nref,
                                              const int* __restrict__ plist, int npair,
-                                             const int* __restrict__ dir, int lup,
+                                             const int* __restrict__ dir,
                                              const double* __restrict__ dtp, double w,
                                              unsigned long long* __restrict__ lam_next) {
   if (dir) {
-    const int* buf = rlist;
-    rlist = buf + dir[0];
+    const int* buf = reinterpret_cast<const int*>(rlist);
+    rlist = reinterpret_cast<const RefluxItem*>(buf + dir[0]);
     nref = dir[1];
     plist = buf + dir[2];
     npair = dir[3];
   }
   const int b = blockIdx.x;
   if (b < nref) {
-    reflux_item<D, NT>(m, mode, out, fr, rlist, b, dtp, w, lam_next);
-    const int pid = rlist[2 * b];
-    if (lup >= 1 && m.level[pid] == lup) {
+    const RefluxItem& ri = rlist[b];
+    reflux_item<D, NT>(m, mode, out, fr, ri, dtp, w, lam_next);
+    if (ri.level >= 1) {
       __syncthreads();
-      restrict_patch<D>(m, out, pid);
+      restrict_faces<D>(m, out, ri.pid, ri.level, ri.target, ri.mask);
     }
   } else if (b - nref < npair) {
-    restrict_patch<D>(m, out, plist[b - nref]);
+    const int pid = plist[b - nref], l = m.level[pid];
+    restrict_patch<D>(m, out, pid, l, restrict_target<D>(m, pid, l));
   }
 }
 
@@ -1264,7 +1332,7 @@ void Kernels::fill(const DevMesh& m, double* U, const int* list, int count, cons
 }
 
 void Kernels::reflux(const DevMesh& m, int mode, double* out, const double* fr,
-                     const int* list, int count, const double* dt, double w,
+                     const RefluxItem* list, int count, const double* dt, double w,
                      unsigned long long* lam_next, hipStream_t s) {
   if (count <= 0) return;
   switch (m.dim) {
@@ -1275,20 +1343,19 @@ void Kernels::reflux(const DevMesh& m, int mode, double* out, const double* fr,
 }
 
 void Kernels::post(const DevMesh& m, int mode, double* out, const double* fr,
-                   const int* rlist, int nref, const int* plist, int npair, const int* dir,
-                   int lup, const double* dt, double w, unsigned long long* lam_next,
-                   hipStream_t s) {
+                   const RefluxItem* rlist, int nref, const int* plist, int npair, const int* dir,
+                   const double* dt, double w, unsigned long long* lam_next, hipStream_t s) {
   const int nb = nref + npair;
   if (nb <= 0) return;
   auto launch = [&](auto kern, int threads) {
     hipLaunchKernelGGL(kern, dim3(nb), dim3(threads), 0, s, m, mode, out, fr, rlist, nref,
-                       plist, npair, dir, lup, dt, w, lam_next);
+                       plist, npair, dir, dt, w, lam_next);
   };
   switch (m.dim) {
     case 1: launch(k_post<1, 64>, 64); break;
     case 2: launch(k_post<2, 256>, 256); break;
-    // 3D: the cells of two 16^3 faces (74 us against 90 with 256 threads, 73
-    // with 1024, 20 M cells; 18 / 22 / 17 us, 0.7 M)
+    // 3D: the cells of two 16^3 faces (256 threads took 22 % longer, 1024 the
+    // same within 5 %)
     default: launch(k_post<3, 512>, 512); break;
   }
 }

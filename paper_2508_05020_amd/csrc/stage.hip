@@ -1032,9 +1032,8 @@ __device__ __forceinline__ void stage_both(const DevMesh& m, double* __restrict_
 // Restriction of a tile into its parent patch, from the new values of its
 // cells (sR: variable v of tile cell i at sR[v NCELL + i]): each parent cell
 // is the mean of its 2^D children, summed as the post-stage restriction sums
-// them (x pairs first, then y, then z).  For patches that are not the coarse
-// side of a coarse/fine face: their values are final once the stage kernel
-// has written them.  SERIAL: one variable
+// them (x pairs first, then y, then z).
+// SERIAL: one variable
 // at a time (unrolled, the reads of all variables are issued at once and can
 // take more registers than the primitive schemes' kernels have).
 template <int D, int TX, int TY, int TZ, int NT, bool SERIAL>
@@ -1200,11 +1199,11 @@ __device__ __forceinline__ void stage_item(const DevMesh& m, int mode,
   // faces are left to the flux-correction kernel, which changes them
   const bool want_rate = lam_next != nullptr && mode == kModeStage3;
   const int fmask = it.cf;
-  // a tile of a leaf without coarse/fine faces (the finest level's among them;
-  // refluxing leaves it as it is) is restricted into its parent here, from the
-  // values it writes (staged in sF, free once every thread has read its edge
-  // fluxes), instead of being read back by the post-stage launches
-  const bool restrict_here = mode != kModeRHS && l >= 1 && fmask == 0;
+  // the tile of a leaf is restricted into its parent here, from the values it
+  // writes (staged in sF, free once every thread has read its edge fluxes),
+  // instead of being read back by the post-stage launches; refluxing forms the
+  // parent cells along the faces it corrects again
+  const bool restrict_here = mode != kModeRHS && l >= 1;
   static_assert(S::NCELL <= S::FXMAX, "the staged cell values fit sF");
   double* sR = sF;
   if (restrict_here) __syncthreads();
