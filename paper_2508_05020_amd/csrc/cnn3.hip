@@ -9,11 +9,12 @@
 // 3x3x3 convolutions 5 -> 8 -> 8 -> 1 with bias, ReLU after the first two,
 // give one logit per tile cell.
 //
-// Convolutions as implicit GEMM on the 16x16x16 MFMA: rows = 16 output
+// Convolutions as implicit GEMM on the 16x16x32 MFMA: rows = 16 output
 // voxels, columns = output channels (8 of 16 used), K = (tap, input channel)
-// with 2 taps x 8 channels per 16-wide chunk, 14 chunks for 27 taps.  Weight
-// gradients swap the roles: rows = output channel, columns = (tap of a pair,
-// input channel), K = voxels.  Operand layout: see cnn_device.hpp.
+// with 4 taps x 8 channels per chunk, a lane's 8 values being one voxel's
+// channels (one 16-byte read), 7 chunks for 27 taps.  Weight gradients swap the
+// roles: rows = output channel, columns = (tap of a pair, input channel), K =
+// voxels.  Operand layout: see cnn_device.hpp.
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
@@ -32,14 +33,18 @@ constexpr int T = CNN3_TILE;
 constexpr int CH = CNN3_CH;
 constexpr int W0 = T + 6, W1 = T + 4, W2 = T + 2;
 constexpr int P0 = CNN3_P0, P1 = CNN3_P1, P2 = CNN3_P2, P3 = CNN3_P3;
-constexpr int KCH = 14;  // K chunks: taps (2 kc, 2 kc + 1), 8 channels each
+constexpr int KCH = 7;     // K chunks of a convolution: taps 4 kc .. 4 kc + 3
+constexpr int WPAIRS = 14;  // tap pairs of a weight gradient
+// weights of one convolution in LDS as B operands: [28 taps][8 columns][8 K
+// channels], tap 27 zero
+constexpr int OPS = 4 * KCH * 8 * 8;
 // threads per block: the loops stride over the block's waves, so more waves
 // shorten a tile's latency (a training batch is only tens of tiles)
-constexpr int FWD_THREADS = 512;
+constexpr int FWD_THREADS = 1024;
 constexpr int TRAIN_THREADS = 1024;
 constexpr int TRAIN_WAVES = TRAIN_THREADS / 64;
 
-static_assert(CH == 8, "two taps of 8 channels per MFMA K chunk");
+static_assert(CH == 8, "a lane's 8 K values are one voxel's channels");
 static_assert(P1 % 16 == 0, "layer-1 voxels in whole MFMA row blocks");
 
 // ---------------------------------------------------------------------------
@@ -92,68 +97,62 @@ __global__ __launch_bounds__(256) void k_cnn3_gather(DevMesh m, const double* __
 }
 
 // ---------------------------------------------------------------------------
-// forward of one tile per block (4 waves); activations in LDS
+// forward of one tile per block (16 waves); activations in LDS
 // ---------------------------------------------------------------------------
 
-// Reads of the K chunks of a 3x3x3 convolution from a box of edge WI with 8
-// channels per voxel: chunk kc holds taps 2 kc (lanes of half 0) and 2 kc + 1
-// (half 1), FLIP reading tap t at the mirrored place.  The second tap lies at
-// one of three distances from the first, so three lane bases and immediate
-// offsets address every chunk.
+// A operands of a 3x3x3 convolution over a box of edge WI with 8 channels per
+// voxel: chunk kc holds the taps 4 kc + kq of the lane groups kq, FLIP reading
+// tap t at the mirrored place.  Tap 27 does not exist: zero.
 template <int WI, bool FLIP>
 struct TapReads {
-  static constexpr int at(int tap) {
-    const int z = tap / 9, y = (tap / 3) % 3, x = tap % 3;
-    return (FLIP ? ((2 - z) * WI + 2 - y) * WI + 2 - x : (z * WI + y) * WI + x) * CH;
+  int off[KCH];  // voxels from the voxel at tap 0 (2 2 2 of a mirrored one)
+  bool last;     // the lane has a tap in the last chunk
+  __device__ __forceinline__ explicit TapReads(int kq) : last(kq < 3) {
+#pragma unroll
+    for (int kc = 0; kc < KCH; ++kc) {
+      const int t = min(4 * kc + kq, 26), tap = FLIP ? 26 - t : t;
+      off[kc] = ((tap / 9) * WI + (tap / 3) % 3) * WI + tap % 3;
+    }
   }
-  static constexpr int kind(int kc) { return (2 * kc) % 9 == 8 ? 2 : ((2 * kc) % 3 == 2 ? 1 : 0); }
-  const unsigned short* base[3];
-  int half;
-  __device__ __forceinline__ TapReads(const unsigned short* p, int half_, int cg) : half(half_) {
-    base[0] = p + cg + half * (at(1) - at(0));
-    base[1] = p + cg + half * (at(3) - at(2));
-    base[2] = p + cg + half * (at(9) - at(8));
-  }
-  // kc: a constant after unrolling; tap 27 does not exist (read as tap 26, zero)
-  __device__ __forceinline__ s4 operator()(int kc) const {
-    if (kc < KCH - 1) return load4(base[kind(kc)] + at(2 * kc));
-    const s4 a = load4(base[0] + at(26) - half * (at(1) - at(0)));
-    return half == 0 ? a : zero4();
+  __device__ __forceinline__ u4 operator()(const unsigned short* voxel, int kc) const {
+    u4 a = *reinterpret_cast<const u4*>(voxel + off[kc] * CH);
+    if (kc == KCH - 1 && !last) a = u4{0u, 0u, 0u, 0u};
+    return a;
   }
 };
 
-// B operand of chunk kc: weights w[c0 + e][...][tap], at wt + e * stride + tap
-// for this lane's 4 input channels; read in any case (no branch around the
-// loads), zero where the column, tap or channel does not exist.
-__device__ __forceinline__ s4 tap_weights(const unsigned short* wt, int stride, int nch, bool column,
-                                          int tap) {
-  const int t = tap < 27 ? tap : 26;
-  short w[4];
-#pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    const short v = (short)wt[(e < nch ? e : 0) * stride + t];
-    w[e] = column && tap < 27 && e < nch ? v : (short)0;
+// The B operands of a convolution into LDS, by the whole block: column j, K
+// channel k and tap t from w[(j SJ + k SK) 27 + t], k < NK.
+template <int SJ, int SK, int NK>
+__device__ __forceinline__ void stage_operands(unsigned short* ops, const unsigned short* w) {
+  for (int t = threadIdx.x; t < OPS; t += blockDim.x) {
+    const int k = t & 7, j = (t >> 3) & 7, tap = t >> 6;
+    ops[t] = tap < 27 && k < NK ? w[(j * SJ + k * SK) * 27 + tap] : (unsigned short)0;
   }
-  return pack4(w[0], w[1], w[2], w[3]);
 }
 
+struct Operands {
+  u4 b[KCH];
+  __device__ __forceinline__ Operands(const unsigned short* ops, int i, int kq) {
+#pragma unroll
+    for (int kc = 0; kc < KCH; ++kc)
+      b[kc] = reinterpret_cast<const u4*>(ops)[(4 * kc + kq) * 8 + (i & 7)];
+  }
+};
+
 // valid 3x3x3 convolution, 8 output channels, from a voxel-major LDS input of
-// edge WI with 8 stored channels (CI of them weighted) to edge WI - 2 (bias,
-// ReLU, BF16); W layout [8][CI][27].
-template <int WI, int CI>
+// edge WI with 8 stored channels to edge WI - 2 (bias, ReLU, BF16).
+template <int WI>
 __device__ __forceinline__ void conv3(const unsigned short* __restrict__ in,
                                       unsigned short* __restrict__ out,
-                                      const unsigned short* __restrict__ W,
+                                      const unsigned short* __restrict__ ops,
                                       const float* __restrict__ bias) {
   constexpr int WO = WI - 2;
   constexpr int P = WO * WO * WO;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
   const int i = lane & 15, kq = lane >> 4;
-  const int half = kq >> 1, cg = 4 * (kq & 1);
-  s4 bop[KCH];
-#pragma unroll
-  for (int kc = 0; kc < KCH; ++kc)
-    bop[kc] = tap_weights(W + ((i & 7) * CI + cg) * 27, 27, CI - cg, i < 8, 2 * kc + half);
+  const Operands w(ops, i, kq);
+  const TapReads<WI, false> a(kq);
   const float bcol = bias[i & 7];
   constexpr int nblk = (P + 15) / 16;
   for (int blk = wave; blk < nblk; blk += nw) {
@@ -161,10 +160,10 @@ __device__ __forceinline__ void conv3(const unsigned short* __restrict__ in,
     const int pc = p < P ? p : P - 1;
     const int pz = pc / (WO * WO), r = pc - pz * WO * WO;
     const int py = r / WO, px = r - py * WO;
-    const TapReads<WI, false> a(in + ((pz * WI + py) * WI + px) * CH, half, cg);
+    const unsigned short* voxel = in + ((pz * WI + py) * WI + px) * CH;
     f4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int kc = 0; kc < KCH; ++kc) acc = mfma(a(kc), bop[kc], acc);
+    for (int kc = 0; kc < KCH; ++kc) acc = mfma32(a(voxel, kc), w.b[kc], acc);
     if (i < 8) {
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
@@ -176,38 +175,56 @@ __device__ __forceinline__ void conv3(const unsigned short* __restrict__ in,
   }
 }
 
+// A tile's latency is the sum of its phases: with 8 waves, weights packed by
+// every wave from global memory, 16-wide K chunks and layer-3 weights read per
+// tap, 256 tiles took 30.4 us; 14.8 now.
+// LDS (bytes)
+constexpr int FL_X = 0;
+constexpr int FL_A1 = FL_X + P0 * CH * 2;
+constexpr int FL_W1 = FL_A1 + P1 * CH * 2;
+constexpr int FL_W2 = FL_W1 + OPS * 2;
+constexpr int FL_W3 = FL_W2 + OPS * 2;
+constexpr int FL_TOTAL = FL_W3 + 27 * 8 * 4;
+static_assert(2 * FL_TOTAL <= 160 * 1024, "two blocks per CU");
+
 __global__ __launch_bounds__(FWD_THREADS) void k_cnn3_fwd(int count, const unsigned short* __restrict__ X,
                                                       const unsigned short* __restrict__ Wb,
                                                       const float* __restrict__ params,
                                                       float* __restrict__ Z) {
-  extern __shared__ unsigned short smem[];
+  extern __shared__ __align__(16) unsigned char fwd_smem[];
   const int b = blockIdx.x;
   if (b >= count) return;
-  unsigned short* sx = smem;           // P0 x 8
-  unsigned short* s1 = sx + P0 * CH;   // P1 x 8
-  unsigned short* s2 = smem;           // P2 x 8, over sx once layer 1 is done
+  unsigned short* sx = (unsigned short*)(fwd_smem + FL_X);   // P0 x 8
+  unsigned short* s1 = (unsigned short*)(fwd_smem + FL_A1);  // P1 x 8
+  unsigned short* s2 = sx;                                   // P2 x 8, over sx once layer 1 is done
+  unsigned short* w1 = (unsigned short*)(fwd_smem + FL_W1);
+  unsigned short* w2 = (unsigned short*)(fwd_smem + FL_W2);
+  float* w3 = (float*)(fwd_smem + FL_W3);                    // [27][8]
   const uint4* xg = reinterpret_cast<const uint4*>(X) + (long long)b * P0;
-  for (int t = threadIdx.x; t < P0; t += blockDim.x) reinterpret_cast<uint4*>(sx)[t] = xg[t];
+  for (int t = threadIdx.x; t < P0; t += FWD_THREADS) reinterpret_cast<uint4*>(sx)[t] = xg[t];
+  stage_operands<5, 1, 5>(w1, Wb + CNN3_W1);
+  stage_operands<8, 1, 8>(w2, Wb + CNN3_W2);
+  if (threadIdx.x < 27 * 8) w3[(threadIdx.x % 27) * 8 + threadIdx.x / 27] = bf2f(Wb[CNN3_W3 + threadIdx.x]);
   __syncthreads();
-  conv3<W0, 5>(sx, s1, Wb + CNN3_W1, params + CNN3_B1);
+  conv3<W0>(sx, s1, w1, params + CNN3_B1);
   __syncthreads();
-  conv3<W1, 8>(s1, s2, Wb + CNN3_W2, params + CNN3_B2);
+  conv3<W1>(s1, s2, w2, params + CNN3_B2);
   __syncthreads();
   // layer 3 (8 -> 1) on the VALU
   const float b3 = params[CNN3_B3];
-  for (int p = threadIdx.x; p < P3; p += blockDim.x) {
+  for (int p = threadIdx.x; p < P3; p += FWD_THREADS) {
     const int pz = p / (T * T), py = (p / T) % T, px = p % T;
+    const unsigned short* base = s2 + ((pz * W2 + py) * W2 + px) * CH;
     float acc = 0.f;
-    for (int tap = 0; tap < 27; ++tap) {
-      const int tz = tap / 9, ty = (tap / 3) % 3, tx = tap % 3;
-      const uint4 a = *reinterpret_cast<const uint4*>(
-          s2 + (((pz + tz) * W2 + (py + ty)) * W2 + (px + tx)) * CH);
-      const unsigned int u[4] = {a.x, a.y, a.z, a.w};
 #pragma unroll
-      for (int c = 0; c < 8; ++c) {
-        const unsigned short hc = (unsigned short)((u[c >> 1] >> (16 * (c & 1))) & 0xffffu);
-        acc += bf2f(hc) * bf2f(Wb[CNN3_W3 + c * 27 + tap]);
-      }
+    for (int tap = 0; tap < 27; ++tap) {
+      const u4 a = *reinterpret_cast<const u4*>(base + (((tap / 9) * W2 + (tap / 3) % 3) * W2 + tap % 3) * CH);
+      const float4 wa = *reinterpret_cast<const float4*>(w3 + tap * 8);
+      const float4 wb = *reinterpret_cast<const float4*>(w3 + tap * 8 + 4);
+      const float w[8] = {wa.x, wa.y, wa.z, wa.w, wb.x, wb.y, wb.z, wb.w};
+#pragma unroll
+      for (int c = 0; c < 8; ++c)
+        acc += bf2f((unsigned short)(a[c >> 1] >> (16 * (c & 1)))) * w[c];
     }
     Z[(long long)b * P3 + p] = acc + b3;
   }
@@ -220,7 +237,8 @@ __global__ __launch_bounds__(FWD_THREADS) void k_cnn3_fwd(int count, const unsig
 // One tile's latency per launch: the forward (29 us for 64 tiles), the loss
 // (4.6 us) and the backward (124 us) were launches of their own, with
 // activations through memory, bounds checks per tap and serial sums per
-// parameter; one 45.6 us launch now.
+// parameter; one launch now, 45.6 us with 16-wide K chunks and weights packed by
+// every wave, 39.4 with 32-wide chunks and operands staged once.
 //
 // LDS (bytes): dz1 takes the place of the second activation,
 // the logit gradients and the FP32 copy of W3; dz2 has a border of two zero
@@ -234,8 +252,9 @@ constexpr int TL_DZ1 = TL_A2;
 constexpr int TL_DZ2 = TL_DZ1 + P1 * CH * 2;
 constexpr int TL_RED = TL_DZ2 + P0 * CH * 2;      // dz2 with its border is as large as the input
 constexpr int RED_N = 8 * 27 + 1;                 // dW3 and db3 of one wave
-constexpr int TL_WB = TL_RED + ((TRAIN_WAVES * RED_N * 4 + 15) / 16) * 16;
-constexpr int TL_TOTAL = TL_WB + ((CNN3_NPARAM * 2 + 15) / 16) * 16;
+constexpr int TL_W2F = TL_RED + ((TRAIN_WAVES * RED_N * 4 + 15) / 16) * 16;  // W2, mirrored
+constexpr int TL_TOTAL = TL_W2F + OPS * 2;
+constexpr int TL_W1 = TL_DZ2, TL_W2 = TL_W1 + OPS * 2;  // until the forward convolutions are done
 static_assert(TL_W3 + 27 * 8 * 4 <= TL_DZ2, "a2, g and W3 fit under dz1");
 static_assert(TL_TOTAL <= 160 * 1024, "one block per CU");
 static_assert(W2 + 4 == W0, "dz2 with its border has the input's shape");
@@ -255,29 +274,32 @@ __global__ __launch_bounds__(TRAIN_THREADS) void k_cnn3_train(
   unsigned short* dz1 = (unsigned short*)(train_smem + TL_DZ1);   // [P1][8]
   unsigned short* dz2 = (unsigned short*)(train_smem + TL_DZ2);   // [W0^3][8]
   float* red = (float*)(train_smem + TL_RED);
-  unsigned short* Wb = (unsigned short*)(train_smem + TL_WB);
+  unsigned short* w1 = (unsigned short*)(train_smem + TL_W1);
+  unsigned short* w2 = (unsigned short*)(train_smem + TL_W2);
+  unsigned short* w2f = (unsigned short*)(train_smem + TL_W2F);
   float* part = partials + (long long)b * CNN3_NPARAM;
   const int tid = threadIdx.x;
   const int lane = tid & 63, wave = tid >> 6;
   const int i = lane & 15, kq = lane >> 4;
-  const int half = kq >> 1, cg = 4 * (kq & 1);
 
   {
     const uint4* gx = reinterpret_cast<const uint4*>(X) + (long long)b * P0;
     const uint4 z = {0u, 0u, 0u, 0u};
     for (int t = tid; t < P0; t += TRAIN_THREADS) {
       reinterpret_cast<uint4*>(x)[t] = gx[t];
-      reinterpret_cast<uint4*>(dz2)[t] = z;
     }
-    for (int t = tid; t < CNN3_NPARAM; t += TRAIN_THREADS) Wb[t] = Wg[t];
+    stage_operands<5, 1, 5>(w1, Wg + CNN3_W1);
+    stage_operands<8, 1, 8>(w2, Wg + CNN3_W2);
+    stage_operands<1, 8, 8>(w2f, Wg + CNN3_W2);
     if (tid < 2) reinterpret_cast<uint4*>(a1 + P1 * CH)[tid] = z;
     if (tid < 27 * 8) w3[(tid % 27) * 8 + tid / 27] = bf2f(Wg[CNN3_W3 + tid]);
   }
   __syncthreads();
-  conv3<W0, 5>(x, a1, Wb + CNN3_W1, params + CNN3_B1);
+  conv3<W0>(x, a1, w1, params + CNN3_B1);
   __syncthreads();
-  conv3<W1, 8>(a1, a2, Wb + CNN3_W2, params + CNN3_B2);
+  conv3<W1>(a1, a2, w2, params + CNN3_B2);
   __syncthreads();
+  for (int t = tid; t < P0; t += TRAIN_THREADS) reinterpret_cast<uint4*>(dz2)[t] = uint4{0u, 0u, 0u, 0u};
 
   // --- layer 3 and the loss: 2 lanes per voxel, 4 channels each
   {
@@ -374,7 +396,7 @@ __global__ __launch_bounds__(TRAIN_THREADS) void k_cnn3_train(
     for (int k = 0; k < TRAIN_WAVES; ++k) s += red[k * RED_N + tid];
     part[CNN3_W3 + tid] = s;  // db3 follows W3
   }
-  static_assert(CNN3_B3 == CNN3_W3 + 8 * 27 && KCH < TRAIN_WAVES,
+  static_assert(CNN3_B3 == CNN3_W3 + 8 * 27 && WPAIRS < TRAIN_WAVES,
                 "a wave per tap pair and one for the bias sums");
   // column j of a weight-gradient product: (tap of the pair, input channel);
   // in transposed reads this lane points at voxel i / 4 of its K group of 4 x
@@ -390,7 +412,7 @@ __global__ __launch_bounds__(TRAIN_THREADS) void k_cnn3_train(
   // planes together), the same x in each, so that a step's reads differ from
   // the lane's first by a wave-uniform offset; x runs to 12: dz2's border is
   // zero there, and a1 reads at most two voxels past its end.
-  if (wave < KCH) {
+  if (wave < WPAIRS) {
     const int tz = ltap / 9, ty = (ltap / 3) % 3, tx = ltap % 3;
     const unsigned short* za = dz2 + ((2 * W0 + 2 + kq) * W0 + 2 + gx) * CH + c4;
     const unsigned short* aa = a1 + ((tz * W1 + ty + kq) * W1 + tx + gx) * CH + c4;
@@ -402,11 +424,11 @@ __global__ __launch_bounds__(TRAIN_THREADS) void k_cnn3_train(
     static_assert(W2 == 10, "rows 0 .. 7 in blocks of four, 8 and 9 in pairs of planes");
     for (int z = 0; z < W2; ++z) {
 #pragma unroll
-      for (int yb = 0; yb < 2; ++yb)
-#pragma unroll
-        for (int xg = 0; xg < 3; ++xg)
-          acc[xg] = mfma(load4_tr(za + ((z * W0 + 4 * yb) * W0 + 4 * xg) * CH),
-                         load4_tr(aa + ((z * W1 + 4 * yb) * W1 + 4 * xg) * CH), acc[xg]);
+      for (int xg = 0; xg < 3; ++xg)
+        acc[xg] = mfma32(join(load4_tr(za + (z * W0 * W0 + 4 * xg) * CH),
+                              load4_tr(za + ((z * W0 + 4) * W0 + 4 * xg) * CH)),
+                         join(load4_tr(aa + (z * W1 * W1 + 4 * xg) * CH),
+                              load4_tr(aa + ((z * W1 + 4) * W1 + 4 * xg) * CH)), acc[xg]);
       if (z & 1) continue;
 #pragma unroll
       for (int xg = 0; xg < 3; ++xg)
@@ -420,7 +442,7 @@ __global__ __launch_bounds__(TRAIN_THREADS) void k_cnn3_train(
         if (o < 8) part[CNN3_W2 + (o * 8 + wc) * 27 + wtap] = (acc[0][e] + acc[1][e]) + acc[2][e];
       }
     }
-  } else if (wave == KCH) {
+  } else if (wave == WPAIRS) {
     const int o = lane & 7;
     float s = 0.f;
 #pragma unroll 4
@@ -435,20 +457,18 @@ __global__ __launch_bounds__(TRAIN_THREADS) void k_cnn3_train(
   }
 
   // --- dz1[q][c] = relu'(z1) sum_tap sum_o W2[o][c][tap] dz2[q - tap][o]:
-  // D[i = voxel][j = c], K = (tap, o), 2 taps x 8 channels per chunk
+  // D[i = voxel][j = c], K = (tap, o), 4 taps x 8 channels per chunk
   {
-    s4 bop[KCH];
-#pragma unroll
-    for (int kc = 0; kc < KCH; ++kc)
-      bop[kc] = tap_weights(Wb + CNN3_W2 + (cg * 8 + (i & 7)) * 27, 8 * 27, 4, i < 8, 2 * kc + half);
+    const Operands w(w2f, i, kq);
+    const TapReads<W0, true> a(kq);
     constexpr int nblk = P1 / 16;
     for (int blk = TRAIN_WAVES - 1 - wave; blk < nblk; blk += TRAIN_WAVES) {
       const int q = 16 * blk + i;
       const int qz = q / (W1 * W1), qy = (q / W1) % W1, qx = q % W1;
-      const TapReads<W0, true> a(dz2 + ((qz * W0 + qy) * W0 + qx) * CH, half, cg);
+      const unsigned short* voxel = dz2 + ((qz * W0 + qy) * W0 + qx) * CH;
       f4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int kc = 0; kc < KCH; ++kc) acc = mfma(a(kc), bop[kc], acc);
+      for (int kc = 0; kc < KCH; ++kc) acc = mfma32(a(voxel, kc), w.b[kc], acc);
       if (i < 8) {
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
@@ -461,18 +481,21 @@ __global__ __launch_bounds__(TRAIN_THREADS) void k_cnn3_train(
   __syncthreads();
 
   // --- dW1[o][c][tap] = sum_p dz1[p][o] x[p + tap][c], db1 by the wave after
-  if (wave < KCH) {
+  if (wave < WPAIRS) {
     const unsigned short* da = dz1 + (kq * W1 + gx) * CH + c4;
     const unsigned short* xa = x + (((ltap / 9) * W0 + (ltap / 3) % 3 + kq) * W0 + ltap % 3 + gx) * CH + c4;
     f4 acc[3] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
     static_assert(W1 == 12, "three blocks of four rows and of four voxels in x");
-    for (int z = 0; z < W1; ++z)
+    for (int z = 0; z < W1; z += 2)
 #pragma unroll
       for (int yb = 0; yb < 3; ++yb)
 #pragma unroll
-        for (int xg = 0; xg < 3; ++xg)
-          acc[xg] = mfma(load4_tr(da + ((z * W1 + 4 * yb) * W1 + 4 * xg) * CH),
-                         load4_tr(xa + ((z * W0 + 4 * yb) * W0 + 4 * xg) * CH), acc[xg]);
+        for (int xg = 0; xg < 3; ++xg) {
+          const unsigned short* d = da + ((z * W1 + 4 * yb) * W1 + 4 * xg) * CH;
+          const unsigned short* v = xa + ((z * W0 + 4 * yb) * W0 + 4 * xg) * CH;
+          acc[xg] = mfma32(join(load4_tr(d), load4_tr(d + W1 * W1 * CH)),
+                           join(load4_tr(v), load4_tr(v + W0 * W0 * CH)), acc[xg]);
+        }
     if (wtap < 27 && wc < 5) {
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
@@ -480,7 +503,7 @@ __global__ __launch_bounds__(TRAIN_THREADS) void k_cnn3_train(
         if (o < 8) part[CNN3_W1 + (o * 5 + wc) * 27 + wtap] = (acc[0][e] + acc[1][e]) + acc[2][e];
       }
     }
-  } else if (wave == KCH) {
+  } else if (wave == WPAIRS) {
     const int o = lane & 7;
     float s = 0.f;
 #pragma unroll 4
@@ -510,7 +533,7 @@ __global__ __launch_bounds__(256) void k_cnn3_requests(int count, const float* _
 // ---------------------------------------------------------------------------
 // launch wrappers
 // ---------------------------------------------------------------------------
-size_t Cnn3::fwd_lds() { return (size_t)(P0 + P1) * CH * sizeof(unsigned short); }
+size_t Cnn3::fwd_lds() { return FL_TOTAL; }
 
 static void allow_large_lds3() {
   static bool done = false;

@@ -6,7 +6,9 @@
 //   A[i][k]: i = l % 16, k = 4 (l / 16) + e
 //   B[k][j]: j = l % 16, k = 4 (l / 16) + e
 //   D[i][j]: j = l % 16, i = 4 (l / 16) + e
-// (checked on the device by amr_cnn_mfma_selftest).
+// (checked on the device by amr_cnn_mfma_selftest).  The gfx950 form
+// v_mfma_f32_16x16x32_bf16 has twice the K at the same cost: k = 8 (l / 16) + e,
+// e = 0..7, D as above.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -36,6 +38,21 @@ __device__ __forceinline__ float bf2f(unsigned short h) { return __uint_as_float
 
 __device__ __forceinline__ f4 mfma(s4 a, s4 b, f4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b, c, 0, 0, 0);
+}
+
+typedef unsigned u4 __attribute__((ext_vector_type(4)));  // 8 BF16 values
+typedef __bf16 b8 __attribute__((ext_vector_type(8)));
+
+__device__ __forceinline__ f4 mfma32(u4 a, u4 b, f4 c) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(b8, a),
+                                                 __builtin_bit_cast(b8, b), c, 0, 0, 0);
+}
+
+// one operand of mfma32 from two of mfma (the K order is free as long as both
+// operands have the same)
+__device__ __forceinline__ u4 join(s4 a, s4 b) {
+  const uint2 x = __builtin_bit_cast(uint2, a), y = __builtin_bit_cast(uint2, b);
+  return u4{x.x, x.y, y.x, y.y};
 }
 
 __device__ __forceinline__ s4 load4(const unsigned short* p) {
