@@ -64,9 +64,14 @@ __global__ __launch_bounds__(256) void k_cnn_gather(DevMesh m, const double* __r
 }
 
 // ---------------------------------------------------------------------------
-// fused forward of one patch per block (4 waves); activations in LDS
+// fused forward of one patch per block; activations in LDS
 // ---------------------------------------------------------------------------
-constexpr int FWD_THREADS = 256;
+// A block per patch: more waves shorten its latency while a plane has blocks of
+// 16 pixels for them (25 and 21 of them at edge 16, 9 and 7 at edge 8).
+// With 4 waves, weights gathered by every wave from global memory and 16-wide K
+// chunks: 256 patches of edge 16 12.2 us, 4096 70; 7.2 and 40 now.
+constexpr int FWD_THREADS = 1024;
+static int fwd_threads(int n) { return n > 8 ? FWD_THREADS : 512; }
 
 // p / w for the pixel indices of a plane of edge w <= 38 (p < w^2) by one
 // product: m = ceil(2^16 / w) exceeds 2^16 / w by less than 1, so the product
@@ -87,23 +92,59 @@ __device__ __forceinline__ s4 w1_operand(const unsigned short* __restrict__ W, i
   return tap < 9 ? r : zero4();
 }
 
-// layer-2 B operand for tap: B[k = in-channel][j = out-channel] = W2[j][k][tap]
-__device__ __forceinline__ s4 w2_operand(const unsigned short* __restrict__ W, int j, int kq, int tap) {
-  s4 r;
-  r.x = (short)W[(j * 16 + 4 * kq + 0) * 9 + tap];
-  r.y = (short)W[(j * 16 + 4 * kq + 1) * 9 + tap];
-  r.z = (short)W[(j * 16 + 4 * kq + 2) * 9 + tap];
-  r.w = (short)W[(j * 16 + 4 * kq + 3) * 9 + tap];
-  return r;
+// Layer 2 takes K chunks of 32: 2 taps x 16 channels, a lane's 8 values being
+// channels 8 (kq % 2) .. of the pixel at tap 2 kc + kq / 2 (one 16-byte read).
+// Its weights in LDS as B operands: [10 taps][16 columns][16 K channels], tap 9
+// zero.
+constexpr int KC2 = 5;
+constexpr int OPS2 = 2 * KC2 * 16 * 16;
+
+// column j, K channel k and tap t from w[(j SJ + k SK) 9 + t], by the block
+template <int SJ, int SK>
+__device__ __forceinline__ void stage_operands(unsigned short* ops, const unsigned short* w) {
+  for (int t = threadIdx.x; t < OPS2; t += blockDim.x) {
+    const int k = t & 15, j = (t >> 4) & 15, tap = t >> 8;
+    ops[t] = tap < 9 ? w[(j * SJ + k * SK) * 9 + tap] : (unsigned short)0;
+  }
 }
+
+// One 16-pixel block of layer 2 (or, FLIP, of its data gradient): `pixel` is
+// this lane's pixel at tap 0 in a plane of width wi; FLIP reads backwards.
+template <bool FLIP>
+struct Conv2 {
+  u4 w[KC2];
+  int off[KC2];
+  bool last;  // the lane has a tap in the last chunk
+  __device__ __forceinline__ Conv2(const unsigned short* ops, int wi, int j, int kq)
+      : last(kq < 2) {
+#pragma unroll
+    for (int kc = 0; kc < KC2; ++kc) {
+      const int tap = 2 * kc + (kq >> 1), t = min(tap, 8);
+      w[kc] = reinterpret_cast<const u4*>(ops)[(tap * 16 + j) * 2 + (kq & 1)];
+      const int o = ((t / 3) * wi + t % 3) * 16;
+      off[kc] = (FLIP ? -o : o) + 8 * (kq & 1);
+    }
+  }
+  __device__ __forceinline__ f4 operator()(const unsigned short* pixel) const {
+    f4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int kc = 0; kc < KC2; ++kc) {
+      u4 a = *reinterpret_cast<const u4*>(pixel + off[kc]);
+      if (kc == KC2 - 1 && !last) a = u4{0u, 0u, 0u, 0u};
+      acc = mfma32(a, w[kc], acc);
+    }
+    return acc;
+  }
+};
 
 // conv 3x3 valid, 16 output channels, from an HWC LDS input of width wi and
 // CI channels (4 or 16) to an HWC LDS output of width wo = wi - 2 (bias, ReLU,
-// BF16); rows of 16 output pixels per MFMA tile.
+// BF16); rows of 16 output pixels per MFMA tile.  W: layer 1 as stored, layer 2
+// as staged operands.
 template <int CI>
 __device__ __forceinline__ void conv16(const unsigned short* __restrict__ in, int wi,
                                        unsigned short* __restrict__ out,
-                                       const unsigned short* __restrict__ Wb,
+                                       const unsigned short* __restrict__ W,
                                        const float* __restrict__ bias) {
   const int wo = wi - 2;
   const PixelDiv dv(wo);
@@ -112,33 +153,10 @@ __device__ __forceinline__ void conv16(const unsigned short* __restrict__ in, in
   const int wave = threadIdx.x >> 6;
   const int nw = blockDim.x >> 6;
   const int i = lane & 15, kq = lane >> 4;
-  constexpr int KC = CI == 4 ? 3 : 9;  // k-chunks of 16
-  s4 bop[KC];
-#pragma unroll
-  for (int kc = 0; kc < KC; ++kc) bop[kc] = CI == 4 ? w1_operand(Wb, i, kq, kc) : w2_operand(Wb, i, kq, kc);
   const float bcol = bias[i];  // D column j = lane % 16
   const int nblk = (P + 15) / 16;
-  for (int blk = wave; blk < nblk; blk += nw) {
-    // A rows: output pixel p = 16 blk + i (clamped for the tail)
-    int p = 16 * blk + i;
-    const int pc = p < P ? p : P - 1;
-    const int py = dv(pc), px = pc - py * wo;
-    f4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int kc = 0; kc < KC; ++kc) {
-      s4 a;
-      if (CI == 4) {
-        const int tap = 4 * kc + kq, t = tap < 9 ? tap : 8;
-        a = load4(in + ((py + t / 3) * wi + px + t % 3) * 4);
-        if (tap >= 9) a = zero4();
-      } else {
-        const int tap = kc;
-        const int ty = tap / 3, tx = tap - 3 * (tap / 3);
-        a = load4(in + ((py + ty) * wi + (px + tx)) * 16 + 4 * kq);
-      }
-      acc = mfma(a, bop[kc], acc);
-    }
-    // D[i'][j]: j = lane % 16, i' = 4 kq + e -> pixel 16 blk + 4 kq + e
+  // D[i'][j]: j = lane % 16, i' = 4 kq + e -> pixel 16 blk + 4 kq + e
+  auto store = [&](int blk, const f4& acc) {
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       const int q = 16 * blk + 4 * kq + e;
@@ -148,41 +166,101 @@ __device__ __forceinline__ void conv16(const unsigned short* __restrict__ in, in
         out[q * 16 + i] = f2bf_hw(v);
       }
     }
+  };
+  // A rows: output pixel p = 16 blk + i (clamped for the tail), at tap 0
+  auto pixel = [&](int blk) {
+    const int p = 16 * blk + i, pc = p < P ? p : P - 1;
+    const int py = dv(pc);
+    return in + (py * wi + pc - py * wo) * CI;
+  };
+  if constexpr (CI == 4) {
+    s4 bop[3];  // 3 chunks of 16: 4 taps x 4 channels
+    int off[3];
+#pragma unroll
+    for (int kc = 0; kc < 3; ++kc) {
+      const int t = min(4 * kc + kq, 8);
+      bop[kc] = w1_operand(W, i, kq, kc);
+      off[kc] = ((t / 3) * wi + t % 3) * 4;
+    }
+    for (int blk = wave; blk < nblk; blk += nw) {
+      const unsigned short* at = pixel(blk);
+      f4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int kc = 0; kc < 3; ++kc) {
+        s4 a = load4(at + off[kc]);
+        if (4 * kc + kq >= 9) a = zero4();
+        acc = mfma(a, bop[kc], acc);
+      }
+      store(blk, acc);
+    }
+  } else {
+    const Conv2<false> conv(W, wi, i, kq);
+    for (int blk = wave; blk < nblk; blk += nw) store(blk, conv(pixel(blk)));
   }
 }
+
+// LDS of the forward kernel (bytes)
+struct FwdLds {
+  int a1, a2, w1, w2, w3, total;
+  __host__ __device__ explicit FwdLds(int n) {
+    const int P0 = (n + 6) * (n + 6), P1 = (n + 4) * (n + 4), P2 = (n + 2) * (n + 2);
+    a1 = (P0 * 4 * 2 + 15) / 16 * 16;
+    a2 = a1 + P1 * 16 * 2;
+    w1 = a2 + P2 * 16 * 2;
+    w2 = w1 + 16 * 4 * 9 * 2;
+    w3 = w2 + OPS2 * 2;
+    total = w3 + 144 * 4;
+  }
+};
 
 __global__ __launch_bounds__(FWD_THREADS) void k_cnn_fwd(int count, int n,
                                                          const unsigned short* __restrict__ X,
                                                          const unsigned short* __restrict__ Wb,
                                                          const float* __restrict__ params,
                                                          float* __restrict__ Z) {
-  extern __shared__ unsigned short smem[];
+  extern __shared__ __align__(16) unsigned char fwd_smem[];
   const int b = blockIdx.x;
   if (b >= count) return;
+  const FwdLds S(n);
   const int w0 = n + 6, w1 = n + 4, w2 = n + 2;
-  const int P0 = w0 * w0, P1 = w1 * w1, P2 = w2 * w2;
-  unsigned short* sx = smem;                 // P0 x 4
-  unsigned short* s1 = sx + P0 * 4;          // P1 x 16
-  unsigned short* s2 = s1 + P1 * 16;         // P2 x 16
+  const int P0 = w0 * w0;
+  unsigned short* sx = (unsigned short*)fwd_smem;           // P0 x 4
+  unsigned short* s1 = (unsigned short*)(fwd_smem + S.a1);  // P1 x 16
+  unsigned short* s2 = (unsigned short*)(fwd_smem + S.a2);  // P2 x 16
+  unsigned short* W1 = (unsigned short*)(fwd_smem + S.w1);
+  unsigned short* W2 = (unsigned short*)(fwd_smem + S.w2);
+  float* W3 = (float*)(fwd_smem + S.w3);                    // 9 taps x 16
   const unsigned short* xg = X + (long long)b * P0 * 4;
   for (int t = threadIdx.x; t < P0; t += blockDim.x)
     *reinterpret_cast<uint2*>(sx + 4 * t) = *reinterpret_cast<const uint2*>(xg + 4 * t);
+  for (int t = threadIdx.x; t < 576; t += blockDim.x) W1[t] = Wb[CNN_W1 + t];
+  stage_operands<16, 1>(W2, Wb + CNN_W2);
+  for (int t = threadIdx.x; t < 144; t += blockDim.x) W3[(t % 9) * 16 + t / 9] = bf2f(Wb[CNN_W3 + t]);
   __syncthreads();
-  conv16<4>(sx, w0, s1, Wb + CNN_W1, params + CNN_B1);
+  conv16<4>(sx, w0, s1, W1, params + CNN_B1);
   __syncthreads();
-  conv16<16>(s1, w1, s2, Wb + CNN_W2, params + CNN_B2);
+  conv16<16>(s1, w1, s2, W2, params + CNN_B2);
   __syncthreads();
   // layer 3 (16 -> 1) on the VALU
   const int P3 = n * n;
+  const PixelDiv div3(n);
   const float b3 = params[CNN_B3];
   for (int p = threadIdx.x; p < P3; p += blockDim.x) {
-    const int py = p / n, px = p - py * n;
+    const int py = div3(p), px = p - py * n;
     float acc = 0.f;
+#pragma unroll 1  // all 9 taps' weights do not fit the registers
     for (int tap = 0; tap < 9; ++tap) {
-      const int ty = tap / 3, tx = tap % 3;
-      const unsigned short* a = s2 + ((py + ty) * w2 + (px + tx)) * 16;
+      const unsigned short* at = s2 + ((py + tap / 3) * w2 + px + tap % 3) * 16;
 #pragma unroll
-      for (int c = 0; c < 16; ++c) acc += bf2f(a[c]) * bf2f(Wb[CNN_W3 + c * 9 + tap]);
+      for (int h = 0; h < 2; ++h) {
+        const u4 a = *reinterpret_cast<const u4*>(at + 8 * h);
+        const float4 wa = *reinterpret_cast<const float4*>(W3 + tap * 16 + 8 * h);
+        const float4 wb = *reinterpret_cast<const float4*>(W3 + tap * 16 + 8 * h + 4);
+        const float w[8] = {wa.x, wa.y, wa.z, wa.w, wb.x, wb.y, wb.z, wb.w};
+#pragma unroll
+        for (int c = 0; c < 8; ++c)
+          acc += bf2f((unsigned short)(a[c >> 1] >> (16 * (c & 1)))) * w[c];
+      }
     }
     Z[(long long)b * P3 + p] = acc + b3;
   }
@@ -197,7 +275,7 @@ __global__ __launch_bounds__(FWD_THREADS) void k_cnn_fwd(int count, int n,
 // gradients (no activation goes through memory), the reductions spread over
 // the waves as MFMA chains.  It replaces a forward, a loss and a backward
 // launch (with 8 waves and serial per-parameter loops): 11.5 + 4.5 + 68.9 us
-// for 64 patches of edge 16, 20.4 us now.
+// for 64 patches of edge 16; 20.4 us with 16-wide K chunks, 18.5 now.
 constexpr int TRAIN_THREADS = 1024;
 constexpr int TRAIN_WAVES = TRAIN_THREADS / 64;
 
@@ -206,19 +284,21 @@ constexpr int TRAIN_WAVES = TRAIN_THREADS / 64;
 // W3, which are read before it is written; dz2 is stored with a border of two
 // zero pixels, so that the data gradient reads it without bounds checks.
 struct TrainLds {
-  int x, a1, a2, g, w3, dz1, dz2, red, wb, total;
+  int x, a1, a2, g, w3, dz1, dz2, red, w1, w2, w2f, total;
   __host__ __device__ explicit TrainLds(int n) {
     const int P0 = (n + 6) * (n + 6), P1 = (n + 4) * (n + 4), P2 = (n + 2) * (n + 2), P3 = n * n;
     x = 0;
-    a1 = x + P0 * 4 * 2;
+    a1 = x + (P0 * 4 * 2 + 15) / 16 * 16;
     a2 = dz1 = a1 + P1 * 16 * 2;
     g = a2 + P2 * 16 * 2;
     w3 = g + P3 * 4;
     const int after_a = w3 + 144 * 4, after_b = dz1 + (P1 + 15) / 16 * 16 * 32;
-    dz2 = after_a > after_b ? after_a : after_b;
+    dz2 = ((after_a > after_b ? after_a : after_b) + 15) / 16 * 16;
     red = dz2 + P1Z(n) * 16 * 2;
-    wb = red + 12 * 256 * 4;
-    total = wb + ((CNN_NPARAM * 2 + 15) / 16) * 16;
+    w2 = dz2;  // until layer 2 is done
+    w1 = red + 12 * 256 * 4;
+    w2f = w1 + 16 * 4 * 9 * 2;
+    total = w2f + OPS2 * 2;
   }
   static __host__ __device__ int P1Z(int n) { return (n + 6) * (n + 6); }  // dz2 with its border
 };
@@ -241,7 +321,9 @@ __global__ __launch_bounds__(TRAIN_THREADS) void k_cnn_train(
   unsigned short* dz1 = (unsigned short*)(train_smem + S.dz1);  // P1 x 16
   unsigned short* dz2 = (unsigned short*)(train_smem + S.dz2);  // (w2 + 4)^2 x 16
   float* red = (float*)(train_smem + S.red);
-  unsigned short* Wb = (unsigned short*)(train_smem + S.wb);
+  unsigned short* W1 = (unsigned short*)(train_smem + S.w1);
+  unsigned short* W2 = (unsigned short*)(train_smem + S.w2);
+  unsigned short* W2f = (unsigned short*)(train_smem + S.w2f);
   const int w0 = n + 6, w1 = n + 4, w2 = n + 2, wz = n + 6;
   const int P0 = w0 * w0, P1 = w1 * w1, P2 = w2 * w2, P3 = n * n;
   const PixelDiv div1(w1), div2(w2), div3(n);
@@ -252,16 +334,18 @@ __global__ __launch_bounds__(TRAIN_THREADS) void k_cnn_train(
   {
     const uint2* gx = reinterpret_cast<const uint2*>(X + (long long)b * P0 * 4);
     for (int t = tid; t < P0; t += TRAIN_THREADS) reinterpret_cast<uint2*>(x)[t] = gx[t];
-    for (int t = tid; t < CNN_NPARAM; t += TRAIN_THREADS) Wb[t] = Wg[t];
-    const uint4 z = {0u, 0u, 0u, 0u};
-    for (int t = tid; t < wz * wz * 2; t += TRAIN_THREADS) reinterpret_cast<uint4*>(dz2)[t] = z;
+    for (int t = tid; t < 576; t += TRAIN_THREADS) W1[t] = Wg[CNN_W1 + t];
+    stage_operands<16, 1>(W2, Wg + CNN_W2);
+    stage_operands<1, 16>(W2f, Wg + CNN_W2);
     if (tid < 144) w3[(tid % 9) * 16 + tid / 9] = bf2f(Wg[CNN_W3 + tid]);
   }
   __syncthreads();
-  conv16<4>(x, w0, a1, Wb + CNN_W1, params + CNN_B1);
+  conv16<4>(x, w0, a1, W1, params + CNN_B1);
   __syncthreads();
-  conv16<16>(a1, w1, a2, Wb + CNN_W2, params + CNN_B2);
+  conv16<16>(a1, w1, a2, W2, params + CNN_B2);
   __syncthreads();
+  for (int t = tid; t < wz * wz * 2; t += TRAIN_THREADS)
+    reinterpret_cast<uint4*>(dz2)[t] = uint4{0u, 0u, 0u, 0u};
 
   // --- layer 3 and the loss: 4 lanes per pixel, 4 channels each; the logit
   // gradient of the mean over all cells
@@ -367,23 +451,23 @@ __global__ __launch_bounds__(TRAIN_THREADS) void k_cnn_train(
   const int row = 4 * kq + (i16 >> 2), col = 4 * (i16 & 3);
   if (wave < 9) {
     const int shift = ((wave / 3) * w1 + wave % 3) * 16 + col;
-    auto step = [&](int p0, f4 acc) {
-      const int p = p0 + row;
-      // past the last pixel: a border pixel of dz2 (zero)
-      const bool in = p < P2;
-      const int py = div2(in ? p : 0), px = (in ? p : 0) - py * w2;
-      const s4 a = load4_tr(dz2 + (in ? ((py + 2) * wz + px + 2) * 16 : 0) + col);
-      const s4 bb = load4_tr(a1 + (py * w1 + px) * 16 + shift);
-      return mfma(a, bb, acc);
-    };
-    f4 acc0 = {0.f, 0.f, 0.f, 0.f}, acc1 = acc0;
+    f4 acc = {0.f, 0.f, 0.f, 0.f};
     for (int p0 = 0; p0 < P2; p0 += 32) {
-      acc0 = step(p0, acc0);
-      acc1 = step(p0 + 16, acc1);
+      s4 a[2], bb[2];
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const int p = p0 + 16 * h + row;
+        // past the last pixel: a border pixel of dz2 (zero)
+        const bool in = p < P2;
+        const int py = div2(in ? p : 0), px = (in ? p : 0) - py * w2;
+        a[h] = load4_tr(dz2 + (in ? ((py + 2) * wz + px + 2) * 16 : 0) + col);
+        bb[h] = load4_tr(a1 + (py * w1 + px) * 16 + shift);
+      }
+      acc = mfma32(join(a[0], a[1]), join(bb[0], bb[1]), acc);
     }
 #pragma unroll
     for (int e = 0; e < 4; ++e)
-      part[CNN_W2 + ((4 * kq + e) * 16 + i16) * 9 + wave] = acc0[e] + acc1[e];
+      part[CNN_W2 + ((4 * kq + e) * 16 + i16) * 9 + wave] = acc[e];
   } else if (wave == 9) {
     float s = 0.f;
 #pragma unroll 4
@@ -398,23 +482,14 @@ __global__ __launch_bounds__(TRAIN_THREADS) void k_cnn_train(
   // --- dz1[q][c] = relu'(z1) sum_tap sum_o W2[o][c][tap] dz2[q - tap][o]:
   // D[i = pixel][j = c], stored like the activations in whole blocks of 16 pixels
   {
-    s4 bop[9];
-#pragma unroll
-    for (int tap = 0; tap < 9; ++tap) {
-      const unsigned short* w = Wb + CNN_W2 + (4 * kq * 16 + i16) * 9 + tap;
-      bop[tap] = pack4((short)w[0], (short)w[16 * 9], (short)w[32 * 9], (short)w[48 * 9]);
-    }
+    const Conv2<true> conv(W2f, wz, i16, kq);
     const int nblk = (P1 + 15) / 16;
     // the waves without a tap above take their blocks first
     for (int blk = TRAIN_WAVES - 1 - wave; blk < nblk; blk += TRAIN_WAVES) {
       const int p = 16 * blk + i16;
       const int pc = p < P1 ? p : P1 - 1;
       const int qy = div1(pc), qx = pc - qy * w1;
-      const unsigned short* base = dz2 + ((qy + 2) * wz + qx + 2) * 16 + 4 * kq;
-      f4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int tap = 0; tap < 9; ++tap)
-        acc = mfma(load4(base - ((tap / 3) * wz + tap % 3) * 16), bop[tap], acc);
+      const f4 acc = conv(dz2 + ((qy + 2) * wz + qx + 2) * 16);
       // the rows past the last pixel of the last block are zero
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
@@ -434,11 +509,22 @@ __global__ __launch_bounds__(TRAIN_THREADS) void k_cnn_train(
     const int tap = 4 * kc + (i16 & 3);  // taps 9 .. 11 do not exist: columns not used
     const int shift = tap < 9 ? ((tap / 3) * w0 + tap % 3) * 4 : 0;
     f4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll 2
-    for (int p0 = 16 * quarter; p0 < P1; p0 += 64) {
+    auto step = [&](int p0, s4& a, s4& v) {
       const int p = p0 + row, pc = p < P1 ? p : 0;
       const int py = div1(pc), px = pc - py * w1;
-      acc = mfma(load4_tr(dz1 + p * 16 + col), load4_tr(x + (py * w0 + px) * 4 + shift), acc);
+      a = load4_tr(dz1 + p * 16 + col);
+      v = load4_tr(x + (py * w0 + px) * 4 + shift);
+    };
+    int p0 = 16 * quarter;
+    s4 a, v, a2, v2;
+    for (; p0 + 64 < P1; p0 += 128) {
+      step(p0, a, v);
+      step(p0 + 64, a2, v2);
+      acc = mfma32(join(a, a2), join(v, v2), acc);
+    }
+    if (p0 < P1) {
+      step(p0, a, v);
+      acc = mfma(a, v, acc);
     }
 #pragma unroll
     for (int e = 0; e < 4; ++e) red[wave * 256 + (4 * kq + e) * 16 + i16] = acc[e];
@@ -557,10 +643,7 @@ __global__ void k_mfma_selftest(const unsigned short* __restrict__ A, const unsi
 // ---------------------------------------------------------------------------
 // launch wrappers
 // ---------------------------------------------------------------------------
-size_t Cnn::fwd_lds(int n) {
-  const int w0 = n + 6, w1 = n + 4, w2 = n + 2;
-  return (size_t)(w0 * w0 * 4 + w1 * w1 * 16 + w2 * w2 * 16) * sizeof(unsigned short);
-}
+size_t Cnn::fwd_lds(int n) { return FwdLds(n).total; }
 
 void Cnn::gather(const DevMesh& m, const double* U, const int* pids, int count, int n,
                  const CnnNorm& norm, unsigned short* X, hipStream_t s) {
@@ -584,7 +667,7 @@ void Cnn::forward(int count, int n, const unsigned short* X, const unsigned shor
                   const float* params, float* Z, hipStream_t s) {
   if (count <= 0) return;
   allow_large_lds();
-  hipLaunchKernelGGL(k_cnn_fwd, dim3(count), dim3(FWD_THREADS), fwd_lds(n), s, count, n, X, Wb,
+  hipLaunchKernelGGL(k_cnn_fwd, dim3(count), dim3(fwd_threads(n)), fwd_lds(n), s, count, n, X, Wb,
                      params, Z);
 }
 
