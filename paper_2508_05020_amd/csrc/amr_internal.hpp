@@ -168,12 +168,16 @@ struct Kernels {
                   uint8_t* has_tag, uint8_t* raw, bool fuse, hipStream_t s);
   // 3D, fused halo: tag flags of every active patch (`list` in level order,
   // level_count patches per level; prolonged regions filled before); mask:
-  // scratch of max_patches ints
+  // scratch of max_patches ints; raw (nullable): the tag of each patch's own
+  // cells and, in a leaf's ghost places, of the prolonged cells within tag_buffer
   static void tag_flags3(const DevMesh& m, const double* U, const int* list,
                          const int* level_count, const int* regions, int nregions, int* mask,
-                         uint8_t* has_tag, hipStream_t s);
-  static void cell_tags(const DevMesh& m, const uint8_t* raw, const int* list, int count,
-                        uint8_t* out, hipStream_t s);
+                         uint8_t* has_tag, uint8_t* raw, hipStream_t s);
+  // cells of the leaves with a tag within tag_buffer; shared: raw as tag_flags3
+  // (3D) writes it, else as tag does; level_leaves (nullable): leaves per level,
+  // the list in level order
+  static void cell_tags(const DevMesh& m, const uint8_t* raw, const int* leaves, int count,
+                        const int* level_leaves, bool shared, uint8_t* out, hipStream_t s);
   static void requests(const DevMesh& m, const uint8_t* has_tag, const uint8_t* active_leaf,
                        int nslots, uint8_t* refine, uint8_t* coarsen, hipStream_t s);
   static void prolong_new(const DevMesh& m, double* U, const int* list, int count, int* err,

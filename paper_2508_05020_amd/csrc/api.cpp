@@ -133,7 +133,8 @@ struct amr_hierarchy {
   std::vector<int> lists;
   // cffaces: the face regions of cfregions (all the stage kernel reads;
   // the tagger's dilated box reads the edge and corner regions too)
-  int level_count[amr::kMaxLev] = {};  // active patches per level
+  int level_count[amr::kMaxLev] = {};   // active patches per level
+  int level_leaves[amr::kMaxLev] = {};  // leaves per level
   amr::ListView all{}, leaves{}, tiles{}, reflux{}, cfregions{}, cffaces{}, cands{};
   // post-stage restriction (see Kernels::post): level-(L-2) patches with
   // children, and per level the patches with children (the stage kernel
@@ -431,8 +432,12 @@ void sync_tables(amr_hierarchy* h, bool full) {
     ++h->level_count[f.level[pid]];
   }
   const int a1 = begin_list();
+  std::fill(h->level_leaves, h->level_leaves + amr::kMaxLev, 0);
   for (int pid : order)
-    if (f.is_leaf(pid)) L.push_back(pid);
+    if (f.is_leaf(pid)) {
+      L.push_back(pid);
+      ++h->level_leaves[f.level[pid]];
+    }
   // (leaf, ghost region) pairs whose ghost cells are prolonged, then the face
   // regions among them
   const int c0 = begin_list();
@@ -805,10 +810,12 @@ void do_tag(amr_hierarchy* h, int buf, uint8_t* refine, uint8_t* coarsen, uint8_
     do_fill(h, buf, h->leaves);
     do_fill(h, buf, h->cands);
   }
-  if (h->cfg.dim == 3 && fuse && !cells && h->exec_mode == AMR_EXEC_BATCHED) {
-    // flags only: every cell tested once, the patches share the outcome
+  const bool shared = h->cfg.dim == 3 && fuse && h->exec_mode == AMR_EXEC_BATCHED;
+  if (shared) {
+    // every cell tested once, the patches share the outcome
     Kernels::tag_flags3(h->dm, h->U[buf], h->all.ptr, h->level_count, h->cfregions.ptr,
-                        h->cfregions.count, h->d_tag_mask, h->d_has_tag, h->stream);
+                        h->cfregions.count, h->d_tag_mask, h->d_has_tag, cells ? h->d_raw : nullptr,
+                        h->stream);
     h->check_launch();
   } else {
     over_list(h, h->leaves, 1, [&](const int* p, int c) {
@@ -821,7 +828,9 @@ void do_tag(amr_hierarchy* h, int buf, uint8_t* refine, uint8_t* coarsen, uint8_
   }
   if (cells)
     over_list(h, h->leaves, 1, [&](const int* p, int c) {
-      Kernels::cell_tags(h->dm, h->d_raw, p, c, cells, h->stream);
+      Kernels::cell_tags(h->dm, h->d_raw, p, c,
+                         h->exec_mode == AMR_EXEC_BATCHED ? h->level_leaves : nullptr, shared,
+                         cells, h->stream);
     });
   Kernels::requests(h->dm, h->d_has_tag, h->d_active_leaf, h->forest.max_patches, refine, coarsen,
                     h->stream);
