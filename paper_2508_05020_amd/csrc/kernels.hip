@@ -1118,7 +1118,9 @@ __global__ __launch_bounds__(256) void k_tag_cells(DevMesh m, const double* __re
 
 // Ghost regions without a same-level patch, 4 per block: bit 27 of the leaf's
 // mask is set when a cell of the region within tag_buffer of the leaf is
-// tagged (values prolonged into the leaf's ghost layer by the fill).
+// tagged (values prolonged into the leaf's ghost layer by the fill).  Bound by
+// the lines it fetches (1.4 GB for 205 us, mostly ghost rows of 32 bytes);
+// consecutive groups share an XCD as in k_tag_cells (214 us in launch order).
 __global__ __launch_bounds__(128) void k_tag_regions(DevMesh m, const double* __restrict__ U,
                                                      const int* __restrict__ list, int count,
                                                      int* __restrict__ mask, uint8_t* __restrict__ raw) {
@@ -1126,10 +1128,12 @@ __global__ __launch_bounds__(128) void k_tag_regions(DevMesh m, const double* __
   __shared__ long long sNB[G][27];
   __shared__ int s_pid[G], s_code[G], s_lev[G], s_pc[G][3], s_pre[G + 1];
   const int b = m.tag_buffer;
+  const int bb = xcd_chunk<kTagChunk>((count + G - 1) / G);
+  if (bb < 0) return;
   {
     // one neighbour table per region, by the threads [27 g, 27 g + 27)
     const int g = (int)threadIdx.x / 27, t = (int)threadIdx.x - 27 * g;
-    const int i = (int)blockIdx.x * G + g;
+    const int i = bb * G + g;
     if (g < G && i < count) {
       const int pid = list[2 * i], l = m.level[pid], np = m.lv[l].np;
       int q[3];
@@ -1152,7 +1156,7 @@ __global__ __launch_bounds__(128) void k_tag_regions(DevMesh m, const double* __
     s_pre[0] = 0;
 #pragma unroll
     for (int g = 0; g < G; ++g) {
-      const int i = (int)blockIdx.x * G + g;
+      const int i = bb * G + g;
       int cells = 0;
       if (i < count) {
         const int pid = list[2 * i], code = list[2 * i + 1], l = m.level[pid];
@@ -1555,7 +1559,8 @@ void Kernels::tag_flags3(const DevMesh& m, const double* U, const int* list, con
                      list, tl, blocks, mask, raw);
   // without dilation no ghost cell counts
   if (nregions > 0 && m.tag_buffer > 0)
-    hipLaunchKernelGGL(k_tag_regions, dim3((nregions + 3) / 4), dim3(128), 0, s, m, U, regions,
+    hipLaunchKernelGGL(k_tag_regions, dim3(((nregions + 3) / 4 + group - 1) / group * group),
+                       dim3(128), 0, s, m, U, regions,
                        nregions, mask, raw);
   hipLaunchKernelGGL(k_tag_flags, dim3((count + 31) / 32), dim3(256), 0, s, m, list, count, mask,
                      has_tag);
