@@ -183,9 +183,9 @@ amr_status amr_compute_dt(amr_hierarchy* h, int buf, double* dt_dev);
 
 /* One SSP-RK3 stage (1, 2 or 3; async): fill the ghosts of the stage input
  * that the stencils read (as amr_rhs), fused RHS + stage combination on
- * every leaf (tiles of the finest level also restrict themselves into their
- * parents), coarse/fine flux correction, restriction of every other
- * non-leaf patch.  dt is read from the device scalar. */
+ * every leaf (which also restricts it into its parent), coarse/fine flux
+ * correction with the parents' cells along the corrected faces, restriction
+ * of the patches with children.  dt is read from the device scalar. */
 amr_status amr_rk_stage(amr_hierarchy* h, int stage, const double* dt_dev);
 
 /* dt (into *dt_dev) followed by the three stages (async).  In batched mode
@@ -348,7 +348,9 @@ amr_status amr_cnn_mfma_selftest(amr_hierarchy* h, const uint16_t* a_dev, const 
  * directory that regrids rewrite, and after a regrid that changes the mesh
  * the next replay first sets the grid of each list launch in the
  * instantiated graph to the list's new length, so regrids never record the
- * graphs again (with the fused halo off, the explicit ghost fill is sized by
+ * graphs again (eager launches take the lists as they are; when the caller
+ * records a call into a graph of its own they read the directory too, and the
+ * grids stay those of the recording; with the fused halo off, the explicit ghost fill is sized by
  * the leaf count and every mesh change re-records them).  A change of tile
  * variant, execution mode, halo mode, tag dilation or dt pointer re-records
  * them.  Enabling an enabled graph mode keeps the recorded graphs.  Results
@@ -374,8 +376,9 @@ amr_status amr_autotune(amr_hierarchy* h, int reps, int* best, float* best_ms);
 
 /* Halo source of the fused stage kernel: 1 (default) reads halo nodes that
  * lie in same-level neighbours straight from those neighbours, and only the
- * ghost cells that need prolongation are filled beforehand (over the ghost
- * regions without a same-level source); 0 runs the full fill kernel first
+ * ghost cells that need prolongation are filled (over the face ghost regions
+ * without a same-level source; by a launch beforehand in 2D and 3D, by the
+ * stage kernel itself in 1D); 0 runs the full fill kernel first
  * and reads the filled ghost layers.  Results are identical. */
 amr_status amr_set_fused_halo(amr_hierarchy* h, int enable);
 

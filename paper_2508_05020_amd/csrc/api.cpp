@@ -73,6 +73,8 @@ struct amr_hierarchy {
   };
   bool use_graph = false;
   bool capturing = false;
+  // the caller is recording the stream into a graph of its own (note_capture)
+  bool caller_records = false;
   int cap_slot = 0;
   hipStream_t cap_stream = nullptr;
   hipGraph_t step_graph[2] = {nullptr, nullptr};
@@ -659,7 +661,15 @@ void note_node(amr_hierarchy* h, int kind, int e0, int e1 = -1, int e2 = -1) {
   h->gnodes[h->cap_slot].push_back(g);
 }
 
-// The step's kernels: in batched mode one launch over the list; while a step
+// Whether the caller records the work of this call: the launches then read
+// their lists from the directory, as in the library's own graphs.
+void note_capture(amr_hierarchy* h) {
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(h->stream, &st) != hipSuccess) (void)hipGetLastError();
+  h->caller_records = st == hipStreamCaptureStatusActive;
+}
+
+// The step's kernels: in batched mode one launch over the list; while a
 // graph is recorded it reads the list and its live count from the list
 // directory (launch(list buffer, grid count, directory entry)), eagerly it
 // takes them as they are (launch(list, count, null)), one dependent load less
@@ -668,7 +678,7 @@ template <typename F>
 void over_list_dir(amr_hierarchy* h, const amr::ListView& lv, int stride_ints, int kind,
                    F launch) {
   if (h->exec_mode == AMR_EXEC_BATCHED) {
-    if (h->capturing)
+    if (h->capturing || h->caller_records)
       launch(h->d_lists, grid_count(h, lv), lv.dir);
     else
       launch(lv.ptr, lv.count, (const int*)nullptr);
@@ -745,7 +755,7 @@ void do_stage(amr_hierarchy* h, int stage, const double* dt,
     // follow, finest first (lists and counts from the list directory: the two
     // post-stage entries are consecutive)
     const int lup = h->forest.nlev - 2;
-    const bool rec = h->capturing;
+    const bool rec = h->capturing || h->caller_records;
     Kernels::post(h->dm, stage, h->U[d], h->fr, (const amr::RefluxItem*)(rec ? h->d_lists : h->reflux.ptr),
                   grid_count(h, h->reflux), rec ? h->d_lists : h->post_pairs.ptr,
                   grid_count(h, h->post_pairs), rec ? h->reflux.dir : nullptr, dt, w[stage],
@@ -802,6 +812,7 @@ void do_tag(amr_hierarchy* h, int buf, uint8_t* refine, uint8_t* coarsen, uint8_
   // candidates have children, hence every same-level neighbour, and need
   // none); else full fills
   const bool fuse = h->fuse_halo;
+  note_capture(h);
   if (fuse) {
     over_list_dir(h, h->cfregions, 2, kGnFill, [&](const int* p, int c, const int* dir) {
       Kernels::fill_cf(h->dm, h->U[buf], p, c, dir, h->d_flags, h->stream);
@@ -1233,6 +1244,7 @@ amr_status amr_fill_ghosts(amr_hierarchy* h, int buf) {
 amr_status amr_rhs(amr_hierarchy* h, int buf, double* rhs_dev) {
   if (!h || !buf_ok(buf) || !rhs_dev) return AMR_E_ARG;
   return guarded(h, [&]() -> amr_status {
+    note_capture(h);
     stage_fill(h, buf);
     over_list_dir(h, h->tiles, kItemInts, kGnStage, [&](const int* p, int c, const int* dir) {
       Kernels::stage(h->dm, amr::kModeRHS, h->U[buf], h->d_flags, h->U[0], rhs_dev, h->fr,
@@ -1259,6 +1271,7 @@ amr_status amr_rk_stage(amr_hierarchy* h, int stage, const double* dt_dev) {
   if (!h || stage < 1 || stage > 3 || !dt_dev) return AMR_E_ARG;
   h->lam_valid = false;
   return guarded(h, [&]() -> amr_status {
+    note_capture(h);
     do_stage(h, stage, dt_dev);
     return AMR_OK;
   });
@@ -1267,6 +1280,7 @@ amr_status amr_rk_stage(amr_hierarchy* h, int stage, const double* dt_dev) {
 amr_status amr_step(amr_hierarchy* h, double* dt_dev) {
   if (!h) return AMR_E_ARG;
   return guarded(h, [&]() -> amr_status {
+    note_capture(h);
     double* dt = dt_dev ? dt_dev : h->d_dt;
     const int cur = h->lam_cur;
     if (!h->lam_valid) do_rate(h, 0, cur);

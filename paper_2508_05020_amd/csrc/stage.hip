@@ -1298,7 +1298,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(CHAR ? 4 : 6
 
 // Items of a (pid, tile) list, a thread each (see StageItem).
 template <int D>
-__global__ __launch_bounds__(64) void k_stage_items(DevMesh m, const int* __restrict__ tiles,
+__global__ __launch_bounds__(64) void k_item_tables(DevMesh m, const int* __restrict__ tiles,
                                                     int count, int tx, int ty, int tz,
                                                     const uint8_t* __restrict__ cfmask,
                                                     StageItem* __restrict__ items) {
@@ -1355,9 +1355,9 @@ void Kernels::stage_items(const DevMesh& m, const int* tiles, int count, const u
   const TileVariant& t = variant(m.tile);
   const dim3 grid((count + 63) / 64), block(64);
   switch (t.dim) {
-    case 1: hipLaunchKernelGGL(k_stage_items<1>, grid, block, 0, s, m, tiles, count, t.tx, t.ty, t.tz, cfmask, items); break;
-    case 2: hipLaunchKernelGGL(k_stage_items<2>, grid, block, 0, s, m, tiles, count, t.tx, t.ty, t.tz, cfmask, items); break;
-    default: hipLaunchKernelGGL(k_stage_items<3>, grid, block, 0, s, m, tiles, count, t.tx, t.ty, t.tz, cfmask, items); break;
+    case 1: hipLaunchKernelGGL(k_item_tables<1>, grid, block, 0, s, m, tiles, count, t.tx, t.ty, t.tz, cfmask, items); break;
+    case 2: hipLaunchKernelGGL(k_item_tables<2>, grid, block, 0, s, m, tiles, count, t.tx, t.ty, t.tz, cfmask, items); break;
+    default: hipLaunchKernelGGL(k_item_tables<3>, grid, block, 0, s, m, tiles, count, t.tx, t.ty, t.tz, cfmask, items); break;
   }
 }
 
