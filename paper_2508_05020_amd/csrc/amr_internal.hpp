@@ -18,6 +18,11 @@ constexpr int kMaxLev = AMR_MAX_LEVELS;
 // Per-level constants, mirrored on the device by value.
 // XCDs of the MI355X (gfx950): 8 dies of 32 compute units, one L2 each.
 constexpr int kXcds = 8;
+// A CFL-rate slot: the maximum is kept as kXcds parts (the blocks of each XCD
+// raise their own, 128 bytes apart: atomics on one address are served one after
+// the other), and the rate is the largest of them.
+constexpr int kRateStride = 16;                  // 64-bit words between parts
+constexpr int kRateWords = kXcds * kRateStride;  // words of a slot
 
 struct LevelC {
   int n;             // patch edge (cells)
@@ -126,8 +131,8 @@ struct Kernels {
   // lam_next (nullable, stage 3 only): accumulate the next step's CFL rate
   // over leaf cells not on coarse/fine faces
   // ev0/ev1 (optional): events stamped at the dispatch's own start and end.
-  // lam_in (stage 1 only, optional): take dt = CFL / *lam_in instead of *dt,
-  // write it to *dt_out and clear *lam_next (the slot stage 3 accumulates in)
+  // lam_in (stage 1 only, optional): take dt = CFL / the rate in that slot instead of *dt,
+  // write it to *dt_out and clear lam_next (the slot stage 3 accumulates in)
   // In the stage modes a tile of a leaf (level >= 1) also restricts its new
   // values into its parent patch; post corrects this where it refluxes.
   static void stage(const DevMesh& m, int mode, double* Uin, int* err, const double* Un,
@@ -158,8 +163,8 @@ struct Kernels {
                              const int* dir, hipStream_t s);
   static void max_rate(const DevMesh& m, const double* U, const int* list, int count,
                        unsigned long long* lam_bits, hipStream_t s);
-  static void zero_u64(unsigned long long* p, hipStream_t s);
-  // dt = cfl / rate; also zeroes *clear (nullable), the next rate accumulator
+  static void zero_rate(unsigned long long* slot, hipStream_t s);
+  // dt = cfl / rate; also clears the slot `clear` (nullable), the next accumulator
   static void dt_from_rate(const DevMesh& m, const unsigned long long* lam_bits,
                            double* dt, unsigned long long* clear, hipStream_t s);
   // fuse: halo cells read from same-level neighbours directly; ghost layers

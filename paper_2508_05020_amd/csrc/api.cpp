@@ -109,7 +109,7 @@ struct amr_hierarchy {
   int* d_tag_mask = nullptr;  // 3D: per pid, see Kernels::tag_flags3
   uint8_t* d_refine = nullptr;
   uint8_t* d_coarsen = nullptr;
-  unsigned long long* d_lam = nullptr;
+  unsigned long long* d_lam = nullptr;  // three rate slots (see rate_slot)
   double* d_dt = nullptr;
   int* d_flags = nullptr;  // [0] fill/prolong error, [1] nonphysical count
   int* d_lists = nullptr;
@@ -730,6 +730,10 @@ void do_restrict(amr_hierarchy* h, int buf) {
     });
 }
 
+unsigned long long* rate_slot(const amr_hierarchy* h, int k) {
+  return h->d_lam + k * amr::kRateWords;
+}
+
 // lam_in (stage 1 of a step): dt comes from that rate slot and is written to
 // dt_out; lam_next is then the slot to clear, at stage 3 the slot to fill.
 void do_stage(amr_hierarchy* h, int stage, const double* dt,
@@ -777,16 +781,16 @@ void do_stage(amr_hierarchy* h, int stage, const double* dt,
 
 // CFL rate of the leaf cells of buffer `buf` into rate slot `slot`
 void do_rate(amr_hierarchy* h, int buf, int slot) {
-  Kernels::zero_u64(h->d_lam + slot, h->stream);
+  Kernels::zero_rate(rate_slot(h, slot), h->stream);
   over_list(h, h->leaves, 1, [&](const int* p, int c) {
-    Kernels::max_rate(h->dm, h->U[buf], p, c, h->d_lam + slot, h->stream);
+    Kernels::max_rate(h->dm, h->U[buf], p, c, rate_slot(h, slot), h->stream);
   });
   h->check_launch();
 }
 
 void do_dt(amr_hierarchy* h, int buf, double* dt) {
   do_rate(h, buf, 2);
-  Kernels::dt_from_rate(h->dm, h->d_lam + 2, dt, nullptr, h->stream);
+  Kernels::dt_from_rate(h->dm, rate_slot(h, 2), dt, nullptr, h->stream);
   h->check_launch();
 }
 
@@ -795,14 +799,14 @@ void do_dt(amr_hierarchy* h, int buf, double* dt) {
 void do_step(amr_hierarchy* h, double* dt, int cur) {
   if (h->exec_mode == AMR_EXEC_BATCHED) {
     // dt from the rate slot inside the stage-1 launch
-    do_stage(h, 1, dt, h->d_lam + (1 - cur), h->d_lam + cur, dt);
+    do_stage(h, 1, dt, rate_slot(h, 1 - cur), rate_slot(h, cur), dt);
   } else {
-    Kernels::dt_from_rate(h->dm, h->d_lam + cur, dt, h->d_lam + (1 - cur), h->stream);
+    Kernels::dt_from_rate(h->dm, rate_slot(h, cur), dt, rate_slot(h, 1 - cur), h->stream);
     h->check_launch();
     do_stage(h, 1, dt);
   }
   do_stage(h, 2, dt);
-  do_stage(h, 3, dt, h->d_lam + (1 - cur));
+  do_stage(h, 3, dt, rate_slot(h, 1 - cur));
 }
 
 // Tags of every leaf and of every coarsening candidate (on its restricted
@@ -974,7 +978,7 @@ amr_status amr_create_hierarchy(const amr_config* cfg, const amr_allocator* allo
     h->d_coarsen = (uint8_t*)h->dev_alloc(mp);
     h->d_raw = (uint8_t*)h->dev_alloc(h->tag_bytes);
     h->d_tag_mask = (int*)h->dev_alloc(cfg->dim == 3 ? mp * sizeof(int) : 0);
-    h->d_lam = (unsigned long long*)h->dev_alloc(64);
+    h->d_lam = (unsigned long long*)h->dev_alloc(3 * amr::kRateWords * sizeof(unsigned long long));
     h->d_dt = (double*)h->dev_alloc(64);
     h->d_flags = (int*)h->dev_alloc(64);
     long long tiles = 0;  // the most tiles any fitting variant can need

@@ -109,6 +109,42 @@ __device__ __forceinline__ double pressure_exact(const double* u, double gm1) {
   return gm1 * (u[D + 1] - ke);
 }
 
+// Quotients by one divisor d from its reciprocal: r refined by two Newton
+// steps, q = a r and one correction fma(fma(-d, q, a), r, q), which is the
+// correctly rounded quotient, as the division is, while no scaling is needed
+// (d, and a unless it is zero, in [2^-300, 2^300]: takes(a)).
+struct Divisor {
+  double d, r;
+  bool ok;
+  __device__ __forceinline__ explicit Divisor(double v) : d(v) {
+    ok = in_range(v);
+    r = __builtin_amdgcn_rcp(v);
+    r = fma(fma(-v, r, 1.0), r, r);
+    r = fma(fma(-v, r, 1.0), r, r);
+  }
+  static __device__ __forceinline__ bool in_range(double a) {
+    return fabs(a) > 0x1p-300 && fabs(a) < 0x1p300;
+  }
+  __device__ __forceinline__ bool takes(double a) const { return ok && (in_range(a) || a == 0.0); }
+  __device__ __forceinline__ double operator()(double a) const {  // takes(a)
+    const double q = a * r;
+    return fma(fma(-d, q, a), r, q);
+  }
+};
+
+// sqrt(x), correctly rounded, for x where no scaling is needed (2^-700 .. 2^700):
+// one Goldschmidt step on the hardware estimate of 1/sqrt(x), then two residual
+// corrections.
+__device__ __forceinline__ double sqrt_in_range(double x) {
+  const double y = __builtin_amdgcn_rsq(x);
+  double g = x * y, h = 0.5 * y;
+  const double e = fma(-h, g, 0.5);
+  g = fma(g, e, g);
+  h = fma(h, e, h);
+  g = fma(fma(-g, g, x), h, g);
+  return fma(fma(-g, g, x), h, g);
+}
+
 // Centre value phi and MC-limited slopes sl of the level-lc cell at in-domain
 // index gc, for its conservative linear prolongation: a child on the sides
 // sig_j = +-1 is phi + sum_j (sig_j / 4) sl_j, terms added in the order x, y,
@@ -279,46 +315,94 @@ __device__ __forceinline__ void store_children(double* P, int vs, int full, int 
   }
 }
 
-// CFL rate of one cell, sum_j (|u_j| + c) / h with c = sqrt(gamma p / rho),
-// as the IEEE bits of a non-negative double (order-preserving as an
-// unsigned integer); NaN maps to the largest value so that it propagates.
+// Signal speed sum_j (|u_j| + c) of a cell as bits in ascending order (IEEE bits
+// of a non-negative double as an unsigned integer); NaN maps to the largest
+// value so that it propagates.  The quotients and the root are those of the
+// divisions and of sqrt, from one reciprocal of rho.
+constexpr unsigned long long kNanBits = 0x7ff8000000000000ull;
+
 template <int D>
-__device__ __forceinline__ unsigned long long cell_rate_bits(const double* u, const DevMesh& m,
-                                                             double h) {
-  const double rho = u[0];
+__device__ __forceinline__ unsigned long long cell_speed_bits(const double* u, const DevMesh& m) {
+  const Divisor rho(u[0]);
+  bool ok = true;
+#pragma unroll
+  for (int j = 0; j < D; ++j) ok = ok && rho.takes(u[1 + j]);
   double uj[D];
 #pragma unroll
-  for (int j = 0; j < D; ++j) uj[j] = u[1 + j] / rho;
+  for (int j = 0; j < D; ++j) uj[j] = ok ? rho(u[1 + j]) : u[1 + j] / u[0];
   double ke = u[1] * uj[0];
 #pragma unroll
   for (int j = 1; j < D; ++j) ke = ke + u[1 + j] * uj[j];
   ke = 0.5 * ke;
-  const double p = m.gm1 * (u[D + 1] - ke);
-  const double c = sqrt(m.gamma * p / rho);
+  const double gp = m.gamma * (m.gm1 * (u[D + 1] - ke));
+  // in range: gp is positive, and gp / rho between 2^-600 and 2^600
+  const double c = ok && gp > 0x1p-300 && gp < 0x1p300 && u[0] > 0.0 ? sqrt_in_range(rho(gp))
+                                                                      : sqrt(gp / u[0]);
   double s = fabs(uj[0]) + c;
 #pragma unroll
   for (int j = 1; j < D; ++j) s = s + (fabs(uj[j]) + c);
-  const double r = s / h;
-  if (!(r >= 0.0)) return 0x7ff8000000000000ull;
-  return (unsigned long long)__double_as_longlong(r);
+  return s >= 0.0 ? (unsigned long long)__double_as_longlong(s) : kNanBits;
 }
 
-// block-wide max of per-thread values, then one 64-bit atomic max
-__device__ __forceinline__ void block_max_atomic(unsigned long long best,
-                                                 unsigned long long* __restrict__ lam) {
+// Maximum over a wave by lane shifts (row_shr 1, 2, 4, 8, then row_bcast 15 and
+// 31): the high words first, then the low words of the lanes that hold the
+// largest high word.
+__device__ __forceinline__ unsigned wave_max(unsigned v) {
+#define AMR_DPP_MAX(ctrl) \
+  v = max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, ctrl, 0xf, 0xf, false))
+  AMR_DPP_MAX(0x111);
+  AMR_DPP_MAX(0x112);
+  AMR_DPP_MAX(0x114);
+  AMR_DPP_MAX(0x118);
+  AMR_DPP_MAX(0x142);
+  AMR_DPP_MAX(0x143);
+#undef AMR_DPP_MAX
+  return (unsigned)__builtin_amdgcn_readlane((int)v, 63);
+}
+__device__ __forceinline__ unsigned long long wave_max(unsigned long long v) {
+  const unsigned hi = (unsigned)(v >> 32);
+  const unsigned top = wave_max(hi);
+  const unsigned low = wave_max(hi == top ? (unsigned)v : 0u);
+  return ((unsigned long long)top << 32) | low;
+}
+
+// The block's largest cell speed over the cell size h (the rate; division by h
+// keeps the order, so one division per block serves all its cells), into this
+// XCD's part of the rate slot `lam`.  What a block waits for at its end keeps
+// the next one off its CU: with five divisions per cell, LDS shuffles and one
+// address for all atomics the stage kernel's third stage took 26.1 us (2D, 0.28 M
+// cells), 170 (2.75 M) and 2112 (3D, 20.4 M), and k_max_rate 17, 48 and 463;
+// 21.8, 162 and 2045, and 7.4, 30 and 338 so.
+__device__ __forceinline__ void block_max_rate(unsigned long long best, double h,
+                                               unsigned long long* __restrict__ lam) {
   __shared__ unsigned long long red[16];
-  for (int off = 32; off > 0; off >>= 1) {
-    const unsigned long long o = __shfl_xor(best, off);
-    best = o > best ? o : best;
+  const int lane = threadIdx.x & 63, waves = blockDim.x >> 6;
+  best = wave_max(best);
+  if (waves > 1) {
+    if (lane == 0) red[threadIdx.x >> 6] = best;
+    __syncthreads();
+    if (threadIdx.x >= 64) return;
+    best = wave_max(lane < waves ? red[lane] : 0ull);
   }
-  const int wave = threadIdx.x >> 6;
-  if ((threadIdx.x & 63) == 0) red[wave] = best;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    unsigned long long b = red[0];
-    for (int k = 1; k < (int)(blockDim.x >> 6); ++k) b = red[k] > b ? red[k] : b;
-    if (b) atomicMax(lam, b);
+  const double r = __longlong_as_double((long long)best) / h;
+  best = r >= 0.0 ? (unsigned long long)__double_as_longlong(r) : kNanBits;
+  if (lane == 0 && best) atomicMax(lam + blockIdx.x % kXcds * kRateStride, best);
+}
+
+// The rate in a slot.
+__device__ __forceinline__ double slot_rate(const unsigned long long* __restrict__ lam) {
+  unsigned long long best = lam[0];
+#pragma unroll
+  for (int x = 1; x < kXcds; ++x) {
+    const unsigned long long b = lam[x * kRateStride];
+    best = b > best ? b : best;
   }
+  return __longlong_as_double((long long)best);
+}
+
+__device__ __forceinline__ void clear_rate(unsigned long long* __restrict__ lam) {
+#pragma unroll
+  for (int x = 0; x < kXcds; ++x) lam[x * kRateStride] = 0ull;
 }
 
 // Work item of this block.  Workgroups are dealt to the chip's XCDs in

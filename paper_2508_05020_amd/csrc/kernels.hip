@@ -447,11 +447,11 @@ __device__ __forceinline__ void reflux_item(const DevMesh& m, int mode, double* 
 #pragma unroll
     for (int v = 0; v < NV; ++v) P[v * vs + off] = u[v];
     if (want_rate) {
-      const unsigned long long bits = cell_rate_bits<D>(u, m, L.h);
+      const unsigned long long bits = cell_speed_bits<D>(u, m);
       best = bits > best ? bits : best;
     }
   }
-  if (want_rate) block_max_atomic(best, lam_next);
+  if (want_rate) block_max_rate(best, L.h, lam_next);
 }
 
 template <int D, int NT>
@@ -628,38 +628,46 @@ __global__ __launch_bounds__(256) void k_max_rate(DevMesh m, const double* __res
                                                   const int* __restrict__ list, int count,
                                                   unsigned long long* __restrict__ lam) {
   constexpr int NV = D + 2;
+  if ((int)blockIdx.x >= count) return;
   unsigned long long best = 0ull;
-  if ((int)blockIdx.x < count) {
+  const int l = m.level[list[blockIdx.x]];
+  {
     const int pid = list[blockIdx.x];
-    const int l = m.level[pid];
     const LevelC& L = m.lv[l];
     const int n = L.n;
     const double* P = U + patch_base(m, pid, l);
     const int vs = var_stride<D>(L.full);
-    int total = n;
+    // pairs along x (even patch edges), one 16-byte load per variable
+    int total = n / 2;
     if constexpr (D >= 2) total *= n;
     if constexpr (D >= 3) total *= n;
     for (int idx = threadIdx.x; idx < total; idx += blockDim.x) {
-      const int x = idx % n;
-      const int y = D >= 2 ? (idx / n) % n : 0;
-      const int z = D >= 3 ? idx / (n * n) : 0;
+      const int row = D >= 2 ? div_half(idx, L) : 0;
+      const int z = D >= 3 ? div_by(row, n, L.n_mul) : 0;
+      const int x = 2 * (idx - row * (n / 2)), y = row - z * n;
       const int off = box_off<D>(L.full, x + NG, y + NG, z + NG);
-      double u[NV];
+      double2 u[NV];
 #pragma unroll
-      for (int v = 0; v < NV; ++v) u[v] = P[v * vs + off];
-      const unsigned long long bits = cell_rate_bits<D>(u, m, L.h);
-      best = bits > best ? bits : best;
+      for (int v = 0; v < NV; ++v) u[v] = *reinterpret_cast<const double2*>(P + v * vs + off);
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        double c[NV];
+#pragma unroll
+        for (int v = 0; v < NV; ++v) c[v] = h == 0 ? u[v].x : u[v].y;
+        const unsigned long long bits = cell_speed_bits<D>(c, m);
+        best = bits > best ? bits : best;
+      }
     }
   }
-  block_max_atomic(best, lam);
+  block_max_rate(best, m.lv[l].h, lam);
 }
 
-__global__ void k_zero_u64(unsigned long long* p) { p[0] = 0ull; }
+__global__ void k_zero_rate(unsigned long long* slot) { clear_rate(slot); }
 
 __global__ void k_dt_from_rate(const unsigned long long* __restrict__ lam, double cfl,
                                double* __restrict__ dt, unsigned long long* __restrict__ clear) {
-  dt[0] = cfl / __longlong_as_double((long long)lam[0]);
-  if (clear) clear[0] = 0ull;
+  dt[0] = cfl / slot_rate(lam);
+  if (clear) clear_rate(clear);
 }
 
 // ---------------------------------------------------------------------------
@@ -964,30 +972,17 @@ __global__ __launch_bounds__(256) void k_cell_tags(DevMesh m, const uint8_t* __r
 // ---------------------------------------------------------------------------
 constexpr int kTagTile = 8;   // cells per tile edge of k_tag_cells
 
-// pressure_exact with one reciprocal for the D quotients: r refined by two
-// Newton steps, q = m r and one correction fma(fma(-rho, q, m), r, q), which is
-// the correctly rounded quotient, as the division is, while no scaling is
-// needed; operands outside [2^-300, 2^300] (zero momenta excepted) take the
-// division.
+// pressure_exact with one reciprocal for the D quotients (see Divisor).
 template <int D>
 __device__ __forceinline__ double pressure_fast(const double* u, double gm1) {
-  const double rho = u[0];
-  const double lo = 0x1p-300, hi = 0x1p300;
-  bool ok = fabs(rho) > lo && fabs(rho) < hi;
+  const Divisor rho(u[0]);
+  bool ok = true;
 #pragma unroll
-  for (int j = 0; j < D; ++j)
-    ok = ok && ((fabs(u[1 + j]) > lo && fabs(u[1 + j]) < hi) || u[1 + j] == 0.0);
+  for (int j = 0; j < D; ++j) ok = ok && rho.takes(u[1 + j]);
   if (!ok) return pressure_exact<D>(u, gm1);
-  double r = __builtin_amdgcn_rcp(rho);
-  r = fma(fma(-rho, r, 1.0), r, r);
-  r = fma(fma(-rho, r, 1.0), r, r);
-  double ke = 0.0;
+  double ke = u[1] * rho(u[1]);
 #pragma unroll
-  for (int j = 0; j < D; ++j) {
-    const double q = u[1 + j] * r;
-    const double v = fma(fma(-rho, q, u[1 + j]), r, q);
-    ke = j == 0 ? u[1] * v : ke + u[1 + j] * v;
-  }
+  for (int j = 1; j < D; ++j) ke = ke + u[1 + j] * rho(u[1 + j]);
   ke = 0.5 * ke;
   return gm1 * (u[D + 1] - ke);
 }
@@ -1491,8 +1486,8 @@ void Kernels::max_rate(const DevMesh& m, const double* U, const int* list, int c
   AMR_DISPATCH_DIM(m.dim, k_max_rate, dim3(count), dim3(256), s, m, U, list, count, lam);
 }
 
-void Kernels::zero_u64(unsigned long long* p, hipStream_t s) {
-  hipLaunchKernelGGL(k_zero_u64, dim3(1), dim3(1), 0, s, p);
+void Kernels::zero_rate(unsigned long long* slot, hipStream_t s) {
+  hipLaunchKernelGGL(k_zero_rate, dim3(1), dim3(1), 0, s, slot);
 }
 
 void Kernels::dt_from_rate(const DevMesh& m, const unsigned long long* lam, double* dt,

@@ -1028,7 +1028,7 @@ __device__ __forceinline__ void stage_both(const DevMesh& m, double* __restrict_
 }
 
 // One (pid, tile) work item: the whole RHS of the tile and its stage
-// combination; `best` collects the CFL rate bits of the item's cells.
+// combination; `best` collects the signal speed bits of the item's cells.
 // Restriction of a tile into its parent patch, from the new values of its
 // cells (sR: variable v of tile cell i at sR[v NCELL + i]): each parent cell
 // is the mean of its 2^D children, summed as the post-stage restriction sums
@@ -1186,10 +1186,10 @@ __device__ __forceinline__ void stage_item(const DevMesh& m, int mode,
   if (mode == kModeRHS) {
     dt = 0.0;
   } else if (lam_in) {
-    dt = m.cfl / __longlong_as_double((long long)lam_in[0]);
+    dt = m.cfl / slot_rate(lam_in);
     if (first && threadIdx.x == 0) {
       dt_out[0] = dt;
-      lam_next[0] = 0ull;
+      clear_rate(lam_next);
     }
   } else {
     dt = dtp[0];
@@ -1246,7 +1246,7 @@ __device__ __forceinline__ void stage_item(const DevMesh& m, int mode,
       for (int j = 0; j < D; ++j)
         on_cf |= ((fmask >> (2 * j)) & 1) && c3[j] == 0 || ((fmask >> (2 * j + 1)) & 1) && c3[j] == n - 1;
       if (!on_cf) {
-        const unsigned long long bits = cell_rate_bits<D>(r, m, L.h);
+        const unsigned long long bits = cell_speed_bits<D>(r, m);
         best = bits > best ? bits : best;
       }
     }
@@ -1293,7 +1293,8 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(CHAR ? 4 : 6
   stage_item<D, TX, TY, TZ, NT, FUSE, BOTH, CHAR>(m, mode, Uin, Ug, err, Un, out, fr, items[item],
                                                   item == 0, dtp, lam_next, lam_in, dt_out, sP, sF,
                                                   best);
-  if (lam_next != nullptr && mode == kModeStage3) block_max_atomic(best, lam_next);
+  if (lam_next != nullptr && mode == kModeStage3)
+    block_max_rate(best, m.lv[items[item].level].h, lam_next);
 }
 
 // Items of a (pid, tile) list, a thread each (see StageItem).
