@@ -425,8 +425,8 @@ __device__ __forceinline__ int xcd_item(int count) {
 // XCD's items at any time are neighbours in the list and every XCD gets a
 // share of each part of it.  The grid is whole groups of kXcds C blocks.
 template <int C>
-__device__ __forceinline__ int xcd_chunk(int count) {
-  const int b = (int)blockIdx.x, g = b / (kXcds * C) * (kXcds * C);
+__device__ __forceinline__ int xcd_chunk(int count, int b = (int)blockIdx.x) {
+  const int g = b / (kXcds * C) * (kXcds * C);
   const int item = g + (b % kXcds) * C + (b / kXcds) % C;
   return item < count ? item : -1;
 }
