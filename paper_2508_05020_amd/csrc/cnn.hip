@@ -275,7 +275,8 @@ __global__ __launch_bounds__(FWD_THREADS) void k_cnn_fwd(int count, int n,
 // gradients (no activation goes through memory), the reductions spread over
 // the waves as MFMA chains.  It replaces a forward, a loss and a backward
 // launch (with 8 waves and serial per-parameter loops): 11.5 + 4.5 + 68.9 us
-// for 64 patches of edge 16; 20.4 us with 16-wide K chunks, 18.5 now.
+// for 64 patches of edge 16; 20.4 us with 16-wide K chunks, 18.5
+// with a fixed share of dz1 per wave, 17.9 now.
 constexpr int TRAIN_THREADS = 1024;
 constexpr int TRAIN_WAVES = TRAIN_THREADS / 64;
 
@@ -284,7 +285,7 @@ constexpr int TRAIN_WAVES = TRAIN_THREADS / 64;
 // W3, which are read before it is written; dz2 is stored with a border of two
 // zero pixels, so that the data gradient reads it without bounds checks.
 struct TrainLds {
-  int x, a1, a2, g, w3, dz1, dz2, red, w1, w2, w2f, total;
+  int x, a1, a2, g, w3, dz1, dz2, red, w1, w2, w2f, next, total;
   __host__ __device__ explicit TrainLds(int n) {
     const int P0 = (n + 6) * (n + 6), P1 = (n + 4) * (n + 4), P2 = (n + 2) * (n + 2), P3 = n * n;
     x = 0;
@@ -298,7 +299,8 @@ struct TrainLds {
     w2 = dz2;  // until layer 2 is done
     w1 = red + 12 * 256 * 4;
     w2f = w1 + 16 * 4 * 9 * 2;
-    total = w2f + OPS2 * 2;
+    next = w2f + OPS2 * 2;  // block counter of dz1
+    total = next + 16;
   }
   static __host__ __device__ int P1Z(int n) { return (n + 6) * (n + 6); }  // dz2 with its border
 };
@@ -324,6 +326,7 @@ __global__ __launch_bounds__(TRAIN_THREADS) void k_cnn_train(
   unsigned short* W1 = (unsigned short*)(train_smem + S.w1);
   unsigned short* W2 = (unsigned short*)(train_smem + S.w2);
   unsigned short* W2f = (unsigned short*)(train_smem + S.w2f);
+  int* next = (int*)(train_smem + S.next);
   const int w0 = n + 6, w1 = n + 4, w2 = n + 2, wz = n + 6;
   const int P0 = w0 * w0, P1 = w1 * w1, P2 = w2 * w2, P3 = n * n;
   const PixelDiv div1(w1), div2(w2), div3(n);
@@ -337,6 +340,7 @@ __global__ __launch_bounds__(TRAIN_THREADS) void k_cnn_train(
     for (int t = tid; t < 576; t += TRAIN_THREADS) W1[t] = Wg[CNN_W1 + t];
     stage_operands<16, 1>(W2, Wg + CNN_W2);
     stage_operands<1, 16>(W2f, Wg + CNN_W2);
+    if (tid == 0) next[0] = 0;
     if (tid < 144) w3[(tid % 9) * 16 + tid / 9] = bf2f(Wg[CNN_W3 + tid]);
   }
   __syncthreads();
@@ -484,8 +488,8 @@ __global__ __launch_bounds__(TRAIN_THREADS) void k_cnn_train(
   {
     const Conv2<true> conv(W2f, wz, i16, kq);
     const int nblk = (P1 + 15) / 16;
-    // the waves without a tap above take their blocks first
-    for (int blk = TRAIN_WAVES - 1 - wave; blk < nblk; blk += TRAIN_WAVES) {
+    // blocks as the waves come: those with a tap above arrive last
+    for (int blk = take(next); blk < nblk; blk = take(next)) {
       const int p = 16 * blk + i16;
       const int pc = p < P1 ? p : P1 - 1;
       const int qy = div1(pc), qx = pc - qy * w1;

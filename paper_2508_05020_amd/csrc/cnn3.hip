@@ -238,7 +238,8 @@ __global__ __launch_bounds__(FWD_THREADS) void k_cnn3_fwd(int count, const unsig
 // (4.6 us) and the backward (124 us) were launches of their own, with
 // activations through memory, bounds checks per tap and serial sums per
 // parameter; one launch now, 45.6 us with 16-wide K chunks and weights packed by
-// every wave, 39.4 with 32-wide chunks and operands staged once.
+// every wave, 39.4 with 32-wide chunks and operands staged once, 37.9 with the
+// blocks of dz1 taken as the waves come.
 //
 // LDS (bytes): dz1 takes the place of the second activation,
 // the logit gradients and the FP32 copy of W3; dz2 has a border of two zero
@@ -253,7 +254,8 @@ constexpr int TL_DZ2 = TL_DZ1 + P1 * CH * 2;
 constexpr int TL_RED = TL_DZ2 + P0 * CH * 2;      // dz2 with its border is as large as the input
 constexpr int RED_N = 8 * 27 + 1;                 // dW3 and db3 of one wave
 constexpr int TL_W2F = TL_RED + ((TRAIN_WAVES * RED_N * 4 + 15) / 16) * 16;  // W2, mirrored
-constexpr int TL_TOTAL = TL_W2F + OPS * 2;
+constexpr int TL_NEXT = TL_W2F + OPS * 2;  // block counter of dz1
+constexpr int TL_TOTAL = TL_NEXT + 16;
 constexpr int TL_W1 = TL_DZ2, TL_W2 = TL_W1 + OPS * 2;  // until the forward convolutions are done
 static_assert(TL_W3 + 27 * 8 * 4 <= TL_DZ2, "a2, g and W3 fit under dz1");
 static_assert(TL_TOTAL <= 160 * 1024, "one block per CU");
@@ -277,6 +279,7 @@ __global__ __launch_bounds__(TRAIN_THREADS) void k_cnn3_train(
   unsigned short* w1 = (unsigned short*)(train_smem + TL_W1);
   unsigned short* w2 = (unsigned short*)(train_smem + TL_W2);
   unsigned short* w2f = (unsigned short*)(train_smem + TL_W2F);
+  int* next = (int*)(train_smem + TL_NEXT);
   float* part = partials + (long long)b * CNN3_NPARAM;
   const int tid = threadIdx.x;
   const int lane = tid & 63, wave = tid >> 6;
@@ -291,6 +294,7 @@ __global__ __launch_bounds__(TRAIN_THREADS) void k_cnn3_train(
     stage_operands<5, 1, 5>(w1, Wg + CNN3_W1);
     stage_operands<8, 1, 8>(w2, Wg + CNN3_W2);
     stage_operands<1, 8, 8>(w2f, Wg + CNN3_W2);
+    if (tid == 0) next[0] = 0;
     if (tid < 2) reinterpret_cast<uint4*>(a1 + P1 * CH)[tid] = z;
     if (tid < 27 * 8) w3[(tid % 27) * 8 + tid / 27] = bf2f(Wg[CNN3_W3 + tid]);
   }
@@ -462,7 +466,8 @@ __global__ __launch_bounds__(TRAIN_THREADS) void k_cnn3_train(
     const Operands w(w2f, i, kq);
     const TapReads<W0, true> a(kq);
     constexpr int nblk = P1 / 16;
-    for (int blk = TRAIN_WAVES - 1 - wave; blk < nblk; blk += TRAIN_WAVES) {
+    // blocks as the waves come: those with a tap pair above arrive last
+    for (int blk = take(next); blk < nblk; blk = take(next)) {
       const int q = 16 * blk + i;
       const int qz = q / (W1 * W1), qy = (q / W1) % W1, qx = q % W1;
       const unsigned short* voxel = dz2 + ((qz * W0 + qy) * W0 + qx) * CH;

@@ -77,6 +77,13 @@ __device__ __forceinline__ s4 load4_tr(const unsigned short* p) {
   return __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4*)p);
 }
 
+// The next number of a counter in LDS, the same for the whole wave.
+__device__ __forceinline__ int take(int* counter) {
+  int v = 0;
+  if ((threadIdx.x & 63) == 0) v = atomicAdd(counter, 1);
+  return __builtin_amdgcn_readfirstlane(v);
+}
+
 __device__ __forceinline__ s4 zero4() {
   s4 r = {0, 0, 0, 0};
   return r;
