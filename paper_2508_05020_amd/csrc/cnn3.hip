@@ -239,7 +239,7 @@ __global__ __launch_bounds__(FWD_THREADS) void k_cnn3_fwd(int count, const unsig
 // activations through memory, bounds checks per tap and serial sums per
 // parameter; one launch now, 45.6 us with 16-wide K chunks and weights packed by
 // every wave, 39.4 with 32-wide chunks and operands staged once, 37.9 with the
-// blocks of dz1 taken as the waves come.
+// blocks of dz1 taken as the waves come, 37.4 with weights of dz2 read for two voxels.
 //
 // LDS (bytes): dz1 takes the place of the second activation,
 // the logit gradients and the FP32 copy of W3; dz2 has a border of two zero
@@ -369,29 +369,50 @@ __global__ __launch_bounds__(TRAIN_THREADS) void k_cnn3_train(
       red[wave * RED_N + 8 * 27] = gs;
     }
   }
-  // --- dz2 = relu'(z2) * (W3 (x) g) on the layer-2 grid, 4 channels per item
-  for (int t = tid; t < 2 * P2; t += TRAIN_THREADS) {
-    const int q = t >> 1, c4 = 4 * (t & 1);
-    const int qz = q / (W2 * W2), qy = (q / W2) % W2, qx = q % W2;
-    float acc[4] = {0.f, 0.f, 0.f, 0.f};
+  // --- dz2 = relu'(z2) * (W3 (x) g) on the layer-2 grid, 4 channels per item, two
+  // items per thread (t and t + TRAIN_THREADS), which share each weight read
+  {
+    static_assert(2 * P2 <= 2 * TRAIN_THREADS, "two items per thread cover the grid");
+    const int c4 = 4 * (tid & 1);
+    int q[2], qz[2], qy[2], qx[2];
+    float acc[2][4];
 #pragma unroll
-    for (int tap = 0; tap < 27; ++tap) {
-      const int pz = qz - tap / 9, py = qy - (tap / 3) % 3, px = qx - tap % 3;
-      // read in any case (no branch around the loads), zero outside
-      const bool in = (unsigned)pz < (unsigned)T && (unsigned)py < (unsigned)T && (unsigned)px < (unsigned)T;
-      const float gr = g[in ? (pz * T + py) * T + px : 0];
-      const float gv = in ? gr : 0.f;
-      const float4 w = *reinterpret_cast<const float4*>(w3 + tap * 8 + c4);
-      acc[0] += w.x * gv;
-      acc[1] += w.y * gv;
-      acc[2] += w.z * gv;
-      acc[3] += w.w * gv;
+    for (int k = 0; k < 2; ++k) {
+      q[k] = (tid + k * TRAIN_THREADS) >> 1;
+      qz[k] = q[k] / (W2 * W2);
+      qy[k] = (q[k] / W2) % W2;
+      qx[k] = q[k] % W2;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc[k][e] = 0.f;
     }
-    const s4 on = load4(a2 + q * CH + c4);  // a2 = relu(z2) in BF16: nonzero iff z2 > 0
-    uint2 o;
-    o.x = f2bf_hw(on.x ? acc[0] : 0.f) | ((unsigned)f2bf_hw(on.y ? acc[1] : 0.f) << 16);
-    o.y = f2bf_hw(on.z ? acc[2] : 0.f) | ((unsigned)f2bf_hw(on.w ? acc[3] : 0.f) << 16);
-    *reinterpret_cast<uint2*>(dz2 + (((qz + 2) * W0 + qy + 2) * W0 + qx + 2) * CH + c4) = o;
+#pragma unroll 1  // the weights of 9 taps at a time in registers
+    for (int tz = 0; tz < 3; ++tz) {
+#pragma unroll
+      for (int t9 = 0; t9 < 9; ++t9) {
+        const float4 w = *reinterpret_cast<const float4*>(w3 + (9 * tz + t9) * 8 + c4);
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+          const int pz = qz[k] - tz, py = qy[k] - t9 / 3, px = qx[k] - t9 % 3;
+          // read in any case (no branch around the loads), zero outside
+          const bool in = (unsigned)pz < (unsigned)T && (unsigned)py < (unsigned)T && (unsigned)px < (unsigned)T;
+          const float gr = g[in ? (pz * T + py) * T + px : 0];
+          const float gv = in ? gr : 0.f;
+          acc[k][0] += w.x * gv;
+          acc[k][1] += w.y * gv;
+          acc[k][2] += w.z * gv;
+          acc[k][3] += w.w * gv;
+        }
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      if (q[k] >= P2) continue;
+      const s4 on = load4(a2 + q[k] * CH + c4);  // a2 = relu(z2) in BF16: nonzero iff z2 > 0
+      uint2 o;
+      o.x = f2bf_hw(on.x ? acc[k][0] : 0.f) | ((unsigned)f2bf_hw(on.y ? acc[k][1] : 0.f) << 16);
+      o.y = f2bf_hw(on.z ? acc[k][2] : 0.f) | ((unsigned)f2bf_hw(on.w ? acc[k][3] : 0.f) << 16);
+      *reinterpret_cast<uint2*>(dz2 + (((qz[k] + 2) * W0 + qy[k] + 2) * W0 + qx[k] + 2) * CH + c4) = o;
+    }
   }
   __syncthreads();
 
