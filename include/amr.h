@@ -343,18 +343,24 @@ amr_status amr_cnn_mfma_selftest(amr_hierarchy* h, const uint16_t* a_dev, const 
 
 /* hipGraph replay of amr_step in batched mode (default off): the kernels of
  * one step are captured once (two graphs, one per CFL-rate slot) and
- * replayed; the graph holds kernel nodes only.  Batched launches of the
- * step's kernels read their work lists and live counts from a device list
- * directory that regrids rewrite, and after a regrid that changes the mesh
- * the next replay first sets the grid of each list launch in the
+ * replayed; the graph holds kernel nodes only.  Its launches read their work
+ * lists and live counts from a device list directory that regrids rewrite
+ * (eager launches take the lists as they are), and after a regrid that changes
+ * the mesh the next replay first sets the grid of each list launch in the
  * instantiated graph to the list's new length, so regrids never record the
- * graphs again (eager launches take the lists as they are; when the caller
- * records a call into a graph of its own they read the directory too, and the
- * grids stay those of the recording; with the fused halo off, the explicit ghost fill is sized by
+ * graphs again (with the fused halo off, the explicit ghost fill is sized by
  * the leaf count and every mesh change re-records them).  A change of tile
  * variant, execution mode, halo mode, tag dilation or dt pointer re-records
  * them.  Enabling an enabled graph mode keeps the recorded graphs.  Results
- * are identical to eager launches. */
+ * are identical to eager launches.
+ *
+ * Graphs that the caller records: the async calls on the hierarchy (fill,
+ * right-hand side, dt, stage, step, tag, velocity gradient) may be recorded in
+ * batched mode, and a recording may be replayed after regrids: every launch
+ * reads its list from the directory.  Its grids stay those of the recording, so
+ * it covers meshes whose work lists are no longer than they were then.  A
+ * recording made in per-patch mode, or before a change of tile variant, halo
+ * mode or tag dilation, holds for the mesh and the settings it was made with. */
 amr_status amr_set_graph(amr_hierarchy* h, int enable);
 /* Number of step graphs recorded since creation (test and profiling hook). */
 amr_status amr_graph_records(const amr_hierarchy* h, int* recorded);

@@ -63,13 +63,21 @@ struct DevMesh {
 };
 
 // Work lists, all resident in one device int buffer.  `dir` (null for lists
-// outside it) is the list's entry {offset into the buffer, count} of the
-// device list directory, which batched launches of the step's kernels read
-// at run time, so that a recorded step stays valid across regrids as long
-// as each list fits the grid it was recorded with.
+// that no recordable call takes) is the list's entry {offset into the buffer,
+// count} of the device list directory, which recorded launches read at run
+// time, so that they stay valid across regrids as long as each list fits the
+// grid it was recorded with.
 struct ListView {
   const int* ptr;
   int count;
+  const int* dir = nullptr;
+};
+
+// A list as a launch takes it: its entries; in a recorded launch the list
+// buffer and the directory entry, and `count` only sizes the grid.
+struct ListArg {
+  const int* ptr = nullptr;
+  int count = 0;
   const int* dir = nullptr;
 };
 
@@ -104,24 +112,22 @@ static_assert(sizeof(RefluxItem) == 32, "eight ints in the list buffer");
 // Blocks of the 3D tag launch: patches and 8^3 tiles per patch of each level.
 struct TagLevels {
   int count[kMaxLev], tiles[kMaxLev];
+  // recorded launches: the counts are at dir[2 l] instead
+  const int* dir = nullptr;
 };
 
 // Launch wrappers implemented in kernels.hip.
 struct Kernels {
   // ghosts of the listed patches that have a same-level source (copies), and
   // the prolonged ones of the listed (pid, ghost region) pairs
-  static void fill(const DevMesh& m, double* U, const int* list, int count, const int* regions,
-                   int nregions, int* err, hipStream_t s);
-  // prolonged ghost cells only, over (pid, ghost region) pairs
-  // dir (nullable): list directory entry; with it `list` is the list buffer
-  // and the list and its live count are read at run time, and `count` only
-  // sizes the grid (at least the live count: one block per item)
+  static void fill(const DevMesh& m, double* U, const ListArg& list, const ListArg& regions,
+                   int* err, hipStream_t s);
   // Grids (blocks) of the batched launches for a list of `count` items, for
   // updating the launches of a recorded step graph after a regrid.
   static int fill_cf_grid(const DevMesh& m, int count);
   static int stage_grid(int count) { return ((count + kXcds - 1) / kXcds) * kXcds; }
-  static void fill_cf(const DevMesh& m, double* U, const int* list, int count, const int* dir,
-                      int* err, hipStream_t s);
+  // prolonged ghost cells only, over (pid, ghost region) pairs
+  static void fill_cf(const DevMesh& m, double* U, const ListArg& regions, int* err, hipStream_t s);
   // fuse = halo nodes outside the patch with a same-level source are read
   // from that source by the kernel itself; the others are prolonged by the
   // kernel too in 1D (into Uin's ghost layers; *err set where a source is
@@ -146,22 +152,19 @@ struct Kernels {
   // faces with flux registers.  Built again whenever lists or tables change.
   static void stage_items(const DevMesh& m, const int* tiles, int count, const uint8_t* cfmask,
                           StageItem* items, hipStream_t s);
+  // list: of RefluxItem, which start at a multiple of their size in the list buffer
   static void reflux(const DevMesh& m, int mode, double* out, const double* fr,
-                     const RefluxItem* list, int count, const double* dt, double w,
+                     const ListArg& list, const double* dt, double w,
                      unsigned long long* lam_next, hipStream_t s);
   // refluxing with what it changes of the leaves' restriction, and the
   // restriction of the patches with children of level finest - 1 (plist) in one
-  // launch; the stage kernel has restricted the leaves
-  // dir (nullable): the directory entries of the two lists, in order; with it
-  // the list pointers are the list
-  // buffer (reflux: its items start at a multiple of their size), the live counts are read at run
-  // time and nref + npair only sizes the grid.
+  // launch; the stage kernel has restricted the leaves.  Recorded, plist's
+  // directory entry follows rlist's.
   static void post(const DevMesh& m, int mode, double* out, const double* fr,
-                   const RefluxItem* rlist, int nref, const int* plist, int npair, const int* dir,
-                   const double* dt, double w, unsigned long long* lam_next, hipStream_t s);
-  static void restrict_level(const DevMesh& m, double* U, const int* list, int count,
-                             const int* dir, hipStream_t s);
-  static void max_rate(const DevMesh& m, const double* U, const int* list, int count,
+                   const ListArg& rlist, const ListArg& plist, const double* dt, double w,
+                   unsigned long long* lam_next, hipStream_t s);
+  static void restrict_level(const DevMesh& m, double* U, const ListArg& list, hipStream_t s);
+  static void max_rate(const DevMesh& m, const double* U, const ListArg& list,
                        unsigned long long* lam_bits, hipStream_t s);
   static void zero_rate(unsigned long long* slot, hipStream_t s);
   // dt = cfl / rate; also clears the slot `clear` (nullable), the next accumulator
@@ -169,28 +172,30 @@ struct Kernels {
                            double* dt, unsigned long long* clear, hipStream_t s);
   // fuse: halo cells read from same-level neighbours directly; ghost layers
   // hold only the prolonged cells (filled by fill_cf beforehand)
-  static void tag(const DevMesh& m, const double* U, const int* list, int count,
+  static void tag(const DevMesh& m, const double* U, const ListArg& list,
                   uint8_t* has_tag, uint8_t* raw, bool fuse, hipStream_t s);
   // 3D, fused halo: tag flags of every active patch (`list` in level order,
-  // level_count patches per level; prolonged regions filled before); mask:
+  // level_count patches per level, recorded launches read them at level_dir[2 l];
+  // prolonged regions filled before); mask:
   // scratch of max_patches ints; raw (nullable): the tag of each patch's own
   // cells and, in a leaf's ghost places, of the prolonged cells within tag_buffer
-  static void tag_flags3(const DevMesh& m, const double* U, const int* list,
-                         const int* level_count, const int* regions, int nregions, int* mask,
-                         uint8_t* has_tag, uint8_t* raw, hipStream_t s);
+  static void tag_flags3(const DevMesh& m, const double* U, const ListArg& list,
+                         const int* level_count, const int* level_dir, const ListArg& regions,
+                         int* mask, uint8_t* has_tag, uint8_t* raw, hipStream_t s);
   // cells of the leaves with a tag within tag_buffer; shared: raw as tag_flags3
   // (3D) writes it, else as tag does; level_leaves (nullable): leaves per level,
-  // the list in level order
-  static void cell_tags(const DevMesh& m, const uint8_t* raw, const int* leaves, int count,
-                        const int* level_leaves, bool shared, uint8_t* out, hipStream_t s);
+  // the list in level order (recorded launches read them at level_dir[2 l])
+  static void cell_tags(const DevMesh& m, const uint8_t* raw, const ListArg& leaves,
+                        const int* level_leaves, const int* level_dir, bool shared, uint8_t* out,
+                        hipStream_t s);
   static void requests(const DevMesh& m, const uint8_t* has_tag, const uint8_t* active_leaf,
                        int nslots, uint8_t* refine, uint8_t* coarsen, hipStream_t s);
-  static void prolong_new(const DevMesh& m, double* U, const int* list, int count, int* err,
+  static void prolong_new(const DevMesh& m, double* U, const ListArg& list, int* err,
                           hipStream_t s);
   static void scatter_int(int* dst, const int* pairs, int npairs, hipStream_t s);
   static void count_nonzero(const uint8_t* a, int n, int* out, hipStream_t s);
-  static void check(const DevMesh& m, const double* U, const int* list, int count,
-                    int* bad, hipStream_t s);
+  static void check(const DevMesh& m, const double* U, const ListArg& list, int* bad,
+                    hipStream_t s);
   // Tile variants of the stage kernel: extents (cells) and block size.
   struct TileVariant {
     int dim, tx, ty, tz, threads;

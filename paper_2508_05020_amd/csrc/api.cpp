@@ -38,9 +38,11 @@ struct StateError : std::runtime_error {
     }                                                                        \
   } while (0)
 
-// entries of the device list directory
-enum { kDirCf = 0, kDirTiles = 1, kDirReflux = 2, kDirPairs = 3, kDirCfFace = 4, kDirRestr = 5,
-       kDirEntries = kDirRestr + amr::kMaxLev };
+// Entries of the device list directory: {offset, count} of a list; at kDirLevels +
+// level the active patches and the leaves of the level.
+enum { kDirCf = 0, kDirTiles = 1, kDirReflux = 2, kDirPairs = 3, kDirCfFace = 4, kDirAll = 5,
+       kDirLeaves = 6, kDirCands = 7, kDirRestr = 8, kDirLevels = kDirRestr + amr::kMaxLev,
+       kDirEntries = kDirLevels + amr::kMaxLev };
 
 }  // namespace
 
@@ -115,10 +117,9 @@ struct amr_hierarchy {
   int* d_lists = nullptr;
   long long lists_cap = 0;
   amr::StageItem* d_items = nullptr;  // the stage kernel's items, in the order of the tile list
-  // list directory: {offset into d_lists, count} of the lists the step's
-  // kernels take (entries kDirCf, kDirTiles, kDirReflux, kDirPairs,
-  // kDirCfFace, kDirRestr + level), rewritten with the lists; batched
-  // launches read it, so a recorded step survives a regrid
+  // list directory: {offset into d_lists, count} of the lists that recordable
+  // calls take, and the patches per level (kDir*), rewritten with the lists;
+  // recorded batched launches read it, so they survive a regrid
   int* d_dir = nullptr;
   int* h_dir = nullptr;  // the directory in h_stage
   long long pairs_cap = 0;
@@ -548,11 +549,11 @@ void sync_tables(amr_hierarchy* h, bool full) {
   std::copy(pairs.begin(), pairs.end(), sl + pairs_at);
   std::copy(h->h_active_leaf.begin(), h->h_active_leaf.end(), sa);
   const int* dd = h->d_dir;
-  h->all = {h->d_lists + a0, a1 - a0};
-  h->leaves = {h->d_lists + a1, c0 - a1};
+  h->all = {h->d_lists + a0, a1 - a0, dd + 2 * kDirAll};
+  h->leaves = {h->d_lists + a1, c0 - a1, dd + 2 * kDirLeaves};
   h->cfregions = {h->d_lists + c0, (cf1 - c0) / 2, dd + 2 * kDirCf};
   h->cffaces = {h->d_lists + cf1, (k0 - cf1) / 2, dd + 2 * kDirCfFace};
-  h->cands = {h->d_lists + k0, t0 - k0};
+  h->cands = {h->d_lists + k0, t0 - k0, dd + 2 * kDirCands};
   h->tiles = {(const int*)h->d_items, (r_items - t0) / 2, dd + 2 * kDirTiles};
   h->reflux = {h->d_lists + r0, nref, dd + 2 * kDirReflux};
   h->post_pairs = {h->d_lists + pp0, pp1 - pp0, dd + 2 * kDirPairs};
@@ -573,6 +574,13 @@ void sync_tables(amr_hierarchy* h, bool full) {
     put(kDirTiles, h->tiles);
     put(kDirReflux, h->reflux);
     put(kDirPairs, h->post_pairs);
+    put(kDirAll, h->all);
+    put(kDirLeaves, h->leaves);
+    put(kDirCands, h->cands);
+    for (int l = 0; l < f.nlev; ++l) {
+      hd[2 * (kDirLevels + l)] = h->level_count[l];
+      hd[2 * (kDirLevels + l) + 1] = h->level_leaves[l];
+    }
     for (int l = 0; l < f.nlev; ++l) put(kDirRestr + l, h->restr_post[l]);
   }
   // coarse/fine faces of coarse-side leaves, then the faces whose flux
@@ -601,17 +609,6 @@ void sync_tables(amr_hierarchy* h, bool full) {
     h->check_launch();
   }
   Kernels::stage_items(h->dm, h->d_lists + t0, h->tiles.count, h->d_cfmask, h->d_items, h->stream);
-  h->check_launch();
-}
-
-// Per-patch mode launches one kernel per list entry (the unfused baseline).
-template <typename F>
-void over_list(amr_hierarchy* h, const amr::ListView& lv, int stride_ints, F launch) {
-  if (h->exec_mode == AMR_EXEC_BATCHED) {
-    launch(lv.ptr, lv.count);
-  } else {
-    for (int i = 0; i < lv.count; ++i) launch(lv.ptr + (long long)i * stride_ints, 1);
-  }
   h->check_launch();
 }
 
@@ -661,51 +658,58 @@ void note_node(amr_hierarchy* h, int kind, int e0, int e1 = -1, int e2 = -1) {
   h->gnodes[h->cap_slot].push_back(g);
 }
 
-// Whether the caller records the work of this call: the launches then read
-// their lists from the directory, as in the library's own graphs.
+// Whether the caller records the work of this call: its batched launches then
+// read their lists from the directory, as in the library's own graphs.
 void note_capture(amr_hierarchy* h) {
   hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
   if (hipStreamIsCapturing(h->stream, &st) != hipSuccess) (void)hipGetLastError();
   h->caller_records = st == hipStreamCaptureStatusActive;
 }
 
-// The step's kernels: in batched mode one launch over the list; while a
-// graph is recorded it reads the list and its live count from the list
-// directory (launch(list buffer, grid count, directory entry)), eagerly it
-// takes them as they are (launch(list, count, null)), one dependent load less
-// at the start of every block.  Per-patch mode as over_list.
+// The list as a batched launch takes it: eagerly as it is, one dependent load
+// less at the start of every block; while a graph is recorded by its directory
+// entry.
+amr::ListArg list_arg(const amr_hierarchy* h, const amr::ListView& lv) {
+  if (lv.dir && (h->capturing || h->caller_records)) return {h->d_lists, grid_count(h, lv), lv.dir};
+  return {lv.ptr, lv.count, nullptr};
+}
+
+// Batched mode: one launch over the list; per-patch mode: one per list entry
+// (the unfused baseline).
 template <typename F>
-void over_list_dir(amr_hierarchy* h, const amr::ListView& lv, int stride_ints, int kind,
-                   F launch) {
+void over_list(amr_hierarchy* h, const amr::ListView& lv, int stride_ints, F launch) {
   if (h->exec_mode == AMR_EXEC_BATCHED) {
-    if (h->capturing || h->caller_records)
-      launch(h->d_lists, grid_count(h, lv), lv.dir);
-    else
-      launch(lv.ptr, lv.count, (const int*)nullptr);
-    h->check_launch();
-    note_node(h, kind, dir_entry(h, lv.dir));
-    return;
+    launch(list_arg(h, lv));
   } else {
     for (int i = 0; i < lv.count; ++i)
-      launch(lv.ptr + (long long)i * stride_ints, 1, (const int*)nullptr);
+      launch(amr::ListArg{lv.ptr + (long long)i * stride_ints, 1, nullptr});
   }
   h->check_launch();
+}
+
+// The step's kernels: over_list, and the launch is noted in the library's own
+// recording.
+template <typename F>
+void over_list_noted(amr_hierarchy* h, const amr::ListView& lv, int stride_ints, int kind,
+                     F launch) {
+  over_list(h, lv, stride_ints, launch);
+  if (h->exec_mode == AMR_EXEC_BATCHED) note_node(h, kind, dir_entry(h, lv.dir));
 }
 
 // Ghosts of the patches of `lv`: same-level copies, and the prolonged regions
 // of the leaves (patches with children have every same-level neighbour).
 void do_fill(amr_hierarchy* h, int buf, const amr::ListView& lv) {
   if (h->exec_mode == AMR_EXEC_BATCHED) {
-    Kernels::fill(h->dm, h->U[buf], lv.ptr, lv.count, h->cfregions.ptr, h->cfregions.count,
-                  h->d_flags, h->stream);
+    Kernels::fill(h->dm, h->U[buf], list_arg(h, lv), list_arg(h, h->cfregions), h->d_flags,
+                  h->stream);
     h->check_launch();
     return;
   }
-  over_list(h, lv, 1, [&](const int* p, int c) {
-    Kernels::fill(h->dm, h->U[buf], p, c, nullptr, 0, h->d_flags, h->stream);
+  over_list(h, lv, 1, [&](const amr::ListArg& a) {
+    Kernels::fill(h->dm, h->U[buf], a, {}, h->d_flags, h->stream);
   });
-  over_list(h, h->cfregions, 2, [&](const int* p, int c) {
-    Kernels::fill_cf(h->dm, h->U[buf], p, c, nullptr, h->d_flags, h->stream);
+  over_list(h, h->cfregions, 2, [&](const amr::ListArg& a) {
+    Kernels::fill_cf(h->dm, h->U[buf], a, h->d_flags, h->stream);
   });
 }
 
@@ -717,21 +721,26 @@ void stage_fill(amr_hierarchy* h, int buf) {
   if (!h->fuse_halo) {
     do_fill(h, buf, h->leaves);
   } else if (h->cfg.dim > 1) {
-    over_list_dir(h, h->cffaces, 2, kGnFill, [&](const int* p, int c, const int* dir) {
-      Kernels::fill_cf(h->dm, h->U[buf], p, c, dir, h->d_flags, h->stream);
+    over_list_noted(h, h->cffaces, 2, kGnFill, [&](const amr::ListArg& a) {
+      Kernels::fill_cf(h->dm, h->U[buf], a, h->d_flags, h->stream);
     });
   }
 }
 
 void do_restrict(amr_hierarchy* h, int buf) {
   for (int l = h->forest.nlev - 1; l >= 1; --l)
-    over_list(h, h->restr[l], 1, [&](const int* p, int c) {
-      Kernels::restrict_level(h->dm, h->U[buf], p, c, nullptr, h->stream);
+    over_list(h, h->restr[l], 1, [&](const amr::ListArg& a) {
+      Kernels::restrict_level(h->dm, h->U[buf], a, h->stream);
     });
 }
 
 unsigned long long* rate_slot(const amr_hierarchy* h, int k) {
   return h->d_lam + k * amr::kRateWords;
+}
+
+// the stage kernel's items of a launch over h->tiles
+const amr::StageItem* stage_items(const amr_hierarchy* h, const amr::ListArg& t) {
+  return t.dir ? h->d_items : (const amr::StageItem*)t.ptr;
 }
 
 // lam_in (stage 1 of a step): dt comes from that rate slot and is written to
@@ -746,33 +755,28 @@ void do_stage(amr_hierarchy* h, int stage, const double* dt,
   stage_fill(h, s);
   const Kernels::TileVariant tv = Kernels::variant(h->dm.tile);
   const int tcells = tv.tx * tv.ty * tv.tz;
-  over_list_dir(h, h->tiles, kItemInts, kGnStage, [&](const int* p, int c, const int* dir) {
+  over_list_noted(h, h->tiles, kItemInts, kGnStage, [&](const amr::ListArg& t) {
     hipEvent_t a = nullptr, b = nullptr;
-    if (h->profiling) h->prof_pair(&a, &b, (long long)c * tcells);
-    Kernels::stage(h->dm, stage, h->U[s], h->d_flags, h->U[0], h->U[d], h->fr,
-                   dir ? h->d_items : (const amr::StageItem*)p, c, dir, dt, h->fuse_halo,
-                   (stage == 3 || lam_in) ? lam_next : nullptr, h->stream, a, b,
-                   lam_in, dt_out);
+    if (h->profiling) h->prof_pair(&a, &b, (long long)t.count * tcells);
+    Kernels::stage(h->dm, stage, h->U[s], h->d_flags, h->U[0], h->U[d], h->fr, stage_items(h, t),
+                   t.count, t.dir, dt, h->fuse_halo, (stage == 3 || lam_in) ? lam_next : nullptr,
+                   h->stream, a, b, lam_in, dt_out);
   });
   if (h->exec_mode == AMR_EXEC_BATCHED) {
     // refluxing and the restriction of level L-2 share a launch; coarser levels
-    // follow, finest first (lists and counts from the list directory: the two
-    // post-stage entries are consecutive)
+    // follow, finest first
     const int lup = h->forest.nlev - 2;
-    const bool rec = h->capturing || h->caller_records;
-    Kernels::post(h->dm, stage, h->U[d], h->fr, (const amr::RefluxItem*)(rec ? h->d_lists : h->reflux.ptr),
-                  grid_count(h, h->reflux), rec ? h->d_lists : h->post_pairs.ptr,
-                  grid_count(h, h->post_pairs), rec ? h->reflux.dir : nullptr, dt, w[stage],
-                  stage == 3 ? lam_next : nullptr, h->stream);
+    Kernels::post(h->dm, stage, h->U[d], h->fr, list_arg(h, h->reflux), list_arg(h, h->post_pairs), dt,
+                  w[stage], stage == 3 ? lam_next : nullptr, h->stream);
     h->check_launch();
     note_node(h, kGnPost, kDirReflux, kDirPairs);
     for (int l = lup - 1; l >= 1; --l)
-      over_list_dir(h, h->restr_post[l], 1, kGnRestrict, [&](const int* p, int c, const int* dir) {
-        Kernels::restrict_level(h->dm, h->U[d], p, c, dir, h->stream);
+      over_list_noted(h, h->restr_post[l], 1, kGnRestrict, [&](const amr::ListArg& a) {
+        Kernels::restrict_level(h->dm, h->U[d], a, h->stream);
       });
   } else {
-    over_list(h, h->reflux, kRefluxInts, [&](const int* p, int c) {
-      Kernels::reflux(h->dm, stage, h->U[d], h->fr, (const amr::RefluxItem*)p, c, dt, w[stage],
+    over_list(h, h->reflux, kRefluxInts, [&](const amr::ListArg& a) {
+      Kernels::reflux(h->dm, stage, h->U[d], h->fr, a, dt, w[stage],
                       stage == 3 ? lam_next : nullptr, h->stream);
     });
     do_restrict(h, d);
@@ -782,8 +786,8 @@ void do_stage(amr_hierarchy* h, int stage, const double* dt,
 // CFL rate of the leaf cells of buffer `buf` into rate slot `slot`
 void do_rate(amr_hierarchy* h, int buf, int slot) {
   Kernels::zero_rate(rate_slot(h, slot), h->stream);
-  over_list(h, h->leaves, 1, [&](const int* p, int c) {
-    Kernels::max_rate(h->dm, h->U[buf], p, c, rate_slot(h, slot), h->stream);
+  over_list(h, h->leaves, 1, [&](const amr::ListArg& a) {
+    Kernels::max_rate(h->dm, h->U[buf], a, rate_slot(h, slot), h->stream);
   });
   h->check_launch();
 }
@@ -816,36 +820,35 @@ void do_tag(amr_hierarchy* h, int buf, uint8_t* refine, uint8_t* coarsen, uint8_
   // candidates have children, hence every same-level neighbour, and need
   // none); else full fills
   const bool fuse = h->fuse_halo;
-  note_capture(h);
   if (fuse) {
-    over_list_dir(h, h->cfregions, 2, kGnFill, [&](const int* p, int c, const int* dir) {
-      Kernels::fill_cf(h->dm, h->U[buf], p, c, dir, h->d_flags, h->stream);
+    over_list(h, h->cfregions, 2, [&](const amr::ListArg& a) {
+      Kernels::fill_cf(h->dm, h->U[buf], a, h->d_flags, h->stream);
     });
   } else {
     do_fill(h, buf, h->leaves);
     do_fill(h, buf, h->cands);
   }
+  const int* levels = h->d_dir + 2 * kDirLevels;
   const bool shared = h->cfg.dim == 3 && fuse && h->exec_mode == AMR_EXEC_BATCHED;
   if (shared) {
     // every cell tested once, the patches share the outcome
-    Kernels::tag_flags3(h->dm, h->U[buf], h->all.ptr, h->level_count, h->cfregions.ptr,
-                        h->cfregions.count, h->d_tag_mask, h->d_has_tag, cells ? h->d_raw : nullptr,
-                        h->stream);
+    Kernels::tag_flags3(h->dm, h->U[buf], list_arg(h, h->all), h->level_count, levels,
+                        list_arg(h, h->cfregions), h->d_tag_mask, h->d_has_tag,
+                        cells ? h->d_raw : nullptr, h->stream);
     h->check_launch();
   } else {
-    over_list(h, h->leaves, 1, [&](const int* p, int c) {
-      Kernels::tag(h->dm, h->U[buf], p, c, h->d_has_tag, cells ? h->d_raw : nullptr, fuse,
-                   h->stream);
+    over_list(h, h->leaves, 1, [&](const amr::ListArg& a) {
+      Kernels::tag(h->dm, h->U[buf], a, h->d_has_tag, cells ? h->d_raw : nullptr, fuse, h->stream);
     });
-    over_list(h, h->cands, 1, [&](const int* p, int c) {
-      Kernels::tag(h->dm, h->U[buf], p, c, h->d_has_tag, nullptr, fuse, h->stream);
+    over_list(h, h->cands, 1, [&](const amr::ListArg& a) {
+      Kernels::tag(h->dm, h->U[buf], a, h->d_has_tag, nullptr, fuse, h->stream);
     });
   }
   if (cells)
-    over_list(h, h->leaves, 1, [&](const int* p, int c) {
-      Kernels::cell_tags(h->dm, h->d_raw, p, c,
-                         h->exec_mode == AMR_EXEC_BATCHED ? h->level_leaves : nullptr, shared,
-                         cells, h->stream);
+    over_list(h, h->leaves, 1, [&](const amr::ListArg& a) {
+      Kernels::cell_tags(h->dm, h->d_raw, a,
+                         h->exec_mode == AMR_EXEC_BATCHED ? h->level_leaves : nullptr, levels + 1,
+                         shared, cells, h->stream);
     });
   Kernels::requests(h->dm, h->d_has_tag, h->d_active_leaf, h->forest.max_patches, refine, coarsen,
                     h->stream);
@@ -896,8 +899,8 @@ amr_status regrid_impl(amr_hierarchy* h, const uint8_t* refine, const uint8_t* c
   // a missing prolongation source (impossible on a valid mesh) raises the
   // sticky error flag read by amr_fill_error; no synchronisation here
   for (int l = 1; l < h->forest.nlev; ++l)
-    over_list(h, h->fresh[l], 1, [&](const int* p, int c) {
-      Kernels::prolong_new(h->dm, h->U[0], p, c, h->d_flags, h->stream);
+    over_list(h, h->fresh[l], 1, [&](const amr::ListArg& a) {
+      Kernels::prolong_new(h->dm, h->U[0], a, h->d_flags, h->stream);
     });
   if (ncreated) *ncreated = (int)created.size();
   if (ndeleted) *ndeleted = (int)deleted.size();
@@ -1240,6 +1243,7 @@ amr_status amr_set_state_prim_noalloc(amr_hierarchy* h, int buf, const double* p
 amr_status amr_fill_ghosts(amr_hierarchy* h, int buf) {
   if (!h || !buf_ok(buf)) return AMR_E_ARG;
   return guarded(h, [&]() -> amr_status {
+    note_capture(h);
     do_fill(h, buf, h->all);
     return AMR_OK;
   });
@@ -1250,14 +1254,12 @@ amr_status amr_rhs(amr_hierarchy* h, int buf, double* rhs_dev) {
   return guarded(h, [&]() -> amr_status {
     note_capture(h);
     stage_fill(h, buf);
-    over_list_dir(h, h->tiles, kItemInts, kGnStage, [&](const int* p, int c, const int* dir) {
+    over_list(h, h->tiles, kItemInts, [&](const amr::ListArg& t) {
       Kernels::stage(h->dm, amr::kModeRHS, h->U[buf], h->d_flags, h->U[0], rhs_dev, h->fr,
-                     dir ? h->d_items : (const amr::StageItem*)p, c, dir, h->d_dt, h->fuse_halo,
-                     nullptr, h->stream);
+                     stage_items(h, t), t.count, t.dir, h->d_dt, h->fuse_halo, nullptr, h->stream);
     });
-    over_list(h, h->reflux, kRefluxInts, [&](const int* p, int c) {
-      Kernels::reflux(h->dm, amr::kModeRHS, rhs_dev, h->fr, (const amr::RefluxItem*)p, c, h->d_dt, 1.0,
-                      nullptr, h->stream);
+    over_list(h, h->reflux, kRefluxInts, [&](const amr::ListArg& a) {
+      Kernels::reflux(h->dm, amr::kModeRHS, rhs_dev, h->fr, a, h->d_dt, 1.0, nullptr, h->stream);
     });
     return AMR_OK;
   });
@@ -1266,6 +1268,7 @@ amr_status amr_rhs(amr_hierarchy* h, int buf, double* rhs_dev) {
 amr_status amr_compute_dt(amr_hierarchy* h, int buf, double* dt_dev) {
   if (!h || !buf_ok(buf) || !dt_dev) return AMR_E_ARG;
   return guarded(h, [&]() -> amr_status {
+    note_capture(h);
     do_dt(h, buf, dt_dev);
     return AMR_OK;
   });
@@ -1372,6 +1375,7 @@ amr_status amr_tag(amr_hierarchy* h, int buf, uint8_t* refine_req_dev, uint8_t* 
                    uint8_t* cell_tags_dev) {
   if (!h || !buf_ok(buf)) return AMR_E_ARG;
   return guarded(h, [&]() -> amr_status {
+    note_capture(h);
     do_tag(h, buf, refine_req_dev, coarsen_req_dev, cell_tags_dev);
     return AMR_OK;
   });
@@ -1390,6 +1394,7 @@ amr_status amr_adapt(amr_hierarchy* h, int* ncreated, int* ndeleted) {
   if (!h) return AMR_E_ARG;
   return guarded(h, [&]() -> amr_status {
     const int mp = h->forest.max_patches;
+    note_capture(h);
     do_tag(h, 0, h->d_refine, h->d_coarsen, nullptr);
     // into pinned memory: asynchronous copies, one wait
     uint8_t* rq = h->h_req;
@@ -1404,9 +1409,10 @@ amr_status amr_adapt(amr_hierarchy* h, int* ncreated, int* ndeleted) {
 amr_status amr_check(amr_hierarchy* h, int* nonphysical_count) {
   if (!h) return AMR_E_ARG;
   return guarded(h, [&]() -> amr_status {
+    note_capture(h);
     HIP_OK(hipMemsetAsync(h->d_flags + 1, 0, sizeof(int), h->stream));
-    over_list(h, h->leaves, 1, [&](const int* p, int c) {
-      Kernels::check(h->dm, h->U[0], p, c, h->d_flags + 1, h->stream);
+    over_list(h, h->leaves, 1, [&](const amr::ListArg& a) {
+      Kernels::check(h->dm, h->U[0], a, h->d_flags + 1, h->stream);
     });
     const int bad = read_flag(h, 1);
     if (nonphysical_count) *nonphysical_count = bad;
@@ -1421,6 +1427,7 @@ amr_status amr_check(amr_hierarchy* h, int* nonphysical_count) {
 amr_status amr_judge(amr_hierarchy* h, int* uncovered) {
   if (!h || !uncovered) return AMR_E_ARG;
   return guarded(h, [&]() -> amr_status {
+    note_capture(h);
     do_tag(h, 0, h->d_refine, nullptr, nullptr);
     HIP_OK(hipMemsetAsync(h->d_flags + 2, 0, sizeof(int), h->stream));
     Kernels::count_nonzero(h->d_refine, h->forest.max_patches, h->d_flags + 2, h->stream);
@@ -1602,10 +1609,11 @@ amr_status amr_forest_replay(const amr_config* cfg, const int32_t* req, int nreq
 amr_status amr_velocity_gradient(amr_hierarchy* h, int buf, double* out_dev) {
   if (!h || !buf_ok(buf) || !out_dev) return AMR_E_ARG;
   return guarded(h, [&]() -> amr_status {
+    note_capture(h);
     do_fill(h, buf, h->leaves);
     const long long plane = h->state_doubles / h->nvar;
-    over_list(h, h->leaves, 1, [&](const int* p, int c) {
-      amr::Diagnostics::velocity_gradient(h->dm, h->U[buf], p, c, out_dev, plane, h->stream);
+    over_list(h, h->leaves, 1, [&](const amr::ListArg& a) {
+      amr::Diagnostics::velocity_gradient(h->dm, h->U[buf], a, out_dev, plane, h->stream);
     });
     return AMR_OK;
   });
@@ -1817,6 +1825,7 @@ amr_status amr_cnn_gather(amr_cnn* c, int buf, const int* pids_host, int npatch,
       // a 3D patch of edge 8 is the single tile 0
       items[i] = c->dim == 2 ? p : p * amr::CNN3_MAX_TILES;
     }
+    note_capture(h);
     do_fill(h, buf, h->leaves);
     if (npatch > 0)
       HIP_OK(hipMemcpyAsync(c->d_pids, items.data(), npatch * sizeof(int), hipMemcpyHostToDevice,
@@ -1879,6 +1888,7 @@ amr_status amr_cnn_predict(amr_cnn* c, int buf, float tau, uint8_t* refine_req_d
       }
     }
     if ((long long)items.size() > c->items_cap) throw ArgError("predictor item list overflow");
+    note_capture(h);
     do_fill(h, buf, h->leaves);
     HIP_OK(hipMemsetAsync(c->d_pred, 0, f.max_patches, s));
     if (!items.empty())

@@ -405,6 +405,13 @@ __device__ __forceinline__ void clear_rate(unsigned long long* __restrict__ lam)
   for (int x = 0; x < kXcds; ++x) lam[x * kRateStride] = 0ull;
 }
 
+// The entries and live count of a list (see ListArg).
+__device__ __forceinline__ void live_list(ListArg& a) {
+  if (!a.dir) return;
+  a.ptr += a.dir[0];
+  a.count = a.dir[1];
+}
+
 // Work item of this block.  Workgroups are dealt to the chip's XCDs in
 // turn (block b runs on XCD b mod kXcds) and each XCD has its own L2: XCD x
 // takes the contiguous items [x per, (x + 1) per), per = ceil(count /

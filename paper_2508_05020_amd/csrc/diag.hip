@@ -18,10 +18,11 @@ namespace {
 
 template <int D>
 __global__ __launch_bounds__(256) void k_velocity_gradient(DevMesh m, const double* __restrict__ U,
-                                                           const int* __restrict__ leaves, int count,
+                                                           ListArg leaves,
                                                            double* __restrict__ out, long long plane) {
-  for (int b = blockIdx.x; b < count; b += gridDim.x) {
-    const int pid = leaves[b];
+  live_list(leaves);
+  for (int b = blockIdx.x; b < leaves.count; b += gridDim.x) {
+    const int pid = leaves.ptr[b];
     const int l = m.level[pid];
     const LevelC& L = m.lv[l];
     const int n = L.n, f = L.full;
@@ -62,19 +63,16 @@ __global__ __launch_bounds__(256) void k_velocity_gradient(DevMesh m, const doub
 
 }  // namespace
 
-void Diagnostics::velocity_gradient(const DevMesh& m, const double* U, const int* leaves, int count,
+void Diagnostics::velocity_gradient(const DevMesh& m, const double* U, const ListArg& leaves,
                                     double* out, long long plane, hipStream_t s) {
-  if (count <= 0) return;
-  const int blocks = count < 65535 ? count : 65535;
+  if (leaves.count <= 0) return;
+  const int blocks = leaves.count < 65535 ? leaves.count : 65535;
   if (m.dim == 1)
-    hipLaunchKernelGGL(k_velocity_gradient<1>, dim3(blocks), dim3(64), 0, s, m, U, leaves, count, out,
-                       plane);
+    hipLaunchKernelGGL(k_velocity_gradient<1>, dim3(blocks), dim3(64), 0, s, m, U, leaves, out, plane);
   else if (m.dim == 2)
-    hipLaunchKernelGGL(k_velocity_gradient<2>, dim3(blocks), dim3(256), 0, s, m, U, leaves, count,
-                       out, plane);
+    hipLaunchKernelGGL(k_velocity_gradient<2>, dim3(blocks), dim3(256), 0, s, m, U, leaves, out, plane);
   else
-    hipLaunchKernelGGL(k_velocity_gradient<3>, dim3(blocks), dim3(256), 0, s, m, U, leaves, count,
-                       out, plane);
+    hipLaunchKernelGGL(k_velocity_gradient<3>, dim3(blocks), dim3(256), 0, s, m, U, leaves, out, plane);
 }
 
 }  // namespace amr

@@ -109,11 +109,11 @@ __device__ __forceinline__ void copy_ghosts(const DevMesh& m, const double* __re
 }
 
 __global__ __launch_bounds__(256) void k_fill_copy3(DevMesh m, const double* __restrict__ Uin,
-                                                    double* __restrict__ U,
-                                                    const int* __restrict__ list, int count) {
+                                                    double* __restrict__ U, ListArg list) {
   __shared__ long long sNB[27];
-  const int item = xcd_chunk<kCopyChunk>(count);
-  if (item >= 0) copy_ghosts<3, 256>(m, Uin, U, list[item], sNB);
+  live_list(list);
+  const int item = xcd_chunk<kCopyChunk>(list.count);
+  if (item >= 0) copy_ghosts<3, 256>(m, Uin, U, list.ptr[item], sNB);
 }
 
 // Ghost cells without a same-level source: one work item per (leaf, ghost
@@ -160,20 +160,13 @@ __device__ __forceinline__ void fill_cf_region(const DevMesh& m, double* __restr
   }
 }
 
-// One block per region.  With `dir` (batched launches) the list is
-// list + dir[0] and the count dir[1], read at run time (the grid may hold
-// more blocks than regions).
+// One block per region.
 template <int D, int NT>
 __global__ __launch_bounds__(NT) void k_fill_cf(DevMesh m,
-                                                double* __restrict__ U,
-                                                const int* __restrict__ list, int count,
-                                                const int* __restrict__ dir,
+                                                double* __restrict__ U, ListArg regions,
                                                 int* __restrict__ err) {
-  if (dir) {
-    list += dir[0];
-    count = dir[1];
-  }
-  if ((int)blockIdx.x < count) fill_cf_region<D, NT>(m, U, list, blockIdx.x, err);
+  live_list(regions);
+  if ((int)blockIdx.x < regions.count) fill_cf_region<D, NT>(m, U, regions.ptr, blockIdx.x, err);
 }
 
 // The same regions by coarse cell (2D and 3D).  A region's start and extent
@@ -277,21 +270,16 @@ __device__ __forceinline__ void fill_cf_coarse_group(const DevMesh& m, double* _
   }
 }
 
-// A block takes a group of G consecutive regions.  With `dir` (batched
-// launches) the list and count are read at run time.
+// A block takes a group of G consecutive regions.
 template <int D, int NT, int G>
 __global__ __launch_bounds__(NT) void k_fill_cf_coarse(DevMesh m,
-                                                       double* __restrict__ U,
-                                                       const int* __restrict__ list, int count,
-                                                       const int* __restrict__ dir,
+                                                       double* __restrict__ U, ListArg regions,
                                                        int* __restrict__ err) {
   __shared__ RegionGroup<G> s;
-  if (dir) {
-    list += dir[0];
-    count = dir[1];
-  }
+  live_list(regions);
   const int first = (int)blockIdx.x * G;
-  if (first < count) fill_cf_coarse_group<D, NT, G>(m, U, list, count, first, err, s);
+  if (first < regions.count)
+    fill_cf_coarse_group<D, NT, G>(m, U, regions.ptr, regions.count, first, err, s);
 }
 
 // The whole fill in one launch (1D, 2D): prolonged regions (groups of G, by
@@ -306,25 +294,26 @@ constexpr int kFillGroup = 4;
 
 template <int D>
 __global__ __launch_bounds__(fill_threads(D)) void k_fill(DevMesh m, const double* __restrict__ Uin,
-                                                          double* __restrict__ U,
-                                                          const int* __restrict__ list, int count,
-                                                          const int* __restrict__ regions,
-                                                          int nregions, int rblocks,
+                                                          double* __restrict__ U, ListArg list,
+                                                          ListArg regions, int rblocks,
                                                           int* __restrict__ err) {
   constexpr int NT = fill_threads(D);
   __shared__ RegionGroup<kFillGroup> s;
   __shared__ long long sNB[27];
   const int b = (int)blockIdx.x;
   if (b < rblocks) {
+    live_list(regions);
     if constexpr (D == 1) {
-      if (b < nregions) fill_cf_region<D, NT>(m, U, regions, b, err);
+      if (b < regions.count) fill_cf_region<D, NT>(m, U, regions.ptr, b, err);
     } else {
-      if (b * kFillGroup < nregions)
-        fill_cf_coarse_group<D, NT, kFillGroup>(m, U, regions, nregions, b * kFillGroup, err, s);
+      if (b * kFillGroup < regions.count)
+        fill_cf_coarse_group<D, NT, kFillGroup>(m, U, regions.ptr, regions.count, b * kFillGroup,
+                                                err, s);
     }
   } else {
-    const int item = xcd_chunk<kCopyChunk>(count, b - rblocks);
-    if (item >= 0) copy_ghosts<D, NT>(m, Uin, U, list[item], sNB);
+    live_list(list);
+    const int item = xcd_chunk<kCopyChunk>(list.count, b - rblocks);
+    if (item >= 0) copy_ghosts<D, NT>(m, Uin, U, list.ptr[item], sNB);
   }
 }
 
@@ -491,8 +480,13 @@ template <int D, int NT>
 __global__ __launch_bounds__(NT) void k_reflux(DevMesh m, int mode, double* __restrict__ out,
                                                const double* __restrict__ fr,
                                                const RefluxItem* __restrict__ list, int count,
+                                               const int* __restrict__ dir,
                                                const double* __restrict__ dtp, double w,
                                                unsigned long long* __restrict__ lam_next) {
+  if (dir) {
+    list = reinterpret_cast<const RefluxItem*>(reinterpret_cast<const int*>(list) + dir[0]);
+    count = dir[1];
+  }
   if ((int)blockIdx.x >= count) return;
   reflux_item<D, NT>(m, mode, out, fr, list[blockIdx.x], dtp, w, lam_next);
 }
@@ -593,16 +587,11 @@ __device__ __forceinline__ void restrict_faces(const DevMesh& m, double* __restr
 }
 
 template <int D>
-__global__ __launch_bounds__(256) void k_restrict(DevMesh m,
-                                                  double* __restrict__ U,
-                                                  const int* __restrict__ list, int count,
-                                                  const int* __restrict__ dir) {
-  if (dir) {
-    list += dir[0];
-    count = dir[1];
-  }
-  if ((int)blockIdx.x >= count) return;
-  const int pid = list[blockIdx.x], l = m.level[pid];
+__global__ __launch_bounds__(256) void k_restrict(DevMesh m, double* __restrict__ U,
+                                                  ListArg list) {
+  live_list(list);
+  if ((int)blockIdx.x >= list.count) return;
+  const int pid = list.ptr[blockIdx.x], l = m.level[pid];
   restrict_patch<D>(m, U, pid, l, restrict_target<D>(m, pid, l));
 }
 
@@ -616,9 +605,9 @@ __global__ __launch_bounds__(256) void k_restrict(DevMesh m,
 //                  the stage kernel has restricted their final values).
 // A block's restriction after refluxing reads only what the same block wrote
 // (block barrier between); the blocks touch disjoint cells otherwise:
-// refluxing changes leaf cells, restriction writes non-leaf cells.  With
-// `dir` (batched launches) the lists and their counts are read at run time
-// from their directory entries, in order; rlist is then the list buffer.
+// refluxing changes leaf cells, restriction writes non-leaf cells.  Recorded,
+// `dir` has the entries of both lists, in order (one load), and rlist is the
+// list buffer.
 // Restricting the corrected leaves whole, here and in the coarser levels'
 // launches: 76 and 26 us (3D, 20.4 M cells), 67 and 16 so.
 template <int D, int NT>
@@ -658,14 +647,15 @@ __global__ __launch_bounds__(NT) void k_post(DevMesh m, int mode,
 // ---------------------------------------------------------------------------
 template <int D>
 __global__ __launch_bounds__(256) void k_max_rate(DevMesh m, const double* __restrict__ U,
-                                                  const int* __restrict__ list, int count,
+                                                  ListArg list,
                                                   unsigned long long* __restrict__ lam) {
   constexpr int NV = D + 2;
-  if ((int)blockIdx.x >= count) return;
+  live_list(list);
+  if ((int)blockIdx.x >= list.count) return;
   unsigned long long best = 0ull;
-  const int l = m.level[list[blockIdx.x]];
+  const int l = m.level[list.ptr[blockIdx.x]];
   {
-    const int pid = list[blockIdx.x];
+    const int pid = list.ptr[blockIdx.x];
     const LevelC& L = m.lv[l];
     const int n = L.n;
     const double* P = U + patch_base(m, pid, l);
@@ -756,11 +746,11 @@ __device__ __forceinline__ void rho_p_node(const DevMesh& m, const double* __res
 
 template <int D, bool FUSE>
 __global__ __launch_bounds__(256) void k_tag(DevMesh m, const double* __restrict__ U,
-                                             const int* __restrict__ list, int count,
-                                             uint8_t* __restrict__ has_tag,
+                                             ListArg list, uint8_t* __restrict__ has_tag,
                                              uint8_t* __restrict__ raw, int lds_nodes) {
-  if ((int)blockIdx.x >= count) return;
-  const int pid = list[blockIdx.x];
+  live_list(list);
+  if ((int)blockIdx.x >= list.count) return;
+  const int pid = list.ptr[blockIdx.x];
   const int l = m.level[pid];
   const LevelC& L = m.lv[l];
   const int n = L.n, b = m.tag_buffer, w = n + 2 * b;
@@ -866,21 +856,36 @@ __global__ __launch_bounds__(256) void k_tag(DevMesh m, const double* __restrict
 // leaf's own dilated box, 211 shared) and 12.8 us (2D, 384^2 base), 91 and 8.8 so.
 constexpr int cell_tile(int dim) { return dim == 1 ? 256 : (dim == 2 ? 32 : 8); }
 
+// Entry of a list in level order whose tile is block b's, -1 past the last one;
+// b becomes the tile, l the entry's level in `tl`.
+__device__ __forceinline__ int level_item(const DevMesh& m, const TagLevels& tl, int count, int& b,
+                                          int& l) {
+  int first = 0;
+  for (l = 0; l < m.nlev - 1; ++l) {
+    const int here = __builtin_amdgcn_readfirstlane(tl.dir ? tl.dir[2 * l] : tl.count[l]);
+    if (b < here * tl.tiles[l]) break;
+    b -= here * tl.tiles[l];
+    first += here;
+  }
+  const int item = first + b / tl.tiles[l];
+  b %= tl.tiles[l];
+  return item < count ? item : -1;
+}
+
 template <int D, bool SHARED>
 __global__ __launch_bounds__(256) void k_cell_tags(DevMesh m, const uint8_t* __restrict__ raw,
-                                                   const int* __restrict__ leaves, TagLevels tl,
+                                                   ListArg leaves, TagLevels tl,
                                                    uint8_t* __restrict__ out) {
   constexpr int T = cell_tile(D), MAXB = 3, B = T + 2 * MAXB;
   constexpr int NODES = D == 1 ? B : (D == 2 ? B * B : B * B * B);
   constexpr int CENTRE = D == 1 ? 1 : (D == 2 ? 4 : 13);
   __shared__ uint8_t sa[NODES], sb[NODES];
   __shared__ int sN[27];
-  int bl = blockIdx.x, first = 0, k = 0;
-  for (; k < m.nlev - 1 && bl >= tl.count[k] * tl.tiles[k]; ++k) {
-    bl -= tl.count[k] * tl.tiles[k];
-    first += tl.count[k];
-  }
-  const int tile = bl % tl.tiles[k], pid = leaves[first + bl / tl.tiles[k]];
+  live_list(leaves);
+  int bl = blockIdx.x, k;
+  const int item = level_item(m, tl, leaves.count, bl, k);
+  if (item < 0) return;
+  const int tile = bl, pid = leaves.ptr[item];
   const int l = m.level[pid];
   const LevelC& L = m.lv[l];
   const int n = L.n, b = m.tag_buffer, vs = var_stride<D>(L.full), nt = (n + T - 1) / T;
@@ -1067,20 +1072,19 @@ __device__ __forceinline__ void tag_node(const DevMesh& m, const double* __restr
 constexpr int kTagChunk = 16;
 
 __global__ __launch_bounds__(256) void k_tag_cells(DevMesh m, const double* __restrict__ U,
-                                                   const int* __restrict__ list, TagLevels tl,
-                                                   int blocks, int* __restrict__ mask,
+                                                   ListArg list, TagLevels tl, int blocks,
+                                                   int* __restrict__ mask,
                                                    uint8_t* __restrict__ raw) {
   constexpr int B = kTagTile + 2;
   __shared__ long long sNB[27];
   __shared__ double sr[B * B * B], sp[B * B * B];
   __shared__ int sm;
-  int b = xcd_chunk<kTagChunk>(blocks), first = 0, l = 0;
+  live_list(list);
+  int b = xcd_chunk<kTagChunk>(blocks), l;
   if (b < 0) return;
-  for (; l < m.nlev - 1 && b >= tl.count[l] * tl.tiles[l]; ++l) {
-    b -= tl.count[l] * tl.tiles[l];
-    first += tl.count[l];
-  }
-  const int tile = b % tl.tiles[l], pid = list[first + b / tl.tiles[l]];
+  const int item = level_item(m, tl, list.count, b, l);
+  if (item < 0) return;
+  const int tile = b, pid = list.ptr[item];
   const LevelC& L = m.lv[l];
   const int n = L.n, full = L.full, vs = var_stride<3>(full);
   const int nt = (n + kTagTile - 1) / kTagTile;
@@ -1150,12 +1154,14 @@ __global__ __launch_bounds__(256) void k_tag_cells(DevMesh m, const double* __re
 // the lines it fetches (1.4 GB for 205 us, mostly ghost rows of 32 bytes);
 // consecutive groups share an XCD as in k_tag_cells (214 us in launch order).
 __global__ __launch_bounds__(128) void k_tag_regions(DevMesh m, const double* __restrict__ U,
-                                                     const int* __restrict__ list, int count,
-                                                     int* __restrict__ mask, uint8_t* __restrict__ raw) {
+                                                     ListArg regions, int* __restrict__ mask,
+                                                     uint8_t* __restrict__ raw) {
   constexpr int G = 4, CENTRE = 1 << 13;
   __shared__ long long sNB[G][27];
   __shared__ int s_pid[G], s_code[G], s_lev[G], s_pc[G][3], s_pre[G + 1];
-  const int b = m.tag_buffer;
+  live_list(regions);
+  const int* list = regions.ptr;
+  const int b = m.tag_buffer, count = regions.count;
   const int bb = xcd_chunk<kTagChunk>((count + G - 1) / G);
   if (bb < 0) return;
   {
@@ -1242,13 +1248,14 @@ __global__ __launch_bounds__(128) void k_tag_regions(DevMesh m, const double* __
 // Tag flag of every patch of `list`: a tagged cell of its own, one of its
 // prolonged regions, or one of a neighbour within tag_buffer of it (the
 // neighbour at offset code k faces it with its side 26 - k).  8 lanes a patch.
-__global__ __launch_bounds__(256) void k_tag_flags(DevMesh m, const int* __restrict__ list,
-                                                   int count, const int* __restrict__ mask,
+__global__ __launch_bounds__(256) void k_tag_flags(DevMesh m, ListArg list,
+                                                   const int* __restrict__ mask,
                                                    uint8_t* __restrict__ has_tag) {
+  live_list(list);
   const int i = (int)(blockIdx.x * blockDim.x + threadIdx.x) >> 3, lane = threadIdx.x & 7;
   int any = 0, pid = -1;
-  if (i < count) {
-    pid = list[i];
+  if (i < list.count) {
+    pid = list.ptr[i];
     const int l = m.level[pid], np = m.lv[l].np;
     const int pc[3] = {m.coord[3 * pid], m.coord[3 * pid + 1], m.coord[3 * pid + 2]};
     if (lane == 0) any = mask[pid] & (1 << 13 | 1 << 27);
@@ -1317,12 +1324,11 @@ __global__ __launch_bounds__(256) void k_requests(DevMesh m, const uint8_t* __re
 // 30.3 us now)
 template <int D, int NT>
 __global__ __launch_bounds__(NT) void k_prolong_new(DevMesh m, const double* __restrict__ Uin,
-                                                    double* __restrict__ U,
-                                                    const int* __restrict__ list, int count,
+                                                    double* __restrict__ U, ListArg list,
                                                     int* __restrict__ err) {
   constexpr int NV = D + 2;
-  if ((int)blockIdx.x >= count) return;
-  const int pid = list[blockIdx.x];
+  if ((int)blockIdx.x >= list.count) return;
+  const int pid = list.ptr[blockIdx.x];
   const int l = m.level[pid];
   const LevelC& L = m.lv[l];
   const int n = L.n, h = n / 2;
@@ -1364,11 +1370,11 @@ __global__ void k_scatter_int(int* __restrict__ dst, const int* __restrict__ pai
 
 template <int D>
 __global__ __launch_bounds__(256) void k_check(DevMesh m, const double* __restrict__ U,
-                                               const int* __restrict__ list, int count,
-                                               int* __restrict__ bad) {
+                                               ListArg list, int* __restrict__ bad) {
   constexpr int NV = D + 2;
-  if ((int)blockIdx.x >= count) return;
-  const int pid = list[blockIdx.x];
+  live_list(list);
+  if ((int)blockIdx.x >= list.count) return;
+  const int pid = list.ptr[blockIdx.x];
   const int l = m.level[pid];
   const LevelC& L = m.lv[l];
   const int n = L.n;
@@ -1422,13 +1428,13 @@ int Kernels::fill_cf_grid(const DevMesh& m, int count) {
   return (count + g - 1) / g;
 }
 
-void Kernels::fill_cf(const DevMesh& m, double* U, const int* list, int count, const int* dir,
-                      int* err, hipStream_t s) {
-  if (count <= 0) return;
+void Kernels::fill_cf(const DevMesh& m, double* U, const ListArg& regions, int* err,
+                      hipStream_t s) {
+  if (regions.count <= 0) return;
   // one block per region (group of regions)
   auto launch = [&](auto kern, int threads) {
-    hipLaunchKernelGGL(kern, dim3(fill_cf_grid(m, count)), dim3(threads), 0, s, m, U, list, count,
-                       dir, err);
+    hipLaunchKernelGGL(kern, dim3(fill_cf_grid(m, regions.count)), dim3(threads), 0, s, m, U, regions,
+                       err);
   };
   switch (m.dim) {
     case 1: launch(k_fill_cf<1, 64>, 64); break;
@@ -1459,47 +1465,53 @@ void Kernels::fill_cf(const DevMesh& m, double* U, const int* list, int count, c
   }
 }
 
-void Kernels::fill(const DevMesh& m, double* U, const int* list, int count, const int* regions,
-                   int nregions, int* err, hipStream_t s) {
+void Kernels::fill(const DevMesh& m, double* U, const ListArg& list, const ListArg& regions,
+                   int* err, hipStream_t s) {
   const int group = kXcds * kCopyChunk;  // blocks per group of chunks (xcd_chunk)
-  const int copies = (count + group - 1) / group * group;
+  const int copies = (list.count + group - 1) / group * group;
   if (m.dim == 3) {
     if (copies > 0)
-      hipLaunchKernelGGL(k_fill_copy3, dim3(copies), dim3(256), 0, s, m, U, U, list, count);
-    fill_cf(m, U, regions, nregions, nullptr, err, s);
+      hipLaunchKernelGGL(k_fill_copy3, dim3(copies), dim3(256), 0, s, m, U, U, list);
+    fill_cf(m, U, regions, err, s);
     return;
   }
   const int per = m.dim == 1 ? 1 : kFillGroup;
   // whole groups of kXcds blocks, so that a copy block's XCD follows its index
-  const int rblocks = ((nregions + per - 1) / per + kXcds - 1) / kXcds * kXcds;
+  const int rblocks = ((regions.count + per - 1) / per + kXcds - 1) / kXcds * kXcds;
   if (rblocks + copies <= 0) return;
   if (m.dim == 1)
     hipLaunchKernelGGL(k_fill<1>, dim3(rblocks + copies), dim3(fill_threads(1)), 0, s, m, U, U, list,
-                       count, regions, nregions, rblocks, err);
+                       regions, rblocks, err);
   else
     hipLaunchKernelGGL(k_fill<2>, dim3(rblocks + copies), dim3(fill_threads(2)), 0, s, m, U, U, list,
-                       count, regions, nregions, rblocks, err);
+                       regions, rblocks, err);
 }
 
 void Kernels::reflux(const DevMesh& m, int mode, double* out, const double* fr,
-                     const RefluxItem* list, int count, const double* dt, double w,
+                     const ListArg& list, const double* dt, double w,
                      unsigned long long* lam_next, hipStream_t s) {
-  if (count <= 0) return;
+  if (list.count <= 0) return;
+  auto launch = [&](auto kern, int threads) {
+    hipLaunchKernelGGL(kern, dim3(list.count), dim3(threads), 0, s, m, mode, out, fr,
+                       reinterpret_cast<const RefluxItem*>(list.ptr), list.count, list.dir, dt, w,
+                       lam_next);
+  };
   switch (m.dim) {
-    case 1: k_reflux<1, 64><<<count, 64, 0, s>>>(m, mode, out, fr, list, count, dt, w, lam_next); break;
-    case 2: k_reflux<2, 64><<<count, 64, 0, s>>>(m, mode, out, fr, list, count, dt, w, lam_next); break;
-    default: k_reflux<3, 512><<<count, 512, 0, s>>>(m, mode, out, fr, list, count, dt, w, lam_next); break;
+    case 1: launch(k_reflux<1, 64>, 64); break;
+    case 2: launch(k_reflux<2, 64>, 64); break;
+    default: launch(k_reflux<3, 512>, 512); break;
   }
 }
 
 void Kernels::post(const DevMesh& m, int mode, double* out, const double* fr,
-                   const RefluxItem* rlist, int nref, const int* plist, int npair, const int* dir,
-                   const double* dt, double w, unsigned long long* lam_next, hipStream_t s) {
-  const int nb = nref + npair;
+                   const ListArg& rlist, const ListArg& plist, const double* dt, double w,
+                   unsigned long long* lam_next, hipStream_t s) {
+  const int nb = rlist.count + plist.count;
   if (nb <= 0) return;
   auto launch = [&](auto kern, int threads) {
-    hipLaunchKernelGGL(kern, dim3(nb), dim3(threads), 0, s, m, mode, out, fr, rlist, nref,
-                       plist, npair, dir, dt, w, lam_next);
+    hipLaunchKernelGGL(kern, dim3(nb), dim3(threads), 0, s, m, mode, out, fr,
+                       reinterpret_cast<const RefluxItem*>(rlist.ptr), rlist.count, plist.ptr,
+                       plist.count, rlist.dir, dt, w, lam_next);
   };
   switch (m.dim) {
     case 1: launch(k_post<1, 64>, 64); break;
@@ -1510,13 +1522,11 @@ void Kernels::post(const DevMesh& m, int mode, double* out, const double* fr,
   }
 }
 
-void Kernels::restrict_level(const DevMesh& m, double* U, const int* list, int count,
-                             const int* dir, hipStream_t s) {
-  if (count <= 0) return;
+void Kernels::restrict_level(const DevMesh& m, double* U, const ListArg& list, hipStream_t s) {
+  if (list.count <= 0) return;
   // one block per child patch, one thread per covered parent cell
   auto launch = [&](auto kern, int threads) {
-    const int nb = count;
-    hipLaunchKernelGGL(kern, dim3(nb), dim3(threads), 0, s, m, U, list, count, dir);
+    hipLaunchKernelGGL(kern, dim3(list.count), dim3(threads), 0, s, m, U, list);
   };
   switch (m.dim) {
     case 1: launch(k_restrict<1>, 64); break;
@@ -1526,10 +1536,10 @@ void Kernels::restrict_level(const DevMesh& m, double* U, const int* list, int c
   }
 }
 
-void Kernels::max_rate(const DevMesh& m, const double* U, const int* list, int count,
+void Kernels::max_rate(const DevMesh& m, const double* U, const ListArg& list,
                        unsigned long long* lam, hipStream_t s) {
-  if (count <= 0) return;
-  AMR_DISPATCH_DIM(m.dim, k_max_rate, dim3(count), dim3(256), s, m, U, list, count, lam);
+  if (list.count <= 0) return;
+  AMR_DISPATCH_DIM(m.dim, k_max_rate, dim3(list.count), dim3(256), s, m, U, list, lam);
 }
 
 void Kernels::zero_rate(unsigned long long* slot, hipStream_t s) {
@@ -1541,9 +1551,10 @@ void Kernels::dt_from_rate(const DevMesh& m, const unsigned long long* lam, doub
   hipLaunchKernelGGL(k_dt_from_rate, dim3(1), dim3(1), 0, s, lam, m.cfl, dt, clear);
 }
 
-void Kernels::tag(const DevMesh& m, const double* U, const int* list, int count,
-                  uint8_t* has_tag, uint8_t* raw, bool fuse, hipStream_t s) {
-  if (count <= 0) return;
+void Kernels::tag(const DevMesh& m, const double* U, const ListArg& list, uint8_t* has_tag,
+                  uint8_t* raw, bool fuse, hipStream_t s) {
+  const int nb = list.count;
+  if (nb <= 0) return;
   // LDS for rho and p on the box [-b-1, n+b]^D of the largest patch edge
   // (1D/2D), or of the largest edge whose box fits 64 KB (3D)
   int lds_nodes = 0;
@@ -1571,8 +1582,8 @@ void Kernels::tag(const DevMesh& m, const double* U, const int* list, int count,
   }
 #define AMR_TAG(D)                                                                           \
   do {                                                                                       \
-    if (fuse) k_tag<D, true><<<count, 256, lds, s>>>(m, U, list, count, has_tag, raw, lds_nodes); \
-    else k_tag<D, false><<<count, 256, lds, s>>>(m, U, list, count, has_tag, raw, lds_nodes);    \
+    if (fuse) k_tag<D, true><<<nb, 256, lds, s>>>(m, U, list, has_tag, raw, lds_nodes);      \
+    else k_tag<D, false><<<nb, 256, lds, s>>>(m, U, list, has_tag, raw, lds_nodes);          \
   } while (0)
   if (m.dim == 1) AMR_TAG(1);
   else if (m.dim == 2) AMR_TAG(2);
@@ -1580,37 +1591,39 @@ void Kernels::tag(const DevMesh& m, const double* U, const int* list, int count,
 #undef AMR_TAG
 }
 
-void Kernels::tag_flags3(const DevMesh& m, const double* U, const int* list, const int* level_count,
-                         const int* regions, int nregions, int* mask, uint8_t* has_tag,
-                         uint8_t* raw, hipStream_t s) {
+void Kernels::tag_flags3(const DevMesh& m, const double* U, const ListArg& list,
+                         const int* level_count, const int* level_dir, const ListArg& regions,
+                         int* mask, uint8_t* has_tag, uint8_t* raw, hipStream_t s) {
+  const int count = list.count;
+  if (count <= 0) return;
   TagLevels tl{};
-  int blocks = 0, count = 0;
+  if (list.dir) tl.dir = level_dir;
+  int blocks = 0;
   for (int l = 0; l < m.nlev; ++l) {
     const int nt = (m.lv[l].n + kTagTile - 1) / kTagTile;
     tl.count[l] = level_count[l];
     tl.tiles[l] = nt * nt * nt;
     blocks += tl.count[l] * tl.tiles[l];
-    count += tl.count[l];
   }
-  if (count <= 0) return;
   hipLaunchKernelGGL(k_zero_int, dim3((m.max_patches + 255) / 256), dim3(256), 0, s, mask,
                      m.max_patches);
   const int group = kXcds * kTagChunk;  // blocks per group of chunks (xcd_chunk)
   hipLaunchKernelGGL(k_tag_cells, dim3((blocks + group - 1) / group * group), dim3(256), 0, s, m, U,
                      list, tl, blocks, mask, raw);
   // without dilation no ghost cell counts
-  if (nregions > 0 && m.tag_buffer > 0)
-    hipLaunchKernelGGL(k_tag_regions, dim3(((nregions + 3) / 4 + group - 1) / group * group),
-                       dim3(128), 0, s, m, U, regions,
-                       nregions, mask, raw);
-  hipLaunchKernelGGL(k_tag_flags, dim3((count + 31) / 32), dim3(256), 0, s, m, list, count, mask,
-                     has_tag);
+  if (regions.count > 0 && m.tag_buffer > 0)
+    hipLaunchKernelGGL(k_tag_regions, dim3(((regions.count + 3) / 4 + group - 1) / group * group),
+                       dim3(128), 0, s, m, U, regions, mask, raw);
+  hipLaunchKernelGGL(k_tag_flags, dim3((count + 31) / 32), dim3(256), 0, s, m, list, mask, has_tag);
 }
 
-void Kernels::cell_tags(const DevMesh& m, const uint8_t* raw, const int* leaves, int count,
-                        const int* level_leaves, bool shared, uint8_t* out, hipStream_t s) {
+void Kernels::cell_tags(const DevMesh& m, const uint8_t* raw, const ListArg& leaves,
+                        const int* level_leaves, const int* level_dir, bool shared, uint8_t* out,
+                        hipStream_t s) {
+  const int count = leaves.count;
   if (count <= 0) return;
   TagLevels tl{};
+  if (leaves.dir) tl.dir = level_dir;
   const int T = cell_tile(m.dim);
   int most = 0, blocks = 0;
   for (int l = 0; l < m.nlev; ++l) {
@@ -1645,14 +1658,15 @@ void Kernels::requests(const DevMesh& m, const uint8_t* has_tag, const uint8_t* 
                      active_leaf, nslots, refine, coarsen);
 }
 
-void Kernels::prolong_new(const DevMesh& m, double* U, const int* list, int count, int* err,
+void Kernels::prolong_new(const DevMesh& m, double* U, const ListArg& list, int* err,
                           hipStream_t s) {
-  if (count <= 0) return;
+  const int nb = list.count;
+  if (nb <= 0) return;
   // a new patch of 8^3 has 64 coarse cells, one wave's worth
   switch (m.dim) {
-    case 1: k_prolong_new<1, 64><<<count, 64, 0, s>>>(m, U, U, list, count, err); break;
-    case 2: k_prolong_new<2, 64><<<count, 64, 0, s>>>(m, U, U, list, count, err); break;
-    default: k_prolong_new<3, 64><<<count, 64, 0, s>>>(m, U, U, list, count, err); break;
+    case 1: k_prolong_new<1, 64><<<nb, 64, 0, s>>>(m, U, U, list, err); break;
+    case 2: k_prolong_new<2, 64><<<nb, 64, 0, s>>>(m, U, U, list, err); break;
+    default: k_prolong_new<3, 64><<<nb, 64, 0, s>>>(m, U, U, list, err); break;
   }
 }
 
@@ -1668,10 +1682,10 @@ void Kernels::scatter_int(int* dst, const int* pairs, int npairs, hipStream_t s)
                      npairs);
 }
 
-void Kernels::check(const DevMesh& m, const double* U, const int* list, int count, int* bad,
+void Kernels::check(const DevMesh& m, const double* U, const ListArg& list, int* bad,
                     hipStream_t s) {
-  if (count <= 0) return;
-  AMR_DISPATCH_DIM(m.dim, k_check, dim3(count), dim3(256), s, m, U, list, count, bad);
+  if (list.count <= 0) return;
+  AMR_DISPATCH_DIM(m.dim, k_check, dim3(list.count), dim3(256), s, m, U, list, bad);
 }
 
 }  // namespace amr
