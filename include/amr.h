@@ -223,9 +223,11 @@ amr_status amr_check(amr_hierarchy* h, int* nonphysical_count);
 /* Pids created by the most recent regrid, in creation order (no device work). */
 amr_status amr_last_created(const amr_hierarchy* h, int* pids, int cap, int* n);
 
-/* Reads and clears the sticky ghost-fill/prolongation error flag: 1 when a
- * fill or the prolongation of a new patch found no same-level or coarser
- * source (an invalid mesh) since the flag was last read (sync). */
+/* Reads and clears the sticky error flag: 1 when a fill or the prolongation
+ * of a new patch found no same-level or coarser source (an invalid mesh), or a
+ * replay of a graph that the caller recorded met a work list longer than the
+ * recording covers (its results may then be incomplete), since the flag was
+ * last read (sync). */
 amr_status amr_fill_error(amr_hierarchy* h, int* flag);
 
 /* Host-only replay of mesh adaptation, for checking the refinement and
@@ -358,7 +360,8 @@ amr_status amr_cnn_mfma_selftest(amr_hierarchy* h, const uint16_t* a_dev, const 
  * right-hand side, dt, stage, step, tag, velocity gradient) may be recorded in
  * batched mode, and a recording may be replayed after regrids: every launch
  * reads its list from the directory.  Its grids stay those of the recording, so
- * it covers meshes whose work lists are no longer than they were then.  A
+ * it covers meshes whose work lists are no longer than they were then; on others
+ * the replay may leave entries out, and sets the flag of amr_fill_error.  A
  * recording made in per-patch mode, or before a change of tile variant, halo
  * mode or tag dilation, holds for the mesh and the settings it was made with. */
 amr_status amr_set_graph(amr_hierarchy* h, int enable);

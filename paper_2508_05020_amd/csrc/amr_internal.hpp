@@ -109,6 +109,18 @@ struct alignas(32) RefluxItem {
 };
 static_assert(sizeof(RefluxItem) == 32, "eight ints in the list buffer");
 
+// What a recording of the caller covers: dir[at] weighs `weight` in a sum that
+// goes on with the next term where `cover` is negative, and else must not exceed
+// it (see Kernels::check_covers).
+struct CoverTerm {
+  int at, weight, cover;
+};
+struct CoverTerms {
+  static constexpr int kMax = 48;
+  CoverTerm t[kMax];
+  int n;
+};
+
 // Blocks of the 3D tag launch: patches and 8^3 tiles per patch of each level.
 struct TagLevels {
   int count[kMaxLev], tiles[kMaxLev];
@@ -192,6 +204,11 @@ struct Kernels {
                        int nslots, uint8_t* refine, uint8_t* coarsen, hipStream_t s);
   static void prolong_new(const DevMesh& m, double* U, const ListArg& list, int* err,
                           hipStream_t s);
+  // sets the error flag when a list directory entry has outgrown a recording
+  static void check_covers(const int* dir, const CoverTerms& c, int* err, hipStream_t s);
+  // blocks per patch of edge n of the 3D tag launch and of the dilation
+  static int tag_tiles(int n);
+  static int cell_tiles(int dim, int n);
   static void scatter_int(int* dst, const int* pairs, int npairs, hipStream_t s);
   static void count_nonzero(const uint8_t* a, int n, int* out, hipStream_t s);
   static void check(const DevMesh& m, const double* U, const ListArg& list, int* bad,

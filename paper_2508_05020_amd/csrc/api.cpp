@@ -77,6 +77,7 @@ struct amr_hierarchy {
   bool capturing = false;
   // the caller is recording the stream into a graph of its own (note_capture)
   bool caller_records = false;
+  std::vector<amr::CoverTerm> covers;  // of the lists that the call recorded has taken
   int cap_slot = 0;
   hipStream_t cap_stream = nullptr;
   hipGraph_t step_graph[2] = {nullptr, nullptr};
@@ -612,12 +613,12 @@ void sync_tables(amr_hierarchy* h, bool full) {
   h->check_launch();
 }
 
-// Grid size (in work items) of a batched launch over a directory list: the
-// live count, or while a step graph is recorded at least 1, so that the
-// launch node exists and a later regrid can size it (blocks past the live
-// count exit at once).
+// Grid size (in work items) of a recorded batched launch: the live count, at
+// least 1, so that a list that is empty now has its launch when it no longer
+// is: in a step graph a later regrid sizes it (blocks past the live count exit
+// at once).  On one level no list fills.
 int grid_count(const amr_hierarchy* h, const amr::ListView& lv) {
-  return h->capturing ? std::max(lv.count, 1) : lv.count;
+  return h->capturing || h->forest.nlev > 1 ? std::max(lv.count, 1) : lv.count;
 }
 
 enum { kGnFill = 0, kGnStage = 1, kGnPost = 2, kGnRestrict = 3 };
@@ -664,14 +665,54 @@ void note_capture(amr_hierarchy* h) {
   hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
   if (hipStreamIsCapturing(h->stream, &st) != hipSuccess) (void)hipGetLastError();
   h->caller_records = st == hipStreamCaptureStatusActive;
+  h->covers.clear();
 }
 
 // The list as a batched launch takes it: eagerly as it is, one dependent load
 // less at the start of every block; while a graph is recorded by its directory
 // entry.
-amr::ListArg list_arg(const amr_hierarchy* h, const amr::ListView& lv) {
-  if (lv.dir && (h->capturing || h->caller_records)) return {h->d_lists, grid_count(h, lv), lv.dir};
-  return {lv.ptr, lv.count, nullptr};
+amr::ListArg list_arg(amr_hierarchy* h, const amr::ListView& lv) {
+  if (!lv.dir || !(h->capturing || h->caller_records)) return {lv.ptr, lv.count, nullptr};
+  const int n = grid_count(h, lv);
+  if (!h->capturing) h->covers.push_back({2 * dir_entry(h, lv.dir) + 1, 1, n});
+  return {h->d_lists, n, lv.dir};
+}
+
+// the same for a launch over the tiles of the patches of each level: patches[l] of
+// them (directory entry kDirLevels + l, word `word`), tiles(n) blocks each
+template <typename F>
+void cover_levels(amr_hierarchy* h, const int* patches, int word, F tiles) {
+  if (!h->caller_records || h->capturing) return;
+  int sum = 0;
+  for (int l = 0; l < h->forest.nlev; ++l) {
+    const int w = tiles(h->forest.n[l]);
+    sum += patches[l] * w;
+    h->covers.push_back({2 * (kDirLevels + l) + word, w, l + 1 < h->forest.nlev ? -1 : sum});
+  }
+}
+
+// The end of a call that the caller may be recording: a launch that sets the
+// error flag in replays on meshes whose lists the recorded grids do not cover.
+void report_longer_lists(amr_hierarchy* h) {
+  if (h->covers.empty() || h->forest.nlev == 1) return;
+  std::vector<amr::CoverTerm> all;
+  auto same = [](const amr::CoverTerm& a, const amr::CoverTerm& b) {
+    return a.at == b.at && a.weight == b.weight && a.cover == b.cover;
+  };
+  for (size_t i = 0; i < h->covers.size(); ++i) {  // a list taken twice counts once
+    const bool alone = h->covers[i].cover >= 0 && (i == 0 || h->covers[i - 1].cover >= 0);
+    if (!alone || std::none_of(all.begin(), all.end(), [&](const auto& c) { return same(c, h->covers[i]); }))
+      all.push_back(h->covers[i]);
+  }
+  for (size_t i = 0; i < all.size();) {
+    amr::CoverTerms c{};
+    size_t end = std::min(all.size(), i + amr::CoverTerms::kMax);
+    while (all[end - 1].cover < 0) --end;  // whole sums (of one term per level at most)
+    for (; i < end; ++i) c.t[c.n++] = all[i];
+    Kernels::check_covers(h->d_dir, c, h->d_flags, h->stream);
+  }
+  h->check_launch();
+  h->covers.clear();
 }
 
 // Batched mode: one launch over the list; per-patch mode: one per list entry
@@ -835,6 +876,7 @@ void do_tag(amr_hierarchy* h, int buf, uint8_t* refine, uint8_t* coarsen, uint8_
     Kernels::tag_flags3(h->dm, h->U[buf], list_arg(h, h->all), h->level_count, levels,
                         list_arg(h, h->cfregions), h->d_tag_mask, h->d_has_tag,
                         cells ? h->d_raw : nullptr, h->stream);
+    cover_levels(h, h->level_count, 0, Kernels::tag_tiles);
     h->check_launch();
   } else {
     over_list(h, h->leaves, 1, [&](const amr::ListArg& a) {
@@ -844,12 +886,15 @@ void do_tag(amr_hierarchy* h, int buf, uint8_t* refine, uint8_t* coarsen, uint8_
       Kernels::tag(h->dm, h->U[buf], a, h->d_has_tag, nullptr, fuse, h->stream);
     });
   }
-  if (cells)
+  if (cells) {
     over_list(h, h->leaves, 1, [&](const amr::ListArg& a) {
       Kernels::cell_tags(h->dm, h->d_raw, a,
                          h->exec_mode == AMR_EXEC_BATCHED ? h->level_leaves : nullptr, levels + 1,
                          shared, cells, h->stream);
     });
+    if (h->exec_mode == AMR_EXEC_BATCHED)
+      cover_levels(h, h->level_leaves, 1, [&](int n) { return Kernels::cell_tiles(h->cfg.dim, n); });
+  }
   Kernels::requests(h->dm, h->d_has_tag, h->d_active_leaf, h->forest.max_patches, refine, coarsen,
                     h->stream);
   h->check_launch();
@@ -930,6 +975,17 @@ amr_status guarded(amr_hierarchy* h, F body) {
     if (h) h->err = e.what();
     return AMR_E_ARG;
   }
+}
+
+// A call that the caller may record into a graph of its own.
+template <typename F>
+amr_status recordable(amr_hierarchy* h, F body) {
+  return guarded(h, [&]() -> amr_status {
+    note_capture(h);
+    const amr_status st = body();
+    report_longer_lists(h);
+    return st;
+  });
 }
 
 int buf_ok(int buf) { return buf >= 0 && buf < 3; }
@@ -1242,8 +1298,7 @@ amr_status amr_set_state_prim_noalloc(amr_hierarchy* h, int buf, const double* p
 
 amr_status amr_fill_ghosts(amr_hierarchy* h, int buf) {
   if (!h || !buf_ok(buf)) return AMR_E_ARG;
-  return guarded(h, [&]() -> amr_status {
-    note_capture(h);
+  return recordable(h, [&]() -> amr_status {
     do_fill(h, buf, h->all);
     return AMR_OK;
   });
@@ -1251,8 +1306,7 @@ amr_status amr_fill_ghosts(amr_hierarchy* h, int buf) {
 
 amr_status amr_rhs(amr_hierarchy* h, int buf, double* rhs_dev) {
   if (!h || !buf_ok(buf) || !rhs_dev) return AMR_E_ARG;
-  return guarded(h, [&]() -> amr_status {
-    note_capture(h);
+  return recordable(h, [&]() -> amr_status {
     stage_fill(h, buf);
     over_list(h, h->tiles, kItemInts, [&](const amr::ListArg& t) {
       Kernels::stage(h->dm, amr::kModeRHS, h->U[buf], h->d_flags, h->U[0], rhs_dev, h->fr,
@@ -1267,8 +1321,7 @@ amr_status amr_rhs(amr_hierarchy* h, int buf, double* rhs_dev) {
 
 amr_status amr_compute_dt(amr_hierarchy* h, int buf, double* dt_dev) {
   if (!h || !buf_ok(buf) || !dt_dev) return AMR_E_ARG;
-  return guarded(h, [&]() -> amr_status {
-    note_capture(h);
+  return recordable(h, [&]() -> amr_status {
     do_dt(h, buf, dt_dev);
     return AMR_OK;
   });
@@ -1277,8 +1330,7 @@ amr_status amr_compute_dt(amr_hierarchy* h, int buf, double* dt_dev) {
 amr_status amr_rk_stage(amr_hierarchy* h, int stage, const double* dt_dev) {
   if (!h || stage < 1 || stage > 3 || !dt_dev) return AMR_E_ARG;
   h->lam_valid = false;
-  return guarded(h, [&]() -> amr_status {
-    note_capture(h);
+  return recordable(h, [&]() -> amr_status {
     do_stage(h, stage, dt_dev);
     return AMR_OK;
   });
@@ -1286,8 +1338,7 @@ amr_status amr_rk_stage(amr_hierarchy* h, int stage, const double* dt_dev) {
 
 amr_status amr_step(amr_hierarchy* h, double* dt_dev) {
   if (!h) return AMR_E_ARG;
-  return guarded(h, [&]() -> amr_status {
-    note_capture(h);
+  return recordable(h, [&]() -> amr_status {
     double* dt = dt_dev ? dt_dev : h->d_dt;
     const int cur = h->lam_cur;
     if (!h->lam_valid) do_rate(h, 0, cur);
@@ -1374,8 +1425,7 @@ amr_status amr_set_graph(amr_hierarchy* h, int enable) {
 amr_status amr_tag(amr_hierarchy* h, int buf, uint8_t* refine_req_dev, uint8_t* coarsen_req_dev,
                    uint8_t* cell_tags_dev) {
   if (!h || !buf_ok(buf)) return AMR_E_ARG;
-  return guarded(h, [&]() -> amr_status {
-    note_capture(h);
+  return recordable(h, [&]() -> amr_status {
     do_tag(h, buf, refine_req_dev, coarsen_req_dev, cell_tags_dev);
     return AMR_OK;
   });
@@ -1608,8 +1658,7 @@ amr_status amr_forest_replay(const amr_config* cfg, const int32_t* req, int nreq
 
 amr_status amr_velocity_gradient(amr_hierarchy* h, int buf, double* out_dev) {
   if (!h || !buf_ok(buf) || !out_dev) return AMR_E_ARG;
-  return guarded(h, [&]() -> amr_status {
-    note_capture(h);
+  return recordable(h, [&]() -> amr_status {
     do_fill(h, buf, h->leaves);
     const long long plane = h->state_doubles / h->nvar;
     over_list(h, h->leaves, 1, [&](const amr::ListArg& a) {

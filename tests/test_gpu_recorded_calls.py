@@ -181,3 +181,84 @@ def test_replays_follow_regrids(name, fused):
         assert hg.fill_error() == 0 and he.fill_error() == 0
         hg.close()
         he.close()
+
+
+CALLS = {"fill": lambda h, out: h.fill_ghosts(0), "gradient": lambda h, out: h.velocity_gradient(0, out["gradient"]),
+         "rhs": lambda h, out: h.rhs(0, out["rhs"]), "dt": lambda h, out: h.compute_dt(0, out["dt"]),
+         "tags": lambda h, out: out.update(tags=h.tag(0, cell_tags=True)),
+         "flags": lambda h, out: out.update(tags=h.tag(0)), "stage": lambda h, out: h.rk_stage(1, out["step"]),
+         "step": lambda h, out: h.step(out["step"])}
+
+
+def results(h, out, call, table):
+    """What a call leaves on a mesh, in table order."""
+    d, leaves = h.cfg.dim, [t for t in table if t["nchildren"] == 0]
+    if call == "fill":
+        return list(boxes(h, h.state_tensor(0), table, h.nvar).values())
+    if call in ("stage", "step"):
+        return [H.interior(b, d) for b in boxes(h, h.state_tensor(1 if call == "stage" else 0), table, h.nvar).values()]
+    if call == "dt":
+        return [out["dt"].cpu().numpy()]
+    if call in ("tags", "flags"):
+        cells = boxes(h, out["tags"][2], leaves, 1) if call == "tags" else {}
+        return [t.cpu().numpy() for t in out["tags"][:2]] + [H.interior(b, d) for b in cells.values()]
+    if call == "rhs":
+        return [H.interior(b, d) for b in boxes(h, out["rhs"], leaves, h.nvar).values()]
+    plane = h.state_tensor(0).numel() // h.nvar
+    return [H.interior(b, d) for v in range(d * d + 1)
+            for b in boxes(h, out["gradient"].flatten()[v * plane:(v + 1) * plane], leaves, 1).values()]
+
+
+@pytest.mark.parametrize("call", CALLS)
+@pytest.mark.parametrize("name", ["1d", "2d", "3d", "3d-uneven"])
+def test_longer_lists_are_reported(name, call):
+    """Recorded on level 0 alone, where the lists of the coarse/fine faces are
+    empty: on finer meshes a replay is the eager call, or sets the error flag."""
+    import torch
+    import paper_2508_05020_amd.amr as A
+    o, _ = H.oracle_for(name)
+    cfg = o.cfg
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        hg, he = A.Hierarchy(cfg), A.Hierarchy(cfg)
+        outs = [buffers(h) for h in (hg, he)]
+        base = hg.patch_table()
+        for h, out in zip((hg, he), outs):
+            upload(o, h, base, 0)
+            out["step"].fill_(1e-5)
+            CALLS[call](h, out)
+            upload(o, h, base, 0)
+        side.synchronize()
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=side):
+            CALLS[call](hg, outs[0])
+        flags = []
+        for mesh in ("base", "one", "full", "base again"):
+            for h in (hg, he):
+                coarsen(h, 0)
+                for level in range(cfg.max_levels - 1):
+                    at = {(t["level"], t["coord"]): t["pid"] for t in h.patch_table()}
+                    want = [k for k in o.forest.keys() if k[0] == level and not o.forest.is_leaf(k)]
+                    f = np.zeros(cfg.max_patches, np.uint8)
+                    if mesh == "full":
+                        f[[at[k] for k in want]] = 1
+                    elif mesh == "one" and level == 0:
+                        f[at[want[0]]] = 1
+                    h.regrid(f, np.zeros_like(f))
+            now = hg.patch_table()
+            assert now == he.patch_table()
+            for h, out in zip((hg, he), outs):
+                upload(o, h, now, 5)
+                out["step"].fill_(1e-5)
+                assert h.fill_error() == 0
+            g.replay()
+            CALLS[call](he, outs[1])
+            side.synchronize()
+            flags.append(hg.fill_error())
+            assert he.fill_error() == 0
+            same = all(np.array_equal(a, b, equal_nan=a.dtype.kind == "f")
+                       for a, b in zip(results(hg, outs[0], call, now), results(he, outs[1], call, now)))
+            assert same or flags[-1], mesh
+        assert flags[0] == flags[3] == 0 and flags[2] == 1, flags
+        hg.close()
+        he.close()
