@@ -127,8 +127,8 @@ struct amr_hierarchy {
   // What a regrid uploads, in one copy: the directory, d_active_leaf, d_cfmask
   // and the lists at fixed offsets, the changed table entries after the lists.
   // d_lists and those are places in one device buffer, laid out as the pinned
-  // host staging (reused; every regrid first drains the stream, so earlier
-  // copies from it have completed).
+  // host staging (reused; every call that rebuilds the lists first drains the
+  // stream, so earlier copies from it have completed).
   char* h_stage = nullptr;
   size_t lists_off = 0;  // of the lists, from the directory's start
   uint8_t* h_req = nullptr;  // pinned: refine and coarsen requests read back by amr_adapt
@@ -364,7 +364,8 @@ constexpr int kItemInts = sizeof(amr::StageItem) / sizeof(int);
 constexpr int kRefluxInts = sizeof(amr::RefluxItem) / sizeof(int);
 
 // Rebuild work lists on the host and upload them (plus the changed table
-// entries) to the device.
+// entries) to the device.  The stream must be drained: the last upload reads
+// the same pinned staging.
 // byte offset of the pinned flag slot in h_req (after 2 max_patches bytes of
 // requests, 64-byte aligned)
 size_t req_flag_offset(int mp) { return ((2 * (size_t)mp + 63) / 64) * 64; }
@@ -1525,6 +1526,7 @@ amr_status amr_autotune(amr_hierarchy* h, int reps, int* best, float* best_ms) {
   return guarded(h, [&]() -> amr_status {
     // time the stage kernel in RHS mode on U^n, writing into stage buffer B
     // (scratch outside a step) and the flux registers
+    h->sync();  // the last regrid's upload reads the staging that sync_tables fills
     double* scratch = h->U[2];
     hipEvent_t e0, e1;
     HIP_OK(hipEventCreate(&e0));
