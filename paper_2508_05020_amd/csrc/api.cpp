@@ -738,19 +738,19 @@ void over_list_noted(amr_hierarchy* h, const amr::ListView& lv, int stride_ints,
   if (h->exec_mode == AMR_EXEC_BATCHED) note_node(h, kind, dir_entry(h, lv.dir));
 }
 
-// Ghosts of the patches of `lv`: same-level copies, and the prolonged regions
-// of the leaves (patches with children have every same-level neighbour).
-void do_fill(amr_hierarchy* h, int buf, const amr::ListView& lv) {
+// Ghosts of the patches of `lv`: same-level copies, and the prolonged ones of
+// `regions` (of the leaves: patches with children have every same-level
+// neighbour).
+void do_fill(amr_hierarchy* h, int buf, const amr::ListView& lv, const amr::ListView& regions) {
   if (h->exec_mode == AMR_EXEC_BATCHED) {
-    Kernels::fill(h->dm, h->U[buf], list_arg(h, lv), list_arg(h, h->cfregions), h->d_flags,
-                  h->stream);
+    Kernels::fill(h->dm, h->U[buf], list_arg(h, lv), list_arg(h, regions), h->d_flags, h->stream);
     h->check_launch();
     return;
   }
   over_list(h, lv, 1, [&](const amr::ListArg& a) {
     Kernels::fill(h->dm, h->U[buf], a, {}, h->d_flags, h->stream);
   });
-  over_list(h, h->cfregions, 2, [&](const amr::ListArg& a) {
+  over_list(h, regions, 2, [&](const amr::ListArg& a) {
     Kernels::fill_cf(h->dm, h->U[buf], a, h->d_flags, h->stream);
   });
 }
@@ -761,7 +761,7 @@ void do_fill(amr_hierarchy* h, int buf, const amr::ListView& lv) {
 // 1D it forms and writes itself
 void stage_fill(amr_hierarchy* h, int buf) {
   if (!h->fuse_halo) {
-    do_fill(h, buf, h->leaves);
+    do_fill(h, buf, h->leaves, h->cfregions);
   } else if (h->cfg.dim > 1) {
     over_list_noted(h, h->cffaces, 2, kGnFill, [&](const amr::ListArg& a) {
       Kernels::fill_cf(h->dm, h->U[buf], a, h->d_flags, h->stream);
@@ -867,8 +867,8 @@ void do_tag(amr_hierarchy* h, int buf, uint8_t* refine, uint8_t* coarsen, uint8_
       Kernels::fill_cf(h->dm, h->U[buf], a, h->d_flags, h->stream);
     });
   } else {
-    do_fill(h, buf, h->leaves);
-    do_fill(h, buf, h->cands);
+    do_fill(h, buf, h->leaves, h->cfregions);
+    do_fill(h, buf, h->cands, {});
   }
   const int* levels = h->d_dir + 2 * kDirLevels;
   const bool shared = h->cfg.dim == 3 && fuse && h->exec_mode == AMR_EXEC_BATCHED;
@@ -1300,7 +1300,7 @@ amr_status amr_set_state_prim_noalloc(amr_hierarchy* h, int buf, const double* p
 amr_status amr_fill_ghosts(amr_hierarchy* h, int buf) {
   if (!h || !buf_ok(buf)) return AMR_E_ARG;
   return recordable(h, [&]() -> amr_status {
-    do_fill(h, buf, h->all);
+    do_fill(h, buf, h->all, h->cfregions);
     return AMR_OK;
   });
 }
@@ -1661,7 +1661,7 @@ amr_status amr_forest_replay(const amr_config* cfg, const int32_t* req, int nreq
 amr_status amr_velocity_gradient(amr_hierarchy* h, int buf, double* out_dev) {
   if (!h || !buf_ok(buf) || !out_dev) return AMR_E_ARG;
   return recordable(h, [&]() -> amr_status {
-    do_fill(h, buf, h->leaves);
+    do_fill(h, buf, h->leaves, h->cfregions);
     const long long plane = h->state_doubles / h->nvar;
     over_list(h, h->leaves, 1, [&](const amr::ListArg& a) {
       amr::Diagnostics::velocity_gradient(h->dm, h->U[buf], a, out_dev, plane, h->stream);
@@ -1877,7 +1877,7 @@ amr_status amr_cnn_gather(amr_cnn* c, int buf, const int* pids_host, int npatch,
       items[i] = c->dim == 2 ? p : p * amr::CNN3_MAX_TILES;
     }
     note_capture(h);
-    do_fill(h, buf, h->leaves);
+    do_fill(h, buf, h->leaves, h->cfregions);
     if (npatch > 0)
       HIP_OK(hipMemcpyAsync(c->d_pids, items.data(), npatch * sizeof(int), hipMemcpyHostToDevice,
                             h->stream));
@@ -1940,7 +1940,7 @@ amr_status amr_cnn_predict(amr_cnn* c, int buf, float tau, uint8_t* refine_req_d
     }
     if ((long long)items.size() > c->items_cap) throw ArgError("predictor item list overflow");
     note_capture(h);
-    do_fill(h, buf, h->leaves);
+    do_fill(h, buf, h->leaves, h->cfregions);
     HIP_OK(hipMemsetAsync(c->d_pred, 0, f.max_patches, s));
     if (!items.empty())
       HIP_OK(hipMemcpyAsync(c->d_pids, items.data(), items.size() * sizeof(int),

@@ -85,3 +85,35 @@ print(json.dumps(fake.fake_rewritten()))
 A._lib.amr_destroy_hierarchy(h.h)
 """)
     assert got == 0
+
+
+@pytest.mark.parametrize("dim,base,patches", [(1, 64, [16, 16, 16]), (2, 64, [16, 16, 16]), (3, 32, [8, 8, 8])])
+def test_filled_tags_prolong_each_region_once(fake, dim, base, patches):
+    """Tags with every halo filled beforehand: the fill of the coarsening
+    candidates, which have no prolonged ghosts, repeated that of the leaves."""
+    got = run(fake, f"""
+cfg = W.AMRConfig(name="tag", dim={dim}, base_cells={base}, patch_cells={patches}, periodic=[True] * {dim},
+                  max_patches=2048)
+out = []
+for mode in (A.EXEC_PER_PATCH, A.EXEC_BATCHED):
+    h = Host(cfg, mode)
+    h.call("set_fused_halo", 0)
+    h.regrid(refine=[h.table()[0].pid])
+    h.regrid(refine=[next(t.pid for t in h.table() if t.level == 1)])
+    t = h.table()
+    inner = set(r.pid for r in t if r.nchildren)
+    leaves = len(t) - len(inner)
+    cands = len(inner - set(r.parent for r in t if r.pid in inner))
+    fill = h.call("fill_ghosts", 0)
+    flags = (C.c_uint8 * cfg.max_patches)()
+    out.append([len(t), leaves, cands, fill, h.call("tag", 0, flags, flags, None)])
+    A._lib.amr_destroy_hierarchy(h.h)
+print(json.dumps(out))
+""")
+    (active, leaves, cands, fill, tag), batched = got
+    regions = fill - active
+    assert regions > 0 and cands > 0
+    # fills of the leaves, their regions and the candidates, a test of each, the requests
+    assert tag == 2 * leaves + regions + 2 * cands + 1
+    if dim == 3:        # copies and regions of the leaves, copies of the candidates, two tests, the requests
+        assert batched[4] == 6
