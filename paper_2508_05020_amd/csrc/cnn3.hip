@@ -436,7 +436,8 @@ __global__ __launch_bounds__(TRAIN_THREADS) void k_cnn3_train(
   // step's 4 K groups are 4 rows y of one plane (the last two rows of two
   // planes together), the same x in each, so that a step's reads differ from
   // the lane's first by a wave-uniform offset; x runs to 12: dz2's border is
-  // zero there, and a1 reads at most two voxels past its end.
+  // zero there, a1 reads at most two voxels past its end, and what it reads for
+  // those x is cleared (zero times an infinite activation would be NaN).
   if (wave < WPAIRS) {
     const int tz = ltap / 9, ty = (ltap / 3) % 3, tx = ltap % 3;
     const unsigned short* za = dz2 + ((2 * W0 + 2 + kq) * W0 + 2 + gx) * CH + c4;
@@ -447,18 +448,23 @@ __global__ __launch_bounds__(TRAIN_THREADS) void k_cnn3_train(
     const unsigned short* ab = a1 + (((tz + kz) * W1 + ty + ky) * W1 + tx + gx) * CH + c4;
     f4 acc[3] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
     static_assert(W2 == 10, "rows 0 .. 7 in blocks of four, 8 and 9 in pairs of planes");
+    auto act = [](const unsigned short* p, int xg) {
+      s4 v = load4_tr(p);
+      if (xg == 2) v.z = v.w = 0;  // x = 10 and 11
+      return v;
+    };
     for (int z = 0; z < W2; ++z) {
 #pragma unroll
       for (int xg = 0; xg < 3; ++xg)
         acc[xg] = mfma32(join(load4_tr(za + (z * W0 * W0 + 4 * xg) * CH),
                               load4_tr(za + ((z * W0 + 4) * W0 + 4 * xg) * CH)),
-                         join(load4_tr(aa + (z * W1 * W1 + 4 * xg) * CH),
-                              load4_tr(aa + ((z * W1 + 4) * W1 + 4 * xg) * CH)), acc[xg]);
+                         join(act(aa + (z * W1 * W1 + 4 * xg) * CH, xg),
+                              act(aa + ((z * W1 + 4) * W1 + 4 * xg) * CH, xg)), acc[xg]);
       if (z & 1) continue;
 #pragma unroll
       for (int xg = 0; xg < 3; ++xg)
         acc[xg] = mfma(load4_tr(zb + (z * W0 * W0 + 4 * xg) * CH),
-                       load4_tr(ab + (z * W1 * W1 + 4 * xg) * CH), acc[xg]);
+                       act(ab + (z * W1 * W1 + 4 * xg) * CH, xg), acc[xg]);
     }
     if (wtap < 27) {
 #pragma unroll
