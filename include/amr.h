@@ -358,12 +358,14 @@ amr_status amr_cnn_mfma_selftest(amr_hierarchy* h, const uint16_t* a_dev, const 
  *
  * Graphs that the caller records: the async calls on the hierarchy (fill,
  * right-hand side, dt, stage, step, tag, velocity gradient) may be recorded in
- * batched mode, and a recording may be replayed after regrids: every launch
- * reads its list from the directory.  Its grids stay those of the recording, so
- * it covers meshes whose work lists are no longer than they were then; on others
- * the replay may leave entries out, and sets the flag of amr_fill_error.  A
- * recording made in per-patch mode, or before a change of tile variant, halo
- * mode or tag dilation, holds for the mesh and the settings it was made with. */
+ * batched mode (the step as launches, whether replay is enabled or not), and a
+ * recording may be replayed after regrids: every launch reads its list from the
+ * directory.  Its grids stay those of the recording, so it covers meshes whose
+ * work lists are no longer than they were then; on others the replay may leave
+ * entries out, and sets the flag of amr_fill_error.  It keeps the halo mode and
+ * the tag dilation it was made with.  A recording made in per-patch mode must not
+ * be replayed after a regrid, and none after a change of the tile variant
+ * (amr_set_tile_variant, amr_autotune). */
 amr_status amr_set_graph(amr_hierarchy* h, int enable);
 /* Number of step graphs recorded since creation (test and profiling hook). */
 amr_status amr_graph_records(const amr_hierarchy* h, int* recorded);

@@ -1343,7 +1343,9 @@ amr_status amr_step(amr_hierarchy* h, double* dt_dev) {
     double* dt = dt_dev ? dt_dev : h->d_dt;
     const int cur = h->lam_cur;
     if (!h->lam_valid) do_rate(h, 0, cur);
-    const bool graph = h->use_graph && h->exec_mode == AMR_EXEC_BATCHED && !h->profiling;
+    // (a graph launch is not recorded into the caller's: its launches are)
+    const bool graph = h->use_graph && h->exec_mode == AMR_EXEC_BATCHED && !h->profiling &&
+                       !h->caller_records;
     if (!graph) {
       do_step(h, dt, cur);
     } else {

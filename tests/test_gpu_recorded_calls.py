@@ -262,3 +262,37 @@ def test_longer_lists_are_reported(name, call):
         assert flags[0] == flags[3] == 0 and flags[2] == 1, flags
         hg.close()
         he.close()
+
+
+@pytest.mark.parametrize("warm", [0, 4])
+def test_step_in_graph_mode_is_recorded(warm):
+    """With the library's own replay enabled a recorded step holds its launches
+    (a launch of the library's graph would leave the recording empty)."""
+    import torch
+    import paper_2508_05020_amd.amr as A
+    o, _ = H.oracle_for("2d")
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        hg, he = A.Hierarchy(o.cfg), A.Hierarchy(o.cfg)
+        for h in (hg, he):
+            H.mirror(o, h)
+            h.set_graph(True)
+            for _ in range(warm):
+                h.step()
+            upload(o, h, h.patch_table(), 1)
+        dts = [torch.zeros(1, dtype=torch.float64, device="cuda") for _ in range(2)]
+        side.synchronize()
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=side):
+            hg.step(dts[0])
+        table = hg.patch_table()
+        for _ in range(3):
+            g.replay()
+            he.step(dts[1])
+            side.synchronize()
+            assert dts[0].item() == dts[1].item() > 0
+            a, b = (boxes(h, h.state_tensor(0), table, h.nvar) for h in (hg, he))
+            for key in a:
+                assert np.array_equal(H.interior(a[key], 2), H.interior(b[key], 2)), key
+        hg.close()
+        he.close()
