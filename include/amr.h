@@ -379,7 +379,8 @@ amr_status amr_graph_records(const amr_hierarchy* h, int* recorded);
  * Every variant performs the same operations per cell: results are
  * identical.  amr_set_tile_variant (sync) selects one; amr_autotune (sync)
  * times `reps` launches of each admissible variant on the current mesh
- * (writing the stage buffer B and the flux registers) and keeps the fastest. */
+ * (writing the stage buffer B and the flux registers, and in 1D the prolonged
+ * face ghosts of U^n, as a step does) and keeps the fastest. */
 amr_status amr_set_tile_variant(amr_hierarchy* h, int variant);
 amr_status amr_get_tile_variant(const amr_hierarchy* h, int* variant, int* tx, int* ty, int* tz,
                                 int* threads);

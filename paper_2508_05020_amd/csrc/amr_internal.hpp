@@ -15,7 +15,6 @@ namespace amr {
 constexpr int kNG = AMR_GHOST;   // ghost layers (flux-form Eq. (9) + WENO5 need 4)
 constexpr int kMaxLev = AMR_MAX_LEVELS;
 
-// Per-level constants, mirrored on the device by value.
 // XCDs of the MI355X (gfx950): 8 dies of 32 compute units, one L2 each.
 constexpr int kXcds = 8;
 // A CFL-rate slot: the maximum is kept as kXcds parts (the blocks of each XCD
@@ -24,6 +23,7 @@ constexpr int kXcds = 8;
 constexpr int kRateStride = 16;                  // 64-bit words between parts
 constexpr int kRateWords = kXcds * kRateStride;  // words of a slot
 
+// Per-level constants, mirrored on the device by value.
 struct LevelC {
   int n;             // patch edge (cells)
   int full;          // n + 2 ng

@@ -70,7 +70,7 @@ struct amr_hierarchy {
   struct GridNode {
     hipGraphNode_t node;
     int kind;        // kGn* below
-    int e[3], ne;    // directory entries whose counts add up to the items
+    int e[2], ne;    // directory entries whose counts add up to the items
     int grid;        // blocks in the instantiated graph
   };
   bool use_graph = false;
@@ -363,13 +363,13 @@ void build_devmesh(amr_hierarchy* h) {
 constexpr int kItemInts = sizeof(amr::StageItem) / sizeof(int);
 constexpr int kRefluxInts = sizeof(amr::RefluxItem) / sizeof(int);
 
-// Rebuild work lists on the host and upload them (plus the changed table
-// entries) to the device.  The stream must be drained: the last upload reads
-// the same pinned staging.
 // byte offset of the pinned flag slot in h_req (after 2 max_patches bytes of
 // requests, 64-byte aligned)
 size_t req_flag_offset(int mp) { return ((2 * (size_t)mp + 63) / 64) * 64; }
 
+// Rebuild work lists on the host and upload them (plus the changed table
+// entries) to the device.  The stream must be drained: the last upload reads
+// the same pinned staging.
 void sync_tables(amr_hierarchy* h, bool full) {
   ++h->mesh_version;  // recorded step graphs resize their launches before the next replay
   amr::Forest& f = h->forest;
@@ -639,7 +639,7 @@ int node_grid(const amr_hierarchy* h, int kind, int items) {
 
 // While a step graph is recorded: the kernel node the last launch added, and
 // the directory entries whose live counts size it.
-void note_node(amr_hierarchy* h, int kind, int e0, int e1 = -1, int e2 = -1) {
+void note_node(amr_hierarchy* h, int kind, int e0, int e1 = -1) {
   if (!h->capturing) return;
   hipStreamCaptureStatus st;
   const hipGraphNode_t* deps = nullptr;
@@ -652,8 +652,7 @@ void note_node(amr_hierarchy* h, int kind, int e0, int e1 = -1, int e2 = -1) {
   g.kind = kind;
   g.e[0] = e0;
   g.e[1] = e1;
-  g.e[2] = e2;
-  g.ne = e2 >= 0 ? 3 : (e1 >= 0 ? 2 : 1);
+  g.ne = e1 >= 0 ? 2 : 1;
   int items = 0;
   for (int k = 0; k < g.ne; ++k) items += h->h_dir[2 * g.e[k] + 1];
   g.grid = node_grid(h, kind, items);
@@ -1541,13 +1540,14 @@ amr_status amr_autotune(amr_hierarchy* h, int reps, int* best, float* best_ms) {
       h->dm.tile = v;
       h->last_created.clear();
       sync_tables(h, false);
-      // the launch the batched step makes (list and count from the directory)
-      Kernels::stage(h->dm, amr::kModeRHS, h->U[0], h->d_flags, h->U[0], scratch, h->fr, h->d_items,
-                     h->tiles.count, h->tiles.dir, h->d_dt, h->fuse_halo, nullptr, h->stream);
-      HIP_OK(hipEventRecord(e0, h->stream));
-      for (int r = 0; r < reps; ++r)
+      // the launch that an eager batched step makes
+      auto launch = [&]() {
         Kernels::stage(h->dm, amr::kModeRHS, h->U[0], h->d_flags, h->U[0], scratch, h->fr, h->d_items,
-                       h->tiles.count, h->tiles.dir, h->d_dt, h->fuse_halo, nullptr, h->stream);
+                       h->tiles.count, nullptr, h->d_dt, h->fuse_halo, nullptr, h->stream);
+      };
+      launch();
+      HIP_OK(hipEventRecord(e0, h->stream));
+      for (int r = 0; r < reps; ++r) launch();
       HIP_OK(hipEventRecord(e1, h->stream));
       HIP_OK(hipEventSynchronize(e1));
       float ms = 0.f;

@@ -110,8 +110,8 @@ __device__ __forceinline__ double pressure_exact(const double* u, double gm1) {
 }
 
 // Quotients by one divisor d from its reciprocal: r refined by two Newton
-// steps, q = a r and one correction fma(fma(-d, q, a), r, q), which is the
-// correctly rounded quotient, as the division is, while no scaling is needed
+// steps, q = a r and one correction by the residual, fma(fma(-d, q, a), r, q)
+// (Markstein 1990), which is the correctly rounded quotient, as the division is, while no scaling is needed
 // (d, and a unless it is zero, in [2^-300, 2^300]: takes(a)).
 struct Divisor {
   double d, r;

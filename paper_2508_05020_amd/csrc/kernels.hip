@@ -318,7 +318,7 @@ __global__ __launch_bounds__(fill_threads(D)) void k_fill(DevMesh m, const doubl
 }
 
 // ---------------------------------------------------------------------------
-// coarse/fine flux correction: list of (pid, face mask); faces are processed
+// coarse/fine flux correction: list of RefluxItem; a cell's faces are corrected
 // in the order x-, x+, y-, y+, z-, z+ so that corner cells see a fixed order
 // ---------------------------------------------------------------------------
 // The fine side of a coarse cell's c/f face: the same-level position of the
@@ -504,10 +504,9 @@ __device__ __forceinline__ long long restrict_target(const DevMesh& m, int cpid,
   return patch_base(m, ppid, lf - 1) + box_off<D>(C.full, q[0], q[1], q[2]);
 }
 
-// Restriction of one child patch into the covered cells of its parent:
-// pairwise sums in x, then y, then z order, times 2^-D.
-// One covered parent cell ((a, b, c) among those the child covers): the
-// pairwise sum of its 2^D child cells times 2^-D.
+// Restriction into one covered parent cell ((a, b, c) among those the child
+// covers): the sum of its 2^D child cells in pairs, x, then y, then z, times
+// 2^-D.
 template <int D>
 __device__ __forceinline__ void restrict_cell(const DevMesh& m, double* __restrict__ U, int cpid,
                                               long long target, int lf, int a, int b, int c) {
@@ -642,8 +641,9 @@ __global__ __launch_bounds__(NT) void k_post(DevMesh m, int mode,
 
 // ---------------------------------------------------------------------------
 // CFL rate: max over leaf cells of sum_j (|u_j| + c) / h, as IEEE bits of a
-// non-negative double (order-preserving), reduced with a wave shuffle, LDS and
-// one 64-bit atomic max per block
+// non-negative double (order-preserving): the cells' speeds reduced by lane
+// shifts and LDS, one division by h and one 64-bit atomic max per block, into
+// the part of the rate slot that its XCD owns (block_max_rate)
 // ---------------------------------------------------------------------------
 template <int D>
 __global__ __launch_bounds__(256) void k_max_rate(DevMesh m, const double* __restrict__ U,
@@ -653,36 +653,33 @@ __global__ __launch_bounds__(256) void k_max_rate(DevMesh m, const double* __res
   live_list(list);
   if ((int)blockIdx.x >= list.count) return;
   unsigned long long best = 0ull;
-  const int l = m.level[list.ptr[blockIdx.x]];
-  {
-    const int pid = list.ptr[blockIdx.x];
-    const LevelC& L = m.lv[l];
-    const int n = L.n;
-    const double* P = U + patch_base(m, pid, l);
-    const int vs = var_stride<D>(L.full);
-    // pairs along x (even patch edges), one 16-byte load per variable
-    int total = n / 2;
-    if constexpr (D >= 2) total *= n;
-    if constexpr (D >= 3) total *= n;
-    for (int idx = threadIdx.x; idx < total; idx += blockDim.x) {
-      const int row = D >= 2 ? div_half(idx, L) : 0;
-      const int z = D >= 3 ? div_by(row, n, L.n_mul) : 0;
-      const int x = 2 * (idx - row * (n / 2)), y = row - z * n;
-      const int off = box_off<D>(L.full, x + NG, y + NG, z + NG);
-      double2 u[NV];
+  const int pid = list.ptr[blockIdx.x], l = m.level[pid];
+  const LevelC& L = m.lv[l];
+  const int n = L.n;
+  const double* P = U + patch_base(m, pid, l);
+  const int vs = var_stride<D>(L.full);
+  // pairs along x (even patch edges), one 16-byte load per variable
+  int total = n / 2;
+  if constexpr (D >= 2) total *= n;
+  if constexpr (D >= 3) total *= n;
+  for (int idx = threadIdx.x; idx < total; idx += blockDim.x) {
+    const int row = D >= 2 ? div_half(idx, L) : 0;
+    const int z = D >= 3 ? div_by(row, n, L.n_mul) : 0;
+    const int x = 2 * (idx - row * (n / 2)), y = row - z * n;
+    const int off = box_off<D>(L.full, x + NG, y + NG, z + NG);
+    double2 u[NV];
 #pragma unroll
-      for (int v = 0; v < NV; ++v) u[v] = *reinterpret_cast<const double2*>(P + v * vs + off);
+    for (int v = 0; v < NV; ++v) u[v] = *reinterpret_cast<const double2*>(P + v * vs + off);
 #pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        double c[NV];
+    for (int h = 0; h < 2; ++h) {
+      double c[NV];
 #pragma unroll
-        for (int v = 0; v < NV; ++v) c[v] = h == 0 ? u[v].x : u[v].y;
-        const unsigned long long bits = cell_speed_bits<D>(c, m);
-        best = bits > best ? bits : best;
-      }
+      for (int v = 0; v < NV; ++v) c[v] = h == 0 ? u[v].x : u[v].y;
+      const unsigned long long bits = cell_speed_bits<D>(c, m);
+      best = bits > best ? bits : best;
     }
   }
-  block_max_rate(best, m.lv[l].h, lam);
+  block_max_rate(best, L.h, lam);
 }
 
 __global__ void k_zero_rate(unsigned long long* slot) { clear_rate(slot); }

@@ -768,7 +768,7 @@ struct Line {
 // thread each, and 704 edges.  With one phase of 704 edges, each forming the
 // indicators of both its nodes, a stage launch took 2225 us against 1959 us
 // (3D, 20.4 M leaf cells, mostly 8^3 patches; 44.2 against 37.6 wave
-// instructions per cell, the FP64 VALU busy 72 % of the clocks), 180 against
+// instructions per cell, 37.0 with the later steps), 180 against
 // 163 us (2D, 2.75 M cells in 32^2 patches) and 24.2 against 21.4 us (2D, 0.28 M
 // cells).
 template <int D, int TX, int TY, int TZ, int NT, int J, bool UNION, bool CHAR>
@@ -1027,15 +1027,12 @@ __device__ __forceinline__ void stage_both(const DevMesh& m, double* __restrict_
   cells_at<D, TX, TY, 1, NT, 1>(sFy, frp, n, o, acc, inv_h, wmask);
 }
 
-// One (pid, tile) work item: the whole RHS of the tile and its stage
-// combination; `best` collects the signal speed bits of the item's cells.
 // Restriction of a tile into its parent patch, from the new values of its
 // cells (sR: variable v of tile cell i at sR[v NCELL + i]): each parent cell
 // is the mean of its 2^D children, summed as the post-stage restriction sums
-// them (x pairs first, then y, then z).
-// SERIAL: one variable
-// at a time (unrolled, the reads of all variables are issued at once and can
-// take more registers than the primitive schemes' kernels have).
+// them (x pairs first, then y, then z).  SERIAL: one variable at a time
+// (unrolled, the reads of all variables are issued at once and can take more
+// registers than the primitive schemes' kernels have).
 template <int D, int TX, int TY, int TZ, int NT, bool SERIAL>
 __device__ __forceinline__ void restrict_tile(const DevMesh& m, double* __restrict__ out,
                                               const StageItem& it, const double* sR) {
@@ -1073,6 +1070,8 @@ __device__ __forceinline__ void restrict_tile(const DevMesh& m, double* __restri
   }
 }
 
+// One (pid, tile) work item: the whole RHS of the tile and its stage
+// combination; `best` collects the signal speed bits of the item's cells.
 template <int D, int TX, int TY, int TZ, int NT, bool FUSE, bool BOTH, bool CHAR>
 __device__ __forceinline__ void stage_item(const DevMesh& m, int mode,
                                            const double* __restrict__ Uin, double* Ug, int* err,
