@@ -23,6 +23,10 @@ COMMON = ["-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}",
           # no packed FP32 instructions (see the design notes)
           "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
           "-Wall", "-Wno-unused-function", "-Wno-unused-variable"]
+# host sources: functions and loops on cache lines, so that a regrid's scans over
+# all patch slots do not depend on where the linker puts them (the same code took
+# 39 to 48 us of host time for two small regrids from one build to the next)
+HOST = ["-falign-functions=64", "-falign-loops=64"]
 
 
 def _hipcc() -> str:
@@ -42,7 +46,7 @@ def _compile(src: str) -> str:
     obj = os.path.join(OBJ, os.path.basename(src) + ".o")
     cmd = [_hipcc(), *COMMON, "-c", src, "-o", obj]
     if src.endswith(".cpp"):
-        cmd[1:1] = ["-x", "hip"]
+        cmd[1:1] = ["-x", "hip", *HOST]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError(f"compile failed: {' '.join(cmd)}\n{r.stdout}\n{r.stderr}")
