@@ -911,9 +911,12 @@ __global__ __launch_bounds__(256) void k_cell_tags(DevMesh m, const uint8_t* __r
     }
     __syncthreads();
   }
+  // places up to the tile's last row or plane (small patches and the last tiles
+  // fill a part of the LDS box)
+  const int live = D == 1 ? e[0] + 2 * b : (D == 2 ? B * (e[1] + 2 * b) : B * B * (e[2] + 2 * b));
   const uint8_t* level = raw + L.tag_off;
   const uint8_t* own = level + (long long)(pid - L.pid_base) * vs;
-  for (int idx = threadIdx.x; idx < NODES; idx += 256) {
+  for (int idx = threadIdx.x; idx < live; idx += 256) {
     const int t[3] = {idx % B, D >= 2 ? idx / B % B : 0, D >= 3 ? idx / (B * B) : 0};
     int c[3] = {0, 0, 0};
     bool in = true;
@@ -952,7 +955,7 @@ __global__ __launch_bounds__(256) void k_cell_tags(DevMesh m, const uint8_t* __r
   // along direction j (T_j cells from T_j + 2 b places; the others keep theirs)
   auto dilate = [&](int j, const uint8_t* from, auto put) {
     const int st = j == 0 ? 1 : (j == 1 ? B : B * B);
-    for (int idx = threadIdx.x; idx < NODES; idx += 256) {
+    for (int idx = threadIdx.x; idx < live; idx += 256) {
       const int t[3] = {idx % B, D >= 2 ? idx / B % B : 0, D >= 3 ? idx / (B * B) : 0};
       bool in = true;
 #pragma unroll
