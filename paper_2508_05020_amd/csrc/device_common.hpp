@@ -405,9 +405,12 @@ __device__ __forceinline__ void clear_rate(unsigned long long* __restrict__ lam)
   for (int x = 0; x < kXcds; ++x) lam[x * kRateStride] = 0ull;
 }
 
-// The entries and live count of a list (see ListArg).
+// The entries and live count of a list (see ListArg).  The count is loaded with
+// `dir`, not behind the branch, and the recorded form stands outside the eager
+// launches' path.
 __device__ __forceinline__ void live_list(ListArg& a) {
-  if (!a.dir) return;
+  asm("" : "+s"(a.count));
+  if (__builtin_expect(a.dir == nullptr, 1)) return;
   a.ptr += a.dir[0];
   a.count = a.dir[1];
 }

@@ -854,19 +854,30 @@ __global__ __launch_bounds__(256) void k_tag(DevMesh m, const double* __restrict
 constexpr int cell_tile(int dim) { return dim == 1 ? 256 : (dim == 2 ? 32 : 8); }
 
 // Entry of a list in level order whose tile is block b's, -1 past the last one;
-// b becomes the tile, l the entry's level in `tl`.
-__device__ __forceinline__ int level_item(const DevMesh& m, const TagLevels& tl, int count, int& b,
-                                          int& l) {
+// b becomes the tile, l the entry's level in `tl`.  (Branches marked as rare keep
+// the recorded form out of the eager launches' instruction lines.)
+__device__ __forceinline__ int level_item(const DevMesh& m, const TagLevels& tl, ListArg& list,
+                                          int& b, int& l) {
   int first = 0;
-  for (l = 0; l < m.nlev - 1; ++l) {
-    const int here = __builtin_amdgcn_readfirstlane(tl.dir ? tl.dir[2 * l] : tl.count[l]);
-    if (b < here * tl.tiles[l]) break;
-    b -= here * tl.tiles[l];
-    first += here;
+  l = 0;
+  if (__builtin_expect(tl.dir != nullptr, 0)) {
+    for (; l < m.nlev - 1; ++l) {
+      const int here = __builtin_amdgcn_readfirstlane(tl.dir[2 * l]);
+      if (b < here * tl.tiles[l]) break;
+      b -= here * tl.tiles[l];
+      first += here;
+    }
+    live_list(list);
+    if (first + b / tl.tiles[l] >= list.count) return -1;
+  } else {
+    for (; l < m.nlev - 1 && b >= tl.count[l] * tl.tiles[l]; ++l) {
+      b -= tl.count[l] * tl.tiles[l];
+      first += tl.count[l];
+    }
   }
   const int item = first + b / tl.tiles[l];
   b %= tl.tiles[l];
-  return item < count ? item : -1;
+  return item;
 }
 
 template <int D, bool SHARED>
@@ -878,9 +889,8 @@ __global__ __launch_bounds__(256) void k_cell_tags(DevMesh m, const uint8_t* __r
   constexpr int CENTRE = D == 1 ? 1 : (D == 2 ? 4 : 13);
   __shared__ uint8_t sa[NODES], sb[NODES];
   __shared__ int sN[27];
-  live_list(leaves);
   int bl = blockIdx.x, k;
-  const int item = level_item(m, tl, leaves.count, bl, k);
+  const int item = level_item(m, tl, leaves, bl, k);
   if (item < 0) return;
   const int tile = bl, pid = leaves.ptr[item];
   const int l = m.level[pid];
@@ -1079,10 +1089,9 @@ __global__ __launch_bounds__(256) void k_tag_cells(DevMesh m, const double* __re
   __shared__ long long sNB[27];
   __shared__ double sr[B * B * B], sp[B * B * B];
   __shared__ int sm;
-  live_list(list);
   int b = xcd_chunk<kTagChunk>(blocks), l;
   if (b < 0) return;
-  const int item = level_item(m, tl, list.count, b, l);
+  const int item = level_item(m, tl, list, b, l);
   if (item < 0) return;
   const int tile = b, pid = list.ptr[item];
   const LevelC& L = m.lv[l];
