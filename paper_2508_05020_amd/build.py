@@ -23,10 +23,13 @@ COMMON = ["-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}",
           # no packed FP32 instructions (see the design notes)
           "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
           "-Wall", "-Wno-unused-function", "-Wno-unused-variable"]
-# host sources: functions and loops on cache lines, so that a regrid's scans over
-# all patch slots do not depend on where the linker puts them (the same code took
-# 39 to 48 us of host time for two small regrids from one build to the next)
-HOST = ["-falign-functions=64", "-falign-loops=64"]
+# Host sources: functions on cache lines, and the loops of api.cpp, which scan all
+# patch slots at a regrid, so that a regrid's time does not move with the layout
+# of the library (two small regrids 71 to 76 us from one build to the next; 71.3
+# so).  The short inner loops of forest.cpp are better without (272 created
+# patches: 270 us, 285 with theirs aligned too).
+HOST = {"api.cpp": ["-falign-functions=64", "-falign-loops=64"],
+        "forest.cpp": ["-falign-functions=64"]}
 
 
 def _hipcc() -> str:
@@ -46,7 +49,7 @@ def _compile(src: str) -> str:
     obj = os.path.join(OBJ, os.path.basename(src) + ".o")
     cmd = [_hipcc(), *COMMON, "-c", src, "-o", obj]
     if src.endswith(".cpp"):
-        cmd[1:1] = ["-x", "hip", *HOST]
+        cmd[1:1] = ["-x", "hip", *HOST.get(os.path.basename(src), [])]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError(f"compile failed: {' '.join(cmd)}\n{r.stdout}\n{r.stderr}")
